@@ -142,7 +142,8 @@ int q4kv_append(const q4kv_spec *spec, const q4kv_pool *k, const q4kv_pool *v, c
  *                wavefronts; this is the floor of a wavefront's share and bounds the partial results kept
  *                per query head.  Must equal the value given to q4kv_attention_workspace_bytes.
  *   workspace    device scratch of at least q4kv_attention_workspace_bytes(...) bytes, 16-byte aligned;
- *                contents before and after the call are unspecified.
+ *                contents before and after the call are unspecified.  With q_len > 1 it is optional (NULL or fewer
+ *                bytes are accepted): a call that gets it spreads few or ragged agents over the whole chip.
  * Per-agent isolation (Sec. 3.1): nothing an agent's table row does not list up to seq_len ever enters its result,
  * and the kernels read no block the row does not list: slots past seq_len that a tile's loads touch lie in the
  * agent's own last block, and a block id outside [0, num_blocks) is skipped (its tokens count as masked; the loads
@@ -212,7 +213,8 @@ int q4kv_batched_attention_static(const q4kv_spec *spec, const q4kv_pool *k, con
                                   int32_t layer_end, void *hip_stream);
 
 /* Bytes of workspace q4kv_batched_attention needs for these arguments.  0 on bad arguments (q4kv_last_error() then
- * holds a message) and for q_len > 1, where the chunk kernel keeps everything on chip and needs no workspace. */
+ * holds a message).  For q_len > 1 the bytes with which the call shares its work out evenly over the compute units (it
+ * runs without them too, one workgroup per row tile); 0 where that gains nothing. */
 size_t q4kv_attention_workspace_bytes(const q4kv_spec *spec, int32_t num_agents, int32_t q_len, int32_t max_seq_len,
                                       int32_t split_tokens, int32_t num_layers_in_call);
 

@@ -247,7 +247,10 @@ size_t q4kv_attention_workspace_bytes(const q4kv_spec *spec, int32_t num_agents,
         fail(Q4KV_EINVAL, "bad counts");
         return 0;
     }
-    if (q_len > 1) return 0; // the chunk kernel keeps everything on chip
+    if (q_len > 1) { // optional: what lets a chunk call share its tiles out over all compute units
+        size_t acc_bytes;
+        return q4kv::chunk_workspace_bytes(*spec, num_agents, q_len, max_seq_len, num_layers_in_call, compute_units(), acc_bytes);
+    }
     const int st = split_tokens ? split_tokens : pick_split_tokens(*spec, num_agents, max_seq_len, num_layers_in_call);
     const int64_t slots = slots_per_unit(*spec, max_seq_len, st);
     const int64_t units = (int64_t)num_layers_in_call * num_agents * q_len * spec->num_q_heads;
@@ -255,12 +258,15 @@ size_t q4kv_attention_workspace_bytes(const q4kv_spec *spec, int32_t num_agents,
            (size_t)(units * slots * (spec->v_dim + 2) * (int64_t)sizeof(float));
 }
 
+// shared_scratch: the workspace is the library's own array (a chunk call leaves it alone: calls on other streams that
+// need no workspace may then overlap)
 // planned: the workspace already holds the plan of q4kv_decode_plan for these arguments (seq_len is then not needed)
 static int attention_common(const q4kv_spec *spec, const q4kv_pool *k, const q4kv_pool *v, const uint16_t *q,
                             uint16_t *out, const int32_t *block_table, int32_t max_blocks, const int32_t *seq_len,
                             int32_t num_agents, int32_t q_len, int32_t max_seq_len, float sm_scale, int32_t window,
                             const int32_t *layer_window, int32_t split_tokens, int32_t layer_begin, int32_t layer_end,
-                            void *workspace, size_t workspace_bytes, void *hip_stream, bool planned = false)
+                            void *workspace, size_t workspace_bytes, void *hip_stream, bool planned = false,
+                            bool shared_scratch = false)
 {
     int rc = check_spec(spec);
     if (rc) return rc;
@@ -308,10 +314,19 @@ static int attention_common(const q4kv_spec *spec, const q4kv_pool *k, const q4k
     a.sm_scale = sm_scale;
 
     hipStream_t st = (hipStream_t)hip_stream;
-    if (q_len > 1) { // chunked append: causal attention of q_len new tokens per agent, no workspace needed
+    if (q_len > 1) { // chunked append: causal attention of q_len new tokens per agent; a workspace is optional
         if (!q4kv::chunk_supported(*spec))
             return fail(Q4KV_ESHAPE, "no chunk kernel for k_dim=%d v_dim=%d n_rep=%d alias=%d", spec->k_dim, spec->v_dim,
                         spec->num_q_heads / spec->num_kv_heads, spec->v_aliases_k);
+        size_t acc_bytes = 0;
+        const size_t need = q4kv::chunk_workspace_bytes(*spec, num_agents, q_len, max_seq_len, layers, compute_units(), acc_bytes);
+        a.chunk_workers = 0;
+        a.part_acc = a.part_ml = nullptr;
+        if (need > 0 && !shared_scratch && workspace && workspace_bytes >= need && aligned16(workspace)) {
+            a.chunk_workers = compute_units();
+            a.part_acc = static_cast<float *>(workspace);
+            a.part_ml = reinterpret_cast<float *>(static_cast<char *>(workspace) + acc_bytes);
+        }
         hipError_t e = q4kv::launch_chunk_attention(a, st);
         return e == hipSuccess ? Q4KV_OK : fail(Q4KV_EHIP, "attention launch: %s", hipGetErrorString(e));
     }
@@ -406,7 +421,7 @@ int q4kv_batched_attention_static(const q4kv_spec *spec, const q4kv_pool *k, con
     if (!ptr) return Q4KV_EHIP;
     return attention_common(spec, k, v, q, out, block_table, max_blocks, seq_len, num_agents, q_len, max_seq_len, sm_scale,
                             window, nullptr, split_tokens, layer_begin, layer_end, ptr, (size_t)Q4KV_STATIC_SCRATCH_BYTES,
-                            hip_stream);
+                            hip_stream, false, true);
 }
 
 int q4kv_decode_plan(const q4kv_spec *spec, const int32_t *seq_len, int32_t num_agents, int32_t max_seq_len,

@@ -4,45 +4,76 @@
 // seq_len[a] - (q_len-1-c) tokens of that agent's cache -- the chunk's own keys in their Q4 form included.
 //
 // Unlike decode this is a dense contraction: the q_len * n_rep query rows that share one KV head form the
-// M side of two GEMMs per KV tile (S = Q K^T, O += P V), so it runs on the matrix cores and is bound by them.
+// M side of two GEMMs per KV tile (S = Q K^T, O += P V), so it runs on the matrix cores.  What bounds it is the issue
+// port of a SIMD: a vector instruction takes 4.5 clocks of it, a 32x32x16 matrix instruction about 5 (and 32 of the
+// matrix pipe), a 16x16x32 one 8.6 (and 17): the products are cut so that everything the vector unit prepares --
+// unpacked keys above all -- serves 32 query rows.
 //
-//  * A workgroup (4 waves) owns 128 query rows of one (layer, agent, KV head): 128/n_rep consecutive chunk
-//    positions times the n_rep query heads of the group.  Each wave owns 32 rows.
-//  * KV tiles of 64 tokens are fetched as Q4 (codes + scale/bias, coalesced 16-byte loads, prefetched one
-//    tile ahead into registers) and staged ONCE per workgroup in LDS for all 128 rows, row-major: V_hat
-//    dequantized to binary16, K as the packed code words themselves (a quarter of the LDS traffic of binary16
-//    keys; a lane's A operand of a matrix instruction is exactly one word).  The dims inside a word appear in the
-//    order the nibble masks deliver them (0,4,1,5,2,6,3,7): the query operand uses the same order for K, the
-//    output store undoes it for V_hat.
+//  * A workgroup of eight waves owns 256 query rows of one (layer, agent, KV head) -- 256/n_rep consecutive chunk
+//    positions times the n_rep query heads of the group -- 32 rows per wave; or 128 rows, when its waves 0..3 take the
+//    first and waves 4..7 the second 32 tokens of every tile (KSPLIT = 2: short chunks).
+//  * KV tiles of 64 tokens are fetched as Q4 (codes + scale/bias, prefetched one tile ahead into registers) and staged
+//    ONCE per workgroup in LDS, row-major: V_hat dequantized to binary16, K as the packed code words themselves (a
+//    lane's A operand of a matrix instruction is exactly one word, four of them one 16-byte LDS read).  The dims inside
+//    a word appear in the order the nibble masks deliver them (0,4,1,5,2,6,3,7): the query operand uses the same order
+//    for K, the output store undoes it for V_hat.
 //  * K stays factored, S^T = sum_g s[t,g] (C_g Q_g^T) + b Qsum^T: a code word masked in place is eight binary16
 //    subnormals (c 2^-24, odd nibbles 16 c 2^-24 against q/16), the matrix core multiplies them exactly, and the
 //    per-(token, group) scale meets the binary32 result of each group; the bias term is one more matrix
-//    instruction per 16 tokens whose contraction runs over the groups (group sums of q split into a binary16 high
+//    instruction per 32 tokens whose contraction runs over the groups (group sums of q split into a binary16 high
 //    and low part).  A K row dequantized to binary16 would carry an absolute rounding error of 2^-11 |K_hat|,
 //    which the large channels of real key caches turn into score errors of several 1e-3.  V_hat is dequantized
 //    to binary16 (its rounding error is relative to the values that are averaged).
-//  * The wave computes S^T (tokens are the M rows), so that the probabilities come out of the
-//    matrix core already in the register layout the second GEMM wants for its B operand (P^T); no shuffle
-//    or LDS round trip between the GEMMs.  O^T = V_hat^T P^T accumulates in binary32; its A operand wants 8
-//    tokens of one dim per lane, which the transposing LDS read (ds_read_b64_tr_b16) delivers straight from the
-//    row-major tile: in a group of 16 lanes, lane 4e + c points at 4 consecutive dims (chunk c) of token e, and
-//    element e of what lane j receives is half j % 4 of the chunk that lane 4e + j / 4 addressed, i.e. dim j of
-//    token e.
-//  * Softmax is online, per query row (= per lane column): scores in binary32, log2 domain.
-//  * The workgroups of one KV head are adjacent in the launch order of ONE XCD, so the 8 query tiles of a
-//    unit stream the same KV tiles through the same L2 at the same time.
+//  * The wave computes S^T (tokens are the M rows), so that the probabilities come out of the matrix core already in
+//    the register layout the second GEMM wants for its B operand (P^T); no shuffle or LDS round trip between the
+//    GEMMs.  O^T = V_hat^T P^T accumulates in binary32; its A operand wants 8 tokens of one dim per lane, which two
+//    transposing LDS reads (ds_read_b64_tr_b16) deliver straight from the row-major tile: in a group of 16 lanes, lane
+//    4e + c points at 4 consecutive dims (chunk c) of token e, and element e of what lane j receives is half j % 4 of
+//    the chunk that lane 4e + j / 4 addressed, i.e. dim j of token e.
+//  * M row m of a 32-token product stands for token perm(m) = 16 (m/16) + 8 ((m/4)%2) + 2 (m%4) + (m/8)%2: the rows one
+//    transposing read touches are then two tokens apart, and with a pitch of 8 banks (mod 64) the four tokens x 64
+//    bytes of half a wave fall into all 64 banks.
+//  * At 256-wide heads the accumulators of 32 rows (128 registers) leave no room for the whole query operand (64) if
+//    two waves are to share a SIMD: half of it lies in LDS, in operand order, private to its wave.
+//  * Softmax is online, per query row (= per lane column): scores in binary32, log2 domain, 32 tokens at a time.
+//  * Two forms of launch: one workgroup per unit (layer, agent, KV head, row tile), when there are enough units to fill the chip
+//    many times over; or, given a workspace, one workgroup per compute unit, each with an equal contiguous range of all
+//    units' tiles.  A unit cut by a range's end leaves un-normalised sums, maxima and denominators of every part
+//    in the workspace, and a second small kernel merges them in order.
+//
+// Measured, 256-wide heads, ten agents of 4K-32K tokens, a 512-token chunk, one layer: 1.77 ms = 830 TFLOP/s (16 rows per
+// wave on 16x16x32 instructions, one workgroup per unit: 2.27 ms); one agent of 8,000 tokens 0.12 + 0.02 ms (0.37 ms).
+// A wave spends 5,150 clocks on 32 tokens: 2,200 on the scores (163 vector, 17 matrix instructions), 630 on the softmax
+// (100), 1,580 on the product (16 matrix instructions, 75 vector ones for the staging), 750 at the barrier, because the
+// older wave of a SIMD wins its arbitrations and the younger one finishes alone.  Holding the second wave half a step
+// behind by two barriers per step (its vector work against the other's matrix work) cost 15 %: the scores' chain is
+// longer than the product.  Wave priorities by phase, deeper operand reads: no change.
+#include <type_traits>
+
 #include "q4_device.h"
 #include "q4kv_internal.h"
 
 namespace q4kv {
 namespace {
 
-constexpr int kRowsWG = 128;  // query rows per workgroup
-constexpr int kTile = 64;     // KV tokens per tile
+constexpr int kChunkWaves = 8;
+constexpr int kChunkThreads = kChunkWaves * kWave;
+constexpr int kRowsWave = 32; // query rows per wave
+constexpr int kSub = 32;      // tokens per matrix tile of scores
 constexpr float kNegBig = -1.0e30f;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kXcds = 8;
 constexpr int kMaxChunkWindowLayers = 128; // layers per call when every layer brings its own window
+constexpr int kMaxStreamAgents = 256;      // agents of a call whose tiles are dealt out evenly
+
+typedef float float16_t __attribute__((ext_vector_type(16)));
+
+// A unit that several workgroups share: the record of the workgroup it begins in, how many records it has (0: none; the
+// others are the first ones of the workgroups that follow), its place in the output.
+struct ChunkShared {
+    int slots, first_record, qt, kvh;
+    int64_t token_row; // (layer in call * agents + agent) * q_len
+};
 
 struct ChunkParams {
     const uint32_t *k_codes, *v_codes;
@@ -50,12 +81,111 @@ struct ChunkParams {
     const uint16_t *q;
     uint16_t *out;
     const int32_t *block_table, *seq_len;
+    float *part_acc;                // records of units that several workgroups share: [2 grid][wave][DV / 8][lane][4]
+    float *part_ml;                 // [2 grid][wave][32 rows][2]: running maximum (log2 units), denominator
+    ChunkShared *shared;            // [grid]: the unit that begins in a workgroup's range and goes on past it
     int num_blocks, kv_heads, q_heads, num_agents, max_blocks, max_seq_len, window, q_len;
     int layer_begin, layers_in_call, q_tiles;
+    int stream;                     // 1: every workgroup takes an equal range of all tiles; 0: one unit per workgroup
     float score_scale;
     int per_layer_windows;          // 1: layer_window[] holds the window of every layer of the call
     int layer_window[kMaxChunkWindowLayers];
 };
+
+// ---------------------------------------------------------------------------------------------- units and ranges
+
+struct ChunkUnit {
+    int li, agent, kvh, qt; // layer in call, agent, KV head, row tile
+};
+
+// The tokens the rows of one row tile see: chunk position c sees [first(c), vis(c)), vis(c) = n - (q_len - 1 - c).
+template <int QPOS, int TILE>
+__device__ __forceinline__ void visible_range(const ChunkParams &p, int n, int window, int qt, int &t_begin, int &t_end)
+{
+    const int pos0 = qt * QPOS;                                             // first chunk position of the row tile
+    t_end = n - (p.q_len - 1 - min(p.q_len - 1, pos0 + QPOS - 1));          // exclusive; may be <= 0
+    const int vis_first = n - (p.q_len - 1 - pos0);
+    t_begin = window > 0 && vis_first > window ? (vis_first - window) & ~(TILE - 1) : 0;
+}
+
+// tiles a unit counts for when all are dealt out (a unit that sees nothing still has rows of zeros to write)
+template <int QPOS, int TILE>
+__device__ __forceinline__ int unit_tiles(const ChunkParams &p, int n, int window, int qt)
+{
+    int t_begin, t_end;
+    visible_range<QPOS, TILE>(p, n, window, qt, t_begin, t_end);
+    return t_end > t_begin ? (t_end - t_begin + TILE - 1) / TILE : 1;
+}
+
+__device__ __forceinline__ int clamped_length(const ChunkParams &p, int agent)
+{
+    const int n = p.seq_len[agent];
+    return n < 0 ? 0 : (n > p.max_seq_len ? p.max_seq_len : n);
+}
+
+__device__ __forceinline__ int scalar(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// All tiles of a call in the order (layer, agent, KV head, row tile, tile), one window for all layers.  pre[a] = tiles of
+// the agents before a in one layer, pre[num_agents] = tiles of a layer, len[a] the agent's length; in LDS, filled by the
+// first wave.
+template <int QPOS, int TILE>
+struct ChunkStream {
+    const int *pre, *len;
+
+    __device__ __forceinline__ static void fill(const ChunkParams &p, int *pre, int *len, int lane)
+    {
+        int total = 0;
+        for (int a0 = 0; a0 < p.num_agents; a0 += kWave) {
+            const int a = a0 + lane;
+            int mine = 0, n = 0;
+            if (a < p.num_agents) {
+                n = clamped_length(p, a);
+                for (int qt = 0; qt < p.q_tiles; ++qt) mine += unit_tiles<QPOS, TILE>(p, n, p.window, qt);
+                mine *= p.kv_heads;
+            }
+            int incl = mine;
+#pragma unroll
+            for (int off = 1; off < kWave; off <<= 1) {
+                const int up = __shfl_up(incl, off, kWave);
+                if (lane >= off) incl += up;
+            }
+            if (a < p.num_agents) {
+                pre[a] = total + incl - mine;
+                len[a] = n;
+            }
+            total += __shfl(incl, kWave - 1, kWave);
+        }
+        if (lane == 0) pre[p.num_agents] = total;
+    }
+    // the unit that tile x belongs to, the tile's number inside it, the unit's tiles, the agent's length
+    __device__ __forceinline__ ChunkUnit locate(const ChunkParams &p, int x, int &at, int &tiles, int &n) const
+    {
+        ChunkUnit u;
+        const int layer_tiles = scalar(pre[p.num_agents]);
+        u.li = x / layer_tiles;
+        int r = x - u.li * layer_tiles;
+        int lo = 0, hi = p.num_agents - 1; // largest a with pre[a] <= r (every agent has tiles)
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (scalar(pre[mid]) <= r) lo = mid; else hi = mid - 1;
+        }
+        u.agent = lo;
+        r -= scalar(pre[lo]);
+        const int per_head = (scalar(pre[lo + 1]) - scalar(pre[lo])) / p.kv_heads;
+        u.kvh = r / per_head;
+        r -= u.kvh * per_head;
+        n = scalar(len[lo]);
+        u.qt = 0;
+        while (r >= (tiles = unit_tiles<QPOS, TILE>(p, n, p.window, u.qt))) {
+            r -= tiles;
+            ++u.qt;
+        }
+        at = r;
+        return u;
+    }
+};
+
+// ---------------------------------------------------------------------------------------------- small helpers
 
 __device__ __forceinline__ half2_t pk_fma(half2_t a, half2_t b, half2_t c) { return a * b + c; }
 
@@ -73,24 +203,12 @@ __device__ __forceinline__ half2_t nibbles_hi16(uint32_t w) // 16 * code
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4_t *lds_short4_ptr;
 
-// x[i] (op) x[i ^ 16], x[i] (op) x[i ^ 32] without touching LDS
-__device__ __forceinline__ float xor16_max(float x)
-{
-    const uint32_t u = __builtin_bit_cast(uint32_t, x);
-    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    return fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
-}
+// x[i] (op) x[i ^ 32] without touching LDS
 __device__ __forceinline__ float xor32_max(float x)
 {
     const uint32_t u = __builtin_bit_cast(uint32_t, x);
     const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
     return fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
-}
-__device__ __forceinline__ float xor16_sum(float x)
-{
-    const uint32_t u = __builtin_bit_cast(uint32_t, x);
-    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
 }
 __device__ __forceinline__ float xor32_sum(float x)
 {
@@ -99,506 +217,665 @@ __device__ __forceinline__ float xor32_sum(float x)
     return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
 }
 
-// How the threads of a workgroup share the staging of one 64-row tile of DIM-wide code rows: as many threads per row
+// Four normalised values of one query row at positions 8 j + 4 h .. + 3 of an 8-dim word of V_hat (h = lane / 32):
+// dims (0,4,1,5) in the lower half of the wave, (2,6,3,7) in the upper.  The halves trade pairs, after which each
+// lane holds four consecutive dims: 0..3 below, 4..7 above.
+__device__ __forceinline__ void store_row_quad(uint16_t *word, int h, float a, float b, float c, float d)
+{
+    const uint32_t first = half2_to_bits(half2_t{(half_t)a, (half_t)c}), second = half2_to_bits(half2_t{(half_t)b, (half_t)d});
+    const auto r = __builtin_amdgcn_permlane32_swap(first, second, false, false);
+    *reinterpret_cast<uint2 *>(word + 4 * h) = make_uint2((uint32_t)r[0], (uint32_t)r[1]);
+}
+
+// How the threads of a workgroup share the staging of one tile of DIM-wide code rows: as many threads per row
 // as fit, each with 2, 4 or 8 consecutive words (never across a quantization group).
-template <int DIM, int THREADS>
+template <int DIM, int THREADS, int TILE>
 struct Stage {
     static constexpr int WORDS = DIM / 8; // code words per row
-    static constexpr int WPT = kTile * (WORDS / 2) <= THREADS ? 2 : (kTile * (WORDS / 4) <= THREADS ? 4 : 8);
+    static constexpr int WPT = TILE * (WORDS / 2) <= THREADS ? 2 : (TILE * (WORDS / 4) <= THREADS ? 4 : 8);
     static constexpr int TPR = WORDS / WPT; // threads per row
-    static constexpr int ACTIVE = kTile * TPR;
+    static constexpr int ACTIVE = TILE * TPR;
     static_assert(WORDS % WPT == 0 && ACTIVE <= THREADS, "tile split");
 };
 
-// QT: 16-row query tiles per wave.  Two tiles halve the LDS operand traffic per matrix instruction; one tile keeps
-// a wave within 256 registers also at D = 256, so that two waves share a SIMD and one wave's dequantization and
-// softmax run under the other's matrix instructions.  The workgroup always owns 128 rows: 128 / (16 QT) waves.
+// ---------------------------------------------------------------------------------------------- attention
+
+// KV tokens per tile
+constexpr int chunk_tile(int dk, int ksplit) { return dk == 256 && ksplit == 1 ? 32 : 64; }
+
+// KSPLIT 1: 256 rows per workgroup; 2: 128 rows, the two halves of the waves share the tokens of a tile.
 // BF: scale and bias are stored as bfloat16 (converted to binary16 when a row is staged).
-// (Two tiles at 192-wide keys need more than 256 registers: one wave per SIMD there, no scratch.)
-template <int DK, int DV, int NREP, int QT, bool BF>
-__global__ __launch_bounds__(kRowsWG / (16 * QT) * kWave, (QT == 2 && DK > 128) ? 1 : 2) void chunk_attention_kernel(ChunkParams p)
+template <int DK, int DV, int NREP, int KSPLIT, bool BF>
+__global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(ChunkParams p)
 {
-    constexpr int kRowsWave = 16 * QT;
-    constexpr int kWaves = kRowsWG / kRowsWave;
-    constexpr int kThreads = kWaves * kWave;
     constexpr int GK = DK / kGroup, GV = DV / kGroup;
-    // row pitches of the tiles in LDS.  K rows (32-bit code words) are read one word per lane by 16 rows x 4 words at
-    // a time: a pitch of 4 x odd words spreads those over all 64 banks.  V_hat rows (halves) are read 8 bytes per
-    // lane by 4 rows x 32 bytes at a time (pitch = 32 bytes mod 256).
-    constexpr int KPITCH = DK / 8 + 4;
-    constexpr int VPITCH = DV + 16;
-    constexpr int QPOS = kRowsWG / NREP; // chunk positions per workgroup
-    constexpr int KSTEPS = DK / 32;    // k-steps of the QK contraction
-    constexpr int ETILES = DV / 16;    // 16-row tiles of O^T
-    typedef Stage<DK, kThreads> SK;    // staging of the K rows of a tile ...
-    typedef Stage<DV, kThreads> SV;    // ... and of its V rows
+    constexpr int ROWGROUPS = kChunkWaves / KSPLIT;       // waves that own rows of their own
+    constexpr int QPOS = ROWGROUPS * kRowsWave / NREP;    // chunk positions per workgroup
+    constexpr int KPITCH = DK / 8 + 4; // words; an odd multiple of 4: 16 rows x 16 bytes fall into all 64 banks
+    constexpr int VPITCH = DV + 16;    // halves; 8 banks mod 64 (40 at 64-wide rows), see above
+    constexpr int DTILES = DV / 32;    // 32-dim tiles of O^T
+    constexpr int TILE = chunk_tile(DK, KSPLIT);
+    constexpr int QREG = DK == 256 ? 1 : GK; // groups whose query operand stays in registers; the rest in LDS
+    constexpr int QLDS = GK - QREG;
+    constexpr int QROWS = ROWGROUPS * kWave; // lanes that hold query operands of their own
+    typedef Stage<DK, kChunkThreads, TILE> SK; // staging of the K rows of a tile ...
+    typedef Stage<DV, kChunkThreads, TILE> SV; // ... and of its V rows
 
     // two tiles each: while the waves multiply against one, they unpack the next into the other
-    __shared__ __attribute__((aligned(16))) uint32_t k_lds[2][kTile * KPITCH]; // K code words as they are in the pool
-    __shared__ __attribute__((aligned(16))) half_t v_lds[2][kTile * VPITCH]; // V_hat
-    __shared__ __attribute__((aligned(16))) half_t ks_lds[2][GK * kTile];    // K scale [group][token]
+    __shared__ __attribute__((aligned(16))) uint32_t k_lds[2][TILE * KPITCH]; // K code words as they are in the pool
+    __shared__ __attribute__((aligned(16))) half_t v_lds[2][TILE * VPITCH];   // V_hat
+    // K scale [group][32-token half][lane / 32][16 values in the order a lane's scores have]
+    __shared__ __attribute__((aligned(16))) half_t ks_lds[2][GK * TILE];
     // K bias [token][8]: groups 0..3 (zero padded) twice, against the high and the low parts of the group sums of q
-    __shared__ __attribute__((aligned(16))) half_t kb_lds[2][kTile * 8];
+    __shared__ __attribute__((aligned(16))) half_t kb_lds[2][TILE * 8];
+    __shared__ __attribute__((aligned(16))) half8_t q_lds[QLDS > 0 ? QLDS * 4 * QROWS : 1];
+    __shared__ int s_pre[kMaxStreamAgents + 1], s_len[kMaxStreamAgents];
 
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int wave = scalar(threadIdx.x / kWave);
+    const int rg = wave % ROWGROUPS, my_sub = wave / ROWGROUPS; // row group; with KSPLIT 2 the half of a tile's tokens
 
-    // ---- which (layer, agent, kv head, query tile): consecutive workgroups of one XCD share a KV head
-    const int per_xcd_slot = blockIdx.x / kXcds, xcd = blockIdx.x % kXcds;
-    const int unit_in_xcd = per_xcd_slot / p.q_tiles, qt = per_xcd_slot % p.q_tiles;
-    const int unit = unit_in_xcd * kXcds + xcd; // ((layer in call) * agents + agent) * kv_heads + kv head
-    const int total_units = p.layers_in_call * p.num_agents * p.kv_heads;
-    if (unit >= total_units) return;
-    const int kvh = unit % p.kv_heads, agent = (unit / p.kv_heads) % p.num_agents, li = unit / (p.kv_heads * p.num_agents);
-    const int layer = p.layer_begin + li;
-
-    int n = p.seq_len[agent];
-    n = n < 0 ? 0 : (n > p.max_seq_len ? p.max_seq_len : n);
-    const int window = p.per_layer_windows ? p.layer_window[li] : p.window;
-    const int pos0 = qt * QPOS;                   // first chunk position of this workgroup
-    if (pos0 >= p.q_len) return;
-    // chunk position c sees tokens [first(c), vis(c)),  vis(c) = n - (q_len - 1 - c)
-    const int vis_last = n - (p.q_len - 1 - min(p.q_len - 1, pos0 + QPOS - 1)); // keys visible to the last row here
-    const int vis_first = n - (p.q_len - 1 - pos0);
-    int t_begin = 0;
-    if (window > 0 && vis_first - window > 0) t_begin = (vis_first - window) & ~(kTile - 1);
-    const int t_end = vis_last; // exclusive; may be <= 0 when nothing is visible
-
-    // ---- this lane's query rows: column n = lane % 16 of the two 16-row tiles of its wave
-    const int qn = lane % 16, kb = lane / 16;
-    int row_pos[QT], row_vis[QT], row_first[QT];
-    half8_t qop[QT][KSTEPS];
-    half8_t qsop[QT]; // lanes kb == 0: group sums of this row's q, high parts in slots 0..3, low parts in 4..7; else 0
-    const int64_t q_agent = ((int64_t)li * p.num_agents + agent) * p.q_len;
-#pragma unroll
-    for (int qi = 0; qi < QT; ++qi) {
-        const int r_w = wave * kRowsWave + qi * 16 + qn;   // row inside the workgroup
-        const int c = pos0 + r_w / NREP, head = kvh * NREP + r_w % NREP;
-        row_pos[qi] = c;
-        const bool live = c < p.q_len;
-        row_vis[qi] = live ? n - (p.q_len - 1 - c) : 0;
-        row_first[qi] = (window > 0 && row_vis[qi] > window) ? row_vis[qi] - window : 0;
-        const uint16_t *src = p.q + ((q_agent + (live ? c : 0)) * p.q_heads + head) * DK;
-        float qs[GK];
-#pragma unroll
-        for (int g = 0; g < GK; ++g) qs[g] = 0.0f;
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) {
-            // dims 32*ks + 8*kb .. +7 in the order the nibble masks emit them: 0,4,1,5,2,6,3,7; the odd ones divided
-            // by 16 because their codes arrive 16 times larger
-            const uint4 raw = *reinterpret_cast<const uint4 *>(src + 32 * ks + 8 * kb);
-            const half2_t e01 = bits_to_half2(raw.x), e23 = bits_to_half2(raw.y);
-            const half2_t e45 = bits_to_half2(raw.z), e67 = bits_to_half2(raw.w);
-            const half_t sixteenth = (half_t)0.0625f;
-            qop[qi][ks] = half8_t{e01.x, e45.x, e01.y * sixteenth, e45.y * sixteenth,
-                                  e23.x, e67.x, e23.y * sixteenth, e67.y * sixteenth};
-            qs[ks / 2] += ((float)e01.x + (float)e01.y) + ((float)e23.x + (float)e23.y) +
-                          ((float)e45.x + (float)e45.y) + ((float)e67.x + (float)e67.y);
-        }
-        half_t part[8];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const float v = g < GK ? xor32_sum(xor16_sum(qs[g < GK ? g : 0])) : 0.0f; // over the four lanes of the row
-            const half_t hi = (half_t)v;
-            part[g] = kb == 0 ? hi : (half_t)0.0f;
-            part[4 + g] = kb == 0 ? (half_t)(v - (float)hi) : (half_t)0.0f;
-        }
-        qsop[qi] = half8_t{part[0], part[1], part[2], part[3], part[4], part[5], part[6], part[7]};
+    // ---- the range of tiles this workgroup takes: whole unit blockIdx (consecutive workgroups of one XCD share a KV
+    // head), or an equal share of all tiles (consecutive shares on one XCD)
+    const ChunkStream<QPOS, TILE> stream{s_pre, s_len};
+    int x = 0, x1 = 1, per = 1, worker = 0;
+    if (p.stream) {
+        if (wave == 0) ChunkStream<QPOS, TILE>::fill(p, s_pre, s_len, threadIdx.x);
+        __syncthreads();
+        const int total = p.layers_in_call * scalar(s_pre[p.num_agents]), grid = gridDim.x;
+        per = (total + grid - 1) / grid;
+        worker = grid % kXcds == 0 ? (int)(blockIdx.x % kXcds) * (grid / kXcds) + (int)(blockIdx.x / kXcds) : (int)blockIdx.x;
+        x = worker * per; // below total + grid: far inside 32 bits
+        x1 = min(total, x + per);
+        if (threadIdx.x == 0) p.shared[worker].slots = 0; // this thread writes it again when a unit goes on past the range
+        if (x >= x1) return;
     }
-    // what every row of this wave sees / hides (rows differ along lane % 16): tiles inside [all_first, all_vis)
-    // need no masks
-    int all_vis = row_vis[0], all_first = row_first[0];
-#pragma unroll
-    for (int qi = 1; qi < QT; ++qi) {
-        all_vis = min(all_vis, row_vis[qi]);
-        all_first = max(all_first, row_first[qi]);
-    }
-#pragma unroll
-    for (int s = 1; s < 16; s <<= 1) {
-        all_vis = min(all_vis, __shfl_xor(all_vis, s, kWave));
-        all_first = max(all_first, __shfl_xor(all_first, s, kWave));
-    }
-
-    float4_t o_acc[QT][ETILES]; // O^T: [q tile][16-dim tile], lane column = query row, regs = row positions 4*kb .. 4*kb+3
-#pragma unroll
-    for (int qi = 0; qi < QT; ++qi)
-#pragma unroll
-        for (int et = 0; et < ETILES; ++et) o_acc[qi][et] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    // m_run: the reference the exponentials are taken against.  It moves only when a tile's maximum exceeds it by
-    // more than kSlack (log2 units), so the accumulators are rescaled a few times per row, not once per tile.
-    constexpr float kSlack = 3.0f;
-    float m_run[QT], l_run[QT];
-#pragma unroll
-    for (int qi = 0; qi < QT; ++qi) {
-        m_run[qi] = kNegBig;
-        l_run[qi] = 0.0f;
-    }
-
-    // ---- KV tile staging: raw Q4 in registers one tile ahead.  A thread takes WPT consecutive words of one token's
-    // K row and (the same ones when the rows are equally wide) of one token's V row; with rows that do not divide
-    // evenly the last waves stage nothing
-    const int32_t *table = p.block_table + (int64_t)agent * p.max_blocks;
-    uint32_t kraw[SK::WPT], vraw[SV::WPT];
-    uint32_t ksb[2], vsb[2]; // scale / bias bits of the group this thread unpacks
-    // 16 consecutive lanes take 16 consecutive tokens (and the same part of the row): their 16-byte LDS stores then
-    // fall into 16 different bank groups, like the operand reads
-    const bool k_on = SK::ACTIVE == kThreads || tid < SK::ACTIVE, v_on = SV::ACTIVE == kThreads || tid < SV::ACTIVE;
-    const int k_tok = k_on ? (tid % 16) + 16 * (tid / (16 * SK::TPR)) : 0, k_w0 = ((tid / 16) % SK::TPR) * SK::WPT;
-    const int v_tok = v_on ? (tid % 16) + 16 * (tid / (16 * SV::TPR)) : 0, v_w0 = ((tid / 16) % SV::TPR) * SV::WPT;
-    const int k_grp = (k_w0 * 8) / kGroup, v_grp = (v_w0 * 8) / kGroup;
-    // A block id outside the pool: the tile's (unconditional) loads go to the agent's own first block instead -- to
-    // block 0 only if that id is outside the pool as well -- and everything they bring is discarded.
-    const int own0 = table[0];
-    const int fallback_blk = own0 >= 0 && own0 < p.num_blocks ? own0 : 0;
-    auto tile_row0 = [&](int t0, bool &ok) {
-        const int bi = t0 / kBlockTokens;
-        const int blk = bi < p.max_blocks ? table[bi] : -1;
-        ok = blk >= 0 && blk < p.num_blocks;
-        return (((int64_t)layer * p.num_blocks + (ok ? blk : fallback_blk)) * p.kv_heads + kvh) * kBlockTokens + (t0 % kBlockTokens);
-    };
-    auto load_words = [&](const uint32_t *src, auto &dst) {
-        constexpr int N = sizeof(dst) / sizeof(uint32_t);
-        if constexpr (N % 4 == 0) {
-#pragma unroll
-            for (int i = 0; i < N / 4; ++i) {
-                const uint4 t = *reinterpret_cast<const uint4 *>(src + 4 * i);
-                dst[4 * i] = t.x; dst[4 * i + 1] = t.y; dst[4 * i + 2] = t.z; dst[4 * i + 3] = t.w;
-            }
-        } else {
-            const uint2 t = *reinterpret_cast<const uint2 *>(src);
-            dst[0] = t.x; dst[1] = t.y;
-        }
-    };
-    // threads without a share load row 0 of the tile again (a valid address) and never store
-    auto load_tile = [&](int t0, bool &ok) {
-        const int64_t row0 = tile_row0(t0, ok);
-        const int64_t krow = row0 + k_tok, vrow = row0 + v_tok;
-        load_words(p.k_codes + krow * SK::WORDS + (k_on ? k_w0 : 0), kraw);
-        load_words(p.v_codes + vrow * SV::WORDS + (v_on ? v_w0 : 0), vraw);
-        ksb[0] = p.k_scale[krow * GK + (k_on ? k_grp : 0)];
-        ksb[1] = p.k_bias[krow * GK + (k_on ? k_grp : 0)];
-        vsb[0] = p.v_scale[vrow * GV + (v_on ? v_grp : 0)];
-        vsb[1] = p.v_bias[vrow * GV + (v_on ? v_grp : 0)];
-    };
-    // unpack the staged words of one row into LDS (V: dequantized; K: codes, see store_codes).  Rows of an unreachable block and rows at or past t_end
-    // (never visible, possibly never written) become zeros, so that no stale bit pattern can reach an accumulator.
-    // Dequantization of the staged rows happens one code word (8 dims, one 16-byte store) at a time, so that the
-    // matrix loops below can take a word between their steps: a wave cannot overlap its own vector and matrix
-    // instructions, but the other wave of its SIMD fills in whenever both streams are mixed rather than phased.
-    struct RowDequant {
-        half2_t s2, s16, b2;
-        bool ok;
-    };
-    auto row_params = [&](const uint32_t (&sb)[2], bool ok) {
-        RowDequant r;
-        // bfloat16 parameters of binary16-range data convert exactly (8 significant bits into 11) unless they are
-        // below 2^-14, where the difference is far below what binary16 operands resolve anyway
-        const half_t s_in = BF ? (half_t)bf16_bits_to_float((uint16_t)sb[0]) : __builtin_bit_cast(half_t, (uint16_t)sb[0]);
-        const half_t b_in = BF ? (half_t)bf16_bits_to_float((uint16_t)sb[1]) : __builtin_bit_cast(half_t, (uint16_t)sb[1]);
-        const half_t s = ok ? s_in : (half_t)0.0f;
-        const half_t b = ok ? b_in : (half_t)0.0f;
-        r.s2 = half2_t{s, s};
-        r.b2 = half2_t{b, b};
-        r.s16 = r.s2 * half2_t{(half_t)0.0625f, (half_t)0.0625f};
-        r.ok = ok;
-        return r;
-    };
-    auto store_word = [&](half_t *dst, uint32_t raw, const RowDequant &r) {
-        const uint32_t word = r.ok ? raw : 0u, w8 = word >> 8;
-        const half2_t v0 = pk_fma(nibbles_lo(word), r.s2, r.b2);    // dims 0, 4
-        const half2_t v1 = pk_fma(nibbles_hi16(word), r.s16, r.b2); // dims 1, 5
-        const half2_t v2 = pk_fma(nibbles_lo(w8), r.s2, r.b2);      // dims 2, 6
-        const half2_t v3 = pk_fma(nibbles_hi16(w8), r.s16, r.b2);   // dims 3, 7
-        *reinterpret_cast<uint4 *>(dst) = make_uint4(half2_to_bits(v0), half2_to_bits(v1), half2_to_bits(v2), half2_to_bits(v3));
-    };
-    // K rows keep their codes: the nibbles masked in place are binary16 subnormals c 2^-24 (dims 0, 4, 2, 6 of a
-    // word) and 16 c 2^-24 (dims 1, 5, 3, 7); the row's scale and bias go to LDS beside them, written by the thread
-    // that holds the first word of the group
-    // the staged K words of this thread go to LDS as they are, 16 (or 8) bytes per store: 16 consecutive lanes
-    // are 16 consecutive tokens, whose rows start 4 x odd banks apart
-    auto store_codes = [&](uint32_t *dst, const uint32_t (&raw)[SK::WPT], bool ok) {
-        if constexpr (SK::WPT % 4 == 0) {
-#pragma unroll
-            for (int w = 0; w < SK::WPT; w += 4)
-                *reinterpret_cast<uint4 *>(dst + w) =
-                    ok ? make_uint4(raw[w], raw[w + 1], raw[w + 2], raw[w + 3]) : make_uint4(0u, 0u, 0u, 0u);
-        } else {
-            *reinterpret_cast<uint2 *>(dst) = ok ? make_uint2(raw[0], raw[1]) : make_uint2(0u, 0u);
-        }
-    };
-    // a code word as the A operand of a matrix instruction: the nibbles masked in place are binary16 subnormals
-    // c 2^-24 (dims 0, 4, 2, 6 of the word) and 16 c 2^-24 (dims 1, 5, 3, 7)
-    auto code_operand = [&](uint32_t w) {
-        const uint32_t w8 = w >> 8;
-        return __builtin_bit_cast(half8_t, make_uint4(w & 0x000F000Fu, w & 0x00F000F0u, w8 & 0x000F000Fu, w8 & 0x00F000F0u));
-    };
-    const bool k_params_writer = k_on && (k_w0 * 8) % kGroup == 0;
-    auto store_k_params = [&](int b, const RowDequant &r) {
-        ks_lds[b][k_grp * kTile + k_tok] = r.s2.x;
-        kb_lds[b][k_tok * 8 + k_grp] = r.b2.x;
-        kb_lds[b][k_tok * 8 + 4 + k_grp] = r.b2.x;
-    };
     if constexpr (GK < 4) { // bias slots of groups the rows do not have: zero once (their q sums are zero too)
-        for (int i = tid; i < 2 * kTile * 8 / 2; i += kThreads) reinterpret_cast<uint32_t *>(&kb_lds[0][0])[i] = 0u;
+        for (int i = threadIdx.x; i < 2 * TILE * 8 / 2; i += kChunkThreads) reinterpret_cast<uint32_t *>(&kb_lds[0][0])[i] = 0u;
         __syncthreads();
     }
-    // rows of an unreachable block and rows at or past t_end (never visible, possibly never written) become zeros,
-    // so that no stale bit pattern can reach an accumulator
-    auto row_ok = [&](int t0, int tok, bool ok_tile) { return ok_tile && (t0 + tok < t_end); };
-    const int k_dst = k_tok * KPITCH + k_w0, v_dst = v_tok * VPITCH + v_w0 * 8;
 
-    // transposing read of V_hat: this lane's address inside a tile for (16-dim tile 0, 32-token block 0, first
-    // half): token 4 kb + (lane % 16) / 4, dims 4 (lane % 4) ..
-    const int v_lane = (4 * kb + qn / 4) * VPITCH + 4 * (qn % 4);
-
-    // One barrier per tile: tile i is multiplied out of buffer i % 2 while tile i + 1 (already in registers) is
-    // unpacked into the other buffer and tile i + 2 is fetched.
-    bool ok_next = false, ok_cur = false;
-    int buf = 0;
-    const int t_last = t_begin < t_end ? t_begin + (t_end - 1 - t_begin) / kTile * kTile : 0; // start of the last tile
-    if (t_begin < t_end) {
-        load_tile(t_begin, ok_next);
-        const RowDequant kr = row_params(ksb, row_ok(t_begin, k_tok, ok_next));
-        const RowDequant vr = row_params(vsb, row_ok(t_begin, v_tok, ok_next));
-        if (k_on) store_codes(k_lds[0] + k_dst, kraw, kr.ok);
-        if (k_params_writer) store_k_params(0, kr);
-        if (v_on) {
-#pragma unroll
-            for (int w = 0; w < SV::WPT; ++w) store_word(v_lds[0] + v_dst + 8 * w, vraw[w], vr);
+    const int range_begin = x;
+    while (x < x1) {
+        // Everything derived from the thread's index is worked out anew for every part: kept from one to the next (the
+        // compiler would lift it out of this loop) it costs two dozen registers that the tile loop does not have.
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & (kWave - 1), qn = lane % 32, h = lane / 32;
+        ChunkUnit u;
+        int begin = 0, tiles = 0, part_end, n;
+        if (p.stream) {
+            u = stream.locate(p, x, begin, tiles, n);
+            part_end = min(tiles, begin + (x1 - x));
+        } else {
+            const int slot = blockIdx.x / kXcds, xcd = blockIdx.x % kXcds;
+            const int unit = slot / p.q_tiles * kXcds + xcd;
+            if (unit >= p.layers_in_call * p.num_agents * p.kv_heads) return;
+            u.qt = slot % p.q_tiles;
+            u.kvh = unit % p.kv_heads;
+            u.agent = unit / p.kv_heads % p.num_agents;
+            u.li = unit / (p.kv_heads * p.num_agents);
+            part_end = 1;
+            n = scalar(clamped_length(p, u.agent));
         }
-        ok_cur = ok_next;
-        if (t_begin + kTile < t_end) load_tile(t_begin + kTile, ok_next);
-    }
-    __syncthreads();
-    for (int t0 = t_begin; t0 < t_end; t0 += kTile) {
-        const uint32_t *k_cur = k_lds[buf];
-        const half_t *v_cur = v_lds[buf];
+        const int layer = p.layer_begin + u.li;
+        const int window = p.per_layer_windows ? p.layer_window[u.li] : p.window;
+        int t_begin, t_end;
+        visible_range<QPOS, TILE>(p, n, window, u.qt, t_begin, t_end);
+        const int part_t0 = t_begin + begin * TILE;
+        const int part_t1 = p.stream ? min(t_end, t_begin + part_end * TILE) : t_end; // exclusive; may be <= part_t0
 
-        // ---- S^T = sum_g s_g (C_g Q_g^T) + b Qsum^T : [64 tokens][16 QT query rows] per wave, binary32, in units of
-        // 2^-24.  An item is one (group, 16-token tile): two matrix instructions per query tile over the group's 64
-        // dims into a fresh accumulator; while they run, the item before meets its scales (one fused multiply-add
-        // per score).  Operands and scales are fetched two items ahead; the next tile's K rows go registers -> LDS
-        // (other buffer) between the items.  Past the last tile that stores zeros into the idle buffer:
-        // straight-line code keeps the mix.
-        const bool ok_this = ok_cur;
-        const bool more = t0 + kTile < t_end;
-        const RowDequant kr = row_params(ksb, row_ok(t0 + kTile, k_tok, ok_next && more));
-        const RowDequant vr = row_params(vsb, row_ok(t0 + kTile, v_tok, ok_next && more));
-        const half_t *ks_cur = ks_lds[buf], *kb_cur = kb_lds[buf];
-        const float4_t zero4 = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        float4_t st[QT][kTile / 16]; // [q tile][token tile]: lane column = query row, regs = tokens 4*kb .. 4*kb+3
+        // ---- KV tile staging: raw Q4 in registers one tile ahead.  A thread takes WPT consecutive words of one token's
+        // K row and (the same ones when the rows are equally wide) of one token's V row; with rows that do not divide
+        // evenly the last waves stage nothing
+        const int32_t *table = p.block_table + (int64_t)u.agent * p.max_blocks;
+        uint32_t kraw[SK::WPT], vraw[SV::WPT];
+        uint32_t ksb[2], vsb[2]; // scale / bias bits of the group this thread unpacks
+        // 16 consecutive lanes take 16 consecutive tokens (and the same part of the row): their 16-byte LDS stores of K
+        // then fall into 16 different bank groups, like the operand reads
+        const bool k_on = SK::ACTIVE == kChunkThreads || tid < SK::ACTIVE, v_on = SV::ACTIVE == kChunkThreads || tid < SV::ACTIVE;
+        const int k_tok = k_on ? (tid % 16) + 16 * (tid / (16 * SK::TPR)) : 0, k_w0 = k_on ? ((tid / 16) % SK::TPR) * SK::WPT : 0;
+        const int v_tok = v_on ? (tid % 16) + 16 * (tid / (16 * SV::TPR)) : 0, v_w0 = v_on ? ((tid / 16) % SV::TPR) * SV::WPT : 0;
+        const int k_grp = (k_w0 * 8) / kGroup, v_grp = (v_w0 * 8) / kGroup;
+        const uint32_t k_off = 4 * (k_tok * SK::WORDS + k_w0), v_off = 4 * (v_tok * SV::WORDS + v_w0);
+        const uint32_t k_poff = 2 * (k_tok * GK + k_grp), v_poff = 2 * (v_tok * GV + v_grp);
+        // A block id outside the pool: the tile's (unconditional) loads go to the agent's own first block instead -- to
+        // block 0 only if that id is outside the pool as well -- and everything they bring is discarded.
+        const int own0 = scalar(table[0]);
+        const int fallback_blk = own0 >= 0 && own0 < p.num_blocks ? own0 : 0;
+        auto block_of = [&](int t0) { // fetched well before it is needed: a trip to memory in the tile loop otherwise
+            const int bi = t0 / kBlockTokens;
+            return bi < p.max_blocks ? table[bi] : -1;
+        };
+        auto tile_row0 = [&](int t0, int entry, bool &ok) {
+            const int blk = scalar(entry);
+            ok = blk >= 0 && blk < p.num_blocks;
+            return (((int64_t)layer * p.num_blocks + (ok ? blk : fallback_blk)) * p.kv_heads + u.kvh) * kBlockTokens + (t0 % kBlockTokens);
+        };
+        auto load_words = [&](const uint32_t *src, auto &dst) {
+            constexpr int N = sizeof(dst) / sizeof(uint32_t);
+            if constexpr (N % 4 == 0) {
 #pragma unroll
-        for (int tt = 0; tt < kTile / 16; ++tt) { // bias term: A = b[token][group slots], B = group sums of q
-            const half8_t ba = *reinterpret_cast<const half8_t *>(kb_cur + (tt * 16 + qn) * 8);
+                for (int i = 0; i < N / 4; ++i) {
+                    const uint4 t = *reinterpret_cast<const uint4 *>(src + 4 * i);
+                    dst[4 * i] = t.x; dst[4 * i + 1] = t.y; dst[4 * i + 2] = t.z; dst[4 * i + 3] = t.w;
+                }
+            } else {
+                const uint2 t = *reinterpret_cast<const uint2 *>(src);
+                dst[0] = t.x; dst[1] = t.y;
+            }
+        };
+        // a uniform base and a 32-bit byte offset per lane
+        auto at = [](auto *base, uint32_t byte_off) {
+            asm volatile("" : "+v"(byte_off)); // else base + offset is kept as one 64-bit pointer per lane and array
+            return reinterpret_cast<decltype(base)>(reinterpret_cast<const char *>(base) + byte_off);
+        };
+        // threads without a share load row 0 of the tile again (a valid address) and never store
+        auto load_k = [&](int64_t row0) {
+            load_words(at(p.k_codes + row0 * SK::WORDS, k_off), kraw);
+            ksb[0] = *at(p.k_scale + row0 * GK, k_poff);
+            ksb[1] = *at(p.k_bias + row0 * GK, k_poff);
+        };
+        auto load_v = [&](int64_t row0) {
+            load_words(at(p.v_codes + row0 * SV::WORDS, v_off), vraw);
+            vsb[0] = *at(p.v_scale + row0 * GV, v_poff);
+            vsb[1] = *at(p.v_bias + row0 * GV, v_poff);
+        };
+        // Dequantization of the staged rows happens one code word (8 dims, one 16-byte store) at a time, so that the
+        // matrix loops below can take a word between their steps.  Rows of an unreachable block and rows at or past
+        // t_end (never visible, possibly never written) become zeros, so that no stale bit pattern can reach an
+        // accumulator.
+        struct RowDequant {
+            half2_t s2, s16, b2;
+            bool ok;
+        };
+        auto row_params = [&](const uint32_t (&sb)[2], bool ok) {
+            RowDequant r;
+            // bfloat16 parameters of binary16-range data convert exactly (8 significant bits into 11) unless they are
+            // below 2^-14, where the difference is far below what binary16 operands resolve anyway
+            const half_t s_in = BF ? (half_t)bf16_bits_to_float((uint16_t)sb[0]) : __builtin_bit_cast(half_t, (uint16_t)sb[0]);
+            const half_t b_in = BF ? (half_t)bf16_bits_to_float((uint16_t)sb[1]) : __builtin_bit_cast(half_t, (uint16_t)sb[1]);
+            const half_t s = ok ? s_in : (half_t)0.0f;
+            const half_t b = ok ? b_in : (half_t)0.0f;
+            r.s2 = half2_t{s, s};
+            r.b2 = half2_t{b, b};
+            r.s16 = r.s2 * half2_t{(half_t)0.0625f, (half_t)0.0625f};
+            r.ok = ok;
+            return r;
+        };
+        auto store_word = [&](half_t *dst, uint32_t raw, const RowDequant &r) {
+            const uint32_t word = r.ok ? raw : 0u, w8 = word >> 8;
+            const half2_t v0 = pk_fma(nibbles_lo(word), r.s2, r.b2);    // dims 0, 4
+            const half2_t v1 = pk_fma(nibbles_hi16(word), r.s16, r.b2); // dims 1, 5
+            const half2_t v2 = pk_fma(nibbles_lo(w8), r.s2, r.b2);      // dims 2, 6
+            const half2_t v3 = pk_fma(nibbles_hi16(w8), r.s16, r.b2);   // dims 3, 7
+            *reinterpret_cast<uint4 *>(dst) = make_uint4(half2_to_bits(v0), half2_to_bits(v1), half2_to_bits(v2), half2_to_bits(v3));
+        };
+        auto store_codes = [&](uint32_t *dst, const uint32_t (&raw)[SK::WPT], bool ok) {
+            if constexpr (SK::WPT % 4 == 0) {
 #pragma unroll
-            for (int qi = 0; qi < QT; ++qi) st[qi][tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ba, qsop[qi], zero4, 0, 0, 0);
+                for (int w = 0; w < SK::WPT; w += 4)
+                    *reinterpret_cast<uint4 *>(dst + w) =
+                        ok ? make_uint4(raw[w], raw[w + 1], raw[w + 2], raw[w + 3]) : make_uint4(0u, 0u, 0u, 0u);
+            } else {
+                *reinterpret_cast<uint2 *>(dst) = ok ? make_uint2(raw[0], raw[1]) : make_uint2(0u, 0u);
+            }
+        };
+        // a code word as the A operand of a matrix instruction: the nibbles masked in place are binary16 subnormals
+        // c 2^-24 (dims 0, 4, 2, 6 of the word) and 16 c 2^-24 (dims 1, 5, 3, 7)
+        auto code_operand = [&](uint32_t w) {
+            const uint32_t w8 = w >> 8;
+            return __builtin_bit_cast(half8_t, make_uint4(w & 0x000F000Fu, w & 0x00F000F0u, w8 & 0x000F000Fu, w8 & 0x00F000F0u));
+        };
+        // scale and bias of a K row go to LDS beside the codes, written by the thread that holds the first word of the
+        // group; token t of a 32-token half is score register 4 (2 (t/16) + t%2) + (t%8)/2 of half (t%16)/8 of the wave
+        const bool k_params_writer = k_on && (k_w0 * 8) % kGroup == 0;
+        const int ks_dst = k_grp * TILE + (k_tok / kSub) * kSub + ((k_tok % 16) / 8) * 16 +
+                           4 * (2 * ((k_tok % kSub) / 16) + k_tok % 2) + (k_tok % 8) / 2;
+        auto store_k_params = [&](int b, const RowDequant &r) {
+            ks_lds[b][ks_dst] = r.s2.x;
+            kb_lds[b][k_tok * 8 + k_grp] = r.b2.x;
+            kb_lds[b][k_tok * 8 + 4 + k_grp] = r.b2.x;
+        };
+        auto row_ok = [&](int t0, int tok, bool ok_tile) { return ok_tile && (t0 + tok < t_end); };
+        const int k_dst = k_tok * KPITCH + k_w0, v_dst = v_tok * VPITCH + v_w0 * 8;
+
+        // the first tile is on its way while the queries are read
+        const int t_last = part_t0 < part_t1 ? part_t0 + (part_t1 - 1 - part_t0) / TILE * TILE : 0; // start of the last tile
+        const int second = min(part_t0 + TILE, t_last);
+        bool ok_next = false, ok_cur = false;
+        int64_t row_b = 0;
+        if (part_t0 < part_t1) {
+            const int entry0 = block_of(part_t0), entry1 = block_of(second);
+            const int64_t row_a = tile_row0(part_t0, entry0, ok_cur);
+            row_b = tile_row0(second, entry1, ok_next);
+            load_k(row_a);
+            load_v(row_a);
         }
-        // TPI token tiles per item.  One: the two dependent matrix instructions of an item follow each other
-        // directly, which measured faster than pairing token tiles for two independent chains (742 against 732
-        // TFLOP/s at D = 256) because the operand ring stays small.
-        constexpr int TPI = 1;
-        constexpr int kItemsPerGroup = kTile / 16 / TPI;
-        constexpr int kItems = GK * kItemsPerGroup;
-        constexpr int kAhead = 1; // items the operand reads run ahead (1: 757, 2: 750, 3: 750 TFLOP/s at D = 256)
-        struct ItemIn {
-            uint32_t a0[TPI], a1[TPI]; // code words of token 16 tt + qn: dims 64 g + 8 kb .. and 64 g + 32 + 8 kb ..
-            uint2 s4[TPI];            // scales of tokens 16 tt + 4 kb .. + 3, group g
-        };
-        auto load_item = [&](int it) {
-            const int g = it / kItemsPerGroup, tt0 = (it % kItemsPerGroup) * TPI;
-            ItemIn in;
+
+        // ---- this lane's query row: column qn of its wave's 32 (both halves of the wave hold the same row)
+        const int c = u.qt * QPOS + (rg * kRowsWave + qn) / NREP, head = u.kvh * NREP + (rg * kRowsWave + qn) % NREP;
+        const bool wave_live = u.qt * QPOS + rg * kRowsWave / NREP < p.q_len; // the wave's first row; wave-uniform
+        // rows past the chunk repeat its last position (and are not stored)
+        auto row_sees = [&](int pos) { return n - (p.q_len - 1 - min(pos, p.q_len - 1)); };
+        auto row_hides = [&](int vis) { return window > 0 && vis > window ? vis - window : 0; };
+        const int row_vis = row_sees(c), row_first = row_hides(row_vis);
+        // tokens inside [all_first, all_vis) are visible to every row of this wave and need no masks
+        const int all_vis = row_sees(u.qt * QPOS + rg * kRowsWave / NREP);
+        const int all_first = row_hides(row_sees(u.qt * QPOS + (rg * kRowsWave + kRowsWave - 1) / NREP));
+        const int64_t q_row = (((int64_t)u.li * p.num_agents + u.agent) * p.q_len + min(c, p.q_len - 1)) * p.q_heads + head;
+        half8_t qop[QREG][4]; // [group][matrix instruction]: the 8 dims of word 8 g + 4 h + i
+        half8_t qsop;         // lower half of the wave: group sums of q, high parts in slots 0..3, low parts in 4..7; else 0
+        {
+            float qs[GK];
+            const uint16_t *src = p.q + q_row * DK + 32 * h;
 #pragma unroll
-            for (int j = 0; j < TPI; ++j) {
-                const uint32_t *row = k_cur + ((tt0 + j) * 16 + qn) * KPITCH + 8 * g + kb;
-                in.a0[j] = row[0];
-                in.a1[j] = row[4];
-                in.s4[j] = *reinterpret_cast<const uint2 *>(ks_cur + g * kTile + (tt0 + j) * 16 + 4 * kb);
-            }
-            return in;
-        };
-        ItemIn item[kAhead + 1];
+            for (int g = 0; g < GK; ++g) {
+                qs[g] = 0.0f;
 #pragma unroll
-        for (int it = 0; it < kAhead; ++it) item[it] = load_item(it);
-        float4_t dq[2][TPI][QT]; // raw group products of the item in flight and of the one before
-        uint2 s_prev[TPI];
-#pragma unroll
-        for (int it = 0; it <= kItems; ++it) {
-            if (it + kAhead < kItems) item[(it + kAhead) % (kAhead + 1)] = load_item(it + kAhead);
-            if (it < kItems) {
-                const int g = it / kItemsPerGroup;
-                const ItemIn &in = item[it % (kAhead + 1)];
-#pragma unroll
-                for (int j = 0; j < TPI; ++j)
-#pragma unroll
-                    for (int qi = 0; qi < QT; ++qi)
-                        dq[it & 1][j][qi] = __builtin_amdgcn_mfma_f32_16x16x32_f16(code_operand(in.a0[j]), qop[qi][2 * g], zero4, 0, 0, 0);
-#pragma unroll
-                for (int j = 0; j < TPI; ++j)
-#pragma unroll
-                    for (int qi = 0; qi < QT; ++qi)
-                        dq[it & 1][j][qi] =
-                            __builtin_amdgcn_mfma_f32_16x16x32_f16(code_operand(in.a1[j]), qop[qi][2 * g + 1], dq[it & 1][j][qi], 0, 0, 0);
-            }
-            if (it > 0) { // the item before: scores += scale * product
-                const int g = (it - 1) / kItemsPerGroup, tt0 = ((it - 1) % kItemsPerGroup) * TPI;
-#pragma unroll
-                for (int j = 0; j < TPI; ++j) {
-                    const half2_t s01 = bits_to_half2(s_prev[j].x), s23 = bits_to_half2(s_prev[j].y);
-#pragma unroll
-                    for (int qi = 0; qi < QT; ++qi) {
-                        float4_t acc = st[qi][tt0 + j];
-                        if (g == 0) acc = acc * 0x1p-24f; // the bias term enters in the products' unit
-                        const float4_t d = dq[(it - 1) & 1][j][qi];
-                        acc[0] = fmaf((float)s01.x, d[0], acc[0]);
-                        acc[1] = fmaf((float)s01.y, d[1], acc[1]);
-                        acc[2] = fmaf((float)s23.x, d[2], acc[2]);
-                        acc[3] = fmaf((float)s23.y, d[3], acc[3]);
-                        st[qi][tt0 + j] = acc;
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    // 8 dims in the order the nibble masks emit them: 0,4,1,5,2,6,3,7; the odd ones divided by 16
+                    // because their codes arrive 16 times larger
+                    const uint4 raw = *reinterpret_cast<const uint4 *>(src + kGroup * g + 8 * i);
+                    const half2_t e01 = bits_to_half2(raw.x), e23 = bits_to_half2(raw.y);
+                    const half2_t e45 = bits_to_half2(raw.z), e67 = bits_to_half2(raw.w);
+                    const half_t sixteenth = (half_t)0.0625f;
+                    const half8_t v = half8_t{e01.x, e45.x, e01.y * sixteenth, e45.y * sixteenth,
+                                              e23.x, e67.x, e23.y * sixteenth, e67.y * sixteenth};
+                    qs[g] += ((float)e01.x + (float)e01.y) + ((float)e23.x + (float)e23.y) +
+                             ((float)e45.x + (float)e45.y) + ((float)e67.x + (float)e67.y);
+                    if (g < QREG) qop[g < QREG ? g : 0][i] = v;
+                    else if (my_sub == 0) q_lds[((g - QREG) * 4 + i) * QROWS + rg * kWave + lane] = v;
                 }
             }
-            if (it < kItems) {
+            half_t part[8];
 #pragma unroll
-                for (int j = 0; j < TPI; ++j) s_prev[j] = item[it % (kAhead + 1)].s4[j];
+            for (int g = 0; g < 4; ++g) {
+                const float v = g < GK ? xor32_sum(qs[g < GK ? g : 0]) : 0.0f;
+                const half_t hi = (half_t)v;
+                part[g] = h == 0 ? hi : (half_t)0.0f;
+                part[4 + g] = h == 0 ? (half_t)(v - (float)hi) : (half_t)0.0f;
             }
-            if (it == 0 && k_on) store_codes(k_lds[buf ^ 1] + k_dst, kraw, kr.ok); // the next tile's K words
-            if (it == 1 && k_params_writer) store_k_params(buf ^ 1, kr);
-            __builtin_amdgcn_sched_barrier(0);
+            qsop = half8_t{part[0], part[1], part[2], part[3], part[4], part[5], part[6], part[7]};
         }
-        const float zscale = p.score_scale * 16777216.0f; // scores are in units of 2^-24
+        float16_t o_acc[DTILES]; // O^T: lane column = query row, register i = row position 8 (i/4) + 4 h + i%4
+#pragma unroll
+        for (int d = 0; d < DTILES; ++d)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o_acc[d][i] = 0.0f;
+        // m_run: the reference the exponentials are taken against.  It moves only when a tile's maximum exceeds it by
+        // more than kSlack (log2 units), so the accumulators are rescaled a few times per row, not once per tile.
+        constexpr float kSlack = 3.0f;
+        float m_run = kNegBig, l_run = 0.0f; // l_run: this lane's tokens only
 
-        // ---- online softmax per query row (lane column), then P^T in binary16 as the next B operand
-        const bool masked = !(ok_this && t0 >= all_first && t0 + kTile <= all_vis); // wave-uniform
-        const bool general = masked || !(p.score_scale > 0.0f); // the path that assumes nothing
-        half8_t pt[QT][kTile / 32]; // [q tile][32-token block]: tokens 4*kb..+3 of both 16-token tiles of the block
-        bool any_moved = false;
-        float alpha[QT];
+        // operand reads: K row of M row qn; V_hat by the transposing read (token 8 h + 2 e (+ 1), dims 16 (lane/16 % 2) + 4 c)
+        const int m_token = 16 * (qn / 16) + 8 * ((qn / 4) % 2) + 2 * (qn % 4) + (qn / 8) % 2;
+        const int k_lane = m_token * KPITCH + 4 * h;
+        const int v_lane = (8 * h + 2 * ((lane % 16) / 4)) * VPITCH + 16 * ((lane / 16) % 2) + 4 * (lane % 4);
+
+        // One barrier per tile: tile i is multiplied out of buffer i % 2 while tile i + 1 (already in registers) is
+        // unpacked into the other buffer and tile i + 2 is fetched.
+        int buf = 0;
+        if (part_t0 < part_t1) {
+            const RowDequant kr = row_params(ksb, row_ok(part_t0, k_tok, ok_cur));
+            const RowDequant vr = row_params(vsb, row_ok(part_t0, v_tok, ok_cur));
+            if (k_on) store_codes(k_lds[0] + k_dst, kraw, kr.ok);
+            if (k_params_writer) store_k_params(0, kr);
+            if (v_on) {
 #pragma unroll
-        for (int qi = 0; qi < QT; ++qi) {
-            float mx = kNegBig;
-            if (general) {
+                for (int w = 0; w < SV::WPT; ++w) store_word(v_lds[0] + v_dst + 8 * w, vraw[w], vr);
+            }
+            load_k(row_b);
+            load_v(row_b);
+        }
+        __syncthreads();
+        for (int t0 = part_t0; t0 < part_t1; t0 += TILE) {
+            const uint32_t *k_cur = k_lds[buf];
+            const half_t *v_cur = v_lds[buf], *ks_cur = ks_lds[buf], *kb_cur = kb_lds[buf];
+            const bool ok_this = ok_cur;
+            const bool more = t0 + TILE < part_t1;
+            const int t_ahead = min(t0 + 2 * TILE, t_last), entry_ahead = block_of(t_ahead); // past the end: the last tile again, never used
+            int64_t row_ahead = 0;
+            bool ok_ahead = false;
+
+            // One 32-token half of the tile: scores, softmax, product with V_hat.  `half`: which of this wave's halves
+            // (compile time), sub: which of the tile's
+            constexpr int HALVES = TILE / kSub / KSPLIT;
+            auto take_half = [&](auto half_c, int sub) {
+                constexpr int half = decltype(half_c)::value;
+                const int ts = t0 + kSub * sub;
+                const uint32_t *k_row = k_cur + sub * kSub * KPITCH + k_lane;
+                const half_t *ks_row = ks_cur + sub * kSub + 16 * h;
+                // ---- S^T = sum_g s_g (C_g Q_g^T) + b Qsum^T in binary32, in units of 2^-24
+                float16_t zero;
 #pragma unroll
-                for (int tt = 0; tt < kTile / 16; ++tt)
+                for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
+                const half8_t ba = *reinterpret_cast<const half8_t *>(kb_cur + (sub * kSub + m_token) * 8);
+                float16_t st = __builtin_amdgcn_mfma_f32_32x32x16_f16(ba, qsop, zero, 0, 0, 0);
+                auto q_operand = [&](int k) { // matrix instruction k = 4 group + i
+                    if (k / 4 < QREG) return qop[k / 4 < QREG ? k / 4 : 0][k % 4];
+                    return q_lds[(k - 4 * QREG) * QROWS + rg * kWave + lane];
+                };
+                uint4 words = *reinterpret_cast<const uint4 *>(k_row); // code words 8 g + 4 h .. + 3 of this lane's token
+                half8_t qk = q_operand(0);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        float z = st[qi][tt][e] * zscale;
-                        const int t = t0 + tt * 16 + 4 * kb + e;
-                        if (!(ok_this && t < row_vis[qi] && t >= row_first[qi])) z = kNegBig;
-                        st[qi][tt][e] = z;
+                for (int g = 0; g < GK; ++g) {
+                    const uint32_t w[4] = {words.x, words.y, words.z, words.w};
+                    float16_t d = zero;
+                    uint4 sc, sc1; // scales of the lane's first and last 8 scores
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const half8_t qi = qk;
+                        if (4 * g + i + 1 < 4 * GK) qk = q_operand(4 * g + i + 1);
+                        if (i == 2) sc = *reinterpret_cast<const uint4 *>(ks_row + g * TILE);
+                        if (i == 3) sc1 = *reinterpret_cast<const uint4 *>(ks_row + g * TILE + 8);
+                        if (i == 3 && g + 1 < GK) words = *reinterpret_cast<const uint4 *>(k_row + 8 * (g + 1));
+                        d = __builtin_amdgcn_mfma_f32_32x32x16_f16(code_operand(w[i]), qi, d, 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const uint32_t s2 = i % 8 < 2 ? sc.x : (i % 8 < 4 ? sc.y : (i % 8 < 6 ? sc.z : sc.w));
+                        const half2_t sh = bits_to_half2(s2);
+                        const float prev = g == 0 ? st[i] * 0x1p-24f : st[i]; // the bias term enters in the products' unit
+                        st[i] = fmaf((float)((i & 1) ? sh.y : sh.x), d[i], prev);
+                        if (i == 7) sc = sc1;
+                    }
+                    // pinned: else the multiplies of all groups sink to the scores' first use and every product stays live
+#pragma unroll
+                    for (int i = 0; i < 16; i += 8)
+                        asm volatile("" : "+v"(st[i]), "+v"(st[i + 1]), "+v"(st[i + 2]), "+v"(st[i + 3]), "+v"(st[i + 4]), "+v"(st[i + 5]),
+                                     "+v"(st[i + 6]), "+v"(st[i + 7]));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                const float zscale = p.score_scale * 16777216.0f; // scores are in units of 2^-24
+
+                // ---- online softmax per query row (lane column), then P^T in binary16 as the next B operand
+                const bool masked = !(ok_this && ts >= all_first && ts + kSub <= all_vis); // wave-uniform
+                const bool general = masked || !(p.score_scale > 0.0f); // the path that assumes nothing
+                float mx = kNegBig;
+                if (general) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        float z = st[i] * zscale;
+                        const int t = ts + 16 * (i / 8) + 8 * h + 2 * (i % 4) + ((i / 4) & 1);
+                        if (!(ok_this && t < row_vis && t >= row_first)) z = kNegBig;
+                        st[i] = z;
                         mx = fmaxf(mx, z);
                     }
-            } else { // interior tile, positive scale: the maximum can be taken before the scale is applied
+                } else { // interior, positive scale: the maximum can be taken before the scale is applied
 #pragma unroll
-                for (int tt = 0; tt < kTile / 16; ++tt)
+                    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, st[i]);
+                    mx *= zscale;
+                }
+                mx = xor32_max(mx); // the row's tokens live in two lanes
+                const bool moved = mx > m_run + kSlack;
+                const float m_new = moved ? mx : m_run;
+                float sum = 0.0f;
+                if (general) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) mx = fmaxf(mx, st[qi][tt][e]);
-                mx *= zscale;
-            }
-            // the row's tokens live in the 4 lanes qn, qn+16, qn+32, qn+48
-            mx = xor32_max(xor16_max(mx));
-            const bool moved = mx > m_run[qi] + kSlack;
-            const float m_new = moved ? mx : m_run[qi];
-            alpha[qi] = moved ? __builtin_amdgcn_exp2f(m_run[qi] - m_new) : 1.0f;
-            any_moved |= moved;
-            m_run[qi] = m_new;
-            float sum = 0.0f;
-            if (general) {
-#pragma unroll
-                for (int tt = 0; tt < kTile / 16; ++tt)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        float pr = __builtin_amdgcn_exp2f(st[qi][tt][e] - m_new);
-                        pr = st[qi][tt][e] > 0.5f * kNegBig ? pr : 0.0f; // also a row with nothing visible yet
-                        st[qi][tt][e] = pr;
+                    for (int i = 0; i < 16; ++i) {
+                        float pr = __builtin_amdgcn_exp2f(st[i] - m_new);
+                        pr = st[i] > 0.5f * kNegBig ? pr : 0.0f; // also a row with nothing visible yet
+                        st[i] = pr;
                         sum += pr;
                     }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const float pr = __builtin_amdgcn_exp2f(fmaf(st[i], zscale, -m_new));
+                        st[i] = pr;
+                        sum += pr;
+                    }
+                }
+                half8_t pt[2]; // [16-token step]
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+                    pt[s] = half8_t{(half_t)st[8 * s], (half_t)st[8 * s + 1], (half_t)st[8 * s + 2], (half_t)st[8 * s + 3],
+                                    (half_t)st[8 * s + 4], (half_t)st[8 * s + 5], (half_t)st[8 * s + 6], (half_t)st[8 * s + 7]};
+                if (__builtin_amdgcn_ballot_w64(moved) != 0ull) { // rare after a row's first tiles
+                    const float alpha = moved ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.0f;
+                    l_run *= alpha;
+#pragma unroll
+                    for (int d = 0; d < DTILES; ++d)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) o_acc[d][i] *= alpha;
+                }
+                m_run = m_new;
+                l_run += sum;
+
+                // ---- O^T += V_hat^T P^T, the operand reads one step ahead; the next tile's V rows are dequantized
+                // between the steps
+                const half_t *v_row = v_cur + sub * kSub * VPITCH + v_lane;
+                auto load_va = [&](int step) { // step = 2 * dim tile + 16-token step
+                    const half_t *src = v_row + (step & 1) * 16 * VPITCH + (step >> 1) * 32;
+                    const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)src);
+                    const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(src + VPITCH));
+                    return __builtin_bit_cast(half8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                };
+                // The next tile's words were asked for at the end of the tile before: they are not touched before this
+                // point, late in the tile, so that memory has most of a tile's time to answer.  Past the last tile the
+                // staging stores zeros into the idle buffer: straight-line code keeps the mix.
+                const RowDequant vr = row_params(vsb, row_ok(t0 + TILE, v_tok, ok_next && more));
+                constexpr int kSteps = 2 * DTILES, kAhead = 2;
+                half8_t va[kAhead];
+#pragma unroll
+                for (int s = 0; s < kAhead; ++s) va[s] = load_va(s);
+#pragma unroll
+                for (int s = 0; s < kSteps; ++s) {
+                    const half8_t a = va[s % kAhead];
+                    if (s + kAhead < kSteps) va[s % kAhead] = load_va(s + kAhead);
+                    o_acc[s >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pt[s & 1], o_acc[s >> 1], 0, 0, 0);
+                    // this half's share of the words (both shares, if this wave takes one half only)
+                    if (half == 0 && s == 0) {
+                        const RowDequant kr = row_params(ksb, row_ok(t0 + TILE, k_tok, ok_next && more));
+                        if (k_on) store_codes(k_lds[buf ^ 1] + k_dst, kraw, kr.ok);
+                        if (k_params_writer) store_k_params(buf ^ 1, kr);
+                        row_ahead = tile_row0(t_ahead, entry_ahead, ok_ahead); // the registers are free: the tile after that
+                        load_k(row_ahead);
+                    }
+                    constexpr int MINE = SV::WPT / HALVES;
+#pragma unroll
+                    for (int w = 0; w < MINE; ++w)
+                        if (w * kSteps / MINE == s && v_on)
+                            store_word(v_lds[buf ^ 1] + v_dst + 8 * (half * MINE + w), vraw[half * MINE + w], vr);
+                    if (half == HALVES - 1 && s == (MINE - 1) * kSteps / MINE + 1) load_v(row_ahead);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            if constexpr (KSPLIT == 2) {
+                take_half(std::integral_constant<int, 0>{}, my_sub);
             } else {
+                take_half(std::integral_constant<int, 0>{}, 0);
+                if constexpr (HALVES == 2) take_half(std::integral_constant<int, 1>{}, 1);
+            }
+            ok_cur = ok_next;
+            ok_next = ok_ahead;
+            __syncthreads(); // every wave is done with this buffer and has filled its part of the other
+            buf ^= 1;
+        }
+
+        float l_tot = xor32_sum(l_run);
+        if constexpr (KSPLIT == 2) {
+            // The upper half of the waves hands its sums to the lower one through the V buffers, a few dim tiles at a
+            // time; the maxima and denominators travel in the K buffers.
+            constexpr int MT = (int)(2 * TILE * VPITCH * sizeof(half_t) / (ROWGROUPS * kWave * 16 * sizeof(float))) < DTILES
+                                   ? (int)(2 * TILE * VPITCH * sizeof(half_t) / (ROWGROUPS * kWave * 16 * sizeof(float))) : DTILES;
+            static_assert(MT >= 1, "room for one dim tile");
+            float *ml = reinterpret_cast<float *>(&k_lds[0][0]);
+            float *xch = reinterpret_cast<float *>(&v_lds[0][0]);
+            if (my_sub == 1) {
+                ml[(rg * 2) * kWave + lane] = m_run;
+                ml[(rg * 2 + 1) * kWave + lane] = l_tot;
+            }
+            __syncthreads();
+            float w_lo = 1.0f, w_hi = 0.0f;
+            if (my_sub == 0) {
+                const float m_hi = ml[(rg * 2) * kWave + lane], l_hi = ml[(rg * 2 + 1) * kWave + lane];
+                const float m_new = fmaxf(m_run, m_hi);
+                w_lo = __builtin_amdgcn_exp2f(m_run - m_new);
+                w_hi = __builtin_amdgcn_exp2f(m_hi - m_new);
+                l_tot = fmaf(l_hi, w_hi, l_tot * w_lo);
+                m_run = m_new;
+            }
 #pragma unroll
-                for (int tt = 0; tt < kTile / 16; ++tt)
+            for (int d0 = 0; d0 < DTILES; d0 += MT) {
+                if (my_sub == 1) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float pr = __builtin_amdgcn_exp2f(fmaf(st[qi][tt][e], zscale, -m_new));
-                        st[qi][tt][e] = pr;
-                        sum += pr;
+                    for (int d = d0; d < d0 + MT && d < DTILES; ++d)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            *reinterpret_cast<float4_t *>(xch + (((rg * MT + d - d0) * 4 + j) * kWave + lane) * 4) =
+                                float4_t{o_acc[d][4 * j], o_acc[d][4 * j + 1], o_acc[d][4 * j + 2], o_acc[d][4 * j + 3]};
+                }
+                __syncthreads();
+                if (my_sub == 0) {
+#pragma unroll
+                    for (int d = d0; d < d0 + MT && d < DTILES; ++d)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const float4_t v = *reinterpret_cast<const float4_t *>(xch + (((rg * MT + d - d0) * 4 + j) * kWave + lane) * 4);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) o_acc[d][4 * j + e] = fmaf(v[e], w_hi, o_acc[d][4 * j + e] * w_lo);
+                        }
+                }
+                __syncthreads();
+            }
+        }
+
+        const bool whole = !p.stream || (begin == 0 && part_end == tiles);
+        if (wave_live && my_sub == 0) {
+            if (whole) { // ---- normalise and store
+                const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
+                // the row's place again, from values the compiler does not know to be the same: kept through the tile
+                // loop they would cost registers that it does not have
+                int ln = threadIdx.x & (kWave - 1);
+                asm volatile("" : "+v"(ln));
+                const int r = rg * kRowsWave + ln % 32, pos = u.qt * QPOS + r / NREP;
+                const bool store = pos < p.q_len;
+                uint16_t *dst = p.out + ((((int64_t)u.li * p.num_agents + u.agent) * p.q_len + pos) * p.q_heads + u.kvh * NREP + r % NREP) * DV;
+#pragma unroll
+                for (int d = 0; d < DTILES; ++d)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float a = o_acc[d][4 * j] * inv, b = o_acc[d][4 * j + 1] * inv;
+                        const float e = o_acc[d][4 * j + 2] * inv, f = o_acc[d][4 * j + 3] * inv;
+                        if (store) store_row_quad(dst + 32 * d + 8 * j, ln / 32, a, b, e, f);
                     }
+            } else { // ---- this workgroup's part of a shared unit, un-normalised
+                const int64_t rec = ((int64_t)worker * 2 + (x - begin > range_begin ? 1 : 0)) * ROWGROUPS + rg;
+                float *acc = p.part_acc + (rec * (DV / 8) * kWave + lane) * 4;
+#pragma unroll
+                for (int d = 0; d < DTILES; ++d)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        *reinterpret_cast<float4_t *>(acc + (d * 4 + j) * kWave * 4) =
+                            float4_t{o_acc[d][4 * j], o_acc[d][4 * j + 1], o_acc[d][4 * j + 2], o_acc[d][4 * j + 3]};
+                if (h == 0) *reinterpret_cast<float2 *>(p.part_ml + (rec * kRowsWave + qn) * 2) = make_float2(m_run, l_tot);
             }
-            l_run[qi] = fmaf(l_run[qi], alpha[qi], sum); // this lane's tokens only; lanes are added up at the end
-#pragma unroll
-            for (int tb = 0; tb < kTile / 32; ++tb)
-                pt[qi][tb] = half8_t{(half_t)st[qi][2 * tb][0], (half_t)st[qi][2 * tb][1], (half_t)st[qi][2 * tb][2],
-                                     (half_t)st[qi][2 * tb][3], (half_t)st[qi][2 * tb + 1][0], (half_t)st[qi][2 * tb + 1][1],
-                                     (half_t)st[qi][2 * tb + 1][2], (half_t)st[qi][2 * tb + 1][3]};
         }
-        if (__builtin_amdgcn_ballot_w64(any_moved) != 0ull) {
-            // Rare after a row's first tiles.  (This file is compiled with matrix results in vector registers, so
-            // the accumulators are ordinary operands here.)
-#pragma unroll
-            for (int qi = 0; qi < QT; ++qi)
-#pragma unroll
-                for (int et = 0; et < ETILES; ++et) o_acc[qi][et] = o_acc[qi][et] * alpha[qi];
+        if (p.stream && threadIdx.x == 0 && begin == 0 && part_end < tiles) {
+            ChunkShared *s = p.shared + worker;
+            s->slots = (x + tiles - 1) / per - worker + 1;
+            s->first_record = worker * 2 + (x > range_begin ? 1 : 0);
+            s->qt = u.qt;
+            s->kvh = u.kvh;
+            s->token_row = ((int64_t)u.li * p.num_agents + u.agent) * p.q_len;
         }
-
-        // ---- O^T += V_hat^T P^T : A operand = 8 tokens of one dim in P^T's token order (tokens 4 kb .. + 3 of
-        // both 16-token tiles of a 32-token block), fetched with two transposing reads one step ahead; the next
-        // tile's V rows are dequantized between the steps
-        constexpr int VA_AHEAD = 2; // steps the operand reads run ahead
-        half8_t va[VA_AHEAD + 1][2]; // [step in the ring][32-token block]
-        auto load_va = [&](int et) {
-#pragma unroll
-            for (int tb = 0; tb < kTile / 32; ++tb) {
-                const half_t *src = v_cur + v_lane + tb * 32 * VPITCH + et * 16;
-                const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)src);
-                const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(src + 16 * VPITCH));
-                va[et % (VA_AHEAD + 1)][tb] = __builtin_bit_cast(half8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-            }
-        };
-#pragma unroll
-        for (int et = 0; et < VA_AHEAD; ++et) load_va(et);
-#pragma unroll
-        for (int et = 0; et < ETILES; ++et) {
-            if (et + VA_AHEAD < ETILES) load_va(et + VA_AHEAD);
-#pragma unroll
-            for (int tb = 0; tb < kTile / 32; ++tb)
-#pragma unroll
-                for (int qi = 0; qi < QT; ++qi)
-                    o_acc[qi][et] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[et % (VA_AHEAD + 1)][tb], pt[qi][tb], o_acc[qi][et], 0, 0, 0);
-#pragma unroll
-            for (int w = 0; w < SV::WPT; ++w)
-                if (w * ETILES / SV::WPT == et && v_on) store_word(v_lds[buf ^ 1] + v_dst + 8 * w, vraw[w], vr);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        ok_cur = ok_next;
-        load_tile(min(t0 + 2 * kTile, t_last), ok_next); // past the end: the last tile again, never used
-        __syncthreads(); // every wave is done with this buffer and has filled its part of the other
-        buf ^= 1;
-    }
-
-    // ---- normalise and store: lane column = query row, regs = 4 consecutive row positions of V_hat, which hold
-    // dims (0,4,1,5) or (2,6,3,7) of an 8-dim word
-#pragma unroll
-    for (int qi = 0; qi < QT; ++qi) {
-        const float l_tot = xor32_sum(xor16_sum(l_run[qi]));
-        if (row_pos[qi] >= p.q_len) continue;
-        const int r_w = wave * kRowsWave + qi * 16 + qn;
-        const int head = kvh * NREP + r_w % NREP;
-        const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
-        uint16_t *dst = p.out + ((q_agent + row_pos[qi]) * p.q_heads + head) * DV;
-#pragma unroll
-        for (int et = 0; et < ETILES; ++et) {
-            uint16_t *d8 = dst + et * 16 + 8 * (kb / 2) + 2 * (kb % 2); // the word of 8 dims, dims 0.. or 2..
-            d8[0] = float_to_half_bits(o_acc[qi][et][0] * inv);
-            d8[4] = float_to_half_bits(o_acc[qi][et][1] * inv);
-            d8[1] = float_to_half_bits(o_acc[qi][et][2] * inv);
-            d8[5] = float_to_half_bits(o_acc[qi][et][3] * inv);
-        }
+        x += p.stream ? part_end - begin : 1;
     }
 }
 
-template <int DK, int DV, int NREP>
-hipError_t launch_chunk_t(const AttentionArgs &a, hipStream_t stream)
+// ---------------------------------------------------------------------------------------------- merging shared units
+
+constexpr int kMergeThreads = 256;
+constexpr int kMergeQuads = 4; // float4 pieces of a lane that a wave merges at a time
+
+// pieces a unit's merge is cut into: one wave each
+template <int DV, int ROWGROUPS>
+constexpr int merge_items() { return ROWGROUPS * (DV / 8 / kMergeQuads); }
+template <int DV, int ROWGROUPS>
+constexpr int merge_parts() { return merge_items<DV, ROWGROUPS>() / (kMergeThreads / kWave); }
+
+// The unit that begins in worker w's range and goes on past it: workgroups (w, part) merge its records in worker order.
+// Reading the records once is all there is to do, so every wave has four 16-byte loads of each record in flight.
+template <int DV, int NREP, int ROWGROUPS>
+__global__ __launch_bounds__(kMergeThreads) void chunk_merge_kernel(ChunkParams p)
 {
-    constexpr int QT = (DK == 128 || DK >= 256) ? 1 : 2; // two tiles where the registers allow it without scratch
-    constexpr int kThreads = kRowsWG / (16 * QT) * kWave;
+    constexpr int QPOS = ROWGROUPS * kRowsWave / NREP, PARTS = merge_parts<DV, ROWGROUPS>();
+    constexpr int kQuads = DV / 8; // float4 pieces per lane and record
+    static_assert(merge_items<DV, ROWGROUPS>() % (kMergeThreads / kWave) == 0, "whole workgroups");
+    const int worker = blockIdx.x / PARTS, part = blockIdx.x % PARTS;
+    const ChunkShared u = p.shared[worker];
+    if (u.slots == 0) return;
+    const int lane = threadIdx.x & (kWave - 1), wave = scalar(threadIdx.x / kWave), qn = lane % 32, h = lane / 32;
+    const int item = part * (kMergeThreads / kWave) + wave;
+    const int rg = item / (kQuads / kMergeQuads), quad0 = item % (kQuads / kMergeQuads) * kMergeQuads;
+    if (u.qt * QPOS + rg * kRowsWave / NREP >= p.q_len) return; // a row group past the chunk left no record
+    auto record = [&](int s) { return (int64_t)(s == 0 ? u.first_record : (worker + s) * 2) * ROWGROUPS + rg; };
+    auto max_and_sum = [&](int s) { return *reinterpret_cast<const float2 *>(p.part_ml + (record(s) * kRowsWave + qn) * 2); };
+    float m_ref = kNegBig;
+#pragma unroll 8
+    for (int s = 0; s < u.slots; ++s) {
+        const float2 ml = max_and_sum(s);
+        if (ml.y > 0.0f) m_ref = fmaxf(m_ref, ml.x);
+    }
+    float l = 0.0f;
+    float4_t o[kMergeQuads];
+#pragma unroll
+    for (int k = 0; k < kMergeQuads; ++k) o[k] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 2
+    for (int s = 0; s < u.slots; ++s) {
+        const float2 ml = max_and_sum(s);
+        const float4_t *src = reinterpret_cast<const float4_t *>(p.part_acc) + (record(s) * kQuads + quad0) * kWave + lane;
+        float4_t v[kMergeQuads];
+#pragma unroll
+        for (int k = 0; k < kMergeQuads; ++k) v[k] = src[k * kWave];
+        const float wgt = ml.y > 0.0f ? __builtin_amdgcn_exp2f(ml.x - m_ref) : 0.0f;
+        l = fmaf(ml.y, wgt, l);
+#pragma unroll
+        for (int k = 0; k < kMergeQuads; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[k][e] = fmaf(v[k][e], wgt, o[k][e]);
+    }
+    const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+    const int r = rg * kRowsWave + qn, c = u.qt * QPOS + r / NREP;
+    if (c >= p.q_len) return;
+    uint16_t *dst = p.out + ((u.token_row + c) * p.q_heads + u.kvh * NREP + r % NREP) * DV + 8 * quad0;
+#pragma unroll
+    for (int k = 0; k < kMergeQuads; ++k) store_row_quad(dst + 8 * k, h, o[k][0] * inv, o[k][1] * inv, o[k][2] * inv, o[k][3] * inv);
+}
+
+// ---------------------------------------------------------------------------------------------- launch
+
+// Rows per workgroup.  With 128 rows a tile costs about 0.6 of what it costs with 256 (its staging does not shrink), so
+// 128 are taken where 256 would be padding.  Measured (one layer, equal shares, 128 against 256 rows): 128 query rows of
+// 256-wide heads, ten agents of 4K-32K tokens 295 / 460 us; 384 rows, two agents of 4K 77 / 83 us; 280 rows of 128-wide
+// heads, four agents of up to 6K 62 / 60 us.
+int rows_per_workgroup(int rows)
+{
+    const int wide = (rows + 255) / 256, narrow = (rows + 127) / 128;
+    return 0.6 * narrow < wide ? 128 : 256;
+}
+
+// Whether a call's tiles are dealt out evenly over the compute units (needs a workspace) instead of one unit per
+// workgroup.  Measured (us, one unit per workgroup / equal shares): 256-wide heads, 512-token chunk, one agent of 300,
+// 2,000, 8,000 tokens 74 / 57, 187 / 72, 571 / 133; ten agents of 4K-32K (320 units) 2,130 / 1,842; six layers of ten
+// agents of 1K-1.5K (1,920 units) 1,191 / 1,145, twelve (3,840) 2,278 / 2,239; 128-wide heads, 16 tokens behind 8,000
+// 202 / 37.  With sixteen units per compute unit the hardware's own dispatch is as even, and at 256 tokens a unit has
+// too few tiles to share.
+bool stream_pays(const q4kv_spec &s, int num_agents, int q_len, int max_seq_len, int layers, int compute_units)
+{
+    const int rows = q_len * (s.num_q_heads / s.num_kv_heads), per_wg = rows_per_workgroup(rows);
+    const int64_t units = (int64_t)layers * num_agents * s.num_kv_heads * ((rows + per_wg - 1) / per_wg);
+    return num_agents <= kMaxStreamAgents && max_seq_len > 256 && units < 16 * (int64_t)compute_units &&
+           units * (max_seq_len / kSub + 2) < 0x3fffffff; // tiles are numbered with 32-bit integers
+}
+
+template <int DK, int DV, int NREP, int KSPLIT>
+hipError_t launch_chunk_k(const AttentionArgs &a, hipStream_t stream)
+{
+    constexpr int ROWGROUPS = kChunkWaves / KSPLIT;
+    constexpr int QPOS = ROWGROUPS * kRowsWave / NREP;
     ChunkParams p;
     p.k_codes = a.k.codes; p.k_scale = a.k.scale; p.k_bias = a.k.bias;
     p.v_codes = a.v.codes; p.v_scale = a.v.scale; p.v_bias = a.v.bias;
@@ -607,22 +884,38 @@ hipError_t launch_chunk_t(const AttentionArgs &a, hipStream_t stream)
     p.num_agents = a.num_agents; p.max_blocks = a.max_blocks; p.max_seq_len = a.max_seq_len;
     p.window = a.window; p.q_len = a.q_len;
     p.per_layer_windows = a.layer_window != nullptr;
+    if (p.per_layer_windows && a.layers_in_call == 1) {
+        p.window = a.layer_window[0];
+        p.per_layer_windows = 0;
+    }
     for (int i = 0; i < kMaxChunkWindowLayers; ++i)
-        p.layer_window[i] = (a.layer_window && i < a.layers_in_call) ? a.layer_window[i] : 0;
+        p.layer_window[i] = (p.per_layer_windows && i < a.layers_in_call) ? a.layer_window[i] : 0;
     p.layer_begin = a.layer_begin; p.layers_in_call = a.layers_in_call;
-    constexpr int QPOS = kRowsWG / NREP;
     p.q_tiles = (a.q_len + QPOS - 1) / QPOS;
     p.score_scale = a.sm_scale * kLog2e;
+    p.part_acc = a.part_acc; p.part_ml = a.part_ml;
+    p.shared = reinterpret_cast<ChunkShared *>(a.part_ml + 2 * (size_t)a.chunk_workers * ROWGROUPS * kRowsWave * 2);
+    // a.chunk_workers > 0: the workspace holds two records for each of that many workgroups
+    p.stream = a.chunk_workers > 0 && !p.per_layer_windows;
     const int64_t units = (int64_t)a.layers_in_call * a.num_agents * a.spec.num_kv_heads;
-    const int64_t units_padded = (units + kXcds - 1) / kXcds * kXcds;
-    const int64_t grid = units_padded * p.q_tiles;
+    const int64_t grid = p.stream ? a.chunk_workers : (units + kXcds - 1) / kXcds * kXcds * p.q_tiles;
     if (grid <= 0) return hipSuccess;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     if (a.spec.param_format == Q4KV_PARAMS_BF16)
-        hipLaunchKernelGGL((chunk_attention_kernel<DK, DV, NREP, QT, true>), dim3((unsigned)grid), dim3(kThreads), 0, stream, p);
+        hipLaunchKernelGGL((chunk_attention_kernel<DK, DV, NREP, KSPLIT, true>), dim3((unsigned)grid), dim3(kChunkThreads), 0, stream, p);
     else
-        hipLaunchKernelGGL((chunk_attention_kernel<DK, DV, NREP, QT, false>), dim3((unsigned)grid), dim3(kThreads), 0, stream, p);
+        hipLaunchKernelGGL((chunk_attention_kernel<DK, DV, NREP, KSPLIT, false>), dim3((unsigned)grid), dim3(kChunkThreads), 0, stream, p);
+    if (p.stream)
+        hipLaunchKernelGGL((chunk_merge_kernel<DV, NREP, ROWGROUPS>), dim3((unsigned)grid * merge_parts<DV, ROWGROUPS>()),
+                           dim3(kMergeThreads), 0, stream, p);
     return hipGetLastError();
+}
+
+template <int DK, int DV, int NREP>
+hipError_t launch_chunk_t(const AttentionArgs &a, hipStream_t stream)
+{
+    return rows_per_workgroup(a.q_len * NREP) == 256 ? launch_chunk_k<DK, DV, NREP, 1>(a, stream)
+                                                     : launch_chunk_k<DK, DV, NREP, 2>(a, stream);
 }
 
 template <int DK, int DV>
@@ -638,6 +931,16 @@ hipError_t launch_chunk_d(const AttentionArgs &a, int n_rep, hipStream_t stream)
 }
 
 } // namespace
+
+size_t chunk_workspace_bytes(const q4kv_spec &s, int num_agents, int q_len, int max_seq_len, int layers, int compute_units,
+                             size_t &acc_bytes)
+{
+    acc_bytes = 0;
+    if (!chunk_supported(s) || !stream_pays(s, num_agents, q_len, max_seq_len, layers, compute_units)) return 0;
+    const size_t rows = 2 * (size_t)compute_units * rows_per_workgroup(q_len * (s.num_q_heads / s.num_kv_heads));
+    acc_bytes = rows * s.v_dim * sizeof(float);
+    return acc_bytes + rows * 2 * sizeof(float) + compute_units * sizeof(ChunkShared);
+}
 
 bool chunk_supported(const q4kv_spec &s)
 {

@@ -37,6 +37,7 @@ struct AttentionArgs {
     float *part_acc;            // workspace: [units][max_slots][v_dim]
     float *part_ml;             // workspace: [units][max_slots][2]  (running max in log2 units, denominator)
     int32_t *arrivals;          // workspace: [layers_in_call][kv_heads][num_agents] waves that have left a unit
+    int chunk_workers;          // q_len > 1: workgroups that share all tiles evenly (part_acc, part_ml: two records each); 0: none
     int plan_signature;         // hash of the arguments the plan depends on, kept in the plan and checked by the kernels
 };
 
@@ -64,6 +65,10 @@ hipError_t launch_mla_decode_attention(const AttentionArgs &a, hipStream_t strea
 
 // true when a chunk (q_len > 1, causal) kernel exists for these head shapes
 bool chunk_supported(const q4kv_spec &spec);
+// bytes of workspace with which the tiles of such a call are dealt out evenly over the compute units (acc_bytes: the
+// sums, in front of the maxima and denominators); 0: the call has units enough, or too little work, to gain from it
+size_t chunk_workspace_bytes(const q4kv_spec &spec, int num_agents, int q_len, int max_seq_len, int layers, int compute_units,
+                             size_t &acc_bytes);
 hipError_t launch_chunk_attention(const AttentionArgs &a, hipStream_t stream);
 
 // persist.hip: bytes of one (layer, block) record of a block image; gather (to_image) or scatter of `num_blocks`

@@ -235,3 +235,44 @@ def test_append_and_chunk_attention_replay_from_a_graph():
         torch.cuda.synchronize()
         assert torch.equal(out, want), f"replay {step}"
     assert torch.equal(kpool.codes, kpool2.codes) and torch.equal(vpool.scale, vpool2.scale)
+
+
+# (query heads, KV heads, D, cached tokens, chunk): row counts around the 128 and 256 rows of a workgroup and the 32 of a
+# wave, lengths around the tiles of 32 and 64 tokens, agents without a token, one unit shared by every workgroup
+SHARED = [
+    (4, 2, 256, (1300, 0, 700), 64),          # 128 rows: a workgroup's waves share the tokens of a tile
+    (4, 2, 256, (641, 990), 65),              # one row pair more
+    (2, 2, 256, (2049,), 256),                # 256 rows, 32-token tiles, lengths one past a tile
+    (2, 2, 256, (480, 1000), 33),
+    (8, 2, 128, (1999, 64, 513), 70),         # 280 rows: the last row tile nearly empty
+    (4, 4, (192, 128), (1500, 300), 130),
+    (8, 1, 64, (5000,), 2),                   # one unit of 79 tiles: every workgroup takes one
+    (8, 1, 64, (700,) * 70, 3),               # more agents than lanes
+]
+
+
+@pytest.mark.parametrize("param_format", [0, 1])
+@pytest.mark.parametrize("case", SHARED)
+def test_chunk_shared_by_workgroups_matches_oracle(case, param_format):
+    """With a workspace the tiles of all units are dealt out over the compute units and shared units are merged; without
+    one a workgroup takes a unit.  Both against the oracle, with and without a window; the workspace is not left, the result
+    does not change from run to run."""
+    Hq, Hkv, D, lens, C = case
+    Dk, Dv = D if isinstance(D, tuple) else (D, D)
+    w = synth.small(61, 2, Hq, Hkv, Dk, Dv, False, lens, q_len=C)
+    got, (spec, kpool, vpool, table_d) = append_chunk_and_attend(w, param_format=param_format)
+    ospec, okp, ovp, otable = host_cache(w, param_format=param_format)
+    sl = torch.tensor(w.final_lens(), dtype=torch.int32, device=DEV)
+    msl, q = max(w.final_lens()), w.q_all(DEV)
+    need = b.q4kv_attention_workspace_bytes(spec, w.num_agents, C, msl, 0, w.num_layers)
+    assert need > 0
+    for window in (0, 300):
+        want = oracle.attention(ospec, okp, ovp, w.q_all().numpy(), otable, w.final_lens(), w.sm_scale, window=window)
+        ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device=DEV)
+        outs = [b.q4kv_batched_attention(spec, kpool, vpool, q, table_d, sl, msl, w.sm_scale, window, workspace=ws[:size])
+                for size in (need, need, need - 1)]
+        torch.cuda.synchronize()
+        assert bool((ws[need:] == 0x5A).all())
+        assert torch.equal(outs[0], outs[1])
+        assert_close(outs[0].cpu().numpy(), want, f"{case} window {window}, shared")
+        assert_close(outs[2].cpu().numpy(), want, f"{case} window {window}, one unit per workgroup")
