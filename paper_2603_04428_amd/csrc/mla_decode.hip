@@ -151,8 +151,7 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
     const int tok_q = lane % 4, tok_e = (lane % 32) / 4, tok_h2 = lane / 32; // where token `lane` sits in sc / bg
     const uint32_t nibble_mask = col < 8 ? 0x0F0F0F0Fu : 0xF0F0F0F0u;
 
-    typedef CursorT<int> Cursor;
-    Cursor cur = ts.locate<Cursor>(x0);
+    Cursor cur = ts.locate(x0);
 
     uint32_t sraw[GK], braw[GK]; // scale / bias bits of token `lane` of the tile in flight
 

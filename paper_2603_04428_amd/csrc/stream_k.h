@@ -57,22 +57,25 @@ struct StreamParams {
 // Position of a wave in the tile stream; every field is wave-uniform and lives in scalar registers.
 // Everything that needs a division, a wide multiply or a memory lookup is refreshed only where it can
 // change: per unit (unit_row, first) or per 256-token block (row of the block, reachable).
-// Flag is the type of `reachable`: a kernel picks the one its register allocation fares better with.
-template <typename Flag>
-struct CursorT {
+// No field is narrower than a register and there is no padding: with a bool in it the compiler kept the padding bytes
+// of copies of the struct as an array per thread, moved that to LDS, and read the workgroup's size from the dispatch
+// packet to place it.  The packet lies in host memory, and 2,000 waves waited 2 to 14 us for that read at the start of
+// every decode call (one layer of ten 256-wide agents 43 -> 36 us, one of three 192-wide ones 27 -> 17 us, the smallest call
+// 18 -> 14.6 us).
+struct Cursor {
+    int64_t unit_row;    // pool row of (layer, block 0, kv head, slot 0)
+    int64_t row;         // pool row of the tile's first token
     int li, kvh, agent;  // unit: layer in call, KV head, agent
     int cb;              // plan offset of the class block of layer li
     int j, tiles;        // tile inside the unit, tiles of the unit
     int t0;              // first token of the tile
     int n, first;        // visible tokens of the agent, first visible token (sliding window)
-    int64_t unit_row;    // pool row of (layer, block 0, kv head, slot 0)
-    int64_t row;         // pool row of the tile's first token
     int fallback_blk;    // where the loads of a tile go whose block id is outside the pool: the agent's first block
-    Flag reachable;      // the tile's block id is inside the pool
+    int reachable;       // 1: the tile's block id is inside the pool
     int blk_ahead;       // table entry of the block after the tile's (-1 past the table): fetched one block early so
                          // that the lookup is never on the path of the next tile's loads
 };
-typedef CursorT<bool> Cursor;
+static_assert(sizeof(Cursor) == 2 * sizeof(int64_t) + 12 * sizeof(int), "no padding");
 
 struct TileStream {
     StreamParams sp;
@@ -93,8 +96,7 @@ struct TileStream {
         if (!valid) N = 0;
     }
 
-    template <typename C>
-    __device__ __forceinline__ void place_block(C &c, int blk) const
+    __device__ __forceinline__ void place_block(Cursor &c, int blk) const
     {
         c.reachable = blk >= 0 && blk < sp.num_blocks;
         // the (unconditional) loads of a tile whose block id is outside the pool go to the agent's own first block
@@ -103,8 +105,7 @@ struct TileStream {
                 (c.t0 % kBlockTokens);
     }
 
-    template <typename C>
-    __device__ __forceinline__ void enter_block(C &c) const
+    __device__ __forceinline__ void enter_block(Cursor &c) const
     {
         const int bi = c.t0 / kBlockTokens;
         const int32_t *row = sp.block_table + (long long)c.agent * sp.max_blocks;
@@ -116,8 +117,7 @@ struct TileStream {
     }
 
     // the same when the tile stream walks from one block of an agent into the next
-    template <typename C>
-    __device__ __forceinline__ void next_block(C &c) const
+    __device__ __forceinline__ void next_block(Cursor &c) const
     {
         const int bi = c.t0 / kBlockTokens;
         const int blk = c.blk_ahead;
@@ -125,8 +125,7 @@ struct TileStream {
         place_block(c, blk);
     }
 
-    template <typename C>
-    __device__ __forceinline__ void enter_unit(C &c) const
+    __device__ __forceinline__ void enter_unit(Cursor &c) const
     {
         const int32_t *tpre = pv.tpre(c.cb);
         const int window = pv.window(c.cb);
@@ -137,8 +136,7 @@ struct TileStream {
     }
 
     // to the next tile of the stream (meaningful while it stays below the wave's last tile)
-    template <typename C>
-    __device__ __forceinline__ void step(C &c) const
+    __device__ __forceinline__ void step(Cursor &c) const
     {
         if (++c.j < c.tiles) {
             c.t0 += kWave;
@@ -184,8 +182,7 @@ struct TileStream {
     // `stride` tiles ahead (stride <= 4, the target stays below the stream's end): the walk of one wave of a
     // workgroup whose waves take the tiles of the workgroup's range in turn.  Inside a unit with stride 4 the target
     // is the same slot range of the next 256-token block.
-    template <typename C>
-    __device__ __forceinline__ void advance(C &c, int stride) const
+    __device__ __forceinline__ void advance(Cursor &c, int stride) const
     {
         c.j += stride;
         if (__builtin_expect(c.j < c.tiles, 1)) {
@@ -210,10 +207,9 @@ struct TileStream {
 
     // where tile x lies: layer by binary search over the layer prefix, agent by binary search over the class's
     // per-agent prefix
-    template <typename C = Cursor>
-    __device__ __forceinline__ C locate(int x) const
+    __device__ __forceinline__ Cursor locate(int x) const
     {
-        C c;
+        Cursor c;
         const int32_t *LT = pv.plan + pv.lt_off();
         int lo = 0, hi = sp.layers - 1; // largest li with LT[li] <= x (layers without tiles are stepped over)
         while (lo < hi) {
