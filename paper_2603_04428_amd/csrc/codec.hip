@@ -227,9 +227,14 @@ struct AppendParams {
     int max_blocks, chunk_len, heads, layer_begin, num_blocks, layers;
 };
 
-template <bool BF>
+// STEPS: a wave's round is 16 * STEPS groups.  Four steps fill whole lines of scales and biases (long chunks on many
+// agents: the kernel is then bound by the memory system and the vector ALUs).  A launch that does not fill the chip is a
+// chain of trips to memory -- the length, the block table, the rows of every step -- and takes one step per round: more
+// waves, and the rows, which depend on neither, are asked for before the table.
+template <bool BF, int STEPS>
 __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams pp)
 {
+    constexpr int ROUND = 16 * STEPS; // groups
     const int sub = threadIdx.x & 7;
     const int which = blockIdx.z >= (unsigned)pp.layers ? 1 : 0;
     const int a = blockIdx.y, li = blockIdx.z - which * pp.layers, agents = gridDim.y;
@@ -248,7 +253,7 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams pp)
     // generations of the launch: workgroups in launch order (x fastest), about 256 of them per generation
     const uint32_t linear = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     const int generation = linear / max(1u, gridDim.x * gridDim.y * gridDim.z / kWorkgroupsPerCu);
-    // 64 consecutive groups per wave and round, in four steps of two groups per octet of lanes, the parameters
+    // ROUND consecutive groups per wave and round, in steps of two groups per octet of lanes, the parameters
     // gathered in LDS and stored two per lane, as in quantize_kernel.  Where a group comes from and where it goes is
     // worked out once per round, by lane l for group l of the round, and kept in LDS: worked out by every lane of an
     // octet for each of its eight groups it was a third of the kernel's vector instructions, and the kernel is bound
@@ -259,7 +264,7 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams pp)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool words_ok = ((reinterpret_cast<uintptr_t>(scale) | reinterpret_cast<uintptr_t>(bias)) & 3u) == 0;
     const float inv_gpr = 1.0f / (float)p.groups_per_row, inv_chunk = 1.0f / (float)p.chunk_len;
-    for (uint32_t c0 = (blockIdx.x * (kThreads / 64) + wave) * 64; c0 < per_unit; c0 += gridDim.x * kThreads) {
+    for (uint32_t c0 = (blockIdx.x * (kThreads / 64) + wave) * ROUND; c0 < per_unit; c0 += gridDim.x * (kThreads / 64) * ROUND) {
         rotate_wave_priority(generation);
         // Where the round begins -- head, chunk token, group in the row -- is the same for the whole wave and costs
         // two integer divisions per round.  A lane is at most 63 groups further on: its own place follows from two
@@ -272,6 +277,15 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams pp)
         // -- was measured slower: 0.69 against 0.65 ms on the 10-agent, 48-layer chunk.)
         const uint32_t row0 = c0 / (uint32_t)p.groups_per_row, g0 = c0 - row0 * p.groups_per_row;
         const uint32_t h0 = row0 / (uint32_t)p.chunk_len, cr0 = row0 - h0 * p.chunk_len;
+        uint4 raw[2];
+        auto load_rows = [&](int step) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const uint32_t l = step * 16 + 8 * j + (lane >> 3);
+                raw[j] = c0 + l < per_unit ? *reinterpret_cast<const uint4 *>(x + (src0 + s_src[wave][l]) * kGroup + sub * 8)
+                                           : make_uint4(0, 0, 0, 0);
+            }
+        };
         {
             const uint32_t gl = g0 + lane;
             const uint32_t rows = (uint32_t)(((float)gl + 0.5f) * inv_gpr);
@@ -279,8 +293,16 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams pp)
             const uint32_t cl = cr0 + rows;
             const uint32_t heads = (uint32_t)(((float)cl + 0.5f) * inv_chunk);
             const uint32_t h = h0 + heads, c = cl - heads * p.chunk_len;
+            const bool mine = lane < ROUND && c0 + lane < per_unit;
+            if (lane < ROUND) s_src[wave][lane] = (c * p.heads + h) * p.groups_per_row + g;
+            if constexpr (STEPS == 1) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                load_rows(0);
+            }
             int64_t dgrp = -1;
-            if (c0 + lane < per_unit) {
+            if (mine) {
                 const int t = n0 + (int)c;
                 const int bi = t / kBlockTokens;
                 if (t >= 0 && bi < p.max_blocks) {
@@ -292,21 +314,14 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams pp)
                     }
                 }
             }
-            s_src[wave][lane] = (c * p.heads + h) * p.groups_per_row + g;
-            s_dst[wave][lane] = dgrp;
+            if (lane < ROUND) s_dst[wave][lane] = dgrp;
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll 1
-        for (int step = 0; step < 4; ++step) {
-            uint4 raw[2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const uint32_t l = step * 16 + 8 * j + (lane >> 3);
-                const uint32_t src = s_src[wave][l];
-                raw[j] = c0 + l < per_unit ? *reinterpret_cast<const uint4 *>(x + (src0 + src) * kGroup + sub * 8) : make_uint4(0, 0, 0, 0);
-            }
+        for (int step = 0; step < STEPS; ++step) {
+            if constexpr (STEPS > 1) load_rows(step);
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const uint32_t l = step * 16 + 8 * j + (lane >> 3);
@@ -328,7 +343,8 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams pp)
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         {
             const int which_par = lane >> 5, pair = lane & 31; // lanes 0-31 the scales, 32-63 the biases
-            const int64_t d0 = s_dst[wave][2 * pair], d1 = s_dst[wave][2 * pair + 1];
+            const bool on = 2 * pair < ROUND;
+            const int64_t d0 = on ? s_dst[wave][2 * pair] : -1, d1 = on ? s_dst[wave][2 * pair + 1] : -1;
             const uint32_t two = *reinterpret_cast<const uint32_t *>(&s_par[wave][which_par][2 * pair]);
             uint16_t *arr = which_par ? bias : scale;
             if (words_ok && d0 >= 0 && d1 == d0 + 1 && (d0 & 1) == 0) {
@@ -450,15 +466,24 @@ hipError_t launch_append(const q4kv_spec &spec, const q4kv_pool &k, const q4kv_p
     p.layers = layers;
     // workgroups per (pool, layer, agent): enough for the chunk, and at most 8 per compute unit over the whole
     // launch (rounded down: a launch of 1.2 rounds takes as long as one of 2)
-    int64_t gx = (per_unit + kThreads - 1) / kThreads;
-    const int64_t cap = (int64_t)compute_units * kWorkgroupsPerCu / ((int64_t)pools * layers * num_agents);
+    const int64_t units = (int64_t)pools * layers * num_agents, slots = (int64_t)compute_units * kWorkgroupsPerCu;
+    // Rounds of one step while they fit the chip at once.  Measured (us, rounds of four steps / of one): one token of ten
+    // agents, 256-wide heads 5.2 / 4.6, of three agents, sixteen 192 + 128-wide heads 7.6 / 4.6; 70 tokens of four
+    // agents, 128-wide 7.6 / 5.2; 512 tokens of one agent, 256-wide 15.7 / 5.5.
+    const bool small = units * ((per_unit + kThreads / 4 - 1) / (kThreads / 4)) <= slots;
+    const int per_workgroup = small ? kThreads / 4 : kThreads; // groups: 16 or 64 per wave
+    int64_t gx = (per_unit + per_workgroup - 1) / per_workgroup;
+    const int64_t cap = slots / units;
     if (gx > cap) gx = cap;
     if (gx < 1) gx = 1;
-    const dim3 grid((unsigned)gx, (unsigned)num_agents, (unsigned)(pools * layers));
-    if (spec.param_format == Q4KV_PARAMS_BF16)
-        hipLaunchKernelGGL(append_kernel<true>, grid, dim3(kThreads), 0, stream, p);
-    else
-        hipLaunchKernelGGL(append_kernel<false>, grid, dim3(kThreads), 0, stream, p);
+    const dim3 grid((unsigned)gx, (unsigned)num_agents, (unsigned)(pools * layers)), block(kThreads);
+    if (spec.param_format == Q4KV_PARAMS_BF16) {
+        if (small) hipLaunchKernelGGL((append_kernel<true, 1>), grid, block, 0, stream, p);
+        else hipLaunchKernelGGL((append_kernel<true, 4>), grid, block, 0, stream, p);
+    } else {
+        if (small) hipLaunchKernelGGL((append_kernel<false, 1>), grid, block, 0, stream, p);
+        else hipLaunchKernelGGL((append_kernel<false, 4>), grid, block, 0, stream, p);
+    }
     return hipGetLastError();
 }
 

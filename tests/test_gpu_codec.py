@@ -6,7 +6,7 @@ import torch
 import oracle
 from paper_2603_04428_amd import binding as b
 from paper_2603_04428_amd import synth
-from tests.gpu_util import DEV, bits
+from tests.gpu_util import DEV, bits, gpu_cache
 from tests.util import tie_adjacent_rows
 
 pytestmark = pytest.mark.gpu
@@ -241,3 +241,32 @@ def test_read_probe_reads_only():
         assert torch.equal(buf.cpu(), host)
     with pytest.raises(b.Q4KVError):
         b.q4kv_read_probe(buf.view(torch.uint8)[4:4 + 32768], sink)   # not 16-byte aligned
+
+
+@pytest.mark.parametrize("dims", [(256, 256), (192, 128), (64, 64)])
+@pytest.mark.parametrize("chunk", [1, 5, 21, 70])
+def test_small_append_matches_oracle(dims, chunk):
+    """Appends that do not fill the chip (rounds of 16 groups per wave): group counts around a wave's round and a
+    workgroup's four, a chunk that crosses a block boundary, a table entry outside the pool, bit for bit."""
+    w = synth.small(81, 2, 6, 3, dims[0], dims[1], False, (254, 0, 300), q_len=chunk if chunk > 1 else 2)
+    spec, kpool, vpool, table, table_d = gpu_cache(w, tokens=w.seq_lens)
+    bad = table_d.clone()
+    bad[2, 1] = -7                                      # agent 2's tokens from 256 on fall into a block outside the pool
+    k_new = torch.stack([torch.stack([w.k_rows(l, a, n, n + chunk, DEV) for a, n in enumerate(w.seq_lens)]) for l in range(2)])
+    v_new = torch.stack([torch.stack([w.v_rows(l, a, n, n + chunk, DEV) for a, n in enumerate(w.seq_lens)]) for l in range(2)])
+    before = torch.tensor(w.seq_lens, dtype=torch.int32, device=DEV)
+    b.q4kv_append(spec, kpool, vpool, k_new.contiguous(), v_new.contiguous(), bad, before)
+    torch.cuda.synchronize()
+    for l in range(2):
+        for pool, new, dim in ((kpool, k_new, dims[0]), (vpool, v_new, dims[1])):
+            for a, n in enumerate(w.seq_lens):
+                for c in range(chunk):
+                    if a == 2:
+                        continue
+                    blk, slot = int(table[a, (n + c) // 256]), (n + c) % 256
+                    codes, scale, bias = oracle.quantize(new[l, a, c].cpu().numpy())
+                    assert np.array_equal(bits(pool.codes[l, blk, :, slot]), codes)
+                    assert np.array_equal(bits(pool.scale[l, blk, :, slot]), scale)
+                    assert np.array_equal(bits(pool.bias[l, blk, :, slot]), bias)
+            # the skipped agent's own block keeps its poison
+            assert bool((pool.scale[l, int(table[2, 1]), :, 300 - 256:] == 0x7E00).all())
