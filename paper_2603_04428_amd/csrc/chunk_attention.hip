@@ -11,8 +11,12 @@
 //
 //  * A workgroup of eight waves owns 256 query rows of one (layer, agent, KV head) -- 256/n_rep consecutive chunk
 //    positions times the n_rep query heads of the group -- 32 rows per wave; or 128 rows, when its waves 0..3 take the
-//    first and waves 4..7 the second 32 tokens of every tile (KSPLIT = 2: short chunks).
-//  * KV tiles of 64 tokens are fetched as Q4 (codes + scale/bias, prefetched one tile ahead into registers) and staged
+//    first and waves 4..7 the second half of every tile's tokens (KSPLIT = 2: short chunks).
+//  * A wave multiplies 64 tokens at a time as two interleaved pieces of 32 (the second chain of matrix instructions runs
+//    while the first one's results are on their way), 256-wide heads one piece: a KV tile is 32 to 128 tokens.  Measured,
+//    one piece / two: 70 tokens of four agents, 128-wide 60.6 / 50.5 us, 512 tokens of ten agents, six layers 2,878 /
+//    2,738 us; 24 tokens of five agents, 192 + 128-wide 170 / 154 us.
+//  * KV tiles are fetched as Q4 (codes + scale/bias, prefetched one tile ahead into registers) and staged
 //    ONCE per workgroup in LDS, row-major: V_hat dequantized to binary16, K as the packed code words themselves (a
 //    lane's A operand of a matrix instruction is exactly one word, four of them one 16-byte LDS read).  The dims inside
 //    a word appear in the order the nibble masks deliver them (0,4,1,5,2,6,3,7): the query operand uses the same order
@@ -48,8 +52,6 @@
 // older wave of a SIMD wins its arbitrations and the younger one finishes alone.  Holding the second wave half a step
 // behind by two barriers per step (its vector work against the other's matrix work) cost 15 %: the scores' chain is
 // longer than the product.  Wave priorities by phase, deeper operand reads: no change.
-#include <type_traits>
-
 #include "q4_device.h"
 #include "q4kv_internal.h"
 
@@ -240,8 +242,11 @@ struct Stage {
 
 // ---------------------------------------------------------------------------------------------- attention
 
+// 32-token pieces of a tile that a wave multiplies at once.  Two give it two independent chains of matrix instructions
+// and half the barriers; at 256-wide heads there are no registers for the second one's scores and products.
+constexpr int chunk_pieces(int dk) { return dk == 256 ? 1 : 2; }
 // KV tokens per tile
-constexpr int chunk_tile(int dk, int ksplit) { return dk == 256 && ksplit == 1 ? 32 : 64; }
+constexpr int chunk_tile(int dk, int ksplit) { return kSub * chunk_pieces(dk) * ksplit; }
 
 // KSPLIT 1: 256 rows per workgroup; 2: 128 rows, the two halves of the waves share the tokens of a tile.
 // BF: scale and bias are stored as bfloat16 (converted to binary16 when a row is staged).
@@ -254,8 +259,8 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
     constexpr int KPITCH = DK / 8 + 4; // words; an odd multiple of 4: 16 rows x 16 bytes fall into all 64 banks
     constexpr int VPITCH = DV + 16;    // halves; 8 banks mod 64 (40 at 64-wide rows), see above
     constexpr int DTILES = DV / 32;    // 32-dim tiles of O^T
-    constexpr int TILE = chunk_tile(DK, KSPLIT);
-    constexpr int QREG = DK == 256 ? 1 : GK; // groups whose query operand stays in registers; the rest in LDS
+    constexpr int NP = chunk_pieces(DK), TILE = chunk_tile(DK, KSPLIT);
+    constexpr int QREG = DK == 256 ? 1 : (DK == 192 ? 2 : GK); // groups whose query operand stays in registers; the rest in LDS
     constexpr int QLDS = GK - QREG;
     constexpr int QROWS = ROWGROUPS * kWave; // lanes that hold query operands of their own
     typedef Stage<DK, kChunkThreads, TILE> SK; // staging of the K rows of a tile ...
@@ -537,156 +542,169 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             int64_t row_ahead = 0;
             bool ok_ahead = false;
 
-            // One 32-token half of the tile: scores, softmax, product with V_hat.  `half`: which of this wave's halves
-            // (compile time), sub: which of the tile's
-            constexpr int HALVES = TILE / kSub / KSPLIT;
-            auto take_half = [&](auto half_c, int sub) {
-                constexpr int half = decltype(half_c)::value;
-                const int ts = t0 + kSub * sub;
-                const uint32_t *k_row = k_cur + sub * kSub * KPITCH + k_lane;
-                const half_t *ks_row = ks_cur + sub * kSub + 16 * h;
-                // ---- S^T = sum_g s_g (C_g Q_g^T) + b Qsum^T in binary32, in units of 2^-24
-                float16_t zero;
+            // this wave's NP pieces of 32 tokens
+            const int sub = my_sub * NP, ts = t0 + kSub * sub;
+            const uint32_t *k_row = k_cur + sub * kSub * KPITCH + k_lane;
+            const half_t *ks_row = ks_cur + sub * kSub + 16 * h;
+            // ---- S^T = sum_g s_g (C_g Q_g^T) + b Qsum^T in binary32, in units of 2^-24
+            float16_t zero;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
-                const half8_t ba = *reinterpret_cast<const half8_t *>(kb_cur + (sub * kSub + m_token) * 8);
-                float16_t st = __builtin_amdgcn_mfma_f32_32x32x16_f16(ba, qsop, zero, 0, 0, 0);
-                auto q_operand = [&](int k) { // matrix instruction k = 4 group + i
-                    if (k / 4 < QREG) return qop[k / 4 < QREG ? k / 4 : 0][k % 4];
-                    return q_lds[(k - 4 * QREG) * QROWS + rg * kWave + lane];
-                };
-                uint4 words = *reinterpret_cast<const uint4 *>(k_row); // code words 8 g + 4 h .. + 3 of this lane's token
-                half8_t qk = q_operand(0);
+            for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
+            auto q_operand = [&](int k) { // matrix instruction k = 4 group + i
+                if (k / 4 < QREG) return qop[k / 4 < QREG ? k / 4 : 0][k % 4];
+                return q_lds[(k - 4 * QREG) * QROWS + rg * kWave + lane];
+            };
+            float16_t st[NP];
+            uint4 words[NP]; // code words 8 g + 4 h .. + 3 of this lane's token
 #pragma unroll
-                for (int g = 0; g < GK; ++g) {
-                    const uint32_t w[4] = {words.x, words.y, words.z, words.w};
-                    float16_t d = zero;
-                    uint4 sc, sc1; // scales of the lane's first and last 8 scores
+            for (int n = 0; n < NP; ++n) {
+                const half8_t ba = *reinterpret_cast<const half8_t *>(kb_cur + ((sub + n) * kSub + m_token) * 8);
+                st[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ba, qsop, zero, 0, 0, 0);
+            }
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const half8_t qi = qk;
-                        if (4 * g + i + 1 < 4 * GK) qk = q_operand(4 * g + i + 1);
-                        if (i == 2) sc = *reinterpret_cast<const uint4 *>(ks_row + g * TILE);
-                        if (i == 3) sc1 = *reinterpret_cast<const uint4 *>(ks_row + g * TILE + 8);
-                        if (i == 3 && g + 1 < GK) words = *reinterpret_cast<const uint4 *>(k_row + 8 * (g + 1));
-                        d = __builtin_amdgcn_mfma_f32_32x32x16_f16(code_operand(w[i]), qi, d, 0, 0, 0);
-                        __builtin_amdgcn_sched_barrier(0);
+            for (int n = 0; n < NP; ++n) words[n] = *reinterpret_cast<const uint4 *>(k_row + n * kSub * KPITCH);
+            half8_t qk = q_operand(0);
+#pragma unroll
+            for (int g = 0; g < GK; ++g) {
+                uint32_t w[NP][4];
+                float16_t d[NP];
+                uint4 sc[NP], sc1[NP]; // scales of the lane's first and last 8 scores
+#pragma unroll
+                for (int n = 0; n < NP; ++n) {
+                    w[n][0] = words[n].x; w[n][1] = words[n].y; w[n][2] = words[n].z; w[n][3] = words[n].w;
+                    d[n] = zero;
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const half8_t qi = qk;
+                    if (4 * g + i + 1 < 4 * GK) qk = q_operand(4 * g + i + 1);
+#pragma unroll
+                    for (int n = 0; n < NP; ++n) {
+                        if (i == 2) sc[n] = *reinterpret_cast<const uint4 *>(ks_row + g * TILE + n * kSub);
+                        if (i == 3) sc1[n] = *reinterpret_cast<const uint4 *>(ks_row + g * TILE + n * kSub + 8);
+                        if (i == 3 && g + 1 < GK) words[n] = *reinterpret_cast<const uint4 *>(k_row + n * kSub * KPITCH + 8 * (g + 1));
+                        d[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(code_operand(w[n][i]), qi, d[n], 0, 0, 0);
                     }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int n = 0; n < NP; ++n) {
+                    const uint32_t s8[8] = {sc[n].x, sc[n].y, sc[n].z, sc[n].w, sc1[n].x, sc1[n].y, sc1[n].z, sc1[n].w};
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        const uint32_t s2 = i % 8 < 2 ? sc.x : (i % 8 < 4 ? sc.y : (i % 8 < 6 ? sc.z : sc.w));
-                        const half2_t sh = bits_to_half2(s2);
-                        const float prev = g == 0 ? st[i] * 0x1p-24f : st[i]; // the bias term enters in the products' unit
-                        st[i] = fmaf((float)((i & 1) ? sh.y : sh.x), d[i], prev);
-                        if (i == 7) sc = sc1;
+                        const half2_t sh = bits_to_half2(s8[i / 2]);
+                        const float prev = g == 0 ? st[n][i] * 0x1p-24f : st[n][i]; // the bias term enters in the products' unit
+                        st[n][i] = fmaf((float)((i & 1) ? sh.y : sh.x), d[n][i], prev);
                     }
                     // pinned: else the multiplies of all groups sink to the scores' first use and every product stays live
 #pragma unroll
                     for (int i = 0; i < 16; i += 8)
-                        asm volatile("" : "+v"(st[i]), "+v"(st[i + 1]), "+v"(st[i + 2]), "+v"(st[i + 3]), "+v"(st[i + 4]), "+v"(st[i + 5]),
-                                     "+v"(st[i + 6]), "+v"(st[i + 7]));
-                    __builtin_amdgcn_sched_barrier(0);
+                        asm volatile("" : "+v"(st[n][i]), "+v"(st[n][i + 1]), "+v"(st[n][i + 2]), "+v"(st[n][i + 3]), "+v"(st[n][i + 4]),
+                                     "+v"(st[n][i + 5]), "+v"(st[n][i + 6]), "+v"(st[n][i + 7]));
                 }
-                const float zscale = p.score_scale * 16777216.0f; // scores are in units of 2^-24
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const float zscale = p.score_scale * 16777216.0f; // scores are in units of 2^-24
 
-                // ---- online softmax per query row (lane column), then P^T in binary16 as the next B operand
-                const bool masked = !(ok_this && ts >= all_first && ts + kSub <= all_vis); // wave-uniform
-                const bool general = masked || !(p.score_scale > 0.0f); // the path that assumes nothing
-                float mx = kNegBig;
-                if (general) {
+            // ---- online softmax per query row (lane column), then P^T in binary16 as the next B operand
+            const bool masked = !(ok_this && ts >= all_first && ts + NP * kSub <= all_vis); // wave-uniform
+            const bool general = masked || !(p.score_scale > 0.0f); // the path that assumes nothing
+            float mx = kNegBig;
+            if (general) {
+#pragma unroll
+                for (int n = 0; n < NP; ++n)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        float z = st[i] * zscale;
-                        const int t = ts + 16 * (i / 8) + 8 * h + 2 * (i % 4) + ((i / 4) & 1);
+                        float z = st[n][i] * zscale;
+                        const int t = ts + kSub * n + 16 * (i / 8) + 8 * h + 2 * (i % 4) + ((i / 4) & 1);
                         if (!(ok_this && t < row_vis && t >= row_first)) z = kNegBig;
-                        st[i] = z;
+                        st[n][i] = z;
                         mx = fmaxf(mx, z);
                     }
-                } else { // interior, positive scale: the maximum can be taken before the scale is applied
+            } else { // interior, positive scale: the maximum can be taken before the scale is applied
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, st[i]);
-                    mx *= zscale;
-                }
-                mx = xor32_max(mx); // the row's tokens live in two lanes
-                const bool moved = mx > m_run + kSlack;
-                const float m_new = moved ? mx : m_run;
-                float sum = 0.0f;
-                if (general) {
+                for (int n = 0; n < NP; ++n)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        float pr = __builtin_amdgcn_exp2f(st[i] - m_new);
-                        pr = st[i] > 0.5f * kNegBig ? pr : 0.0f; // also a row with nothing visible yet
-                        st[i] = pr;
-                        sum += pr;
-                    }
-                } else {
+                    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, st[n][i]);
+                mx *= zscale;
+            }
+            mx = xor32_max(mx); // the row's tokens live in two lanes
+            const bool moved = mx > m_run + kSlack;
+            const float m_new = moved ? mx : m_run;
+            float sum = 0.0f;
+            if (general) {
+#pragma unroll
+                for (int n = 0; n < NP; ++n)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        const float pr = __builtin_amdgcn_exp2f(fmaf(st[i], zscale, -m_new));
-                        st[i] = pr;
+                        float pr = __builtin_amdgcn_exp2f(st[n][i] - m_new);
+                        pr = st[n][i] > 0.5f * kNegBig ? pr : 0.0f; // also a row with nothing visible yet
+                        st[n][i] = pr;
                         sum += pr;
                     }
-                }
-                half8_t pt[2]; // [16-token step]
-#pragma unroll
-                for (int s = 0; s < 2; ++s)
-                    pt[s] = half8_t{(half_t)st[8 * s], (half_t)st[8 * s + 1], (half_t)st[8 * s + 2], (half_t)st[8 * s + 3],
-                                    (half_t)st[8 * s + 4], (half_t)st[8 * s + 5], (half_t)st[8 * s + 6], (half_t)st[8 * s + 7]};
-                if (__builtin_amdgcn_ballot_w64(moved) != 0ull) { // rare after a row's first tiles
-                    const float alpha = moved ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.0f;
-                    l_run *= alpha;
-#pragma unroll
-                    for (int d = 0; d < DTILES; ++d)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) o_acc[d][i] *= alpha;
-                }
-                m_run = m_new;
-                l_run += sum;
-
-                // ---- O^T += V_hat^T P^T, the operand reads one step ahead; the next tile's V rows are dequantized
-                // between the steps
-                const half_t *v_row = v_cur + sub * kSub * VPITCH + v_lane;
-                auto load_va = [&](int step) { // step = 2 * dim tile + 16-token step
-                    const half_t *src = v_row + (step & 1) * 16 * VPITCH + (step >> 1) * 32;
-                    const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)src);
-                    const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(src + VPITCH));
-                    return __builtin_bit_cast(half8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-                };
-                // The next tile's words were asked for at the end of the tile before: they are not touched before this
-                // point, late in the tile, so that memory has most of a tile's time to answer.  Past the last tile the
-                // staging stores zeros into the idle buffer: straight-line code keeps the mix.
-                const RowDequant vr = row_params(vsb, row_ok(t0 + TILE, v_tok, ok_next && more));
-                constexpr int kSteps = 2 * DTILES, kAhead = 2;
-                half8_t va[kAhead];
-#pragma unroll
-                for (int s = 0; s < kAhead; ++s) va[s] = load_va(s);
-#pragma unroll
-                for (int s = 0; s < kSteps; ++s) {
-                    const half8_t a = va[s % kAhead];
-                    if (s + kAhead < kSteps) va[s % kAhead] = load_va(s + kAhead);
-                    o_acc[s >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pt[s & 1], o_acc[s >> 1], 0, 0, 0);
-                    // this half's share of the words (both shares, if this wave takes one half only)
-                    if (half == 0 && s == 0) {
-                        const RowDequant kr = row_params(ksb, row_ok(t0 + TILE, k_tok, ok_next && more));
-                        if (k_on) store_codes(k_lds[buf ^ 1] + k_dst, kraw, kr.ok);
-                        if (k_params_writer) store_k_params(buf ^ 1, kr);
-                        row_ahead = tile_row0(t_ahead, entry_ahead, ok_ahead); // the registers are free: the tile after that
-                        load_k(row_ahead);
-                    }
-                    constexpr int MINE = SV::WPT / HALVES;
-#pragma unroll
-                    for (int w = 0; w < MINE; ++w)
-                        if (w * kSteps / MINE == s && v_on)
-                            store_word(v_lds[buf ^ 1] + v_dst + 8 * (half * MINE + w), vraw[half * MINE + w], vr);
-                    if (half == HALVES - 1 && s == (MINE - 1) * kSteps / MINE + 1) load_v(row_ahead);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            };
-            if constexpr (KSPLIT == 2) {
-                take_half(std::integral_constant<int, 0>{}, my_sub);
             } else {
-                take_half(std::integral_constant<int, 0>{}, 0);
-                if constexpr (HALVES == 2) take_half(std::integral_constant<int, 1>{}, 1);
+#pragma unroll
+                for (int n = 0; n < NP; ++n)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const float pr = __builtin_amdgcn_exp2f(fmaf(st[n][i], zscale, -m_new));
+                        st[n][i] = pr;
+                        sum += pr;
+                    }
+            }
+            half8_t pt[2 * NP]; // [16-token step]
+#pragma unroll
+            for (int s = 0; s < 2 * NP; ++s) {
+                const float16_t &v = st[s / 2];
+                const int o = 8 * (s % 2);
+                pt[s] = half8_t{(half_t)v[o], (half_t)v[o + 1], (half_t)v[o + 2], (half_t)v[o + 3],
+                                (half_t)v[o + 4], (half_t)v[o + 5], (half_t)v[o + 6], (half_t)v[o + 7]};
+            }
+            if (__builtin_amdgcn_ballot_w64(moved) != 0ull) { // rare after a row's first tiles
+                const float alpha = moved ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.0f;
+                l_run *= alpha;
+#pragma unroll
+                for (int d = 0; d < DTILES; ++d)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) o_acc[d][i] *= alpha;
+            }
+            m_run = m_new;
+            l_run += sum;
+
+            // ---- O^T += V_hat^T P^T, the operand reads one step ahead; the next tile's V rows are dequantized
+            // between the steps
+            const half_t *v_row = v_cur + sub * kSub * VPITCH + v_lane;
+            constexpr int kPerTile = 2 * NP, kSteps = kPerTile * DTILES, kAhead = 2;
+            auto load_va = [&](int step) { // step = 2 NP * dim tile + 16-token step
+                const half_t *src = v_row + (step % kPerTile) * 16 * VPITCH + (step / kPerTile) * 32;
+                const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)src);
+                const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(src + VPITCH));
+                return __builtin_bit_cast(half8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            };
+            // The next tile's words were asked for a tile ago: they are not touched before this point, so that memory has
+            // a whole tile's time to answer.  Past the last tile the staging stores zeros into the idle buffer:
+            // straight-line code keeps the mix.
+            const RowDequant vr = row_params(vsb, row_ok(t0 + TILE, v_tok, ok_next && more));
+            half8_t va[kAhead];
+#pragma unroll
+            for (int s = 0; s < kAhead; ++s) va[s] = load_va(s);
+#pragma unroll
+            for (int s = 0; s < kSteps; ++s) {
+                const half8_t a = va[s % kAhead];
+                if (s + kAhead < kSteps) va[s % kAhead] = load_va(s + kAhead);
+                o_acc[s / kPerTile] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pt[s % kPerTile], o_acc[s / kPerTile], 0, 0, 0);
+                if (s == 0) {
+                    const RowDequant kr = row_params(ksb, row_ok(t0 + TILE, k_tok, ok_next && more));
+                    if (k_on) store_codes(k_lds[buf ^ 1] + k_dst, kraw, kr.ok);
+                    if (k_params_writer) store_k_params(buf ^ 1, kr);
+                    row_ahead = tile_row0(t_ahead, entry_ahead, ok_ahead); // the registers are free: the tile after that
+                    load_k(row_ahead);
+                }
+#pragma unroll
+                for (int w = 0; w < SV::WPT; ++w)
+                    if (w * kSteps / SV::WPT == s && v_on) store_word(v_lds[buf ^ 1] + v_dst + 8 * w, vraw[w], vr);
+                if (s == (SV::WPT - 1) * kSteps / SV::WPT + 1) load_v(row_ahead);
+                __builtin_amdgcn_sched_barrier(0);
             }
             ok_cur = ok_next;
             ok_next = ok_ahead;
