@@ -320,10 +320,11 @@ static int attention_common(const q4kv_spec *spec, const q4kv_pool *k, const q4k
                         spec->num_q_heads / spec->num_kv_heads, spec->v_aliases_k);
         size_t acc_bytes = 0;
         const size_t need = q4kv::chunk_workspace_bytes(*spec, num_agents, q_len, max_seq_len, layers, compute_units(), acc_bytes);
+        a.compute_units = compute_units();
         a.chunk_workers = 0;
         a.part_acc = a.part_ml = nullptr;
         if (need > 0 && !shared_scratch && workspace && workspace_bytes >= need && aligned16(workspace)) {
-            a.chunk_workers = compute_units();
+            a.chunk_workers = a.compute_units;
             a.part_acc = static_cast<float *>(workspace);
             a.part_ml = reinterpret_cast<float *>(static_cast<char *>(workspace) + acc_bytes);
         }

@@ -869,10 +869,16 @@ __global__ __launch_bounds__(kMergeThreads) void chunk_merge_kernel(ChunkParams 
 // 128 are taken where 256 would be padding.  Measured (one layer, equal shares, 128 against 256 rows): 128 query rows of
 // 256-wide heads, ten agents of 4K-32K tokens 295 / 460 us; 384 rows, two agents of 4K 77 / 83 us; 280 rows of 128-wide
 // heads, four agents of up to 6K 62 / 60 us.
-int rows_per_workgroup(int rows)
+// And where a compute unit's share is short: every workgroup of a shared unit leaves a record of its rows, and half the
+// rows are half the record (and, without a workspace, twice the workgroups).  The line is at 448 tokens per compute unit
+// (128 / 256 rows, us): 512 new tokens, 256-wide: 100 tokens per unit 48.6 / 55.6, 189 57.6 / 64.6, 314 68.1 / 70.9, 564
+// 90.3 / 94.4, 1,064 132 / 131; 128-wide: 253 44.5 / 44.4, 628 63.7 / 60.6; 192 + 128: 139 39.6 / 48.9, 439 57.2 / 56.7;
+// 64-wide, 131 tokens: 351 35.0 / 39.6.
+int rows_per_workgroup(const q4kv_spec &s, int num_agents, int q_len, int max_seq_len, int layers, int compute_units)
 {
-    const int wide = (rows + 255) / 256, narrow = (rows + 127) / 128;
-    return 0.6 * narrow < wide ? 128 : 256;
+    const int64_t rows = (int64_t)q_len * (s.num_q_heads / s.num_kv_heads), wide = (rows + 255) / 256, narrow = (rows + 127) / 128;
+    if (0.6 * narrow < wide) return 128;
+    return (double)layers * num_agents * s.num_kv_heads * wide * max_seq_len < 448.0 * compute_units ? 128 : 256;
 }
 
 // Whether a call's tiles are dealt out evenly over the compute units (needs a workspace) instead of one unit per
@@ -883,7 +889,8 @@ int rows_per_workgroup(int rows)
 // too few tiles to share.
 bool stream_pays(const q4kv_spec &s, int num_agents, int q_len, int max_seq_len, int layers, int compute_units)
 {
-    const int rows = q_len * (s.num_q_heads / s.num_kv_heads), per_wg = rows_per_workgroup(rows);
+    const int per_wg = rows_per_workgroup(s, num_agents, q_len, max_seq_len, layers, compute_units);
+    const int64_t rows = (int64_t)q_len * (s.num_q_heads / s.num_kv_heads);
     const int64_t units = (int64_t)layers * num_agents * s.num_kv_heads * ((rows + per_wg - 1) / per_wg);
     return num_agents <= kMaxStreamAgents && max_seq_len > 256 && units < 16 * (int64_t)compute_units &&
            units * (max_seq_len / kSub + 2) < 0x3fffffff; // tiles are numbered with 32-bit integers
@@ -932,8 +939,8 @@ hipError_t launch_chunk_k(const AttentionArgs &a, hipStream_t stream)
 template <int DK, int DV, int NREP>
 hipError_t launch_chunk_t(const AttentionArgs &a, hipStream_t stream)
 {
-    return rows_per_workgroup(a.q_len * NREP) == 256 ? launch_chunk_k<DK, DV, NREP, 1>(a, stream)
-                                                     : launch_chunk_k<DK, DV, NREP, 2>(a, stream);
+    const int rows = rows_per_workgroup(a.spec, a.num_agents, a.q_len, a.max_seq_len, a.layers_in_call, a.compute_units);
+    return rows == 256 ? launch_chunk_k<DK, DV, NREP, 1>(a, stream) : launch_chunk_k<DK, DV, NREP, 2>(a, stream);
 }
 
 template <int DK, int DV>
@@ -955,7 +962,7 @@ size_t chunk_workspace_bytes(const q4kv_spec &s, int num_agents, int q_len, int 
 {
     acc_bytes = 0;
     if (!chunk_supported(s) || !stream_pays(s, num_agents, q_len, max_seq_len, layers, compute_units)) return 0;
-    const size_t rows = 2 * (size_t)compute_units * rows_per_workgroup(q_len * (s.num_q_heads / s.num_kv_heads));
+    const size_t rows = 2 * (size_t)compute_units * rows_per_workgroup(s, num_agents, q_len, max_seq_len, layers, compute_units);
     acc_bytes = rows * s.v_dim * sizeof(float);
     return acc_bytes + rows * 2 * sizeof(float) + compute_units * sizeof(ChunkShared);
 }

@@ -37,6 +37,7 @@ struct AttentionArgs {
     float *part_acc;            // workspace: [units][max_slots][v_dim]
     float *part_ml;             // workspace: [units][max_slots][2]  (running max in log2 units, denominator)
     int32_t *arrivals;          // workspace: [layers_in_call][kv_heads][num_agents] waves that have left a unit
+    int compute_units;          // of the device
     int chunk_workers;          // q_len > 1: workgroups that share all tiles evenly (part_acc, part_ml: two records each); 0: none
     int plan_signature;         // hash of the arguments the plan depends on, kept in the plan and checked by the kernels
 };

@@ -255,24 +255,26 @@ SHARED = [
 @pytest.mark.parametrize("case", SHARED)
 def test_chunk_shared_by_workgroups_matches_oracle(case, param_format):
     """With a workspace the tiles of all units are dealt out over the compute units and shared units are merged; without
-    one a workgroup takes a unit.  Both against the oracle, with and without a window; the workspace is not left, the result
-    does not change from run to run."""
+    one a workgroup takes a unit.  Both against the oracle, with and without a window, with the lengths' own bound and with a
+    bound of 131,072 tokens (the work a call might hold decides how many rows a workgroup takes); the workspace is not
+    left, the result does not change from run to run."""
     Hq, Hkv, D, lens, C = case
     Dk, Dv = D if isinstance(D, tuple) else (D, D)
     w = synth.small(61, 2, Hq, Hkv, Dk, Dv, False, lens, q_len=C)
     got, (spec, kpool, vpool, table_d) = append_chunk_and_attend(w, param_format=param_format)
     ospec, okp, ovp, otable = host_cache(w, param_format=param_format)
     sl = torch.tensor(w.final_lens(), dtype=torch.int32, device=DEV)
-    msl, q = max(w.final_lens()), w.q_all(DEV)
-    need = b.q4kv_attention_workspace_bytes(spec, w.num_agents, C, msl, 0, w.num_layers)
-    assert need > 0
+    q, wide = w.q_all(DEV), torch.nn.functional.pad(table_d, (0, 512 - table_d.shape[1])).contiguous()
     for window in (0, 300):
         want = oracle.attention(ospec, okp, ovp, w.q_all().numpy(), otable, w.final_lens(), w.sm_scale, window=window)
-        ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device=DEV)
-        outs = [b.q4kv_batched_attention(spec, kpool, vpool, q, table_d, sl, msl, w.sm_scale, window, workspace=ws[:size])
-                for size in (need, need, need - 1)]
-        torch.cuda.synchronize()
-        assert bool((ws[need:] == 0x5A).all())
-        assert torch.equal(outs[0], outs[1])
-        assert_close(outs[0].cpu().numpy(), want, f"{case} window {window}, shared")
-        assert_close(outs[2].cpu().numpy(), want, f"{case} window {window}, one unit per workgroup")
+        for table, msl in ((table_d, max(w.final_lens())), (wide, 512 * 256)):
+            need = b.q4kv_attention_workspace_bytes(spec, w.num_agents, C, msl, 0, w.num_layers)
+            assert need > 0
+            ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device=DEV)
+            outs = [b.q4kv_batched_attention(spec, kpool, vpool, q, table, sl, msl, w.sm_scale, window, workspace=ws[:size])
+                    for size in (need, need, need - 1)]
+            torch.cuda.synchronize()
+            assert bool((ws[need:] == 0x5A).all())
+            assert torch.equal(outs[0], outs[1])
+            assert_close(outs[0].cpu().numpy(), want, f"{case} window {window} bound {msl}, shared")
+            assert_close(outs[2].cpu().numpy(), want, f"{case} window {window} bound {msl}, one unit per workgroup")
