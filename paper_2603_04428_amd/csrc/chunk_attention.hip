@@ -885,14 +885,17 @@ int rows_per_workgroup(const q4kv_spec &s, int num_agents, int q_len, int max_se
 // workgroup.  Measured (us, one unit per workgroup / equal shares): 256-wide heads, 512-token chunk, one agent of 300,
 // 2,000, 8,000 tokens 74 / 57, 187 / 72, 571 / 133; ten agents of 4K-32K (320 units) 2,130 / 1,842; six layers of ten
 // agents of 1K-1.5K (1,920 units) 1,191 / 1,145, twelve (3,840) 2,278 / 2,239; 128-wide heads, 16 tokens behind 8,000
-// 202 / 37.  With sixteen units per compute unit the hardware's own dispatch is as even, and at 256 tokens a unit has
-// too few tiles to share.
+// 202 / 37.  The line is at two units per compute unit: a workgroup that takes an equal share holds its compute unit
+// until the call ends, and a decode step on another stream, which gets in whenever a workgroup ends, waits for that
+// long.  48 layers of 512 tokens behind 16,384 (1,536 units) take 7.63 ms with one unit per workgroup, 8.04 with equal
+// shares; decode steps of 0.76 ms beside them then take 2.1 and 4.9 ms.  At 256 tokens a unit has too few tiles to
+// share.
 bool stream_pays(const q4kv_spec &s, int num_agents, int q_len, int max_seq_len, int layers, int compute_units)
 {
     const int per_wg = rows_per_workgroup(s, num_agents, q_len, max_seq_len, layers, compute_units);
     const int64_t rows = (int64_t)q_len * (s.num_q_heads / s.num_kv_heads);
     const int64_t units = (int64_t)layers * num_agents * s.num_kv_heads * ((rows + per_wg - 1) / per_wg);
-    return num_agents <= kMaxStreamAgents && max_seq_len > 256 && units < 16 * (int64_t)compute_units &&
+    return num_agents <= kMaxStreamAgents && max_seq_len > 256 && units < 2 * (int64_t)compute_units &&
            units * (max_seq_len / kSub + 2) < 0x3fffffff; // tiles are numbered with 32-bit integers
 }
 
