@@ -37,23 +37,23 @@ CODEC_FILES = ("codec.hip", "q4_device.h", "q4kv_internal.h")
 CHUNK_FILES = ("chunk_attention.hip", "q4_device.h", "q4kv_internal.h")
 MEASURED_TRAFFIC = {
     "gemma12b_10agents_48layers_ragged_1k_8k_decode": {
-        "read": 4795018480, "written": 12899328, "file": "profiles/decode_attention_gemma10_ragged.md",
-        "files": DECODE_FILES, "sources": "8f2be424bd49"},
+        "read": 4810489180, "written": 12899328, "file": "profiles/decode_attention_gemma10_ragged.md",
+        "files": DECODE_FILES, "sources": "2696fa166c24"},
     "llama8b_5agents_32layers_4k_decode": {
-        "read": 776870455, "written": 8527872, "file": "profiles/decode_attention_llama8b_5x4k.md",
-        "files": DECODE_FILES, "sources": "8f2be424bd49"},
+        "read": 776482287, "written": 8527872, "file": "profiles/decode_attention_llama8b_5x4k.md",
+        "files": DECODE_FILES, "sources": "2696fa166c24"},
     "dsv2lite_mla_per_head_5agents_27layers_8k_decode": {
-        "read": 3190791189, "written": 3088896, "file": "profiles/decode_attention_mla_per_head_5x8k.md",
-        "files": DECODE_FILES, "sources": "8f2be424bd49"},
+        "read": 3190513568, "written": 3088896, "file": "profiles/decode_attention_mla_per_head_5x8k.md",
+        "files": DECODE_FILES, "sources": "2696fa166c24"},
     "dsv2lite_mla_latent_5agents_27layers_32k_decode": {
-        "read": 1444160083, "written": 52912630, "file": "profiles/mla_decode_dsv2lite_5x32k.md",
-        "files": LATENT_FILES, "sources": "d8ce4d131e95"},
+        "read": 1444164298, "written": 52770386, "file": "profiles/mla_decode_dsv2lite_5x32k.md",
+        "files": LATENT_FILES, "sources": "13faf3a37a5c"},
     "quantize_4k_cache": {
-        "read": 1610798278, "written": 452984832, "file": "profiles/decode_attention_gemma10_ragged.md",
-        "files": CODEC_FILES, "sources": "3f4145ff341c"},
+        "read": 1610806417, "written": 452984832, "file": "profiles/decode_attention_gemma10_ragged.md",
+        "files": CODEC_FILES, "sources": "8a85bc6548f9"},
     "dequantize_4k_cache": {
-        "read": 453023141, "written": 1610614784, "file": "profiles/decode_attention_gemma10_ragged.md",
-        "files": CODEC_FILES, "sources": "3f4145ff341c"},
+        "read": 453043366, "written": 1610615430, "file": "profiles/decode_attention_gemma10_ragged.md",
+        "files": CODEC_FILES, "sources": "8a85bc6548f9"},
 }
 
 
