@@ -142,8 +142,11 @@ int q4kv_append(const q4kv_spec *spec, const q4kv_pool *k, const q4kv_pool *v, c
  *                wavefronts; this is the floor of a wavefront's share and bounds the partial results kept
  *                per query head.  Must equal the value given to q4kv_attention_workspace_bytes.
  *   workspace    device scratch of at least q4kv_attention_workspace_bytes(...) bytes, 16-byte aligned;
- *                contents before and after the call are unspecified.  With q_len > 1 it is optional (NULL or fewer
- *                bytes are accepted): a call that gets it spreads few or ragged agents over the whole chip.
+ *                contents before and after the call are unspecified.  With q_len > 1 it is optional: a call whose
+ *                workspace_bytes is exactly what q4kv_attention_workspace_bytes says may use it to spread few or ragged
+ *                agents over the whole chip.  Its contents (a decode plan, say) are then lost, and calls that overlap in
+ *                time need one each.  With any other workspace_bytes (a decode call's workspace) or NULL the call
+ *                runs as well and does not touch the workspace.
  * Per-agent isolation (Sec. 3.1): nothing an agent's table row does not list up to seq_len ever enters its result,
  * and the kernels read no block the row does not list: slots past seq_len that a tile's loads touch lie in the
  * agent's own last block, and a block id outside [0, num_blocks) is skipped (its tokens count as masked; the loads
@@ -213,8 +216,10 @@ int q4kv_batched_attention_static(const q4kv_spec *spec, const q4kv_pool *k, con
                                   int32_t layer_end, void *hip_stream);
 
 /* Bytes of workspace q4kv_batched_attention needs for these arguments.  0 on bad arguments (q4kv_last_error() then
- * holds a message).  For q_len > 1 the bytes with which the call shares its work out evenly over the compute units (it
- * runs without them too, one workgroup per row tile); 0 where that gains nothing. */
+ * holds a message).  For q_len > 1 the bytes with which the call may share its work out evenly over the compute units
+ * (it runs without them too, one workgroup per row tile): up to 136 MB on a GPU of 256 compute units, whatever the
+ * lengths; 0 where it never does.  No q_len == 1 call is told that number, and a chunk call goes by it (see `workspace`
+ * above): pass it as workspace_bytes even if the buffer is larger. */
 size_t q4kv_attention_workspace_bytes(const q4kv_spec *spec, int32_t num_agents, int32_t q_len, int32_t max_seq_len,
                                       int32_t split_tokens, int32_t num_layers_in_call);
 

@@ -323,7 +323,9 @@ static int attention_common(const q4kv_spec *spec, const q4kv_pool *k, const q4k
         a.compute_units = compute_units();
         a.chunk_workers = 0;
         a.part_acc = a.part_ml = nullptr;
-        if (need > 0 && !shared_scratch && workspace && workspace_bytes >= need && aligned16(workspace)) {
+        // Only a workspace of exactly the size that was asked for these arguments is written: one of any other size was
+        // handed over for something else (a decode plan, calls on other streams) and a chunk call does not need it.
+        if (need > 0 && !shared_scratch && workspace && workspace_bytes == need && aligned16(workspace)) {
             a.chunk_workers = a.compute_units;
             a.part_acc = static_cast<float *>(workspace);
             a.part_ml = reinterpret_cast<float *>(static_cast<char *>(workspace) + acc_bytes);

@@ -967,7 +967,9 @@ size_t chunk_workspace_bytes(const q4kv_spec &s, int num_agents, int q_len, int 
     if (!chunk_supported(s) || !stream_pays(s, num_agents, q_len, max_seq_len, layers, compute_units)) return 0;
     const size_t rows = 2 * (size_t)compute_units * rows_per_workgroup(s, num_agents, q_len, max_seq_len, layers, compute_units);
     acc_bytes = rows * s.v_dim * sizeof(float);
-    return acc_bytes + rows * 2 * sizeof(float) + compute_units * sizeof(ChunkShared);
+    // The size tells a workspace that was made for such a call from any other.  Those of decode calls are multiples of 8
+    // (plan and counters in pieces of 256 bytes, records of (v_dim + 2) floats), so 4 more bytes make it one of its own.
+    return acc_bytes + rows * 2 * sizeof(float) + compute_units * sizeof(ChunkShared) + 4;
 }
 
 bool chunk_supported(const q4kv_spec &s)

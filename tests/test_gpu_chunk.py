@@ -278,3 +278,31 @@ def test_chunk_shared_by_workgroups_matches_oracle(case, param_format):
             assert torch.equal(outs[0], outs[1])
             assert_close(outs[0].cpu().numpy(), want, f"{case} window {window} bound {msl}, shared")
             assert_close(outs[2].cpu().numpy(), want, f"{case} window {window} bound {msl}, one unit per workgroup")
+
+
+def test_chunk_call_leaves_a_workspace_of_another_size_alone():
+    """A chunk call uses a workspace of exactly the size it was told; any other (a decode call's, which may hold the plan
+    of the step in progress) keeps its bytes, and the planned calls that follow find their plan."""
+    w = synth.small(62, 2, 4, 2, 256, 256, False, (1300, 0, 700), q_len=64)
+    _, (spec, kpool, vpool, table_d) = append_chunk_and_attend(w)
+    lens, A, L = w.final_lens(), w.num_agents, w.num_layers
+    sl, msl, q = torch.tensor(lens, dtype=torch.int32, device=DEV), max(lens), w.q_all(DEV)
+    need = b.q4kv_attention_workspace_bytes(spec, A, w.q_len, msl, 0, L)
+    decode_need = b.q4kv_attention_workspace_bytes(spec, A, 1, msl, 0, L)
+    assert need > decode_need > 0 and need % 8 == 4 and decode_need % 8 == 0
+    want = b.q4kv_batched_attention(spec, kpool, vpool, q, table_d, sl, msl, w.sm_scale, workspace=torch.empty(16, dtype=torch.uint8, device=DEV))
+    ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device=DEV)
+    for size in (need + 4096, need + 1, need - 1, need - 4, decode_need, 16):
+        got = b.q4kv_batched_attention(spec, kpool, vpool, q, table_d, sl, msl, w.sm_scale, workspace=ws[:size])
+        torch.cuda.synchronize()
+        assert bool((ws == 0x5A).all()), size
+        assert torch.equal(got, want), size
+    # a decode step's plan survives a chunk call that is handed the same workspace
+    q1 = q[:, :, -1:].contiguous()
+    decode = b.q4kv_batched_attention(spec, kpool, vpool, q1, table_d, sl, msl, w.sm_scale)
+    b.q4kv_decode_plan(spec, sl, msl, ws, layers_in_call=L)
+    b.q4kv_batched_attention(spec, kpool, vpool, q, table_d, sl, msl, w.sm_scale, workspace=ws)
+    out = torch.full_like(decode, float("nan"))
+    b.q4kv_batched_attention_planned(spec, kpool, vpool, q1, out, table_d, msl, w.sm_scale, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(out, decode)
