@@ -151,7 +151,9 @@ int q4kv_append(const q4kv_spec *spec, const q4kv_pool *k, const q4kv_pool *v, c
  * and the kernels read no block the row does not list: slots past seq_len that a tile's loads touch lie in the
  * agent's own last block, and a block id outside [0, num_blocks) is skipped (its tokens count as masked; the loads
  * go to the agent's own first block instead, or to block 0 if that id is outside the pool too, and are discarded).
- * Outputs are run-to-run bit-identical for identical arguments. */
+ * Outputs are run-to-run bit-identical for identical arguments.  The order in which an agent's tokens are summed
+ * follows from the sizes of the call (agents, layers, max_seq_len, window; with q_len > 1 also from whether it has its
+ * workspace), so an agent's bits may differ between calls that batch it differently. */
 int q4kv_batched_attention(const q4kv_spec *spec, const q4kv_pool *k, const q4kv_pool *v, const uint16_t *q,
                            uint16_t *out, const int32_t *block_table, int32_t max_blocks, const int32_t *seq_len,
                            int32_t num_agents, int32_t q_len, int32_t max_seq_len, float sm_scale, int32_t window,
@@ -198,7 +200,8 @@ int q4kv_batched_attention_planned(const q4kv_spec *spec, const q4kv_pool *k, co
  * path's workspace (tile plan and partial results) taken from a fixed array of Q4KV_STATIC_SCRATCH_BYTES bytes that
  * the library's code object holds on every GPU it is loaded on, from the first use of the library on that GPU until
  * the process ends.  No workspace arguments; everything else, q and out (caller-owned device memory) included, is as
- * for q4kv_batched_attention, and the results are bit-identical to that call with the same split_tokens.
+ * for q4kv_batched_attention, and the results are bit-identical to that call with the same split_tokens -- with
+ * q_len > 1, to that call without its optional workspace (a chunk call takes nothing from the array).
  *   - The call allocates nothing and frees nothing, on the device or through any library.  The first call on a
  *     device looks the array's address up once (with that device current, as for every call); make that first call
  *     outside a graph capture.

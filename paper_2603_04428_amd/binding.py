@@ -305,13 +305,16 @@ def q4kv_attention_workspace_bytes(spec, num_agents, q_len, max_seq_len, split_t
 def q4kv_batched_attention(spec, kpool, vpool, q, block_table, seq_len, max_seq_len, sm_scale, window=0,
                            split_tokens=0, layer_begin=0, layer_end=None, out=None, workspace=None):
     """q: fp16 [layers_in_call][A][q_len][q_heads][k_dim] -> fp16 out of the same leading shape, v_dim wide.
-    window: one int for all layers, or a sequence with one window per layer of the call (q4kv_batched_attention_windows)."""
+    window: one int for all layers, or a sequence with one window per layer of the call (q4kv_batched_attention_windows).
+    workspace: uint8 tensor on the GPU; None allocates what a decode call needs and nothing for q_len > 1.  A chunk call
+    shares few or ragged agents out over the whole chip if it is given one of exactly q4kv_attention_workspace_bytes(...)
+    bytes (up to 136 MB); without, its results are bit-identical to q4kv_batched_attention_static's."""
     layer_end = spec.num_layers if layer_end is None else layer_end
     Lr, A, q_len = q.shape[0], q.shape[1], q.shape[2]
     if out is None:
         out = torch.empty((Lr, A, q_len, spec.num_q_heads, spec.v_dim), dtype=torch.float16, device=q.device)
-    need = q4kv_attention_workspace_bytes(spec, max(A, 1), q_len, max_seq_len, split_tokens, max(Lr, 1))
     if workspace is None:
+        need = q4kv_attention_workspace_bytes(spec, max(A, 1), q_len, max_seq_len, split_tokens, max(Lr, 1)) if q_len == 1 else 0
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
     kp = kpool.c()
     vp = None if spec.v_aliases_k else vpool.c()

@@ -1,7 +1,7 @@
 """q4kv_batched_attention_static (the entry point for callers that cannot allocate): its output against
 q4kv_batched_attention's on the same arguments, bit for bit (the same kernels run, the workspace alone differs),
 and against the CPU oracle within |gpu - oracle| <= 2e-3 + 2e-3*|oracle|; two calls in a row, the second smaller,
-so that the second call finds the first call's contents in the library's fixed array."""
+so that the second call finds the first call's contents in the library's fixed array.  Chunk calls likewise."""
 import numpy as np
 import pytest
 import torch
@@ -77,3 +77,27 @@ def test_a_call_that_does_not_fit_is_refused_and_launches_nothing():
     # the entry point still works afterwards
     ospec, okp, ovp, otable = host_cache(w)
     check(w, spec, kpool, vpool, table_d, ospec, okp, ovp, otable, [300], 0, 1)
+
+
+@pytest.mark.parametrize("shape", [(2, 8, 2, 128, 128, (700, 130, 0, 65), 70), (1, 4, 2, 256, 256, (2000,), 200),
+                                   (1, 4, 4, 192, 128, (1000, 300), 33), (2, 8, 1, 64, 64, (3000,), 97)])
+def test_chunk_call_gives_the_bits_of_a_plain_call(shape):
+    """q_len > 1: as q4kv_batched_attention without its optional workspace, whether that call is given nothing or the
+    workspace of a decode call."""
+    L, Hq, Hkv, Dk, Dv, lens, C = shape
+    w = synth.small(74, L, Hq, Hkv, Dk, Dv, False, lens, q_len=C)
+    spec, kpool, vpool, table, table_d = gpu_cache(w)
+    ospec, okp, ovp, otable = host_cache(w)
+    q, final = w.q_all(DEV), w.final_lens()
+    sl, msl = torch.tensor(final, dtype=torch.int32, device=DEV), max(final)
+    decode_ws = torch.empty(b.q4kv_attention_workspace_bytes(spec, len(lens), 1, msl, 0, L), dtype=torch.uint8, device=DEV)
+    for window in (0, 100):
+        out = torch.full((L, len(lens), C, Hq, Dv), float("nan"), dtype=torch.float16, device=DEV)
+        b.q4kv_batched_attention_static(spec, kpool, vpool, q, out, table_d, sl, msl, w.sm_scale, window)
+        for workspace in (None, decode_ws):
+            ref = b.q4kv_batched_attention(spec, kpool, vpool, q, table_d, sl, msl, w.sm_scale, window, workspace=workspace)
+            torch.cuda.synchronize()
+            assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
+        want = oracle.attention(ospec, okp, ovp, q.cpu().numpy(), otable, final, w.sm_scale, window=window)
+        ok, over, worst = within_tol(out.cpu().numpy(), want)
+        assert ok, f"exceeds 2e-3 abs/rel by {over:.3e} (max abs err {worst:.3e})"
