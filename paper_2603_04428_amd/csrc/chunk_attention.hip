@@ -52,6 +52,7 @@
 // older wave of a SIMD wins its arbitrations and the younger one finishes alone.  Holding the second wave half a step
 // behind by two barriers per step (its vector work against the other's matrix work) cost 15 %: the scores' chain is
 // longer than the product.  Wave priorities by phase, deeper operand reads: no change.
+#include "chunk_rules.h"
 #include "q4_device.h"
 #include "q4kv_internal.h"
 
@@ -64,7 +65,6 @@ constexpr int kRowsWave = 32; // query rows per wave
 constexpr int kSub = 32;      // tokens per matrix tile of scores
 constexpr float kNegBig = -1.0e30f;
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kXcds = 8;
 constexpr int kMaxChunkWindowLayers = 128; // layers per call when every layer brings its own window
 constexpr int kMaxStreamAgents = 256;      // agents of a call whose tiles are dealt out evenly
 
@@ -865,12 +865,12 @@ __global__ __launch_bounds__(kMergeThreads) void chunk_merge_kernel(ChunkParams 
 
 // ---------------------------------------------------------------------------------------------- launch
 
-// Rows per workgroup.  With 128 rows a tile costs about 0.6 of what it costs with 256 (its staging does not shrink), so
+// Rows per workgroup of a call with equal shares (chunk_rules.h: without).  With 128 rows a tile costs about 0.6 of what it costs with 256 (its staging does not shrink), so
 // 128 are taken where 256 would be padding.  Measured (one layer, equal shares, 128 against 256 rows): 128 query rows of
 // 256-wide heads, ten agents of 4K-32K tokens 295 / 460 us; 384 rows, two agents of 4K 77 / 83 us; 280 rows of 128-wide
 // heads, four agents of up to 6K 62 / 60 us.
 // And where a compute unit's share is short: every workgroup of a shared unit leaves a record of its rows, and half the
-// rows are half the record (and, without a workspace, twice the workgroups).  The line is at 448 tokens per compute unit
+// rows are half the record.  The line is at 448 tokens per compute unit
 // (128 / 256 rows, us): 512 new tokens, 256-wide: 100 tokens per unit 48.6 / 55.6, 189 57.6 / 64.6, 314 68.1 / 70.9, 564
 // 90.3 / 94.4, 1,064 132 / 131; 128-wide: 253 44.5 / 44.4, 628 63.7 / 60.6; 192 + 128: 139 39.6 / 48.9, 439 57.2 / 56.7;
 // 64-wide, 131 tokens: 351 35.0 / 39.6.
@@ -899,6 +899,10 @@ bool stream_pays(const q4kv_spec &s, int num_agents, int q_len, int max_seq_len,
            units * (max_seq_len / kSub + 2) < 0x3fffffff; // tiles are numbered with 32-bit integers
 }
 
+// a.chunk_workers > 0: the call has a workspace of two records for each of that many workgroups.  A call whose layers have
+// windows of their own numbers no tiles.
+bool chunk_shares(const AttentionArgs &a) { return a.chunk_workers > 0 && !(a.layer_window && a.layers_in_call > 1); }
+
 template <int DK, int DV, int NREP, int KSPLIT>
 hipError_t launch_chunk_k(const AttentionArgs &a, hipStream_t stream)
 {
@@ -923,8 +927,7 @@ hipError_t launch_chunk_k(const AttentionArgs &a, hipStream_t stream)
     p.score_scale = a.sm_scale * kLog2e;
     p.part_acc = a.part_acc; p.part_ml = a.part_ml;
     p.shared = reinterpret_cast<ChunkShared *>(a.part_ml + 2 * (size_t)a.chunk_workers * ROWGROUPS * kRowsWave * 2);
-    // a.chunk_workers > 0: the workspace holds two records for each of that many workgroups
-    p.stream = a.chunk_workers > 0 && !p.per_layer_windows;
+    p.stream = chunk_shares(a);
     const int64_t units = (int64_t)a.layers_in_call * a.num_agents * a.spec.num_kv_heads;
     const int64_t grid = p.stream ? a.chunk_workers : (units + kXcds - 1) / kXcds * kXcds * p.q_tiles;
     if (grid <= 0) return hipSuccess;
@@ -942,7 +945,16 @@ hipError_t launch_chunk_k(const AttentionArgs &a, hipStream_t stream)
 template <int DK, int DV, int NREP>
 hipError_t launch_chunk_t(const AttentionArgs &a, hipStream_t stream)
 {
-    const int rows = rows_per_workgroup(a.spec, a.num_agents, a.q_len, a.max_seq_len, a.layers_in_call, a.compute_units);
+    int rows;
+    if (chunk_shares(a)) {
+        rows = rows_per_workgroup(a.spec, a.num_agents, a.q_len, a.max_seq_len, a.layers_in_call, a.compute_units);
+    } else {
+        int tokens[kMaxChunkWindowLayers]; // one entry unless the layers differ
+        const int n = a.layer_window ? a.layers_in_call : 1;
+        for (int i = 0; i < n; ++i) tokens[i] = visible_tokens(a.max_seq_len, a.layer_window ? a.layer_window[i] : a.window, a.q_len, NREP);
+        const ChunkSizes sizes{(int64_t)a.layers_in_call * a.num_agents * a.spec.num_kv_heads, (int64_t)a.q_len * NREP, a.compute_units};
+        rows = rows_alone(sizes, tokens, n);
+    }
     return rows == 256 ? launch_chunk_k<DK, DV, NREP, 1>(a, stream) : launch_chunk_k<DK, DV, NREP, 2>(a, stream);
 }
 
