@@ -66,7 +66,6 @@ constexpr int kSub = 32;      // tokens per matrix tile of scores
 constexpr float kNegBig = -1.0e30f;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kMaxChunkWindowLayers = 128; // layers per call when every layer brings its own window
-constexpr int kMaxStreamAgents = 256;      // agents of a call whose tiles are dealt out evenly
 
 typedef float float16_t __attribute__((ext_vector_type(16)));
 
@@ -865,46 +864,13 @@ __global__ __launch_bounds__(kMergeThreads) void chunk_merge_kernel(ChunkParams 
 
 // ---------------------------------------------------------------------------------------------- launch
 
-// Rows per workgroup of a call with equal shares (chunk_rules.h: without).  With 128 rows a tile costs about 0.6 of what it costs with 256 (its staging does not shrink), so
-// 128 are taken where 256 would be padding.  Measured (one layer, equal shares, 128 against 256 rows): 128 query rows of
-// 256-wide heads, ten agents of 4K-32K tokens 295 / 460 us; 384 rows, two agents of 4K 77 / 83 us; 280 rows of 128-wide
-// heads, four agents of up to 6K 62 / 60 us.
-// And where a compute unit's share is short: every workgroup of a shared unit leaves a record of its rows, and half the
-// rows are half the record.  The line is at 448 tokens per compute unit
-// (128 / 256 rows, us): 512 new tokens, 256-wide: 100 tokens per unit 48.6 / 55.6, 189 57.6 / 64.6, 314 68.1 / 70.9, 564
-// 90.3 / 94.4, 1,064 132 / 131; 128-wide: 253 44.5 / 44.4, 628 63.7 / 60.6; 192 + 128: 139 39.6 / 48.9, 439 57.2 / 56.7;
-// 64-wide, 131 tokens: 351 35.0 / 39.6.
-int rows_per_workgroup(const q4kv_spec &s, int num_agents, int q_len, int max_seq_len, int layers, int compute_units)
+ChunkSizes chunk_sizes(const q4kv_spec &s, int num_agents, int q_len, int layers, int compute_units)
 {
-    const int64_t rows = (int64_t)q_len * (s.num_q_heads / s.num_kv_heads), wide = (rows + 255) / 256, narrow = (rows + 127) / 128;
-    if (0.6 * narrow < wide) return 128;
-    return (double)layers * num_agents * s.num_kv_heads * wide * max_seq_len < 448.0 * compute_units ? 128 : 256;
+    return ChunkSizes{(int64_t)layers * num_agents * s.num_kv_heads, (int64_t)q_len * (s.num_q_heads / s.num_kv_heads), compute_units};
 }
-
-// Whether a call's tiles are dealt out evenly over the compute units (needs a workspace) instead of one unit per
-// workgroup.  Measured (us, one unit per workgroup / equal shares): 256-wide heads, 512-token chunk, one agent of 300,
-// 2,000, 8,000 tokens 74 / 57, 187 / 72, 571 / 133; ten agents of 4K-32K (320 units) 2,130 / 1,842; six layers of ten
-// agents of 1K-1.5K (1,920 units) 1,191 / 1,145, twelve (3,840) 2,278 / 2,239; 128-wide heads, 16 tokens behind 8,000
-// 202 / 37.  The line is at two units per compute unit: a workgroup that takes an equal share holds its compute unit
-// until the call ends, and a decode step on another stream, which gets in whenever a workgroup ends, waits for that
-// long.  48 layers of 512 tokens behind 16,384 (1,536 units) take 7.63 ms with one unit per workgroup, 8.04 with equal
-// shares; decode steps of 0.76 ms beside them then take 2.1 and 4.9 ms.  At 256 tokens a unit has too few tiles to
-// share.
-bool stream_pays(const q4kv_spec &s, int num_agents, int q_len, int max_seq_len, int layers, int compute_units)
-{
-    const int per_wg = rows_per_workgroup(s, num_agents, q_len, max_seq_len, layers, compute_units);
-    const int64_t rows = (int64_t)q_len * (s.num_q_heads / s.num_kv_heads);
-    const int64_t units = (int64_t)layers * num_agents * s.num_kv_heads * ((rows + per_wg - 1) / per_wg);
-    return num_agents <= kMaxStreamAgents && max_seq_len > 256 && units < 2 * (int64_t)compute_units &&
-           units * (max_seq_len / kSub + 2) < 0x3fffffff; // tiles are numbered with 32-bit integers
-}
-
-// a.chunk_workers > 0: the call has a workspace of two records for each of that many workgroups.  A call whose layers have
-// windows of their own numbers no tiles.
-bool chunk_shares(const AttentionArgs &a) { return a.chunk_workers > 0 && !(a.layer_window && a.layers_in_call > 1); }
 
 template <int DK, int DV, int NREP, int KSPLIT>
-hipError_t launch_chunk_k(const AttentionArgs &a, hipStream_t stream)
+hipError_t launch_chunk_k(const AttentionArgs &a, bool shares, hipStream_t stream)
 {
     constexpr int ROWGROUPS = kChunkWaves / KSPLIT;
     constexpr int QPOS = ROWGROUPS * kRowsWave / NREP;
@@ -927,7 +893,7 @@ hipError_t launch_chunk_k(const AttentionArgs &a, hipStream_t stream)
     p.score_scale = a.sm_scale * kLog2e;
     p.part_acc = a.part_acc; p.part_ml = a.part_ml;
     p.shared = reinterpret_cast<ChunkShared *>(a.part_ml + 2 * (size_t)a.chunk_workers * ROWGROUPS * kRowsWave * 2);
-    p.stream = chunk_shares(a);
+    p.stream = shares;
     const int64_t units = (int64_t)a.layers_in_call * a.num_agents * a.spec.num_kv_heads;
     const int64_t grid = p.stream ? a.chunk_workers : (units + kXcds - 1) / kXcds * kXcds * p.q_tiles;
     if (grid <= 0) return hipSuccess;
@@ -945,17 +911,14 @@ hipError_t launch_chunk_k(const AttentionArgs &a, hipStream_t stream)
 template <int DK, int DV, int NREP>
 hipError_t launch_chunk_t(const AttentionArgs &a, hipStream_t stream)
 {
-    int rows;
-    if (chunk_shares(a)) {
-        rows = rows_per_workgroup(a.spec, a.num_agents, a.q_len, a.max_seq_len, a.layers_in_call, a.compute_units);
-    } else {
-        int tokens[kMaxChunkWindowLayers]; // one entry unless the layers differ
-        const int n = a.layer_window ? a.layers_in_call : 1;
-        for (int i = 0; i < n; ++i) tokens[i] = visible_tokens(a.max_seq_len, a.layer_window ? a.layer_window[i] : a.window, a.q_len, NREP);
-        const ChunkSizes sizes{(int64_t)a.layers_in_call * a.num_agents * a.spec.num_kv_heads, (int64_t)a.q_len * NREP, a.compute_units};
-        rows = rows_alone(sizes, tokens, n);
-    }
-    return rows == 256 ? launch_chunk_k<DK, DV, NREP, 1>(a, stream) : launch_chunk_k<DK, DV, NREP, 2>(a, stream);
+    int tokens[kMaxChunkWindowLayers]; // what a workgroup sees; one entry unless the layers have windows of their own
+    const int n = a.layer_window ? a.layers_in_call : 1;
+    for (int i = 0; i < n; ++i) tokens[i] = visible_tokens(a.max_seq_len, a.layer_window ? a.layer_window[i] : a.window, a.q_len, NREP);
+    const ChunkSizes sizes = chunk_sizes(a.spec, a.num_agents, a.q_len, a.layers_in_call, a.compute_units);
+    // a.chunk_workers > 0: the workspace holds two records for each of that many workgroups
+    const bool shares = a.chunk_workers > 0 && n == 1 && shares_pay(sizes, DK, tokens[0]);
+    const int rows = shares ? rows_shared(sizes, tokens[0]) : rows_alone(sizes, tokens, n);
+    return rows == 256 ? launch_chunk_k<DK, DV, NREP, 1>(a, shares, stream) : launch_chunk_k<DK, DV, NREP, 2>(a, shares, stream);
 }
 
 template <int DK, int DV>
@@ -976,8 +939,10 @@ size_t chunk_workspace_bytes(const q4kv_spec &s, int num_agents, int q_len, int 
                              size_t &acc_bytes)
 {
     acc_bytes = 0;
-    if (!chunk_supported(s) || !stream_pays(s, num_agents, q_len, max_seq_len, layers, compute_units)) return 0;
-    const size_t rows = 2 * (size_t)compute_units * rows_per_workgroup(s, num_agents, q_len, max_seq_len, layers, compute_units);
+    const ChunkSizes sizes = chunk_sizes(s, num_agents, q_len, layers, compute_units);
+    if (!chunk_supported(s) || !shares_fit(sizes, num_agents, max_seq_len)) return 0;
+    // a window can only make a call take fewer rows per workgroup than this
+    const size_t rows = 2 * (size_t)compute_units * rows_shared(sizes, max_seq_len);
     acc_bytes = rows * s.v_dim * sizeof(float);
     // The size tells a workspace that was made for such a call from any other.  Those of decode calls are multiples of 8
     // (plan and counters in pieces of 256 bytes, records of (v_dim + 2) floats), so 4 more bytes make it one of its own.

@@ -1,5 +1,6 @@
 """The launch rules of the chunk kernel (csrc/chunk_rules.h) against what was measured on the two sides of each, for 256 compute
-units: with one unit per workgroup a call takes 128 rows per workgroup while 256-row ones leave compute units idle."""
+units: with one unit per workgroup a call takes 128 rows per workgroup while 256-row ones leave compute units idle, and tiles
+are shared out evenly only where that is done first."""
 import os
 import subprocess
 
@@ -18,10 +19,10 @@ def rules(tmp_path_factory):
         args = []
         for width, layers, agents, q_len, max_seq_len, windows in calls:
             heads, rep = SHAPES[width]
-            args += [layers * agents * heads, q_len * rep, rep, max_seq_len, "%d:%s" % (q_len, ",".join(map(str, windows)))]
-        out = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, check=True).stdout.split()
+            args += [width, agents, layers * agents * heads, q_len * rep, rep, max_seq_len, "%d:%s" % (q_len, ",".join(map(str, windows)))]
+        out = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, check=True).stdout.splitlines()
         assert len(out) == len(calls)
-        return [int(x) for x in out]
+        return [tuple(int(x) for x in line.split()) for line in out]
     return ask
 
 
@@ -54,11 +55,56 @@ ALONE = [
 
 
 def test_rows_without_shares_take_the_faster_side(rules):
-    got = rules([call for call, _, _ in ALONE])
+    got = [r[0] for r in rules([call for call, _, _ in ALONE])]
     assert got == [128 if narrow < wide else 256 for _, narrow, wide in ALONE]
 
 
 def test_rows_without_shares_at_the_ends_of_the_range(rules):
     # no cached token at all, one token, the largest bound, 2^31 - 1 tokens of window
-    assert rules([("256", 1, 1, 2, 0, (0,)), ("128", 1, 1, 2, 1, (0,)), ("256", 1, 1, 512, 2 ** 31 - 1, (0,)),
-                  ("256", 1, 1, 512, 8512, (2 ** 31 - 1,)), ("64", 48, 256, 700, 32768, (0,))]) == [128, 128, 128, 128, 256]
+    got = rules([("256", 1, 1, 2, 0, (0,)), ("128", 1, 1, 2, 1, (0,)), ("256", 1, 1, 512, 2 ** 31 - 1, (0,)),
+                  ("256", 1, 1, 512, 8512, (2 ** 31 - 1,)), ("64", 48, 256, 700, 32768, (0,))])
+    assert [r[0] for r in got] == [128, 128, 128, 128, 256]
+    assert [r[2:] for r in got] == [(0, 0), (0, 0), (1, 0), (1, 1), (0, 0)]   # the third has too many tiles to number
+
+
+# ..., us with one unit per workgroup (the better row count), us with equal shares (the row count of the rule)
+SHARES = [
+    (("256", 1, 1, 512, 8512, (0,)), 315.8, 135.3),
+    (("256", 1, 1, 512, 2512, (0,)), 112.3, 70.7),
+    (("256", 1, 10, 512, 33280, (0,)), 2000.0, 1835.9),
+    (("256", 1, 1, 512, 16512, (1024,)), 57.6, 53.5),
+    (("256", 1, 10, 2, 282, (0,)), 25.1, 37.0),
+    (("256", 1, 10, 70, 350, (0,)), 34.1, 50.3),
+    (("256", 1, 3, 512, 792, (0,)), 50.7, 66.1),
+    (("256", 1, 3, 512, 1212, (0,)), 67.4, 80.5),
+    (("256", 1, 1, 70, 350, (0,)), 31.2, 26.7),
+    (("128", 1, 1, 512, 792, (0,)), 30.9, 41.8),
+    (("128", 1, 1, 512, 1212, (0,)), 39.7, 48.6),
+    (("128", 1, 1, 512, 2512, (0,)), 66.6, 61.9),
+    (("128", 1, 1, 512, 8512, (0,)), 182.9, 127.7),
+    (("128", 1, 3, 200, 480, (0,)), 24.8, 39.9),
+    (("128", 1, 10, 16, 296, (0,)), 19.7, 23.4),
+    (("128", 1, 10, 16, 1516, (0,)), 43.7, 32.7),
+    (("128", 1, 1, 512, 16512, (1024,)), 36.2, 47.5),
+    (("192", 1, 10, 70, 350, (0,)), 22.1, 37.9),
+    (("192", 1, 1, 512, 2012, (0,)), 61.9, 49.5),
+    (("192", 1, 3, 2, 702, (0,)), 27.9, 23.2),
+    (("192", 1, 10, 512, 792, (0,)), 105.5, 97.8),
+    (("64", 2, 70, 3, 703, (0,)), 21.0, 27.8),
+    (("64", 1, 1, 512, 8512, (0,)), 134.1, 48.0),
+]
+
+
+def test_shares_are_taken_where_they_are_done_first(rules):
+    got = rules([call for call, _, _ in SHARES])
+    assert [r[2] for r in got] == [1 if shared < alone else 0 for _, alone, shared in SHARES]
+    assert all(r[3] == 1 for r in got)                  # all of them come with a workspace
+
+
+def test_shares_never_need_more_rows_than_the_workspace_was_sized_for(rules):
+    """The size is asked for without a window; the call then goes by what its window lets it see."""
+    calls = [(width, 1, agents, q_len, top, (window,)) for width in SHAPES for agents in (1, 3, 10) for q_len in (2, 70, 300, 512)
+             for top in (600, 5000, 40000, 131072) for window in (0, 1, 300, 1024, 8192)]
+    got = rules(calls)
+    sized = {c[:5]: r[1] for c, r in zip(calls, got) if c[5] == (0,)}
+    assert all(r[1] <= sized[c[:5]] for c, r in zip(calls, got))
