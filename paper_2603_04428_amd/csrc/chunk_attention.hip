@@ -87,7 +87,6 @@ struct ChunkParams {
     ChunkShared *shared;            // [grid]: the unit that begins in a workgroup's range and goes on past it
     int num_blocks, kv_heads, q_heads, num_agents, max_blocks, max_seq_len, window, q_len;
     int layer_begin, layers_in_call, q_tiles;
-    int stream;                     // 1: every workgroup takes an equal range of all tiles; 0: one unit per workgroup
     float score_scale;
     int per_layer_windows;          // 1: layer_window[] holds the window of every layer of the call
     int layer_window[kMaxChunkWindowLayers];
@@ -248,8 +247,9 @@ constexpr int chunk_pieces(int dk) { return dk == 256 ? 1 : 2; }
 constexpr int chunk_tile(int dk, int ksplit) { return kSub * chunk_pieces(dk) * ksplit; }
 
 // KSPLIT 1: 256 rows per workgroup; 2: 128 rows, the two halves of the waves share the tokens of a tile.
+// SHARES: the workgroup takes an equal share of all tiles; else one unit.
 // BF: scale and bias are stored as bfloat16 (converted to binary16 when a row is staged).
-template <int DK, int DV, int NREP, int KSPLIT, bool BF>
+template <int DK, int DV, int NREP, int KSPLIT, bool SHARES, bool BF>
 __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(ChunkParams p)
 {
     constexpr int GK = DK / kGroup, GV = DV / kGroup;
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
     // head), or an equal share of all tiles (consecutive shares on one XCD)
     const ChunkStream<QPOS, TILE> stream{s_pre, s_len};
     int x = 0, x1 = 1, per = 1, worker = 0;
-    if (p.stream) {
+    if constexpr (SHARES) {
         if (wave == 0) ChunkStream<QPOS, TILE>::fill(p, s_pre, s_len, threadIdx.x);
         __syncthreads();
         const int total = p.layers_in_call * scalar(s_pre[p.num_agents]), grid = gridDim.x;
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         const int lane = tid & (kWave - 1), qn = lane % 32, h = lane / 32;
         ChunkUnit u;
         int begin = 0, tiles = 0, part_end, n;
-        if (p.stream) {
+        if constexpr (SHARES) {
             u = stream.locate(p, x, begin, tiles, n);
             part_end = min(tiles, begin + (x1 - x));
         } else {
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         int t_begin, t_end;
         visible_range<QPOS, TILE>(p, n, window, u.qt, t_begin, t_end);
         const int part_t0 = t_begin + begin * TILE;
-        const int part_t1 = p.stream ? min(t_end, t_begin + part_end * TILE) : t_end; // exclusive; may be <= part_t0
+        const int part_t1 = SHARES ? min(t_end, t_begin + part_end * TILE) : t_end; // exclusive; may be <= part_t0
 
         // ---- KV tile staging: raw Q4 in registers one tile ahead.  A thread takes WPT consecutive words of one token's
         // K row and (the same ones when the rows are equally wide) of one token's V row; with rows that do not divide
@@ -759,7 +759,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             }
         }
 
-        const bool whole = !p.stream || (begin == 0 && part_end == tiles);
+        const bool whole = !SHARES || (begin == 0 && part_end == tiles);
         if (wave_live && my_sub == 0) {
             if (whole) { // ---- normalise and store
                 const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
@@ -790,7 +790,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                 if (h == 0) *reinterpret_cast<float2 *>(p.part_ml + (rec * kRowsWave + qn) * 2) = make_float2(m_run, l_tot);
             }
         }
-        if (p.stream && threadIdx.x == 0 && begin == 0 && part_end < tiles) {
+        if (SHARES && threadIdx.x == 0 && begin == 0 && part_end < tiles) {
             ChunkShared *s = p.shared + worker;
             s->slots = (x + tiles - 1) / per - worker + 1;
             s->first_record = worker * 2 + (x > range_begin ? 1 : 0);
@@ -798,7 +798,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             s->kvh = u.kvh;
             s->token_row = ((int64_t)u.li * p.num_agents + u.agent) * p.q_len;
         }
-        x += p.stream ? part_end - begin : 1;
+        x += SHARES ? part_end - begin : 1;
     }
 }
 
@@ -869,8 +869,8 @@ ChunkSizes chunk_sizes(const q4kv_spec &s, int num_agents, int q_len, int layers
     return ChunkSizes{(int64_t)layers * num_agents * s.num_kv_heads, (int64_t)q_len * (s.num_q_heads / s.num_kv_heads), compute_units};
 }
 
-template <int DK, int DV, int NREP, int KSPLIT>
-hipError_t launch_chunk_k(const AttentionArgs &a, bool shares, hipStream_t stream)
+template <int DK, int DV, int NREP, int KSPLIT, bool SHARES>
+hipError_t launch_chunk_k(const AttentionArgs &a, hipStream_t stream)
 {
     constexpr int ROWGROUPS = kChunkWaves / KSPLIT;
     constexpr int QPOS = ROWGROUPS * kRowsWave / NREP;
@@ -893,16 +893,15 @@ hipError_t launch_chunk_k(const AttentionArgs &a, bool shares, hipStream_t strea
     p.score_scale = a.sm_scale * kLog2e;
     p.part_acc = a.part_acc; p.part_ml = a.part_ml;
     p.shared = reinterpret_cast<ChunkShared *>(a.part_ml + 2 * (size_t)a.chunk_workers * ROWGROUPS * kRowsWave * 2);
-    p.stream = shares;
     const int64_t units = (int64_t)a.layers_in_call * a.num_agents * a.spec.num_kv_heads;
-    const int64_t grid = p.stream ? a.chunk_workers : (units + kXcds - 1) / kXcds * kXcds * p.q_tiles;
+    const int64_t grid = SHARES ? a.chunk_workers : (units + kXcds - 1) / kXcds * kXcds * p.q_tiles;
     if (grid <= 0) return hipSuccess;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     if (a.spec.param_format == Q4KV_PARAMS_BF16)
-        hipLaunchKernelGGL((chunk_attention_kernel<DK, DV, NREP, KSPLIT, true>), dim3((unsigned)grid), dim3(kChunkThreads), 0, stream, p);
+        hipLaunchKernelGGL((chunk_attention_kernel<DK, DV, NREP, KSPLIT, SHARES, true>), dim3((unsigned)grid), dim3(kChunkThreads), 0, stream, p);
     else
-        hipLaunchKernelGGL((chunk_attention_kernel<DK, DV, NREP, KSPLIT, false>), dim3((unsigned)grid), dim3(kChunkThreads), 0, stream, p);
-    if (p.stream)
+        hipLaunchKernelGGL((chunk_attention_kernel<DK, DV, NREP, KSPLIT, SHARES, false>), dim3((unsigned)grid), dim3(kChunkThreads), 0, stream, p);
+    if constexpr (SHARES)
         hipLaunchKernelGGL((chunk_merge_kernel<DV, NREP, ROWGROUPS>), dim3((unsigned)grid * merge_parts<DV, ROWGROUPS>()),
                            dim3(kMergeThreads), 0, stream, p);
     return hipGetLastError();
@@ -918,7 +917,8 @@ hipError_t launch_chunk_t(const AttentionArgs &a, hipStream_t stream)
     // a.chunk_workers > 0: the workspace holds two records for each of that many workgroups
     const bool shares = a.chunk_workers > 0 && n == 1 && shares_pay(sizes, DK, tokens[0]);
     const int rows = shares ? rows_shared(sizes, tokens[0]) : rows_alone(sizes, tokens, n);
-    return rows == 256 ? launch_chunk_k<DK, DV, NREP, 1>(a, shares, stream) : launch_chunk_k<DK, DV, NREP, 2>(a, shares, stream);
+    if (shares) return rows == 256 ? launch_chunk_k<DK, DV, NREP, 1, true>(a, stream) : launch_chunk_k<DK, DV, NREP, 2, true>(a, stream);
+    return rows == 256 ? launch_chunk_k<DK, DV, NREP, 1, false>(a, stream) : launch_chunk_k<DK, DV, NREP, 2, false>(a, stream);
 }
 
 template <int DK, int DV>
