@@ -319,8 +319,20 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             u.agent = unit / p.kv_heads % p.num_agents;
             u.li = unit / (p.kv_heads * p.num_agents);
             part_end = 1;
-            n = scalar(clamped_length(p, u.agent));
         }
+        // ---- this lane's query row: column qn of its wave's 32 (both halves of the wave hold the same row).  Asked for before
+        // the length and the block table, which are two trips to memory for the first tile (0.3-0.6 us of every call).
+        const int c = u.qt * QPOS + (rg * kRowsWave + qn) / NREP, head = u.kvh * NREP + (rg * kRowsWave + qn) % NREP;
+        const int64_t q_row = (((int64_t)u.li * p.num_agents + u.agent) * p.q_len + min(c, p.q_len - 1)) * p.q_heads + head;
+        uint4 q_raw[GK][4];
+        {
+            const uint16_t *src = p.q + q_row * DK + 32 * h;
+#pragma unroll
+            for (int g = 0; g < GK; ++g)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) q_raw[g][i] = *reinterpret_cast<const uint4 *>(src + kGroup * g + 8 * i);
+        }
+        if constexpr (!SHARES) n = scalar(clamped_length(p, u.agent));
         const int layer = p.layer_begin + u.li;
         const int window = p.per_layer_windows ? p.layer_window[u.li] : p.window;
         int t_begin, t_end;
@@ -443,21 +455,20 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         auto row_ok = [&](int t0, int tok, bool ok_tile) { return ok_tile && (t0 + tok < t_end); };
         const int k_dst = k_tok * KPITCH + k_w0, v_dst = v_tok * VPITCH + v_w0 * 8;
 
-        // the first tile is on its way while the queries are read
+        // the first tile is on its way while the queries are unpacked
         const int t_last = part_t0 < part_t1 ? part_t0 + (part_t1 - 1 - part_t0) / TILE * TILE : 0; // start of the last tile
         const int second = min(part_t0 + TILE, t_last);
         bool ok_next = false, ok_cur = false;
         int64_t row_b = 0;
-        if (part_t0 < part_t1) {
-            const int entry0 = block_of(part_t0), entry1 = block_of(second);
+        if (part_t0 < part_t1) { // entry 0 of the table is there already
+            const int entry0 = part_t0 < kBlockTokens ? own0 : block_of(part_t0), entry1 = second < kBlockTokens ? own0 : block_of(second);
             const int64_t row_a = tile_row0(part_t0, entry0, ok_cur);
             row_b = tile_row0(second, entry1, ok_next);
             load_k(row_a);
             load_v(row_a);
         }
 
-        // ---- this lane's query row: column qn of its wave's 32 (both halves of the wave hold the same row)
-        const int c = u.qt * QPOS + (rg * kRowsWave + qn) / NREP, head = u.kvh * NREP + (rg * kRowsWave + qn) % NREP;
+        // ---- what this lane's row sees, and its query operand
         const bool wave_live = u.qt * QPOS + rg * kRowsWave / NREP < p.q_len; // the wave's first row; wave-uniform
         // rows past the chunk repeat its last position (and are not stored)
         auto row_sees = [&](int pos) { return n - (p.q_len - 1 - min(pos, p.q_len - 1)); };
@@ -466,12 +477,10 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         // tokens inside [all_first, all_vis) are visible to every row of this wave and need no masks
         const int all_vis = row_sees(u.qt * QPOS + rg * kRowsWave / NREP);
         const int all_first = row_hides(row_sees(u.qt * QPOS + (rg * kRowsWave + kRowsWave - 1) / NREP));
-        const int64_t q_row = (((int64_t)u.li * p.num_agents + u.agent) * p.q_len + min(c, p.q_len - 1)) * p.q_heads + head;
         half8_t qop[QREG][4]; // [group][matrix instruction]: the 8 dims of word 8 g + 4 h + i
         half8_t qsop;         // lower half of the wave: group sums of q, high parts in slots 0..3, low parts in 4..7; else 0
         {
             float qs[GK];
-            const uint16_t *src = p.q + q_row * DK + 32 * h;
 #pragma unroll
             for (int g = 0; g < GK; ++g) {
                 qs[g] = 0.0f;
@@ -479,7 +488,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                 for (int i = 0; i < 4; ++i) {
                     // 8 dims in the order the nibble masks emit them: 0,4,1,5,2,6,3,7; the odd ones divided by 16
                     // because their codes arrive 16 times larger
-                    const uint4 raw = *reinterpret_cast<const uint4 *>(src + kGroup * g + 8 * i);
+                    const uint4 raw = q_raw[g][i];
                     const half2_t e01 = bits_to_half2(raw.x), e23 = bits_to_half2(raw.y);
                     const half2_t e45 = bits_to_half2(raw.z), e67 = bits_to_half2(raw.w);
                     const half_t sixteenth = (half_t)0.0625f;
@@ -712,7 +721,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         }
 
         float l_tot = xor32_sum(l_run);
-        if constexpr (KSPLIT == 2) {
+        if constexpr (KSPLIT == 2) if (part_t1 - part_t0 > kSub * NP) { // else the upper half has seen no token
             // The upper half of the waves hands its sums to the lower one through the V buffers, a few dim tiles at a
             // time; the maxima and denominators travel in the K buffers.
             constexpr int MT = (int)(2 * TILE * VPITCH * sizeof(half_t) / (ROWGROUPS * kWave * 16 * sizeof(float))) < DTILES
@@ -720,13 +729,13 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             static_assert(MT >= 1, "room for one dim tile");
             float *ml = reinterpret_cast<float *>(&k_lds[0][0]);
             float *xch = reinterpret_cast<float *>(&v_lds[0][0]);
-            if (my_sub == 1) {
+            if (my_sub == 1 && wave_live) {
                 ml[(rg * 2) * kWave + lane] = m_run;
                 ml[(rg * 2 + 1) * kWave + lane] = l_tot;
             }
             __syncthreads();
             float w_lo = 1.0f, w_hi = 0.0f;
-            if (my_sub == 0) {
+            if (my_sub == 0 && wave_live) {
                 const float m_hi = ml[(rg * 2) * kWave + lane], l_hi = ml[(rg * 2 + 1) * kWave + lane];
                 const float m_new = fmaxf(m_run, m_hi);
                 w_lo = __builtin_amdgcn_exp2f(m_run - m_new);
@@ -736,7 +745,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             }
 #pragma unroll
             for (int d0 = 0; d0 < DTILES; d0 += MT) {
-                if (my_sub == 1) {
+                if (my_sub == 1 && wave_live) {
 #pragma unroll
                     for (int d = d0; d < d0 + MT && d < DTILES; ++d)
 #pragma unroll
@@ -745,7 +754,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                                 float4_t{o_acc[d][4 * j], o_acc[d][4 * j + 1], o_acc[d][4 * j + 2], o_acc[d][4 * j + 3]};
                 }
                 __syncthreads();
-                if (my_sub == 0) {
+                if (my_sub == 0 && wave_live) {
 #pragma unroll
                     for (int d = d0; d < d0 + MT && d < DTILES; ++d)
 #pragma unroll
