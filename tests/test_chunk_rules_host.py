@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+from tests.test_gpu_chunk import WIDE_ALONE, WIDE_SHARED
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 SHAPES = {"256": (8, 2), "128": (8, 4), "192": (16, 1), "64": (1, 8)}   # head width: KV heads, query heads per KV head
 
@@ -18,7 +20,8 @@ def rules(tmp_path_factory):
     def ask(calls):
         args = []
         for width, layers, agents, q_len, max_seq_len, windows in calls:
-            heads, rep = SHAPES[width]
+            heads, rep = SHAPES[width] if isinstance(width, str) else width[1:]
+            width = width if isinstance(width, str) else width[0]
             args += [width, agents, layers * agents * heads, q_len * rep, rep, max_seq_len, "%d:%s" % (q_len, ",".join(map(str, windows)))]
         out = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, check=True).stdout.splitlines()
         assert len(out) == len(calls)
@@ -108,3 +111,16 @@ def test_shares_never_need_more_rows_than_the_workspace_was_sized_for(rules):
     got = rules(calls)
     sized = {c[:5]: r[1] for c, r in zip(calls, got) if c[5] == (0,)}
     assert all(r[1] <= sized[c[:5]] for c, r in zip(calls, got))
+
+
+def test_the_gpu_tests_of_256_rows_take_256_rows(rules):
+    def call(case, max_seq_len):
+        Hq, Hkv, D, lens, q_len = case
+        return ((D[0] if isinstance(D, tuple) else D, Hkv, Hq // Hkv), 1, len(lens), q_len, max_seq_len or max(lens) + q_len, (0,))
+
+    got = rules([call(c, 131072) for c in WIDE_SHARED])
+    assert [r[1:] for r in got] == [(256, 1, 1)] * len(WIDE_SHARED)
+    got = rules([call(c, 131072)[:5] + ((300,),) for c in WIDE_SHARED])   # with a window they may take either
+    assert all(r[3] == 1 for r in got)
+    got = rules([call(c, 0) for c in WIDE_ALONE])
+    assert [r[0] for r in got] == [256] * len(WIDE_ALONE)

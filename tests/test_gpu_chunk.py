@@ -244,7 +244,7 @@ SHARED = [
     (4, 2, 256, (641, 990), 65),              # one row pair more
     (2, 2, 256, (2049,), 256),                # 256 rows, 32-token tiles, lengths one past a tile
     (2, 2, 256, (480, 1000), 33),
-    (8, 2, 128, (1999, 64, 513), 70),         # 280 rows: the last row tile nearly empty
+    (8, 2, 128, (1999, 64, 513), 70),         # 280 rows: three tiles of 128, the last nearly empty
     (4, 4, (192, 128), (1500, 300), 130),
     (8, 1, 64, (5000,), 2),                   # one unit of 79 tiles: every workgroup takes one
     (8, 1, 64, (700,) * 70, 3),               # more agents than lanes
@@ -256,7 +256,7 @@ SHARED = [
 def test_chunk_shared_by_workgroups_matches_oracle(case, param_format):
     """With a workspace the tiles of all units are dealt out over the compute units and shared units are merged; without
     one a workgroup takes a unit.  Both against the oracle, with and without a window, with the lengths' own bound and with a
-    bound of 131,072 tokens (the work a call might hold decides how many rows a workgroup takes); the workspace is not
+    bound of 131,072 tokens (the work a call might hold decides how many rows a workgroup takes, and whether sharing pays); the workspace is not
     left, the result does not change from run to run."""
     Hq, Hkv, D, lens, C = case
     Dk, Dv = D if isinstance(D, tuple) else (D, D)
@@ -306,3 +306,115 @@ def test_chunk_call_leaves_a_workspace_of_another_size_alone():
     b.q4kv_batched_attention_planned(spec, kpool, vpool, q1, out, table_d, msl, w.sm_scale, ws)
     torch.cuda.synchronize()
     assert torch.equal(out, decode)
+
+
+# Calls that take 256 rows per workgroup: (query heads, KV heads, D, agents' cached tokens, chunk), one for each head width and
+# each number of query heads per KV head, 150 to 248 rows of 256, so that the last waves' rows are ragged or absent.  With
+# the bound of 131,072 tokens they take them with shares; WIDE_ALONE without, having enough units that twice the workgroups
+# would be two rounds (tests/test_chunk_rules_host.py asks the rules for both).
+WIDE_SHARED = [
+    (2, 2, 64, (900, 0), 200), (4, 2, 64, (900, 37), 101), (4, 1, 64, (700,), 61), (8, 1, 64, (3000,), 31),
+    (2, 2, 128, (700, 65), 150), (4, 2, 128, (700,), 97), (8, 2, 128, (1999, 0, 513), 50), (8, 1, 128, (700,), 29),
+    (4, 4, (192, 128), (600, 33), 161), (8, 4, (192, 128), (700, 40), 100), (4, 1, (192, 128), (600,), 50), (8, 1, (192, 128), (900,), 30),
+    (2, 2, 256, (700, 64), 201), (4, 2, 256, (900,), 77), (8, 2, 256, (900, 0), 52), (8, 1, 256, (800,), 31),
+]
+WIDE_ALONE = [(rep * kvh, kvh, D, (150, 0, 37, 64, 3, 101, 33, 70, 5, 128, 1, 90, 31, 12, 55, 200, 17), q_len)
+              for D in (64, 128, (192, 128), 256) for rep, kvh, q_len in ((1, 8, 130), (2, 8, 65), (4, 8, 33), (8, 8, 17))]
+
+
+@pytest.mark.parametrize("case", WIDE_SHARED)
+def test_chunk_of_256_rows_with_shares_matches_oracle(case):
+    Hq, Hkv, D, lens, C = case
+    Dk, Dv = D if isinstance(D, tuple) else (D, D)
+    w = synth.small(63, 1, Hq, Hkv, Dk, Dv, False, lens, q_len=C)
+    _, (spec, kpool, vpool, table_d) = append_chunk_and_attend(w)
+    ospec, okp, ovp, otable = host_cache(w)
+    sl, msl = torch.tensor(w.final_lens(), dtype=torch.int32, device=DEV), 512 * 256
+    q, wide = w.q_all(DEV), torch.nn.functional.pad(table_d, (0, 512 - table_d.shape[1])).contiguous()
+    need = b.q4kv_attention_workspace_bytes(spec, len(lens), C, msl, 0, 1)
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    assert need == units * (2 * 256 * (Dv + 2) * 4 + 24) + 4         # two records of 256 rows for each compute unit
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+    for window in (0, 300):
+        got = b.q4kv_batched_attention(spec, kpool, vpool, q, wide, sl, msl, w.sm_scale, window, workspace=ws)
+        torch.cuda.synchronize()
+        want = oracle.attention(ospec, okp, ovp, w.q_all().numpy(), otable, w.final_lens(), w.sm_scale, window=window)
+        assert_close(got.cpu().numpy(), want, f"{case} window {window}")
+
+
+@pytest.mark.parametrize("case", WIDE_ALONE)
+def test_chunk_of_256_rows_without_shares_matches_oracle(case):
+    Hq, Hkv, D, lens, C = case
+    Dk, Dv = D if isinstance(D, tuple) else (D, D)
+    w = synth.small(64, 1, Hq, Hkv, Dk, Dv, False, lens, q_len=C)
+    got, _ = append_chunk_and_attend(w)
+    ospec, okp, ovp, otable = host_cache(w)
+    want = oracle.attention(ospec, okp, ovp, w.q_all().numpy(), otable, w.final_lens(), w.sm_scale)
+    assert_close(got, want, f"{case}")
+
+
+@pytest.mark.parametrize("scale", [-0.11, 0.0])
+@pytest.mark.parametrize("D", [64, 256])
+def test_shared_chunk_with_a_scale_that_is_not_positive(scale, D):
+    """A scale <= 0 takes the path that assumes nothing about the order of scores; here with shares and without."""
+    w = synth.small(65, 1, 4, 2, D, D, False, (700, 130), q_len=65)
+    _, (spec, kpool, vpool, table_d) = append_chunk_and_attend(w)
+    ospec, okp, ovp, otable = host_cache(w)
+    sl, msl = torch.tensor(w.final_lens(), dtype=torch.int32, device=DEV), 512 * 256
+    q, wide = w.q_all(DEV), torch.nn.functional.pad(table_d, (0, 512 - table_d.shape[1])).contiguous()
+    ws = torch.empty(b.q4kv_attention_workspace_bytes(spec, 2, w.q_len, msl, 0, 1), dtype=torch.uint8, device=DEV)
+    want = oracle.attention(ospec, okp, ovp, w.q_all().numpy(), otable, w.final_lens(), scale)
+    for workspace in (ws, None):
+        got = b.q4kv_batched_attention(spec, kpool, vpool, q, wide, sl, msl, scale, workspace=workspace)
+        torch.cuda.synchronize()
+        assert_close(got.cpu().numpy(), want, f"scale {scale} width {D} shares {workspace is not None}")
+
+
+def test_chunk_of_more_agents_than_shares_are_numbered_for():
+    """Shares are dealt out to 256 agents at most: one more and the call asks for no workspace and runs without."""
+    lens = [(37 * i) % 90 for i in range(257)]
+    w = synth.small(66, 1, 8, 1, 64, 64, False, lens, q_len=3)
+    got, (spec, _, _, _) = append_chunk_and_attend(w)
+    assert b.q4kv_attention_workspace_bytes(spec, 256, 3, 131072, 0, 1) > 0
+    assert b.q4kv_attention_workspace_bytes(spec, 257, 3, 131072, 0, 1) == 0
+    ospec, okp, ovp, otable = host_cache(w)
+    want = oracle.attention(ospec, okp, ovp, w.q_all().numpy(), otable, w.final_lens(), w.sm_scale)
+    assert_close(got, want)
+
+
+def test_shared_chunk_replays_from_a_graph():
+    """The two kernels of a call with shares, recorded once and replayed with other lengths and queries, the program's own work
+    between the replays; every replay equals the eager call."""
+    w = synth.small(67, 1, 4, 2, 256, 256, False, (1300, 700), q_len=64)
+    _, (spec, kpool, vpool, table_d) = append_chunk_and_attend(w)
+    msl, q = max(w.final_lens()), w.q_all(DEV).clone()
+    sl = torch.tensor(w.final_lens(), dtype=torch.int32, device=DEV)
+    ws, ws2 = (torch.empty(b.q4kv_attention_workspace_bytes(spec, 2, w.q_len, msl, 0, 1), dtype=torch.uint8, device=DEV) for _ in range(2))
+
+    def call(out, workspace):
+        return b.q4kv_batched_attention(spec, kpool, vpool, q, table_d, sl, msl, w.sm_scale, out=out, workspace=workspace)
+
+    want = call(None, ws2)
+    out = torch.empty_like(want)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call(out, ws)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(out, ws)
+    alone = call(None, None)
+    torch.cuda.synchronize()
+    assert not torch.equal(alone, want)                 # the call recorded is the one with shares
+    for step, lens in enumerate((w.final_lens(), (64, 700), (1000, 0), w.final_lens())):
+        sl.copy_(torch.tensor(lens, dtype=torch.int32))
+        q.copy_(torch.randn(q.shape, generator=torch.Generator().manual_seed(step)).to(torch.float16))
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        want = call(None, ws2)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), f"replay {step}"

@@ -270,3 +270,38 @@ def test_small_append_matches_oracle(dims, chunk):
                     assert np.array_equal(bits(pool.bias[l, blk, :, slot]), bias)
             # the skipped agent's own block keeps its poison
             assert bool((pool.scale[l, int(table[2, 1]), :, 300 - 256:] == 0x7E00).all())
+
+
+@pytest.mark.parametrize("param_format", [0, 1])
+@pytest.mark.parametrize("dims", [(192, 128), (128, 64)])
+def test_long_append_matches_oracle(dims, param_format):
+    """Appends of more groups than the chip holds at once (rounds of 64 groups per wave): K and V rows of unequal width, group
+    counts that end inside a round, blocks crossed, a table entry outside the pool and one past the table; the whole pools."""
+    heads, chunk = (6, 701) if dims[0] == 192 else (12, 533)
+    w = synth.small(82, 2, heads, heads, dims[0], dims[1], False, (254, 0, 300), q_len=2)
+    A, L, groups = 3, 2, chunk * heads * (dims[0] // 64)
+    assert 2 * L * A * ((groups + 63) // 64) > 8 * torch.cuda.get_device_properties(0).multi_processor_count and groups % 64
+    lens = np.array(w.seq_lens, np.int32)
+    need = (lens + chunk + 255) // 256
+    nb, mb = int(need.sum()) + 1, int(need.max()) - 1               # the longest agent's last block is past the table
+    perm = np.random.default_rng(5).permutation(nb - 1)
+    table, at = np.zeros((A, mb), np.int32), 0
+    for a in range(A):
+        k = min(int(need[a]), mb)
+        table[a, :k] = perm[at:at + k]
+        at += k
+    table[0, 2] = nb                                                # one id past the pool
+    whole = np.concatenate([table, np.full((A, 1), nb + 1, np.int32)], axis=1)   # the oracle has blocks for the skipped tokens
+    gspec = b.make_spec(L, heads, heads, dims[0], dims[1], param_format=param_format)
+    ospec = oracle.make_spec(L, heads, heads, dims[0], dims[1], False, param_format=param_format)
+    fill = 0x7FC0 if param_format else 0x7E00
+    gk, gv = b.Pool(gspec, dims[0], nb, DEV, poison=True), b.Pool(gspec, dims[1], nb, DEV, poison=True)
+    ok, ov = oracle.Pool(ospec, dims[0], nb + 2, fill=fill), oracle.Pool(ospec, dims[1], nb + 2, fill=fill)
+    k_new = torch.stack([torch.stack([w.k_rows(l, a, 0, chunk) for a in range(A)]) for l in range(L)])
+    v_new = torch.stack([torch.stack([w.v_rows(l, a, 0, chunk) for a in range(A)]) for l in range(L)])
+    oracle.append(ospec, ok, ov, k_new.numpy(), v_new.numpy(), whole, lens)
+    b.q4kv_append(gspec, gk, gv, k_new.to(DEV), v_new.to(DEV), torch.from_numpy(table).to(DEV), torch.from_numpy(lens).to(DEV))
+    for gp, op in ((gk, ok), (gv, ov)):
+        assert np.array_equal(bits(gp.codes), op.codes[:, :nb])
+        assert np.array_equal(bits(gp.scale), op.scale[:, :nb])
+        assert np.array_equal(bits(gp.bias), op.bias[:, :nb])
