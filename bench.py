@@ -34,7 +34,7 @@ HBM_PEAK_GBPS = 8000.0   # MI355X published HBM3E bandwidth
 DECODE_FILES = ("decode_attention.hip", "stream_k.h", "q4_device.h", "q4kv_internal.h")
 LATENT_FILES = ("mla_decode.hip", "stream_k.h", "q4_device.h", "q4kv_internal.h")
 CODEC_FILES = ("codec.hip", "q4_device.h", "q4kv_internal.h")
-CHUNK_FILES = ("chunk_attention.hip", "q4_device.h", "q4kv_internal.h")
+CHUNK_FILES = ("chunk_attention.hip", "chunk_rules.h", "q4_device.h", "q4kv_internal.h")
 MEASURED_TRAFFIC = {
     "gemma12b_10agents_48layers_ragged_1k_8k_decode": {
         "read": 4810489180, "written": 12899328, "file": "profiles/decode_attention_gemma10_ragged.md",

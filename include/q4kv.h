@@ -165,7 +165,8 @@ int q4kv_batched_attention(const q4kv_spec *spec, const q4kv_pool *k, const q4kv
  *   window_per_layer  HOST int32 [layer_end - layer_begin], read before the call returns; entry i belongs to layer
  *                     layer_begin + i; <= 0: global attention on that layer.
  * At most 128 layers per call (more -> Q4KV_EINVAL; split the layer range).  Everything else, the workspace size
- * included, is as for q4kv_batched_attention.  On decode the tokens a window hides are never read. */
+ * included, is as for q4kv_batched_attention, but that q_len > 1 with more than one layer makes no use of a workspace.
+ * On decode the tokens a window hides are never read. */
 int q4kv_batched_attention_windows(const q4kv_spec *spec, const q4kv_pool *k, const q4kv_pool *v, const uint16_t *q,
                                    uint16_t *out, const int32_t *block_table, int32_t max_blocks,
                                    const int32_t *seq_len, int32_t num_agents, int32_t q_len, int32_t max_seq_len,
@@ -183,7 +184,8 @@ int q4kv_batched_attention_windows(const q4kv_spec *spec, const q4kv_pool *k, co
  * Every argument the two share must be the same in both calls (the layer range may differ from call to call, its
  * length may not), and seq_len[] must not be relied on to have changed in between: the planned call attends to the
  * lengths the plan was made from.  A workspace may be used for any number of planned calls on one stream, one after
- * the other; when the lengths change (every decode step), plan again.  A workspace prepared for other arguments
+ * the other; when the lengths change (every decode step), or another call has used the workspace, plan again (a call
+ * with q_len > 1 uses one of its own size only, see `workspace` above).  A workspace prepared for other arguments
  * makes the planned call do nothing (it is detected on the device; `out` is left as it was).  Shapes, workspace size,
  * error codes and results (bit-identical to q4kv_batched_attention with the same arguments) as described there. */
 int q4kv_decode_plan(const q4kv_spec *spec, const int32_t *seq_len, int32_t num_agents, int32_t max_seq_len,

@@ -78,8 +78,9 @@ int attention_workgroups(const q4kv_spec &s) { return (q4kv::mla_decode_supporte
 // of very few tiles do not pay); a large job gives every wave an even share whatever the floor is.  Since only the
 // device knows how much of max_seq_len the agents and the sliding windows leave visible, the floor stays small:
 // twice an even share of the largest possible job, between one block and 512 tokens.  Measured on one layer's
-// call: 10 agents of 1K-8K tokens, 256-wide heads (even share 2.7 tiles) 51.6 / 47.8 / 52.6 / 59.9 us at 256 /
-// 512 / 768 / 1,024 tokens; 5 agents of 4K tokens, 128-wide heads (1.25 tiles) 32.6 / 34.2 / 43.6 / 46.7 us.
+// call, 256 / 512 / 768 / 1,024 tokens: 10 agents of 1K-8K tokens, 256-wide heads 40.1 / 39.5 / 39.3 / 43.2 us; 5 agents of 4K
+// tokens, 128-wide 19.6 / 19.5 / 25.3 / 21.1; 3 agents of 0.5K-6K, 192 + 128-wide 21.1 / 21.3 / 21.1 / 23.8; 1 agent of
+// 1K, 128-wide 15.0 / 16.6 / 24.5 / 17.7; 10 agents of 300, 256-wide 21.4 / 28.9 / 35.7 / 39.6.
 // A larger floor leaves waves without work whenever the visible cache is a fraction of the largest job: at
 // 4,096 tokens a quarter of the waves on a 10-agent, 48-layer step whose windows hid two thirds of the cache; at
 // 1,024 tokens four in ten on ten 300-token agents (0.115 ms against 0.090 ms at 512).
@@ -258,15 +259,12 @@ size_t q4kv_attention_workspace_bytes(const q4kv_spec *spec, int32_t num_agents,
            (size_t)(units * slots * (spec->v_dim + 2) * (int64_t)sizeof(float));
 }
 
-// shared_scratch: the workspace is the library's own array (a chunk call leaves it alone: calls on other streams that
-// need no workspace may then overlap)
 // planned: the workspace already holds the plan of q4kv_decode_plan for these arguments (seq_len is then not needed)
 static int attention_common(const q4kv_spec *spec, const q4kv_pool *k, const q4kv_pool *v, const uint16_t *q,
                             uint16_t *out, const int32_t *block_table, int32_t max_blocks, const int32_t *seq_len,
                             int32_t num_agents, int32_t q_len, int32_t max_seq_len, float sm_scale, int32_t window,
                             const int32_t *layer_window, int32_t split_tokens, int32_t layer_begin, int32_t layer_end,
-                            void *workspace, size_t workspace_bytes, void *hip_stream, bool planned = false,
-                            bool shared_scratch = false)
+                            void *workspace, size_t workspace_bytes, void *hip_stream, bool planned = false)
 {
     int rc = check_spec(spec);
     if (rc) return rc;
@@ -324,8 +322,9 @@ static int attention_common(const q4kv_spec *spec, const q4kv_pool *k, const q4k
         a.chunk_workers = 0;
         a.part_acc = a.part_ml = nullptr;
         // Only a workspace of exactly the size that was asked for these arguments is written: one of any other size was
-        // handed over for something else (a decode plan, calls on other streams) and a chunk call does not need it.
-        if (need > 0 && !shared_scratch && workspace && workspace_bytes == need && aligned16(workspace)) {
+        // handed over for something else (a decode plan, calls on other streams, the static array) and a chunk call does
+        // not need it.
+        if (need > 0 && workspace && workspace_bytes == need && aligned16(workspace)) {
             a.chunk_workers = a.compute_units;
             a.part_acc = static_cast<float *>(workspace);
             a.part_ml = reinterpret_cast<float *>(static_cast<char *>(workspace) + acc_bytes);
@@ -424,7 +423,7 @@ int q4kv_batched_attention_static(const q4kv_spec *spec, const q4kv_pool *k, con
     if (!ptr) return Q4KV_EHIP;
     return attention_common(spec, k, v, q, out, block_table, max_blocks, seq_len, num_agents, q_len, max_seq_len, sm_scale,
                             window, nullptr, split_tokens, layer_begin, layer_end, ptr, (size_t)Q4KV_STATIC_SCRATCH_BYTES,
-                            hip_stream, false, true);
+                            hip_stream);
 }
 
 int q4kv_decode_plan(const q4kv_spec *spec, const int32_t *seq_len, int32_t num_agents, int32_t max_seq_len,

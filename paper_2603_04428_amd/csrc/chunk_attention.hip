@@ -4,10 +4,11 @@
 // seq_len[a] - (q_len-1-c) tokens of that agent's cache -- the chunk's own keys in their Q4 form included.
 //
 // Unlike decode this is a dense contraction: the q_len * n_rep query rows that share one KV head form the
-// M side of two GEMMs per KV tile (S = Q K^T, O += P V), so it runs on the matrix cores.  What bounds it is the issue
-// port of a SIMD: a vector instruction takes 4.5 clocks of it, a 32x32x16 matrix instruction about 5 (and 32 of the
-// matrix pipe), a 16x16x32 one 8.6 (and 17): the products are cut so that everything the vector unit prepares --
-// unpacked keys above all -- serves 32 query rows.
+// M side of two GEMMs per KV tile (S = Q K^T, O += P V), so it runs on the matrix cores.  What bounds it is each wave's
+// own chain (operand reads, dependent products, scales, maximum, exponentials, products) and the barrier behind it, with two
+// waves per SIMD to fill the gaps: the issue port is taken two thirds of the time, the matrix pipe 42 %.  A vector instruction takes
+// 4.5 clocks of the port, a 32x32x16 matrix instruction about 5 (and 32 of the pipe), a 16x16x32 one 8.6 (and
+// 17): the products are cut so that everything the vector unit prepares -- unpacked keys above all -- serves 32 query rows.
 //
 //  * A workgroup of eight waves owns 256 query rows of one (layer, agent, KV head) -- 256/n_rep consecutive chunk
 //    positions times the n_rep query heads of the group -- 32 rows per wave; or 128 rows, when its waves 0..3 take the
@@ -38,15 +39,18 @@
 //    transposing read touches are then two tokens apart, and with a pitch of 8 banks (mod 64) the four tokens x 64
 //    bytes of half a wave fall into all 64 banks.
 //  * At 256-wide heads the accumulators of 32 rows (128 registers) leave no room for the whole query operand (64) if
-//    two waves are to share a SIMD: half of it lies in LDS, in operand order, private to its wave.
+//    two waves are to share a SIMD: three of its four groups lie in LDS, in operand order; at 192-wide keys one of three.
+//    With KSPLIT = 2 the two waves of a row group read one copy, which the first one writes before the barrier in front of
+//    the tile loop.
 //  * Softmax is online, per query row (= per lane column): scores in binary32, log2 domain, 32 tokens at a time.
-//  * Two forms of launch: one workgroup per unit (layer, agent, KV head, row tile), when there are enough units to fill the chip
-//    many times over; or, given a workspace, one workgroup per compute unit, each with an equal contiguous range of all
-//    units' tiles.  A unit cut by a range's end leaves un-normalised sums, maxima and denominators of every part
-//    in the workspace, and a second small kernel merges them in order.
+//  * Two forms of launch: one workgroup per unit (layer, agent, KV head, row tile); or, given a workspace, where the units are
+//    fewer than two per compute unit and it gains something (chunk_rules.h), one workgroup per compute unit, each with an
+//    equal contiguous range of all units' tiles.  A unit cut by a range's end leaves un-normalised sums, maxima and
+//    denominators of every part in the workspace, and a second small kernel merges them in order.
 //
-// Measured, 256-wide heads, ten agents of 4K-32K tokens, a 512-token chunk, one layer: 1.77 ms = 830 TFLOP/s (16 rows per
-// wave on 16x16x32 instructions, one workgroup per unit: 2.27 ms); one agent of 8,000 tokens 0.12 + 0.02 ms (0.37 ms).
+// Measured, 256-wide heads, ten agents of 4K-32K tokens, a 512-token chunk, one layer: 1.82 ms = 805 TFLOP/s with shares, 2.0
+// without (16 rows per wave on 16x16x32 instructions, one workgroup per unit: 2.28 ms); one agent of 8,000 tokens 0.11 +
+// 0.02 ms with, 0.315 without (0.364 ms).
 // A wave spends 5,150 clocks on 32 tokens: 2,200 on the scores (163 vector, 17 matrix instructions), 630 on the softmax
 // (100), 1,580 on the product (16 matrix instructions, 75 vector ones for the staging), 750 at the barrier, because the
 // older wave of a SIMD wins its arbitrations and the younger one finishes alone.  Holding the second wave half a step
@@ -954,7 +958,8 @@ size_t chunk_workspace_bytes(const q4kv_spec &s, int num_agents, int q_len, int 
     const size_t rows = 2 * (size_t)compute_units * rows_shared(sizes, max_seq_len);
     acc_bytes = rows * s.v_dim * sizeof(float);
     // The size tells a workspace that was made for such a call from any other.  Those of decode calls are multiples of 8
-    // (plan and counters in pieces of 256 bytes, records of (v_dim + 2) floats), so 4 more bytes make it one of its own.
+    // (plan and counters in pieces of 256 bytes, records of (v_dim + 2) floats), and so is the static array's, so 4 more bytes
+    // make it one of its own.
     return acc_bytes + rows * 2 * sizeof(float) + compute_units * sizeof(ChunkShared) + 4;
 }
 

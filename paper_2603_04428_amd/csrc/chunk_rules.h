@@ -93,7 +93,10 @@ inline int rows_shared(const ChunkSizes &s, int tokens)
 // for.  The line is at two units per compute unit: a workgroup that takes an equal share holds its compute unit
 // until the call ends, and a decode step on another stream, which gets in whenever a workgroup ends, waits for that
 // long.  48 layers of 512 tokens behind 16,384 (1,536 units) take 7.63 ms with one unit per workgroup, 8.04 with equal
-// shares; decode steps of 0.76 ms beside them then take 2.1 and 4.9 ms.
+// shares; decode steps of 0.76 ms beside them then take 2.1 and 4.9 ms.  Below the line: layer by layer, 0.84 ms steps beside
+// 512 tokens of ten agents of 4K-32K take 1.7 ms without shares and 2.65 with, beside one agent's (0.13 ms a call) 0.92.  Alone
+// equal shares would go on to win for a while: 256-wide, four agents of 2K-6K, units per compute unit 1.5 632 / 608 (alone /
+// shares), 2 844 / 804, 3 1,225 / 1,151, 4 1,585 / 1,515, 6 2,269 / 2,319; 128-wide 2 456 / 441, 4 838 / 802, 6 1,185 / 1,168.
 inline bool shares_fit(const ChunkSizes &s, int num_agents, int max_seq_len)
 {
     const int64_t units = s.units * row_tiles(s, rows_shared(s, max_seq_len));
