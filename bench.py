@@ -252,7 +252,7 @@ def bench_append(args, torch, b, synth, build_device_cache, steps=None, warmup=N
         "append_ms_inside_the_step": app_in_step_ms,   # right after a 100 ms attention kernel, mean over the steps
         "roofline": {"bound": "mfma", "achieved": tflops, "peak": MFMA_F16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": tflops / MFMA_F16_PEAK_TFLOPS, "traffic": None,
-                     "kernel": "chunk_attention_kernel<256,256,2,1,false>"},
+                     "kernel": "chunk_attention_kernel<256,256,2,1,false,false>"},
     }
     if not args.skip_cpu_baseline:
         shortest = min(range(w.num_agents), key=lambda a: w.seq_lens[a])
