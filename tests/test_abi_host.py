@@ -179,3 +179,24 @@ def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(b, "LIB_PATH", "/nonexistent/libq4kv.so")
     with pytest.raises(ImportError):
         b.lib()
+
+
+def test_no_decode_workspace_has_the_size_of_a_chunk_workspace():
+    """A chunk call (q_len > 1) tells its own workspace from others by its size: 4 modulo 8, where those of decode calls and the
+    static array are multiples of 8.  0: the call never shares its tiles out."""
+    sizes = 0
+    for hq, hkv, dk, dv in ((32, 8, 128, 128), (16, 8, 256, 256), (16, 16, 192, 128), (8, 1, 64, 64)):
+        spec = b.make_spec(48, hq, hkv, dk, dv)
+        for agents in (1, 3, 10, 257):
+            for top in (1, 300, 5001, 131072):
+                for layers in (1, 12, 48):
+                    decode = b.q4kv_attention_workspace_bytes(spec, agents, 1, top, 0, layers)
+                    assert decode > 0 and decode % 8 == 0
+                    for q_len in (2, 70, 512):
+                        chunk = b.q4kv_attention_workspace_bytes(spec, agents, q_len, top, 0, layers)
+                        assert chunk == 0 or chunk % 8 == 4
+                        sizes += chunk > 0
+    assert sizes > 100 and b.STATIC_SCRATCH_BYTES % 8 == 0
+    latent = b.make_spec(27, 16, 1, 576, 512, True)
+    assert b.q4kv_attention_workspace_bytes(latent, 5, 1, 32768, 0, 27) % 8 == 0
+    assert b.q4kv_attention_workspace_bytes(latent, 5, 2, 32768, 0, 27) == 0      # no chunk kernel
