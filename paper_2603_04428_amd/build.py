@@ -15,9 +15,10 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-fno-gpu-sanitize"]
-# The chunk kernel reads most of its matrix results with vector instructions (scales, softmax), so its matrix
+# These kernels read most of their matrix results with vector instructions (scales, softmax), so their matrix
 # instructions write vector registers directly instead of accumulator registers that must be copied out first.
-FILE_FLAGS = {"chunk_attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+FILE_FLAGS = {"chunk_attention.hip": VGPR_FORM, "mla_decode.hip": VGPR_FORM}
 
 
 def build(verbose=False):

@@ -20,16 +20,22 @@
 //    (nibbles become binary16 subnormals, see q4_device.h), operand B the query in the matching element order.
 //    The bias term is one more instruction per 16 tokens, its contraction index running over the groups with
 //    the group sums of q split into binary16 high and low parts.
-//  * Row i of a 16-token set is token 4*(i%4) + i/4, so the lane that receives S^T for (head, tokens 4r+q) is
-//    the lane that must supply P^T for the same tokens as operand B of the second contraction: probabilities
-//    never leave their registers.
+//  * Row i of set j is the token whose scores lane slot i/4 receives (slot_token below), so the lane that receives S^T
+//    for (head, four tokens of a set) is the lane that must supply P^T for the same tokens as operand B of the second
+//    contraction: probabilities never leave their registers.
 //  * Output, transposed:  O^T[e][h] = sum_t c[t,e] * (p[h,t] s[t,g(e)])  +  sum_t b[t,g(e)] p[h,t].
-//    Operand A wants 8 tokens of one element per lane while a word holds 8 elements of one token; the lane reads
-//    the same word column of 8 rows from LDS (row pitch 72 words: conflict-free), masks the low or the high
-//    nibbles once, and v_perm picks byte M of two tokens into one register: rows 0..7 of tile (g, M) are element
-//    2M of word columns 8g..8g+7, rows 8..15 element 2M+1 (carrying a factor 16 until the end).
+//    Operand A wants 8 tokens of one element per lane while a word holds 8 elements of one token: the transposing LDS
+//    read of 4-bit elements (ds_read_b64_tr_b4) gives a lane 16 tokens of one element, and the four masks that unpack a
+//    code word for the scores unpack 8 tokens here.  One read and ten vector instructions feed four matrix instructions.
+//    (Eight 4-byte reads, eight masks and sixteen v_perm per four operands before: 96 LDS reads and 64 vector instructions
+//    more per tile.)
 //  * Online softmax per tile of 64 tokens, lane-local denominators, accumulators rescaled only when some
-//    head's running maximum moved.
+//    head's running maximum moved far.
+//
+// What bounds it is one instruction stream per SIMD (an instruction every five clocks): 1,060 vector, 206 matrix and 123
+// LDS instructions per 64-token tile.  27 layers of five agents of 32,768 tokens: 347 us a call, 4.1 TB/s, plan and combine
+// included (405 us with 1,414 vector instructions: results copied out of accumulator registers, per-byte permutes,
+// selects for hidden tokens in every tile).
 #include "q4_device.h"
 #include "q4kv_internal.h"
 #include "stream_k.h"
@@ -42,6 +48,7 @@ constexpr int kWaves = kThreads / kWave;
 constexpr int kHeads = 16;          // query heads per latent head: the M (or N) extent of the matrix tiles
 constexpr float kNegBig = -1.0e30f; // "minus infinity" that survives subtraction
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr uint32_t kLiftScaleBits = 0x5FE0; // binary16 504: 2^7 times that is still below 65504
 
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 typedef const __attribute__((address_space(1))) void *global_ptr_t;
@@ -91,6 +98,11 @@ __device__ __forceinline__ float xor16_other(float x, bool odd_row)
     return __builtin_bit_cast(float, (uint32_t)(odd_row ? r[0] : r[1]));
 }
 
+// The 64 tokens of a tile as 4 slots q (a lane's contraction slot) x 4 sets j of 16 consecutive tokens x 4 rows r.  Odd
+// sets turn the slots round by one, so that the 16 rows a transposing read takes for one slot (all j and r) lie two by two
+// in 8 bank groups (the row pitch is 8 banks modulo 64) instead of four by four in 4.
+__device__ __forceinline__ constexpr int slot_token(int q, int j, int r) { return 16 * j + 4 * ((q + (j & 1)) & 3) + r; }
+
 __device__ __forceinline__ half8_t words_to_half8(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
 {
     return __builtin_bit_cast(half8_t, make_uint4(a, b, c, d));
@@ -100,6 +112,15 @@ __device__ __forceinline__ half8_t code_operand(uint32_t w)
 {
     const uint32_t w8 = w >> 8;
     return words_to_half8(w & 0x000F000Fu, w & 0x00F000F0u, w8 & 0x000F000Fu, w8 & 0x00F000F0u);
+}
+
+typedef int int2_t __attribute__((ext_vector_type(2)));
+typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) int2_t *lds_int2_ptr;
+
+__device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, a), __builtin_bit_cast(ushort2_t, b)));
 }
 
 __device__ __forceinline__ float half_of(uint32_t pair, int hi)
@@ -121,8 +142,8 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
     constexpr int BTP = GK > 8 ? 12 : 8;    // binary16 slots per token in the token-major bias copy
 
     __shared__ __attribute__((aligned(16))) uint32_t codes_all[kWaves][2][kTileWords]; // two tile buffers per wave
-    // scale and bias of the tile, [32-token half][group][q][e] <-> token 32*half + 4*e + q: one 16-byte read gives
-    // a lane the 8 tokens of its contraction slots
+    // scale and bias of the tile, [tile half][group][slot q][8]: one 16-byte read gives a lane the 8 tokens of its
+    // contraction slots, register r the tokens slot_token(q, 2 half, r) and slot_token(q, 2 half + 1, r)
     __shared__ __attribute__((aligned(16))) uint16_t sc_all[kWaves][2][GK][4][8];
     __shared__ __attribute__((aligned(16))) uint16_t bg_all[kWaves][2][GV][4][8];
     // bias again, token-major [64][BTP] (groups 0..7, then groups 8.. and zero padding): operand of the score bias term
@@ -147,13 +168,16 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
     // lane roles: col = row of an A operand / column of a B operand or result; qk = the lane's contraction slot
     // (8 of 32 indices) in an operand, the row quad in a result
     const int col = lane % 16, qk = lane / 16;
-    const int trow = 4 * (col % 4) + col / 4;       // token (within its 16-token set) behind A row `col`
-    const int tok_q = lane % 4, tok_e = (lane % 32) / 4, tok_h2 = lane / 32; // where token `lane` sits in sc / bg
-    const uint32_t nibble_mask = col < 8 ? 0x0F0F0F0Fu : 0xF0F0F0F0u;
+    const int row_even = col, row_odd = 4 * ((col / 4 + 1) & 3) + col % 4; // token (in its set) behind A row `col`, sets 0, 2 / 1, 3
+    const int v_row = slot_token(qk, col / 4, col % 4); // token whose codes this lane points the transposing reads at
+    // where token `lane` sits in sc / bg (half index, without the group)
+    const int tok_set = lane / 16, tok_q = (((lane % 16) / 4) - (tok_set & 1)) & 3;
+    const int tok_at = tok_q * 8 + 2 * (lane % 4) + (tok_set & 1), tok_h2 = tok_set / 2;
 
     Cursor cur = ts.locate(x0);
 
-    uint32_t sraw[GK], braw[GK]; // scale / bias bits of token `lane` of the tile in flight
+    constexpr int PW = GK / 2, PT = GK % 2; // whole words and odd halves of a row of scales (or biases)
+    uint32_t sraw[PW + PT], braw[PW + PT];  // scale / bias bits of token `lane` of the tile in flight
 
     // Start the transfer of a tile: kLoads instructions move 1 KiB each straight from global memory into LDS
     // (lane i's 16 bytes land at M0 + offset + 16 i), then the lane's scale and bias loads.  The transfers are
@@ -177,10 +201,11 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
         }
         const uint16_t *sp = p.scale + (c.row + lane) * GK;
         const uint16_t *bp = p.bias + (c.row + lane) * GK;
-#pragma unroll
-        for (int g = 0; g < GK; ++g) {
-            sraw[g] = sp[g];
-            braw[g] = bp[g];
+        __builtin_memcpy(sraw, sp, 4 * PW); // rows of an odd number of groups are only 2-byte aligned
+        __builtin_memcpy(braw, bp, 4 * PW);
+        if constexpr (PT) {
+            sraw[PW] = sp[GK - 1];
+            braw[PW] = bp[GK - 1];
         }
     };
 
@@ -231,14 +256,17 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
             }
             qsop = half8_t{part[0], part[1], part[2], part[3], part[4], part[5], part[6], part[7]};
         }
-        float4_t acc[GV][4]; // [group][byte M]: rows = (word column, low / high nibble), columns = heads
+        float4_t acc[4 * GV]; // [16-element column block]: rows = elements, columns = heads
         float4_t pbacc = float4_t{0.0f, 0.0f, 0.0f, 0.0f}; // rows = groups: sum_t b[t,g] p[h,t]
 #pragma unroll
-        for (int g = 0; g < GV; ++g)
-#pragma unroll
-            for (int m = 0; m < 4; ++m) acc[g][m] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int c = 0; c < 4 * GV; ++c) acc[c] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
         float m_run = kNegBig, l_run = 0.0f; // of head `col`; l_run covers this lane's tokens only
         bool first_tile = true, unit_ends;
+        // The query operand lives in accumulator registers, which matrix instructions read directly; without this the
+        // allocator moved it about in every tile (65 instructions; 347 -> 336 us)
+#pragma unroll
+        for (int g = 0; g < GK; ++g) asm volatile("" : "+a"(qop[g][0]), "+a"(qop[g][1]));
+        asm volatile("" : "+a"(qsop));
 
         do { // ---- the tiles of the unit
             const uint32_t *cb = bufs + buf * kTileWords;
@@ -253,229 +281,215 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
             const bool tok_valid = cur.reachable && tok >= cur.first && tok < cur.n;
             // wave-uniform: some token of the tile lies outside the agent's visible range
             const bool edge = !(cur.reachable && cur.t0 >= cur.first && cur.t0 + kWave <= cur.n);
+            uint32_t s_top = 0; // the larger of this token's value scales, two halves apart
             {
-                // rows outside the agent's range may hold anything: their scale and bias become zero so that no NaN
-                // or infinity reaches a matrix operand (codes are nibbles and always finite)
-                uint32_t s[GK], b[BTP];
+                uint32_t s[PW + PT], b[PW + PT];
+                if constexpr (BF) {
+                    auto both = [](uint32_t w) {
+                        return (uint32_t)float_to_half_bits(bf16_bits_to_float((uint16_t)(w & 0xffffu))) |
+                               (uint32_t)float_to_half_bits(__builtin_bit_cast(float, w & 0xffff0000u)) << 16;
+                    };
 #pragma unroll
-                for (int g = 0; g < GK; ++g) {
-                    s[g] = BF ? (uint32_t)float_to_half_bits(bf16_bits_to_float((uint16_t)sraw[g])) : sraw[g];
-                    b[g] = BF ? (uint32_t)float_to_half_bits(bf16_bits_to_float((uint16_t)braw[g])) : braw[g];
-                }
-                if (edge) { // interior tiles (nearly all) skip the selects
+                    for (int i = 0; i < PW + PT; ++i) {
+                        s[i] = both(sraw[i]);
+                        b[i] = both(braw[i]);
+                    }
+                } else {
 #pragma unroll
-                    for (int g = 0; g < GK; ++g) {
-                        s[g] = tok_valid ? s[g] : 0u;
-                        b[g] = tok_valid ? b[g] : 0u;
+                    for (int i = 0; i < PW + PT; ++i) {
+                        s[i] = sraw[i];
+                        b[i] = braw[i];
                     }
                 }
+                // rows outside the agent's range may hold anything: their scale and bias become zero so that no NaN
+                // or infinity reaches a matrix operand (codes are nibbles and always finite)
+                if (__builtin_expect(edge, 0)) {
+                    asm volatile(""); // a branch: interior tiles (nearly all) must not pay for the selects
 #pragma unroll
-                for (int g = GK; g < BTP; ++g) b[g] = 0u;
+                    for (int i = 0; i < PW + PT; ++i) {
+                        s[i] = tok_valid ? s[i] : 0u;
+                        b[i] = tok_valid ? b[i] : 0u;
+                    }
+                }
+                uint16_t *s_at = sc + tok_h2 * GK * 32 + tok_at, *b_at = bg + tok_h2 * GV * 32 + tok_at;
 #pragma unroll
-                for (int g = 0; g < GK; ++g) sc[((tok_h2 * GK + g) * 4 + tok_q) * 8 + tok_e] = (uint16_t)s[g];
+                for (int g = 0; g < GK; ++g) s_at[g * 32] = (uint16_t)(g % 2 ? s[g / 2] >> 16 : s[g / 2]);
 #pragma unroll
-                for (int g = 0; g < GV; ++g) bg[((tok_h2 * GV + g) * 4 + tok_q) * 8 + tok_e] = (uint16_t)b[g];
+                for (int g = 0; g < GV; ++g) b_at[g * 32] = (uint16_t)(g % 2 ? b[g / 2] >> 16 : b[g / 2]);
                 uint2 *btw = reinterpret_cast<uint2 *>(bt + lane * BTP);
 #pragma unroll
                 for (int i = 0; i < BTP / 4; ++i)
-                    btw[i] = make_uint2(b[4 * i] | (b[4 * i + 1] << 16), b[4 * i + 2] | (b[4 * i + 3] << 16));
+                    btw[i] = make_uint2(2 * i < PW + PT ? b[2 * i] : 0u, 2 * i + 1 < PW + PT ? b[2 * i + 1] : 0u);
+#pragma unroll
+                for (int i = 0; i < GV / 2; ++i) s_top = i == 0 ? s[0] : pk_max_u16(s_top, s[i]);
             }
+            // wave-uniform: some value scale of the tile is too large for probabilities up to 2^7 (see the softmax)
+            const bool big = __builtin_amdgcn_ballot_w64((s_top & 0xffffu) > kLiftScaleBits || (s_top >> 16) > kLiftScaleBits) != 0ull;
             // the next tile starts travelling (into the buffer the previous tile was read from)
             issue_tile(nxt, buf ^ 1);
             __builtin_amdgcn_sched_barrier(0);
             wave_lds_sync();
 
-            // LDS reads are issued ahead of their use (one 16-token set, two value groups) and fenced so that
-            // they stay there: with one wave per SIMD nothing else hides their latency.  LDS returns data in
-            // issue order, so a step waits only for its own operands while the later ones are still on their way.
-            struct SetIn {    // operands of one 16-token set of scores
-                uint2 w[GK];  // code words 8g + 2qk, 8g + 2qk + 1 of this lane's row
-                uint2 s4[GK]; // scale of the four tokens this lane gets results for
-                uint2 b0, b1; // bias row (slots as in qsop)
-            };
-            auto load_set = [&](int h2, int sub) __attribute__((always_inline)) {
-                SetIn in;
-                const int t_row = 32 * h2 + 16 * sub + trow; // this lane's A row
-#pragma unroll
-                for (int g = 0; g < GK; ++g) in.w[g] = *reinterpret_cast<const uint2 *>(cb + t_row * W + 8 * g + 2 * qk);
-#pragma unroll
-                for (int g = 0; g < GK; ++g)
-                    in.s4[g] = *reinterpret_cast<const uint2 *>(sc + ((h2 * GK + g) * 4 + qk) * 8 + 4 * sub);
-                const uint16_t *btp = bt + t_row * BTP + ((GK > 8 && qk >= 2) ? 8 : 0);
-                in.b0 = *reinterpret_cast<const uint2 *>(btp);
-                in.b1 = *reinterpret_cast<const uint2 *>(btp + 4);
-                return in;
-            };
-            struct GroupIn {    // operands of one (32-token half, value group) step
-                uint32_t w[8];  // word column 8g + col % 8 of tokens 32 h2 + 4 e + qk
-                uint4 s8;       // their scales
-            };
-            auto load_group = [&](int step) __attribute__((always_inline)) { // step = h2 * GV + g
-                GroupIn in;
-                const int h2 = step / GV, g = step % GV;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) in.w[e] = cb[(32 * h2 + 4 * e + qk) * W + 8 * g + (col % 8)];
-                in.s8 = *reinterpret_cast<const uint4 *>(sc + ((h2 * GK + g) * 4 + qk) * 8);
-                return in;
-            };
-
-            // ---- scores of the 64 tokens, four 16-token sets: z[h2][sub][r] is token 32 h2 + 16 sub + 4 r + qk, head col
-            float z[2][2][4];
-            const float c_code = p.score_scale * kCodeScaleA;
+            // ---- scores of the 64 tokens, four 16-token sets: z[j][r] is token slot_token(qk, j, r), head col, in units of
+            // 2^-24 / score_scale.  Every operand register is read again from LDS for the next set (the scales: for
+            // the next pair of sets) right after its last use: with one wave per SIMD nothing else hides the latency.
+            float z[4][4];
             const float4_t zero = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-            SetIn set_in = load_set(0, 0);
-            constexpr int kRing = 2; // deeper rings (3, 4) were measured and change nothing
-            GroupIn grp_in[kRing]; // a ring of the next value steps
+            const uint32_t *const k_at[2] = {cb + row_even * W + 2 * qk, cb + row_odd * W + 2 * qk};
+            const uint16_t *const bt_at[2] = {bt + row_even * BTP + ((GK > 8 && qk >= 2) ? 8 : 0),
+                                              bt + row_odd * BTP + ((GK > 8 && qk >= 2) ? 8 : 0)};
+            const uint16_t *const sc_at = sc + qk * 8;
+            uint2 kw[GK]; // code words 8g + 2qk, 8g + 2qk + 1 of this lane's row
+            uint4 s8[GK]; // scales of the tokens this lane gets results for, two sets
+            uint2 b0, b1; // bias row (slots as in qsop)
+            b0 = *reinterpret_cast<const uint2 *>(bt_at[0]);
+            b1 = *reinterpret_cast<const uint2 *>(bt_at[0] + 4);
 #pragma unroll
-            for (int set = 0; set < 4; ++set) {
-                const int h2 = set / 2, sub = set % 2;
-                SetIn set_next;
-                if (set < 3) {
-                    set_next = load_set((set + 1) / 2, (set + 1) % 2);
-                } else {
+            for (int g = 0; g < GK; ++g) {
+                kw[g] = *reinterpret_cast<const uint2 *>(k_at[0] + 8 * g);
+                s8[g] = *reinterpret_cast<const uint4 *>(sc_at + g * 32);
+            }
+            // value side: column block c of the tile's rows, 16 tokens x 16 elements per slot, transposed by the read
+            const uint32_t *const v_at = cb + v_row * W;
+            auto load_columns = [&](int c) __attribute__((always_inline)) {
+                return __builtin_amdgcn_ds_read_tr4_b64_v2i32((lds_int2_ptr)(v_at + 2 * c));
+            };
+            constexpr int kAhead = 4;
+            int2_t vw[kAhead];
 #pragma unroll
-                    for (int i = 0; i < kRing; ++i) grp_in[i] = load_group(i);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                float4_t d[GK];
-#pragma unroll
-                for (int g = 0; g < GK; ++g) {
-                    d[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(code_operand(set_in.w[g].x), qop[g][0], zero, 0, 0, 0);
-                    d[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(code_operand(set_in.w[g].y), qop[g][1], d[g], 0, 0, 0);
+            for (int j = 0; j < 4; ++j) {
+                uint2 c0 = b0, c1 = b1;
+                if (qk >= 2) {
+                    c1 = make_uint2(0u, 0u);
+                    if (GK <= 8) c0 = make_uint2(0u, 0u);
                 }
                 // bias term: A = b[t][.], B = group sums of q
-                uint2 b0 = set_in.b0, b1 = set_in.b1;
-                if (qk >= 2) {
-                    b1 = make_uint2(0u, 0u);
-                    if (GK <= 8) b0 = make_uint2(0u, 0u);
+                float4_t sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(words_to_half8(c0.x, c0.y, c1.x, c1.y), qsop, zero, 0, 0, 0);
+                if (j < 3) {
+                    b0 = *reinterpret_cast<const uint2 *>(bt_at[(j + 1) & 1] + (j + 1) * 16 * BTP);
+                    b1 = *reinterpret_cast<const uint2 *>(bt_at[(j + 1) & 1] + (j + 1) * 16 * BTP + 4);
                 }
-                const float4_t bterm =
-                    __builtin_amdgcn_mfma_f32_16x16x32_f16(words_to_half8(b0.x, b0.y, b1.x, b1.y), qsop, zero, 0, 0, 0);
-                float4_t s_acc = zero;
+                float4_t d[GK];
 #pragma unroll
-                for (int g = 0; g < GK; ++g) {
-                    s_acc[0] = fmaf(half_of(set_in.s4[g].x, 0), d[g][0], s_acc[0]);
-                    s_acc[1] = fmaf(half_of(set_in.s4[g].x, 1), d[g][1], s_acc[1]);
-                    s_acc[2] = fmaf(half_of(set_in.s4[g].y, 0), d[g][2], s_acc[2]);
-                    s_acc[3] = fmaf(half_of(set_in.s4[g].y, 1), d[g][3], s_acc[3]);
+                for (int g = 0; g < GK + 1; ++g) {
+                    if (g < GK) {
+                        d[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(code_operand(kw[g].x), qop[g][0], zero, 0, 0, 0);
+                        d[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(code_operand(kw[g].y), qop[g][1], d[g], 0, 0, 0);
+                        if (j < 3) kw[g] = *reinterpret_cast<const uint2 *>(k_at[(j + 1) & 1] + (j + 1) * 16 * W + 8 * g);
+                    }
+                    if (g == 0) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) sum[r] *= 0x1p-24f; // the products' unit
+                    } else { // the results of the group before
+                        const uint32_t s4[4] = {s8[g - 1].x, s8[g - 1].y, s8[g - 1].z, s8[g - 1].w};
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) sum[r] = fmaf(half_of(s4[r], j & 1), d[g - 1][r], sum[r]);
+                        if (j == 1) s8[g - 1] = *reinterpret_cast<const uint4 *>(sc_at + (GK + g - 1) * 32);
+                        if (j == 3 && g <= kAhead) vw[g - 1] = load_columns(g - 1);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
-                for (int r = 0; r < 4; ++r) z[h2][sub][r] = fmaf(s_acc[r], c_code, bterm[r] * p.score_scale);
-                // pin the scores here: without a use in this block the compiler sinks all the scale multiplies
-                // below the branch that follows and keeps every matrix result of the tile alive until then
-                asm volatile("" : "+v"(z[h2][sub][0]), "+v"(z[h2][sub][1]), "+v"(z[h2][sub][2]), "+v"(z[h2][sub][3]));
-                __builtin_amdgcn_sched_barrier(0);
-                if (set < 3) set_in = set_next;
+                for (int r = 0; r < 4; ++r) z[j][r] = sum[r];
             }
 
-            // ---- online softmax of head col over the tile.  m_run is the reference the exponentials are taken
-            // against, not the exact running maximum: it moves only when a tile's maximum exceeds it by more than
-            // kSlack (in log2 units), so p <= 2^kSlack and p * s stays far inside binary16 for any binary16 scale,
-            // and the accumulators are rescaled a handful of times per unit instead of in every other tile.
-            constexpr float kSlack = 3.0f;
-            if (edge) {
+            // ---- online softmax of head col over the tile.  m_run is the reference the exponentials are taken against,
+            // not the exact running maximum: it moves only when a tile's maximum exceeds it by more than 7 (in log2
+            // units) and then to 4 below that maximum, so the accumulators are rescaled a handful of times per unit instead of
+            // in every other tile.  p <= 2^7 then, and p * s stays inside binary16 for scales up to kLiftScale; a tile with a
+            // larger one (values spread over thousands) keeps p <= 2^3, which is enough for any binary16 scale.
+            float zs = p.score_scale * kCodeScaleA;
+            if (__builtin_expect(!(p.score_scale > 0.0f), 0)) { // the maximum may not be taken before the scale is applied
+                asm volatile("");
 #pragma unroll
-                for (int h2 = 0; h2 < 2; ++h2)
-#pragma unroll
-                    for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int t = cur.t0 + 32 * h2 + 16 * sub + 4 * r + qk;
-                            if (!(cur.reachable && t >= cur.first && t < cur.n)) z[h2][sub][r] = kNegBig;
-                        }
+                for (int i = 0; i < 16; ++i) z[i / 4][i % 4] *= zs;
+                zs = 1.0f;
             }
-            float mt = kNegBig;
+            if (__builtin_expect(edge, 0)) {
+                asm volatile("");
 #pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2)
+                for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int sub = 0; sub < 2; ++sub)
+                    for (int r = 0; r < 4; ++r) {
+                        const int t = cur.t0 + slot_token(qk, j, r);
+                        if (!(cur.reachable && t >= cur.first && t < cur.n)) z[j][r] = -INFINITY;
+                    }
+            }
+            float mt = -INFINITY;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) mt = fmaxf(mt, z[h2][sub][r]);
-            mt = xor32_max(xor16_max(mt));
-            const bool moved = mt > m_run + kSlack; // the same in the four lanes of a head
-            const float m_new = moved ? mt : m_run;
+            for (int i = 0; i < 16; ++i) mt = fmaxf(mt, z[i / 4][i % 4]);
+            mt = xor32_max(xor16_max(mt)) * zs;
+            const bool moved = mt > m_run + (big ? 3.0f : 7.0f); // the same in the four lanes of a head
+            const float m_new = moved ? mt - (big ? 0.0f : 4.0f) : m_run;
             const float alpha = moved ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.0f;
             m_run = m_new;
             float psum = 0.0f;
 #pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2)
-#pragma unroll
-                for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        float pr = __builtin_amdgcn_exp2f(z[h2][sub][r] - m_new);
-                        if (edge && z[h2][sub][r] == kNegBig) pr = 0.0f; // also when the whole tile is masked
-                        z[h2][sub][r] = pr;
-                        psum += pr;
-                    }
+            for (int i = 0; i < 16; ++i) {
+                const float pr = __builtin_amdgcn_exp2f(fmaf(z[i / 4][i % 4], zs, -m_new)); // 0 for a masked token
+                z[i / 4][i % 4] = pr;
+                psum += pr;
+            }
             l_run = fmaf(l_run, alpha, psum);
             if (!first_tile && __builtin_amdgcn_ballot_w64(moved) != 0ull) { // accumulators are zero in a unit's first tile
-                // Rare.  The empty asm statements tie the accumulators to the accumulator registers on entry, and
-                // the products are handed back through a matrix instruction with zero operands (0*0 + C = C) whose
-                // result lives there again: on the path that skips this block the accumulators then never move.
-                const half8_t none = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
-                asm volatile("" : "+a"(pbacc));
-                pbacc = __builtin_amdgcn_mfma_f32_16x16x32_f16(none, none, pbacc * alpha, 0, 0, 0);
+                pbacc *= alpha;
 #pragma unroll
-                for (int g = 0; g < GV; ++g)
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        asm volatile("" : "+a"(acc[g][m]));
-                        acc[g][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(none, none, acc[g][m] * alpha, 0, 0, 0);
-                    }
+                for (int c = 0; c < 4 * GV; ++c) acc[c] *= alpha;
             }
 
-            // ---- values: per 32-token half, B = p * s of tokens 32 h2 + 4 e + qk, e = 0..7, in two binary16 terms.
-            // The product of two binary16 numbers minus its rounded value is a binary16 number again (barring
+            // ---- values: per tile half, B = p * s of tokens slot_token(qk, 2 h2 + {0, 1}, r) in register r, in two binary16
+            // terms.  The product of two binary16 numbers minus its rounded value is a binary16 number again (barring
             // underflow), so hi + lo carries p s to about 22 bits.  With hi alone an agent of a handful of tokens,
             // where one or two rounding errors of p s make up the whole error of an output, can leave the tolerance
             // when the latent holds channels of several times the usual magnitude.
+            // The codes of the odd rows r arrive 16 times larger (code_operand): their p is a sixteenth.  That costs
+            // no bits, because the reference lies 4 below the maximum.
+            half2_t p16[2][4];
 #pragma unroll
             for (int h2 = 0; h2 < 2; ++h2) {
-                half2_t p16[4];
-                p16[0] = half2_t{(half_t)z[h2][0][0], (half_t)z[h2][0][1]};
-                p16[1] = half2_t{(half_t)z[h2][0][2], (half_t)z[h2][0][3]};
-                p16[2] = half2_t{(half_t)z[h2][1][0], (half_t)z[h2][1][1]};
-                p16[3] = half2_t{(half_t)z[h2][1][2], (half_t)z[h2][1][3]};
-                const half8_t pop = words_to_half8(half2_to_bits(p16[0]), half2_to_bits(p16[1]), half2_to_bits(p16[2]),
-                                                   half2_to_bits(p16[3]));
-                const int g_row = (col % 8) < GV ? (col % 8) : GV - 1; // rows past GV repeat a valid row, unused
-                const uint4 braw4 = *reinterpret_cast<const uint4 *>(bg + ((h2 * GV + g_row) * 4 + qk) * 8);
 #pragma unroll
-                for (int g = 0; g < GV; ++g) {
-                    const int step = h2 * GV + g;
-                    const GroupIn in = grp_in[step % kRing];
-                    if (step + kRing < 2 * GV) grp_in[step % kRing] = load_group(step + kRing);
-                    __builtin_amdgcn_sched_barrier(0);
-                    const half2_t s2[4] = {bits_to_half2(in.s8.x), bits_to_half2(in.s8.y), bits_to_half2(in.s8.z),
-                                           bits_to_half2(in.s8.w)};
+                for (int r = 0; r < 4; ++r) p16[h2][r] = half2_t{(half_t)z[2 * h2][r], (half_t)z[2 * h2 + 1][r]};
+                const half8_t pop = words_to_half8(half2_to_bits(p16[h2][0]), half2_to_bits(p16[h2][1]), half2_to_bits(p16[h2][2]),
+                                                   half2_to_bits(p16[h2][3]));
+                // bias sums of this half: rows = groups (rows past GV repeat a valid row, unused)
+                const int g_row = (col % 8) < GV ? (col % 8) : GV - 1;
+                const uint4 b8 = *reinterpret_cast<const uint4 *>(bg + ((h2 * GV + g_row) * 4 + qk) * 8);
+                pbacc = __builtin_amdgcn_mfma_f32_16x16x32_f16(words_to_half8(b8.x, b8.y, b8.z, b8.w), pop, pbacc, 0, 0, 0);
+                const half2_t sixteenth = half2_t{(half_t)0.0625f, (half_t)0.0625f};
+                p16[h2][1] *= sixteenth;
+                p16[h2][3] *= sixteenth;
+            }
+            half8_t ps_hi[2], ps_lo[2];
+            auto scaled = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+                for (int h2 = 0; h2 < 2; ++h2) {
+                    const uint4 sv = *reinterpret_cast<const uint4 *>(sc_at + (h2 * GK + g) * 32);
+                    const half2_t s2[4] = {bits_to_half2(sv.x), bits_to_half2(sv.y), bits_to_half2(sv.z), bits_to_half2(sv.w)};
                     half2_t hi[4], lo[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        hi[i] = p16[i] * s2[i];
-                        lo[i] = __builtin_elementwise_fma(p16[i], s2[i], -hi[i]);
+                    for (int r = 0; r < 4; ++r) {
+                        hi[r] = p16[h2][r] * s2[r];
+                        lo[r] = __builtin_elementwise_fma(p16[h2][r], s2[r], -hi[r]);
                     }
-                    const half8_t ps_hi = words_to_half8(half2_to_bits(hi[0]), half2_to_bits(hi[1]), half2_to_bits(hi[2]),
-                                                         half2_to_bits(hi[3]));
-                    const half8_t ps_lo = words_to_half8(half2_to_bits(lo[0]), half2_to_bits(lo[1]), half2_to_bits(lo[2]),
-                                                         half2_to_bits(lo[3]));
-                    uint32_t wm[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) wm[e] = in.w[e] & nibble_mask;
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        const uint32_t sel = 0x0C040C00u + m * 0x00010001u; // byte m of two tokens into the low bytes of two halves
-                        const half8_t cop =
-                            words_to_half8(__builtin_amdgcn_perm(wm[1], wm[0], sel), __builtin_amdgcn_perm(wm[3], wm[2], sel),
-                                           __builtin_amdgcn_perm(wm[5], wm[4], sel), __builtin_amdgcn_perm(wm[7], wm[6], sel));
-                        acc[g][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(cop, ps_hi, acc[g][m], 0, 0, 0);
-                        acc[g][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(cop, ps_lo, acc[g][m], 0, 0, 0);
-                    }
-                    if (g == GV - 1) // bias sums of this half: rows = groups
-                        pbacc = __builtin_amdgcn_mfma_f32_16x16x32_f16(words_to_half8(braw4.x, braw4.y, braw4.z, braw4.w), pop,
-                                                                       pbacc, 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
+                    ps_hi[h2] = words_to_half8(half2_to_bits(hi[0]), half2_to_bits(hi[1]), half2_to_bits(hi[2]), half2_to_bits(hi[3]));
+                    ps_lo[h2] = words_to_half8(half2_to_bits(lo[0]), half2_to_bits(lo[1]), half2_to_bits(lo[2]), half2_to_bits(lo[3]));
                 }
+            };
+            half8_t cop[2] = {code_operand((uint32_t)vw[0].x), code_operand((uint32_t)vw[0].y)};
+#pragma unroll
+            for (int c = 0; c < 4 * GV; ++c) {
+                if (c % 4 == 0) scaled(c / 4);
+                if (c + kAhead < 4 * GV) vw[c % kAhead] = load_columns(c + kAhead);
+                const half8_t a0 = cop[0], a1 = cop[1];
+                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, ps_hi[0], acc[c], 0, 0, 0);
+                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, ps_lo[0], acc[c], 0, 0, 0);
+                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, ps_hi[1], acc[c], 0, 0, 0);
+                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, ps_lo[1], acc[c], 0, 0, 0);
+                if (c + 1 < 4 * GV) { // the next block's operands, while this one is multiplied
+                    cop[0] = code_operand((uint32_t)vw[(c + 1) % kAhead].x);
+                    cop[1] = code_operand((uint32_t)vw[(c + 1) % kAhead].y);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
             wave_lds_sync(); // the next tile rewrites sc / bg / bt
             first_tile = false;
@@ -485,8 +499,8 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
         } while (!unit_ends);
 
         // ---- this wave's share of the unit is complete: one partial per query head, written straight from the
-        // accumulators.  Lane (head col, quad qk) holds rows 4 qk + r of every tile: word column
-        // 8 g + 4 (qk % 2) + r, nibble 2 m + qk / 2; of the bias sums it holds groups 4 (qk % 2) + r.
+        // accumulators.  Lane (head col, quad qk) holds elements 4 qk .. 4 qk + 3 of every column block; of the bias sums
+        // it holds groups 4 (qk % 2) + r.
         const float l_tot = xor32_sum(xor16_sum(l_run));
         const bool odd = (qk & 1) != 0;
         float pb[8];
@@ -497,14 +511,14 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
             pb[4 + r] = odd ? pbacc[r] : other;
         }
         const int64_t rec = (unit0 + col) * p.max_slots + slot;
-        float *dst = p.part_acc + rec * DV + 8 * (4 * (qk % 2)) + qk / 2;
-        const float unscale = qk >= 2 ? kCodeScaleB : kCodeScaleA;
+        float *dst = p.part_acc + rec * DV + 4 * qk;
 #pragma unroll
-        for (int g = 0; g < GV; ++g)
+        for (int c = 0; c < 4 * GV; ++c) {
+            float4_t o;
 #pragma unroll
-            for (int m = 0; m < 4; ++m)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) dst[kGroup * g + 8 * r + 2 * m] = fmaf(acc[g][m][r], unscale, pb[g]);
+            for (int r = 0; r < 4; ++r) o[r] = fmaf(acc[c][r], kCodeScaleA, pb[c / 4]);
+            *reinterpret_cast<float4_t *>(dst + 16 * c) = o;
+        }
         if (qk == 0) {
             p.part_ml[rec * 2] = m_run;
             p.part_ml[rec * 2 + 1] = l_tot;

@@ -120,6 +120,49 @@ def test_latent_outliers_and_large_scores():
         assert_close(got.cpu().numpy(), want, f"sm_scale {scale}")
 
 
+@pytest.mark.parametrize("sign", [-1.0, 0.0])
+def test_latent_scale_that_is_not_positive(sign):
+    """The maximum of a tile may be taken before sm_scale is applied only when that is positive."""
+    w = mla(45, 1, (300, 64))
+    spec, kpool, vpool, table, table_d = gpu_cache(w)
+    ospec, okp, ovp, otable = host_cache(w)
+    q, scale = w.q_all(), sign * w.sm_scale
+    got = b.q4kv_batched_attention(spec, kpool, vpool, q.to(DEV), table_d,
+                                   torch.tensor(w.seq_lens, dtype=torch.int32, device=DEV), max(w.seq_lens), scale, 0, 0, 0, None)
+    torch.cuda.synchronize()
+    assert_close(got.cpu().numpy(), oracle.attention(ospec, okp, ovp, q.numpy(), otable, w.seq_lens, scale), f"sm_scale {scale}")
+
+
+@pytest.mark.parametrize("param_format", [0, 1])
+@pytest.mark.parametrize("tokens", [(0, 37), (64, 128), (130, 131), (250, 290)])
+def test_latent_value_scales_near_the_end_of_binary16(tokens, param_format):
+    """Tokens whose value group 2 spans +-60,000 (scale 8,000) among ordinary ones: p * s must stay inside binary16, and
+    the reference of the exponentials moves between tiles with and without such tokens.  The queries are zero on that group,
+    so the scores stay ordinary.  Every weight is rounded to binary16 once, hence 2^-11 of the widest value on
+    those elements; the other elements keep the usual tolerance."""
+    w = mla(46, 1, (300,))
+    spec, kpool, vpool, table, table_d = gpu_cache(w, param_format=param_format)
+    ospec, okp, ovp, otable = host_cache(w, param_format=param_format)
+    to_bits = oracle.f2bf if param_format else oracle.f2h
+    scale, bias = to_bits(8000.0), to_bits(-60000.0)
+    for t in range(*tokens):
+        for pool, blk in ((okp, otable[0, t // 256]), (kpool, int(table[0, t // 256]))):
+            for arr, v in ((pool.scale, scale), (pool.bias, bias)):
+                arr[0, blk, 0, t % 256, 2] = v if pool is okp else v - 65536 * (v >> 15)
+    q = w.q_all()
+    q[..., 128:192] = 0
+    got = b.q4kv_batched_attention(spec, kpool, vpool, q.to(DEV), table_d, torch.tensor(w.seq_lens, dtype=torch.int32, device=DEV),
+                                   300, w.sm_scale, 0, 0, 0, None)
+    torch.cuda.synchronize()
+    got = got.cpu().numpy().astype(np.float64)
+    want = oracle.attention(ospec, okp, ovp, q.numpy(), otable, w.seq_lens, w.sm_scale).astype(np.float64)
+    wide = np.zeros(512, bool)
+    wide[128:192] = True
+    assert np.abs(want[..., wide]).max() > 100  # the wide tokens carry weight
+    assert np.all(np.abs(got - want)[..., wide] <= 2.0 ** -11 * 60000 + 2e-3 * np.abs(want[..., wide]))
+    assert_close(got[..., ~wide].astype(np.float16), want[..., ~wide].astype(np.float16), "ordinary elements")
+
+
 def test_config3_full_size_sampled_units():
     """Config 3 (5 agents x 32,768 tokens x 27 layers, 576/512 latent, 16 heads) at full size, all layers in one
     call with the default split, as the benchmark launches it; the oracle recomputes a seeded sample of
