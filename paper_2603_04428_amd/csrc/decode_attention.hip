@@ -393,13 +393,14 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void decode_attention_kern
     constexpr int kPartFloats = kWave * GK * NREP;
     constexpr int kPsFloats = VROWS * GV * kWave / 2;
     constexpr int kFinalFloats = VTPS * NREP * DV + NREP * GV;
-    constexpr int kWaveFloats = (kPartFloats + kPsFloats > kFinalFloats ? kPartFloats + kPsFloats : kFinalFloats) + NREP * GK;
-    __shared__ float lds[kWaves * kWaveFloats];
+    constexpr int kQsumAt = kPartFloats + kPsFloats > kFinalFloats ? kPartFloats + kPsFloats : kFinalFloats;
+    constexpr int kWaveFloats = (kQsumAt + NREP * GK + 3) / 4 * 4; // every wave's region begins on 16 bytes
+    __shared__ __attribute__((aligned(16))) float lds[kWaves * kWaveFloats];
     // what a wave leaves behind when it is done with a segment: sums [NREP][DV], then (maximum, denominator)
     // [NREP][2]; kSegBufs segments can be pending before a wave has to wait for the others
-    constexpr int kSegFloats = NREP * DV + 2 * NREP;
+    constexpr int kSegFloats = (NREP * DV + 2 * NREP + 3) / 4 * 4;
     constexpr int kSegBufs = (NREP >= 8 || NREP * DV >= 2048) ? 1 : 2; // LDS: two workgroups per compute unit
-    __shared__ float seg_lds[kSegBufs * kWaves * kSegFloats];
+    __shared__ __attribute__((aligned(16))) float seg_lds[kSegBufs * kWaves * kSegFloats];
     __shared__ int s_last;
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -426,7 +427,7 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void decode_attention_kern
     float *part = region;                                                  // [64][GK][NREP]
     uint16_t *ps_h = reinterpret_cast<uint16_t *>(region + kPartFloats);   // [VROWS][GV][64] binary16
     const uint2 *ps_q = reinterpret_cast<const uint2 *>(ps_h);            // the same as token quads
-    float *qsum_lds = region + (kWaveFloats - NREP * GK);                  // [NREP][GK]
+    float *qsum_lds = region + kQsumAt;                                    // [NREP][GK]
 
     // This wave's tiles are wx0, wx0 + stride, ... below wx1; a wave of a sharing workgroup whose range holds none
     // keeps a valid cursor that it never uses.  A range (the workgroup's when its waves share, else the wave's own) is
@@ -520,37 +521,63 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void decode_attention_kern
     // which the workgroup that arrives last merges the records.  A wave closes segments only when it needs a buffer
     // for a later one or has run out of tiles.  Barriers here wait for LDS traffic only (loads stay in flight).
     auto lds_barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
-    auto publish = [&]() {
+    // Leaving is the tail of a short call: every instruction and every trip to LDS or memory from here to the output is time
+    // in which nothing streams.  Hence: lane sums of a head's values side by side (one after the other they took 25
+    // instructions each), 8- and 16-byte LDS accesses, records moved as pairs, all of a thread's elements in one pass.  A
+    // decode step of twelve 256-wide layers of ten agents 495 -> 458 us, the smallest call 14.6 -> 14.2.
+    constexpr int EPL = DV / kWave; // consecutive elements of a row that a lane folds: 1, 2 or 4
+    // what a wave of a unit's part holds, folded over lanes and token slots: elements EPL * lane .. of head r (before
+    // the division by the denominator) to take(r, sums), and in lane 63 the denominators in lsum
+    auto fold = [&](float (&lsum)[NREP], auto take) {
         float *fin_acc = region;                      // [VTPS][NREP][DV]
         float *fin_pb = region + VTPS * NREP * DV;    // [NREP][GV]
-        float *mine = seg_lds + ((k_my % kSegBufs) * kWaves + wave) * kSegFloats;
-        float lsum[NREP];
 #pragma unroll
         for (int r = 0; r < NREP; ++r) {
-            float *dst = fin_acc + (vo * NREP + r) * DV + vj * 8;
+            float o[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e)
-                dst[e] = (kTermRows ? acc[0][e][r] + acc[0][e][NREP + r] : acc[r / 4][e][r % 4]) *
-                         ((e & 1) ? kCodeScaleB : kCodeScaleA);
-            lsum[r] = wave_sum(l_run[r]);
+                o[e] = (kTermRows ? acc[0][e][r] + acc[0][e][NREP + r] : acc[r / 4][e][r % 4]) *
+                       ((e & 1) ? kCodeScaleB : kCodeScaleA);
+            float4_t *dst = reinterpret_cast<float4_t *>(fin_acc + (vo * NREP + r) * DV + vj * 8);
+            dst[0] = float4_t{o[0], o[1], o[2], o[3]};
+            dst[1] = float4_t{o[4], o[5], o[6], o[7]};
+        }
 #pragma unroll
-            for (int g = 0; g < GV; ++g) {
-                const float s = wave_sum(pb[r][g]);
-                if (lane == 0) fin_pb[r * GV + g] = s;
+        for (int r = 0; r < NREP; ++r) {
+            float s[1 + GV];
+            s[0] = l_run[r];
+#pragma unroll
+            for (int g = 0; g < GV; ++g) s[1 + g] = pb[r][g];
+            wave_sum_n(s);
+            lsum[r] = s[0];
+            if (lane == kWave - 1) {
+#pragma unroll
+                for (int g = 0; g < GV; ++g) fin_pb[r * GV + g] = s[1 + g];
             }
         }
         wave_lds_sync();
 #pragma unroll
         for (int r = 0; r < NREP; ++r) {
+            typedef float vec_t __attribute__((ext_vector_type(EPL)));
+            const float bias = fin_pb[r * GV + EPL * lane / kGroup];
+            vec_t v = bias;
 #pragma unroll
-            for (int e0 = 0; e0 < DV; e0 += kWave) {
-                const int e = e0 + lane;
-                float o = fin_pb[r * GV + e / kGroup];
+            for (int sl = 0; sl < VTPS; ++sl) v += *reinterpret_cast<const vec_t *>(fin_acc + (sl * NREP + r) * DV + EPL * lane);
+            float o[EPL];
 #pragma unroll
-                for (int sl = 0; sl < VTPS; ++sl) o += fin_acc[(sl * NREP + r) * DV + e];
-                mine[r * DV + e] = o;
-            }
-            if (lane == 0) {
+            for (int i = 0; i < EPL; ++i) o[i] = v[i];
+            take(r, o);
+        }
+    };
+    auto publish = [&]() {
+        float *mine = seg_lds + ((k_my % kSegBufs) * kWaves + wave) * kSegFloats;
+        float lsum[NREP];
+        fold(lsum, [&](int r, const float (&o)[EPL]) {
+            __builtin_memcpy(__builtin_assume_aligned(mine + r * DV + EPL * lane, 4 * EPL), o, 4 * EPL);
+        });
+        if (lane == kWave - 1) {
+#pragma unroll
+            for (int r = 0; r < NREP; ++r) {
                 mine[NREP * DV + 2 * r] = m_run[r];
                 mine[NREP * DV + 2 * r + 1] = lsum[r];
             }
@@ -558,6 +585,8 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void decode_attention_kern
         wave_lds_sync(); // the region is free for the next tile
         pub_mask |= 1u << (k_my - k_old);
     };
+    // A thread finishes VEC consecutive elements at a time, a wave those of one head.
+    constexpr int VEC = NREP * DV / kThreads < 1 ? 1 : (NREP * DV / kThreads < EPL ? NREP * DV / kThreads : EPL);
     auto close_oldest = [&]() {
         const float *buf = seg_lds + (k_old % kSegBufs) * kWaves * kSegFloats;
         if (!(pub_mask & 1u) && lane < NREP) {
@@ -566,13 +595,12 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void decode_attention_kern
             mine[NREP * DV + 2 * lane + 1] = 0.0f;
         }
         pub_mask >>= 1;
-        lds_barrier();
         int slot, slots;
         seg.slot_of(per, wg, slot, slots);
         const bool alone = slots == 1;
         const int64_t u0 = ((int64_t)seg.li * p.stream.num_agents + seg.agent) * p.q_heads + (int64_t)seg.kvh * NREP;
-        // thread tid takes (head, element) pairs tid, tid + 256, ...: the head is the same for a whole wave
-        for (int i = tid; i < NREP * DV; i += kThreads) {
+        lds_barrier();
+        for (int i = tid * VEC; i < NREP * DV; i += kThreads * VEC) {
             const int r = i / DV, e = i % DV;
             float mw[kWaves], lw[kWaves], m_ref = kNegBig;
 #pragma unroll
@@ -581,52 +609,53 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void decode_attention_kern
                 lw[w] = buf[w * kSegFloats + NREP * DV + 2 * r + 1];
                 if (lw[w] > 0.0f) m_ref = fmaxf(m_ref, mw[w]);
             }
-            float o = 0.0f, l = 0.0f;
+            float o[VEC], l = 0.0f;
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) o[k] = 0.0f;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) {
                 if (lw[w] > 0.0f) { // a wave without tiles here left nothing to read
                     const float wgt = __builtin_amdgcn_exp2f(mw[w] - m_ref);
-                    o = fmaf(wgt, buf[w * kSegFloats + r * DV + e], o);
+                    float v[VEC];
+                    __builtin_memcpy(v, __builtin_assume_aligned(buf + w * kSegFloats + i, 4 * VEC), 4 * VEC);
+#pragma unroll
+                    for (int k = 0; k < VEC; ++k) o[k] = fmaf(wgt, v[k], o[k]);
                     l = fmaf(wgt, lw[w], l);
                 }
             }
             if (alone) {
-                p.merge.out[(u0 + r) * DV + e] = float_to_half_bits(l > 0.0f ? o / l : 0.0f);
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) o[k] = l > 0.0f ? o[k] / l : 0.0f;
+                store_halves(p.merge.out + u0 * DV + i, o);
             } else {
                 const int64_t rec = (u0 + r) * p.merge.max_slots + slot;
                 record_store(p.merge.part_acc + rec * DV + e, o);
                 if (e == 0) {
-                    record_store(p.merge.part_ml + rec * 2, m_ref);
-                    record_store(p.merge.part_ml + rec * 2 + 1, l);
+                    const float ml[2] = {m_ref, l};
+                    record_store(p.merge.part_ml + rec * 2, ml);
                 }
             }
         }
         if (!alone) {
+            int32_t *counter = p.merge.arrivals + ((int64_t)seg.li * p.stream.kv_heads + seg.kvh) * p.stream.num_agents + seg.agent;
             // every wave's record stores have reached memory before thread 0 counts the workgroup in
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0)
             lds_barrier();
-            if (tid == 0) {
-                int32_t *counter = p.merge.arrivals +
-                                   ((int64_t)seg.li * p.stream.kv_heads + seg.kvh) * p.stream.num_agents + seg.agent;
-                s_last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == slots - 1;
-            }
+            if (tid == 0) s_last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == slots - 1;
             lds_barrier();
             const bool last = s_last != 0;
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             if (last) {
-                for (int i = tid; i < NREP * DV; i += kThreads) {
+                for (int i = tid * VEC; i < NREP * DV; i += kThreads * VEC) {
                     const int r = i / DV, e = i % DV;
                     const int64_t rec0 = (u0 + r) * p.merge.max_slots;
-                    const float o = merge_element<DV>(p.merge.part_acc + rec0 * DV, p.merge.part_ml + rec0 * 2, slots, e, lane);
-                    p.merge.out[(u0 + r) * DV + e] = float_to_half_bits(o);
+                    float o[VEC];
+                    merge_elements<DV, VEC>(p.merge.part_acc + rec0 * DV, p.merge.part_ml + rec0 * 2, slots, e, lane, o);
+                    store_halves(p.merge.out + u0 * DV + i, o);
                 }
                 // the counter is back at zero for the next call that reuses this plan
-                if (tid == 0) {
-                    int32_t *counter = p.merge.arrivals +
-                                       ((int64_t)seg.li * p.stream.kv_heads + seg.kvh) * p.stream.num_agents + seg.agent;
-                    __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
+                if (tid == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         } else {
             lds_barrier(); // the buffer is free again
@@ -637,46 +666,27 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void decode_attention_kern
 
     // ---- a wave on its own: what publish and close do together, for mseg, without the other waves
     auto finish_alone = [&]() {
-        float *fin_acc = region;                      // [VTPS][NREP][DV]
-        float *fin_pb = region + VTPS * NREP * DV;    // [NREP][GV]
-        float lsum[NREP];
-#pragma unroll
-        for (int r = 0; r < NREP; ++r) {
-            float *dst = fin_acc + (vo * NREP + r) * DV + vj * 8;
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                dst[e] = (kTermRows ? acc[0][e][r] + acc[0][e][NREP + r] : acc[r / 4][e][r % 4]) *
-                         ((e & 1) ? kCodeScaleB : kCodeScaleA);
-            lsum[r] = wave_sum(l_run[r]);
-#pragma unroll
-            for (int g = 0; g < GV; ++g) {
-                const float s = wave_sum(pb[r][g]);
-                if (lane == 0) fin_pb[r * GV + g] = s;
-            }
-        }
-        wave_lds_sync();
         int slot, slots;
         mseg.slot_of_quarter(per, wg * kWaves + wave, slot, slots);
         const bool alone = slots == 1;
         const int64_t u0 = ((int64_t)mseg.li * p.stream.num_agents + mseg.agent) * p.q_heads + (int64_t)mseg.kvh * NREP;
+        float lsum[NREP];
+        fold(lsum, [&](int r, float (&o)[EPL]) {
+            if (alone) {
+                const float l = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lsum[r]), kWave - 1));
+                const float inv = l > 0.0f ? 1.0f / l : 0.0f;
 #pragma unroll
-        for (int r = 0; r < NREP; ++r) {
-            const int64_t rec = (u0 + r) * p.merge.max_slots + slot;
-            const float inv = lsum[r] > 0.0f ? 1.0f / lsum[r] : 0.0f;
-#pragma unroll
-            for (int e0 = 0; e0 < DV; e0 += kWave) {
-                const int e = e0 + lane;
-                float o = fin_pb[r * GV + e / kGroup];
-#pragma unroll
-                for (int sl = 0; sl < VTPS; ++sl) o += fin_acc[(sl * NREP + r) * DV + e];
-                if (alone) p.merge.out[(u0 + r) * DV + e] = float_to_half_bits(o * inv);
-                else record_store(p.merge.part_acc + rec * DV + e, o);
+                for (int i = 0; i < EPL; ++i) o[i] *= inv;
+                store_halves(p.merge.out + (u0 + r) * DV + EPL * lane, o);
+            } else {
+                const int64_t rec = (u0 + r) * p.merge.max_slots + slot;
+                record_store(p.merge.part_acc + rec * DV + EPL * lane, o);
+                if (lane == kWave - 1) {
+                    const float ml[2] = {m_run[r], lsum[r]};
+                    record_store(p.merge.part_ml + rec * 2, ml);
+                }
             }
-            if (!alone && lane == 0) {
-                record_store(p.merge.part_ml + rec * 2, m_run[r]);
-                record_store(p.merge.part_ml + rec * 2 + 1, lsum[r]);
-            }
-        }
+        });
         wave_lds_sync(); // the region is free for the next tile
         if (!alone) {
             int32_t *counter = p.merge.arrivals +
@@ -684,281 +694,271 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void decode_attention_kern
             if (arrive_last(counter, slots, lane)) {
                 for (int r = 0; r < NREP; ++r) {
                     const int64_t rec0 = (u0 + r) * p.merge.max_slots;
-                    merge_row<DV>(p.merge.part_acc + rec0 * DV, p.merge.part_ml + rec0 * 2, slots,
-                                  p.merge.out + (u0 + r) * DV, lane);
+                    float o[EPL];
+                    merge_elements<DV, EPL>(p.merge.part_acc + rec0 * DV, p.merge.part_ml + rec0 * 2, slots, EPL * lane, lane, o);
+                    store_halves(p.merge.out + (u0 + r) * DV + EPL * lane, o);
                 }
                 if (lane == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
     };
 
-    bool have = false; // this wave holds online-softmax state of mseg's unit
-    int64_t unit0 = 0;
-    for (;;) {
-        if (__builtin_expect(!active || x >= mseg.end, 0)) {
-            // this wave is done with mseg: it leaves its result behind (closing the oldest segments first when
-            // no buffer is free) and goes on, or, without a tile left, helps to close everything that remains
-            if (have) {
-                if (coop) {
-                    while (k_my - k_old >= kSegBufs) close_oldest();
-                    publish();
-                } else {
-                    finish_alone();
-                }
-                have = false;
-            }
-            if (!active) {
-                if (coop)
-                    while (seg.begin < x1) close_oldest();
-                break;
-            }
-            while (x >= mseg.end) {
-                mseg.next(ts_, r1);
-                ++k_my;
-            }
+    // Every pass of the outer loop is this wave's part of one segment; nothing of its state outlives the pass, which is what
+    // keeps the registers of the folding below those of the tile loop.
+    while (active) {
+        while (x >= mseg.end) {
+            mseg.next(ts_, r1);
+            ++k_my;
         }
-        if (per >= kPrioMinTiles) { // a short call would spend its whole life in one slice
-            const bool turn = ((wall_clock64() >> kPrioShift) & 1) != 0;
-            if (turn != second_half) __builtin_amdgcn_s_setprio(kPrioLevel); else __builtin_amdgcn_s_setprio(0);
-        }
-        const bool more = x + stride < wx1;
-        Cursor nxt = cur;
-        if (more) ts_.advance(nxt, stride); // the wave's last tile re-reads itself: a valid address, the data is ignored
-        const int64_t row0_next = nxt.row;
-
-        if (__builtin_expect(!have, 0)) { // the common tile continues a unit: that path runs straight through
-            have = true;
-            // first of this unit's NREP query heads
-            unit0 = ((int64_t)cur.li * p.stream.num_agents + cur.agent) * p.q_heads + (int64_t)cur.kvh * NREP;
-            // ---- new unit: its query heads.  Query operand of the matrix core, one per (chunk, word): row
-            // i = lane % 16 stands for query head i % NREP and group-in-chunk (i / NREP) % KGPC; the lane holds
-            // the 8 dims of its k-block in the order unpack_codes emits codes (0,4,1,5,2,6,3,7), odd dims divided
-            // by 16 because their codes arrive 16 times larger, and zeros when its k-block belongs to the row's
-            // other group.
-            const uint16_t *qrow = p.q + unit0 * DK;
-            const int r = kj % NREP, u = (kj / NREP) % KGPC;
-            const bool mine = (KGPC == 1) || (u == kkb / 2);
+        // ---- new unit: its query heads.  Query operand of the matrix core, one per (chunk, word): row
+        // i = lane % 16 stands for query head i % NREP and group-in-chunk (i / NREP) % KGPC; the lane holds
+        // the 8 dims of its k-block in the order unpack_codes emits codes (0,4,1,5,2,6,3,7), odd dims divided
+        // by 16 because their codes arrive 16 times larger, and zeros when its k-block belongs to the row's
+        // other group.
+        const uint16_t *qrow =
+            p.q + (((int64_t)cur.li * p.stream.num_agents + cur.agent) * p.q_heads + (int64_t)cur.kvh * NREP) * DK;
+        const int r = kj % NREP, u = (kj / NREP) % KGPC;
+        const bool mine = (KGPC == 1) || (u == kkb / 2);
 #pragma unroll
-            for (int c = 0; c < KCHUNKS; ++c)
+        for (int c = 0; c < KCHUNKS; ++c)
 #pragma unroll
-                for (int w = 0; w < KWPL; ++w) {
-                    const uint16_t *src = qrow + r * DK + c * (32 * KWPL) + kkb * (8 * KWPL) + 8 * w;
-                    const uint4 raw = *reinterpret_cast<const uint4 *>(src);
-                    const half2_t e01 = bits_to_half2(raw.x), e23 = bits_to_half2(raw.y);
-                    const half2_t e45 = bits_to_half2(raw.z), e67 = bits_to_half2(raw.w);
-                    const half_t sixteenth = (half_t)0.0625f;
-                    half8_t v = {e01.x, e45.x, e01.y * sixteenth, e45.y * sixteenth,
-                                 e23.x, e67.x, e23.y * sixteenth, e67.y * sixteenth};
-                    if (!mine) v = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
-                    qop[c][w] = v;
-                }
-            // sum of q over each 64-wide group: eight lanes per group, 8 dims each, folded inside the octet
-            for (int base = 0; base < NREP * GK * 8; base += kWave) {
-                const int idx = base + lane;
-                if (idx < NREP * GK * 8) {
-                    const uint4 raw = *reinterpret_cast<const uint4 *>(qrow + idx * 8);
-                    const half2_t a = bits_to_half2(raw.x), b = bits_to_half2(raw.y), c = bits_to_half2(raw.z),
-                                  d = bits_to_half2(raw.w);
-                    float s = ((float)a.x + (float)a.y) + ((float)b.x + (float)b.y) + ((float)c.x + (float)c.y) +
-                              ((float)d.x + (float)d.y);
-                    s += Q4KV_DPP(0.0f, s, 0xB1, 0xF);  // quad_perm [1,0,3,2]
-                    s += Q4KV_DPP(0.0f, s, 0x4E, 0xF);  // quad_perm [2,3,0,1]
-                    s += Q4KV_DPP(0.0f, s, 0x141, 0xF); // row_half_mirror
-                    if ((idx & 7) == 0) qsum_lds[idx >> 3] = s;
-                }
+            for (int w = 0; w < KWPL; ++w) {
+                const uint16_t *src = qrow + r * DK + c * (32 * KWPL) + kkb * (8 * KWPL) + 8 * w;
+                const uint4 raw = *reinterpret_cast<const uint4 *>(src);
+                const half2_t e01 = bits_to_half2(raw.x), e23 = bits_to_half2(raw.y);
+                const half2_t e45 = bits_to_half2(raw.z), e67 = bits_to_half2(raw.w);
+                const half_t sixteenth = (half_t)0.0625f;
+                half8_t v = {e01.x, e45.x, e01.y * sixteenth, e45.y * sixteenth,
+                             e23.x, e67.x, e23.y * sixteenth, e67.y * sixteenth};
+                if (!mine) v = half8_t{0, 0, 0, 0, 0, 0, 0, 0};
+                qop[c][w] = v;
             }
-            wave_lds_sync();
-#pragma unroll
-            for (int rr = 0; rr < NREP; ++rr) {
-#pragma unroll
-                for (int g = 0; g < GK; ++g) qsum[rr][g] = qsum_lds[rr * GK + g];
-                m_run[rr] = kNegBig;
-                l_run[rr] = 0.0f;
-#pragma unroll
-                for (int g = 0; g < GV; ++g) pb[rr][g] = 0.0f;
+        // sum of q over each 64-wide group: eight lanes per group, 8 dims each, folded inside the octet
+        for (int base = 0; base < NREP * GK * 8; base += kWave) {
+            const int idx = base + lane;
+            if (idx < NREP * GK * 8) {
+                const uint4 raw = *reinterpret_cast<const uint4 *>(qrow + idx * 8);
+                const half2_t a = bits_to_half2(raw.x), b = bits_to_half2(raw.y), c = bits_to_half2(raw.z),
+                              d = bits_to_half2(raw.w);
+                float s = ((float)a.x + (float)a.y) + ((float)b.x + (float)b.y) + ((float)c.x + (float)c.y) +
+                          ((float)d.x + (float)d.y);
+                s += Q4KV_DPP(0.0f, s, 0xB1, 0xF);  // quad_perm [1,0,3,2]
+                s += Q4KV_DPP(0.0f, s, 0x4E, 0xF);  // quad_perm [2,3,0,1]
+                s += Q4KV_DPP(0.0f, s, 0x141, 0xF); // row_half_mirror
+                if ((idx & 7) == 0) qsum_lds[idx >> 3] = s;
             }
-#pragma unroll
-            for (int h = 0; h < VHQ; ++h)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[h][e] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        }
-
-        // ---- K side: q.c per (token, head, group) on the matrix core, results to LDS in token order;
-        // two 16-token sets at a time keep the accumulators few
-#pragma unroll
-        for (int tp = 0; tp < KSETS; tp += 2) {
-            float4_t d[2][KCHUNKS];
-#pragma unroll
-            for (int ts = 0; ts < 2; ++ts)
-#pragma unroll
-                for (int c = 0; c < KCHUNKS; ++c) d[ts][c] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int w = 0; w < KWPL; ++w)
-#pragma unroll
-                for (int ts = 0; ts < 2; ++ts)
-#pragma unroll
-                    for (int c = 0; c < KCHUNKS; ++c) {
-                        const CodePairs cp = unpack_codes(kc[tp + ts][c].w[w]);
-                        const uint4 packed = make_uint4(half2_to_bits(cp.a0), half2_to_bits(cp.b0),
-                                                        half2_to_bits(cp.a1), half2_to_bits(cp.b1));
-                        d[ts][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qop[c][w], __builtin_bit_cast(half8_t, packed),
-                                                                          d[ts][c], 0, 0, 0);
-                    }
-            // result row i = 4*(lane/16) + reg belongs to (head i % NREP, group-in-chunk i / NREP); rows past
-            // KROWS are repeats.  part[token][group][head] keeps a lane's registers contiguous.
-            constexpr int kRegs = KROWS < 4 ? KROWS : 4;
-            if (4 * kkb < KROWS) {
-#pragma unroll
-                for (int ts = 0; ts < 2; ++ts)
-#pragma unroll
-                    for (int c = 0; c < KCHUNKS; ++c) {
-                        float *dst = part + (((tp + ts) * 16 + kj) * GK + c * KGPC) * NREP + 4 * kkb;
-#pragma unroll
-                        for (int e = 0; e < kRegs; ++e) dst[e] = d[ts][c][e];
-                    }
-            }
-            load_k_pair(tp, row0_next); // these registers are free again: the next tile's codes start travelling
         }
         wave_lds_sync();
+#pragma unroll
+        for (int rr = 0; rr < NREP; ++rr) {
+#pragma unroll
+            for (int g = 0; g < GK; ++g) qsum[rr][g] = qsum_lds[rr * GK + g];
+            m_run[rr] = kNegBig;
+            l_run[rr] = 0.0f;
+#pragma unroll
+            for (int g = 0; g < GV; ++g) pb[rr][g] = 0.0f;
+        }
+#pragma unroll
+        for (int h = 0; h < VHQ; ++h)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[h][e] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
 
-        // ---- the lane that owns token `lane`: finish its scores, online softmax, publish p*s
-        const bool tok_valid = cur.reachable && (cur.t0 + lane >= cur.first) && (cur.t0 + lane < cur.n);
-        float ks[GK], kb[GK], vs[GV], vb[GV];
+        do { // ---- the wave's tiles of the segment
+            if (per >= kPrioMinTiles) { // a short call would spend its whole life in one slice
+                const bool turn = ((wall_clock64() >> kPrioShift) & 1) != 0;
+                if (turn != second_half) __builtin_amdgcn_s_setprio(kPrioLevel); else __builtin_amdgcn_s_setprio(0);
+            }
+            const bool more = x + stride < wx1;
+            Cursor nxt = cur;
+            if (more) ts_.advance(nxt, stride); // the wave's last tile re-reads itself: a valid address, the data is ignored
+            const int64_t row0_next = nxt.row;
+
+            // ---- K side: q.c per (token, head, group) on the matrix core, results to LDS in token order;
+            // two 16-token sets at a time keep the accumulators few
 #pragma unroll
-        for (int g = 0; g < GK; ++g) {
-            ks[g] = group_value<GK, BF>(ks_bits, g) * kCodeScaleA;
-            kb[g] = group_value<GK, BF>(kb_bits, g);
-        }
+            for (int tp = 0; tp < KSETS; tp += 2) {
+                float4_t d[2][KCHUNKS];
 #pragma unroll
-        for (int g = 0; g < GV; ++g) {
-            vs[g] = group_value<GV, BF>(vs_bits, g);
-            vb[g] = group_value<GV, BF>(vb_bits, g);
-        }
-        load_params(row0_next);
-        // With four or eight query heads per KV head the second term of p*s is a matrix instruction of its own, and
-        // a tile takes it only when it has to: one term errs by at most 2^-12 * 15 s per unit of probability, which
-        // stays below 1.8e-3 (inside the output tolerance whatever the values are) while every scale of the tile is
-        // at most kOneTermScale.  Unit-variance values have scales around 0.3.
-        bool two_terms = true;
-        if constexpr (!kTermRows) {
-            float s_max = 0.0f;
+                for (int ts = 0; ts < 2; ++ts)
 #pragma unroll
-            for (int g = 0; g < GV; ++g) s_max = fmaxf(s_max, fabsf(vs[g]));
-            two_terms = __builtin_amdgcn_ballot_w64(tok_valid && !(s_max <= kOneTermScale)) != 0ull;
-        }
-        // A masked row's parameters may hold anything (a NaN included): zeroed once here, they need no further
-        // guard in the products below
-        if (!tok_valid) {
+                    for (int c = 0; c < KCHUNKS; ++c) d[ts][c] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int g = 0; g < GV; ++g) vs[g] = vb[g] = 0.0f;
-        }
-        float alpha[NREP], z[NREP], mx[NREP], pr[NREP];
+                for (int w = 0; w < KWPL; ++w)
 #pragma unroll
-        for (int r = 0; r < NREP; ++r) {
-            float zr = 0.0f;
+                    for (int ts = 0; ts < 2; ++ts)
+#pragma unroll
+                        for (int c = 0; c < KCHUNKS; ++c) {
+                            const CodePairs cp = unpack_codes(kc[tp + ts][c].w[w]);
+                            const uint4 packed = make_uint4(half2_to_bits(cp.a0), half2_to_bits(cp.b0),
+                                                            half2_to_bits(cp.a1), half2_to_bits(cp.b1));
+                            d[ts][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qop[c][w], __builtin_bit_cast(half8_t, packed),
+                                                                              d[ts][c], 0, 0, 0);
+                        }
+                // result row i = 4*(lane/16) + reg belongs to (head i % NREP, group-in-chunk i / NREP); rows past
+                // KROWS are repeats.  part[token][group][head] keeps a lane's registers contiguous.
+                constexpr int kRegs = KROWS < 4 ? KROWS : 4;
+                if (4 * kkb < KROWS) {
+#pragma unroll
+                    for (int ts = 0; ts < 2; ++ts)
+#pragma unroll
+                        for (int c = 0; c < KCHUNKS; ++c) {
+                            float *dst = part + (((tp + ts) * 16 + kj) * GK + c * KGPC) * NREP + 4 * kkb;
+#pragma unroll
+                            for (int e = 0; e < kRegs; ++e) dst[e] = d[ts][c][e];
+                        }
+                }
+                load_k_pair(tp, row0_next); // these registers are free again: the next tile's codes start travelling
+            }
+            wave_lds_sync();
+
+            // ---- the lane that owns token `lane`: finish its scores, online softmax, publish p*s
+            const bool tok_valid = cur.reachable && (cur.t0 + lane >= cur.first) && (cur.t0 + lane < cur.n);
+            float ks[GK], kb[GK], vs[GV], vb[GV];
 #pragma unroll
             for (int g = 0; g < GK; ++g) {
-                zr = fmaf(ks[g], part[(lane * GK + g) * NREP + r], zr);
-                zr = fmaf(kb[g], qsum[r][g], zr);
+                ks[g] = group_value<GK, BF>(ks_bits, g) * kCodeScaleA;
+                kb[g] = group_value<GK, BF>(kb_bits, g);
             }
-            z[r] = mx[r] = tok_valid ? zr * p.score_scale : kNegBig;
-        }
-        wave_max_n(mx); // the tile's maximum of every head, the heads' reductions interleaved
-        // The running maxima settle after a unit's first tiles: one wave-uniform test for all heads, and a tile that
-        // moves none of them takes no exponential for the factors (exp2(0) = 1: the same bits either way).
-        bool any_moved = false;
-#pragma unroll
-        for (int r = 0; r < NREP; ++r) any_moved |= mx[r] > m_run[r];
-        const bool moved = uniform((int)any_moved) != 0;
-#pragma unroll
-        for (int r = 0; r < NREP; ++r) alpha[r] = 1.0f;
-        if (__builtin_expect(moved, 0)) {
-#pragma unroll
-            for (int r = 0; r < NREP; ++r) {
-                const float m_new = fmaxf(m_run[r], mx[r]);
-                alpha[r] = __builtin_amdgcn_exp2f(m_run[r] - m_new);
-                m_run[r] = m_new;
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < NREP; ++r) {
-            pr[r] = tok_valid ? __builtin_amdgcn_exp2f(z[r] - m_run[r]) : 0.0f;
-            l_run[r] = fmaf(l_run[r], alpha[r], pr[r]);
 #pragma unroll
             for (int g = 0; g < GV; ++g) {
-                const half_t hi = (half_t)(pr[r] * vs[g]);
-                ps_h[(r * GV + g) * kWave + ps_slot] = __builtin_bit_cast(uint16_t, hi);
-                pb[r][g] = fmaf(pb[r][g], alpha[r], pr[r] * vb[g]);
+                vs[g] = group_value<GV, BF>(vs_bits, g);
+                vb[g] = group_value<GV, BF>(vb_bits, g);
             }
-        }
-        if (kTermRows || __builtin_expect(two_terms, 0)) { // wave-uniform; one block for all heads: what each hi rounded away
+            load_params(row0_next);
+            // With four or eight query heads per KV head the second term of p*s is a matrix instruction of its own, and
+            // a tile takes it only when it has to: one term errs by at most 2^-12 * 15 s per unit of probability, which
+            // stays below 1.8e-3 (inside the output tolerance whatever the values are) while every scale of the tile is
+            // at most kOneTermScale.  Unit-variance values have scales around 0.3.
+            bool two_terms = true;
+            if constexpr (!kTermRows) {
+                float s_max = 0.0f;
 #pragma unroll
-            for (int r = 0; r < NREP; ++r)
+                for (int g = 0; g < GV; ++g) s_max = fmaxf(s_max, fabsf(vs[g]));
+                two_terms = __builtin_amdgcn_ballot_w64(tok_valid && !(s_max <= kOneTermScale)) != 0ull;
+            }
+            // A masked row's parameters may hold anything (a NaN included): zeroed once here, they need no further
+            // guard in the products below
+            if (!tok_valid) {
+#pragma unroll
+                for (int g = 0; g < GV; ++g) vs[g] = vb[g] = 0.0f;
+            }
+            float alpha[NREP], z[NREP], mx[NREP], pr[NREP];
+#pragma unroll
+            for (int r = 0; r < NREP; ++r) {
+                float zr = 0.0f;
+#pragma unroll
+                for (int g = 0; g < GK; ++g) {
+                    zr = fmaf(ks[g], part[(lane * GK + g) * NREP + r], zr);
+                    zr = fmaf(kb[g], qsum[r][g], zr);
+                }
+                z[r] = mx[r] = tok_valid ? zr * p.score_scale : kNegBig;
+            }
+            wave_max_n(mx); // the tile's maximum of every head, the heads' reductions interleaved
+            // The running maxima settle after a unit's first tiles: one wave-uniform test for all heads, and a tile that
+            // moves none of them takes no exponential for the factors (exp2(0) = 1: the same bits either way).
+            bool any_moved = false;
+#pragma unroll
+            for (int r = 0; r < NREP; ++r) any_moved |= mx[r] > m_run[r];
+            const bool moved = uniform((int)any_moved) != 0;
+#pragma unroll
+            for (int r = 0; r < NREP; ++r) alpha[r] = 1.0f;
+            if (__builtin_expect(moved, 0)) {
+#pragma unroll
+                for (int r = 0; r < NREP; ++r) {
+                    const float m_new = fmaxf(m_run[r], mx[r]);
+                    alpha[r] = __builtin_amdgcn_exp2f(m_run[r] - m_new);
+                    m_run[r] = m_new;
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < NREP; ++r) {
+                pr[r] = tok_valid ? __builtin_amdgcn_exp2f(z[r] - m_run[r]) : 0.0f;
+                l_run[r] = fmaf(l_run[r], alpha[r], pr[r]);
 #pragma unroll
                 for (int g = 0; g < GV; ++g) {
                     const half_t hi = (half_t)(pr[r] * vs[g]);
-                    const half_t lo = (half_t)fmaf(pr[r], vs[g], -(float)hi);
-                    ps_h[((NREP + r) * GV + g) * kWave + ps_slot] = __builtin_bit_cast(uint16_t, lo);
-                }
-        }
-        wave_lds_sync();
-
-        // ---- V side: acc[head][e] += (p s)[t] * c[t][e], four tokens per matrix instruction
-        // One wave-uniform test for all heads: a branch per head made the compiler copy the accumulators round
-        // every one of them.  The running maxima settle after a unit's first tiles, so this is rarely taken.
-        if (__builtin_expect(moved, 0)) {
-#pragma unroll
-            for (int row = 0; row < (kTermRows ? VROWS : NREP); ++row)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[row / 4][e][row % 4] *= alpha[row % NREP];
-        }
-#pragma unroll
-        for (int i = 0; i < VSTEPS; i += 4) {
-            constexpr int kTerms = kTermRows ? 1 : 2; // matrix instructions per accumulator and step (the second: if needed)
-            half4_t pq[kTerms][VHQ];
-#pragma unroll
-            for (int t = 0; t < kTerms; ++t)
-#pragma unroll
-                for (int h = 0; h < VHQ; ++h) {
-                    const uint2 raw = ps_q[((t * NREP + h * 4 + v_row) * GV + vg) * (kWave / 4) + VTPS * (i / 4) + vo];
-                    pq[t][h] = __builtin_bit_cast(half4_t, raw);
-                }
-            half4_t lo[4], hi[4];
-#pragma unroll
-            for (int by = 0; by < 4; ++by) {
-                // byte `by` of the four tokens' words: codes 2*by (low nibble) and 2*by+1 (high nibble)
-                const uint32_t sel = 0x0C040C00u + by * 0x00010001u;
-                const uint32_t p01 = __builtin_amdgcn_perm(vc[i + 1], vc[i], sel);
-                const uint32_t p23 = __builtin_amdgcn_perm(vc[i + 3], vc[i + 2], sel);
-                lo[by] = __builtin_bit_cast(half4_t, make_uint2(p01 & 0x000F000Fu, p23 & 0x000F000Fu));
-                hi[by] = __builtin_bit_cast(half4_t, make_uint2(p01 & 0x00F000F0u, p23 & 0x00F000F0u));
-#pragma unroll
-                for (int h = 0; h < VHQ; ++h) {
-                    acc[h][2 * by] = __builtin_amdgcn_mfma_f32_4x4x4f16(pq[0][h], lo[by], acc[h][2 * by], 0, 0, 0);
-                    acc[h][2 * by + 1] = __builtin_amdgcn_mfma_f32_4x4x4f16(pq[0][h], hi[by], acc[h][2 * by + 1], 0, 0, 0);
+                    ps_h[(r * GV + g) * kWave + ps_slot] = __builtin_bit_cast(uint16_t, hi);
+                    pb[r][g] = fmaf(pb[r][g], alpha[r], pr[r] * vb[g]);
                 }
             }
-            if constexpr (kTerms == 2) {
-                // one wave-uniform test per four tokens' words (a test per byte put sixteen taken branches into every
-                // tile of the usual cache, which needs no second term)
-                if (__builtin_expect(two_terms, 0)) {
+            if (kTermRows || __builtin_expect(two_terms, 0)) { // wave-uniform; one block for all heads: what each hi rounded away
 #pragma unroll
-                    for (int by = 0; by < 4; ++by)
+                for (int r = 0; r < NREP; ++r)
 #pragma unroll
-                        for (int h = 0; h < VHQ; ++h) {
-                            acc[h][2 * by] = __builtin_amdgcn_mfma_f32_4x4x4f16(pq[1][h], lo[by], acc[h][2 * by], 0, 0, 0);
-                            acc[h][2 * by + 1] = __builtin_amdgcn_mfma_f32_4x4x4f16(pq[1][h], hi[by], acc[h][2 * by + 1], 0, 0, 0);
-                        }
-                }
+                    for (int g = 0; g < GV; ++g) {
+                        const half_t hi = (half_t)(pr[r] * vs[g]);
+                        const half_t lo = (half_t)fmaf(pr[r], vs[g], -(float)hi);
+                        ps_h[((NREP + r) * GV + g) * kWave + ps_slot] = __builtin_bit_cast(uint16_t, lo);
+                    }
             }
-            load_v_quad(i, row0_next);
-        }
-        wave_lds_sync(); // the next tile (or the reduction below) overwrites part / ps
+            wave_lds_sync();
 
-        cur = nxt;
-        x += stride;
-        active = more;
+            // ---- V side: acc[head][e] += (p s)[t] * c[t][e], four tokens per matrix instruction
+            // One wave-uniform test for all heads: a branch per head made the compiler copy the accumulators round
+            // every one of them.  The running maxima settle after a unit's first tiles, so this is rarely taken.
+            if (__builtin_expect(moved, 0)) {
+#pragma unroll
+                for (int row = 0; row < (kTermRows ? VROWS : NREP); ++row)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) acc[row / 4][e][row % 4] *= alpha[row % NREP];
+            }
+#pragma unroll
+            for (int i = 0; i < VSTEPS; i += 4) {
+                constexpr int kTerms = kTermRows ? 1 : 2; // matrix instructions per accumulator and step (the second: if needed)
+                half4_t pq[kTerms][VHQ];
+#pragma unroll
+                for (int t = 0; t < kTerms; ++t)
+#pragma unroll
+                    for (int h = 0; h < VHQ; ++h) {
+                        const uint2 raw = ps_q[((t * NREP + h * 4 + v_row) * GV + vg) * (kWave / 4) + VTPS * (i / 4) + vo];
+                        pq[t][h] = __builtin_bit_cast(half4_t, raw);
+                    }
+                half4_t lo[4], hi[4];
+#pragma unroll
+                for (int by = 0; by < 4; ++by) {
+                    // byte `by` of the four tokens' words: codes 2*by (low nibble) and 2*by+1 (high nibble)
+                    const uint32_t sel = 0x0C040C00u + by * 0x00010001u;
+                    const uint32_t p01 = __builtin_amdgcn_perm(vc[i + 1], vc[i], sel);
+                    const uint32_t p23 = __builtin_amdgcn_perm(vc[i + 3], vc[i + 2], sel);
+                    lo[by] = __builtin_bit_cast(half4_t, make_uint2(p01 & 0x000F000Fu, p23 & 0x000F000Fu));
+                    hi[by] = __builtin_bit_cast(half4_t, make_uint2(p01 & 0x00F000F0u, p23 & 0x00F000F0u));
+#pragma unroll
+                    for (int h = 0; h < VHQ; ++h) {
+                        acc[h][2 * by] = __builtin_amdgcn_mfma_f32_4x4x4f16(pq[0][h], lo[by], acc[h][2 * by], 0, 0, 0);
+                        acc[h][2 * by + 1] = __builtin_amdgcn_mfma_f32_4x4x4f16(pq[0][h], hi[by], acc[h][2 * by + 1], 0, 0, 0);
+                    }
+                }
+                if constexpr (kTerms == 2) {
+                    // one wave-uniform test per four tokens' words (a test per byte put sixteen taken branches into every
+                    // tile of the usual cache, which needs no second term)
+                    if (__builtin_expect(two_terms, 0)) {
+#pragma unroll
+                        for (int by = 0; by < 4; ++by)
+#pragma unroll
+                            for (int h = 0; h < VHQ; ++h) {
+                                acc[h][2 * by] = __builtin_amdgcn_mfma_f32_4x4x4f16(pq[1][h], lo[by], acc[h][2 * by], 0, 0, 0);
+                                acc[h][2 * by + 1] = __builtin_amdgcn_mfma_f32_4x4x4f16(pq[1][h], hi[by], acc[h][2 * by + 1], 0, 0, 0);
+                            }
+                    }
+                }
+                load_v_quad(i, row0_next);
+            }
+            wave_lds_sync(); // the next tile (or the reduction below) overwrites part / ps
+
+            cur = nxt;
+            x += stride;
+            active = more;
+        } while (active && x < mseg.end);
+        // the wave is done with mseg: it leaves its result behind (closing the oldest segments first when no buffer is free)
+        if (coop) {
+            while (k_my - k_old >= kSegBufs) close_oldest();
+            publish();
+        } else {
+            finish_alone();
+        }
     }
+    if (coop) // without a tile left it helps to close everything that remains
+        while (seg.begin < x1) close_oldest();
 }
 
 template <int DK, int DV, int NREP>

@@ -112,7 +112,7 @@ __device__ __forceinline__ float wave_max(float v)
 #define Q4KV_MAX_DPP2(CTRL) Q4KV_MAX_DPP(CTRL) "v_max_f32_dpp %1, %1, %1 " CTRL "\n\t"
 #define Q4KV_MAX_DPP4(CTRL)                                                                                             \
     Q4KV_MAX_DPP2(CTRL) "v_max_f32_dpp %2, %2, %2 " CTRL "\n\tv_max_f32_dpp %3, %3, %3 " CTRL "\n\t"
-#define Q4KV_MAX_STEPS(M)                                                                                               \
+#define Q4KV_WAVE_STEPS(M)                                                                                               \
     M("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")                                                                 \
     "s_nop 1\n\t" M("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf")                                                   \
     "s_nop 1\n\t" M("row_half_mirror row_mask:0xf bank_mask:0xf")                                                       \
@@ -124,27 +124,33 @@ __device__ __forceinline__ void wave_max_n(float (&v)[N])
 {
     static_assert(N == 1 || N == 2 || N == 4 || N == 8, "heads per KV head");
     if constexpr (N == 1) {
-        asm("s_nop 4\n\t" Q4KV_MAX_STEPS(Q4KV_MAX_DPP) : "+v"(v[0]));
+        asm("s_nop 4\n\t" Q4KV_WAVE_STEPS(Q4KV_MAX_DPP) : "+v"(v[0]));
     } else if constexpr (N == 2) {
-        asm("s_nop 4\n\t" Q4KV_MAX_STEPS(Q4KV_MAX_DPP2) : "+v"(v[0]), "+v"(v[1]));
+        asm("s_nop 4\n\t" Q4KV_WAVE_STEPS(Q4KV_MAX_DPP2) : "+v"(v[0]), "+v"(v[1]));
     } else {
 #pragma unroll
         for (int i = 0; i < N; i += 4)
-            asm("s_nop 4\n\t" Q4KV_MAX_STEPS(Q4KV_MAX_DPP4) : "+v"(v[i]), "+v"(v[i + 1]), "+v"(v[i + 2]), "+v"(v[i + 3]));
+            asm("s_nop 4\n\t" Q4KV_WAVE_STEPS(Q4KV_MAX_DPP4) : "+v"(v[i]), "+v"(v[i + 1]), "+v"(v[i + 2]), "+v"(v[i + 3]));
     }
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[i]), 63));
 }
 
-__device__ __forceinline__ float wave_sum(float v)
+// The sums of N values over the wave, in the same way; lane 63 holds the results, the other lanes partial sums.
+#define Q4KV_ADD_DPP(R, CTRL) "v_add_f32_dpp %" #R ", %" #R ", %" #R " " CTRL "\n\t"
+#define Q4KV_ADD_DPP2(CTRL) Q4KV_ADD_DPP(0, CTRL) Q4KV_ADD_DPP(1, CTRL)
+#define Q4KV_ADD_DPP3(CTRL) Q4KV_ADD_DPP2(CTRL) Q4KV_ADD_DPP(2, CTRL)
+#define Q4KV_ADD_DPP5(CTRL) Q4KV_ADD_DPP3(CTRL) Q4KV_ADD_DPP(3, CTRL) Q4KV_ADD_DPP(4, CTRL)
+template <int N>
+__device__ __forceinline__ void wave_sum_n(float (&v)[N])
 {
-    v += Q4KV_DPP(0.0f, v, 0xB1, 0xF);
-    v += Q4KV_DPP(0.0f, v, 0x4E, 0xF);
-    v += Q4KV_DPP(0.0f, v, 0x141, 0xF);
-    v += Q4KV_DPP(0.0f, v, 0x140, 0xF);
-    v += Q4KV_DPP(0.0f, v, 0x142, 0xA);
-    v += Q4KV_DPP(0.0f, v, 0x143, 0xC);
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+    static_assert(N == 2 || N == 3 || N == 5, "denominator and bias sums of one, two or four groups");
+    if constexpr (N == 2)
+        asm("s_nop 4\n\t" Q4KV_WAVE_STEPS(Q4KV_ADD_DPP2) : "+v"(v[0]), "+v"(v[1]));
+    else if constexpr (N == 3)
+        asm("s_nop 4\n\t" Q4KV_WAVE_STEPS(Q4KV_ADD_DPP3) : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]));
+    else
+        asm("s_nop 4\n\t" Q4KV_WAVE_STEPS(Q4KV_ADD_DPP5) : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]));
 }
 
 } // namespace q4kv

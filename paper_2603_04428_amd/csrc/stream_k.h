@@ -327,13 +327,33 @@ __device__ __forceinline__ void zero_empty_units(const PlanView &pv, uint16_t *o
 // cache back, drop it on the other side), but costs tens of microseconds per fence on this chip (measured: the
 // 48-layer decode call went from 0.76 to 0.93 ms).  Instead every access to a record is itself a device-scope access:
 // such a store goes through to memory, such a load does not take a cached copy, and nothing else has to move.
-__device__ __forceinline__ void record_store(float *p, float v)
+// Records are float arrays at even offsets; a pair travels as one 8-byte access.
+template <int N>
+__device__ __forceinline__ void record_store(float *p, const float (&v)[N])
 {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if constexpr (N == 1) {
+        __hip_atomic_store(p, v[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; i += 2) {
+            const uint64_t pair = (uint64_t)__builtin_bit_cast(uint32_t, v[i]) | (uint64_t)__builtin_bit_cast(uint32_t, v[i + 1]) << 32;
+            __hip_atomic_store(reinterpret_cast<uint64_t *>(p + i), pair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
 }
-__device__ __forceinline__ float record_load(const float *p)
+template <int N>
+__device__ __forceinline__ void record_load(const float *p, float (&v)[N])
 {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if constexpr (N == 1) {
+        v[0] = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; i += 2) {
+            const uint64_t pair = __hip_atomic_load(reinterpret_cast<const uint64_t *>(p + i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            v[i] = __builtin_bit_cast(float, (uint32_t)pair);
+            v[i + 1] = __builtin_bit_cast(float, (uint32_t)(pair >> 32));
+        }
+    }
 }
 
 // Counts this wave in on a unit whose partial record it has just written with record_store; true for the wave that
@@ -350,32 +370,32 @@ __device__ __forceinline__ bool arrive_last(int32_t *counter, int slots, int lan
     return old == slots - 1;
 }
 
-// One output value of one query head from the `slots` partial records of its unit: element e of every record,
-// binary32, slot order.  All lanes of the wave work on the same head (ml: its [slots][2] maxima and denominators;
+// VEC consecutive output values (from element e on) of one query head from the `slots` partial records of its unit, in
+// slot order, binary32.  All lanes of the wave work on the same head (ml: its [slots][2] maxima and denominators;
 // acc: its [slots][DV] sums).  Records whose denominator is zero (every token masked) are skipped; a head with
-// nothing at all yields zero.  A record load is a trip to memory, so the loads of up to 16 records are issued
-// together with their maxima and denominators and only then used: units of up to 16 records cost one round trip.
-template <int DV>
-__device__ __forceinline__ float merge_element(const float *acc, const float *ml, int slots, int e, int lane)
+// nothing at all yields zero.  A record load is a trip to memory, so the loads of a batch of records are issued
+// together with their maxima and denominators and only then used: a unit of one batch costs one round trip.
+template <int DV, int VEC>
+__device__ __forceinline__ void merge_elements(const float *acc, const float *ml, int slots, int e, int lane, float (&o)[VEC])
 {
-    constexpr int B = 16;
-    float o = 0.0f, m_ref = kMergeNegBig, denom = 0.0f;
+    constexpr int B = VEC <= 2 ? 16 : 32 / VEC; // records per batch
+    float m_ref = kMergeNegBig, denom = 0.0f;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) o[i] = 0.0f;
     for (int s0 = 0; s0 < slots; s0 += B) {
         const int count = slots - s0 < B ? slots - s0 : B;
-        const int s = s0 + (lane < count ? lane : count - 1);
-        const float m_s = record_load(ml + 2 * s);
-        const float l_s = lane < count ? record_load(ml + 2 * s + 1) : 0.0f;
-        float v[B];
+        float ml_s[2], v[B][VEC];
+        record_load(ml + 2 * (s0 + (lane < count ? lane : count - 1)), ml_s);
 #pragma unroll
-        for (int j = 0; j < B; ++j) {
-            const int k = j < count ? j : count - 1; // repeats of the batch's last record are not used
-            v[j] = record_load(acc + (int64_t)(s0 + k) * DV + e);
-        }
+        for (int j = 0; j < B; ++j)
+            record_load(acc + (int64_t)(s0 + (j < count ? j : count - 1)) * DV + e, v[j]); // repeats of the batch's last record are not used
+        const float m_s = ml_s[0], l_s = lane < count ? ml_s[1] : 0.0f;
         const float m_new = fmaxf(m_ref, wave_max(l_s > 0.0f ? m_s : kMergeNegBig));
         const float keep = __builtin_amdgcn_exp2f(m_ref - m_new); // 1 when the reference stays
         m_ref = m_new;
         denom *= keep;
-        o *= keep;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) o[i] *= keep;
         const float w = l_s > 0.0f ? __builtin_amdgcn_exp2f(m_s - m_ref) : 0.0f;
         const float wl = w * l_s;
 #pragma unroll
@@ -383,59 +403,27 @@ __device__ __forceinline__ float merge_element(const float *acc, const float *ml
             if (j < count) { // wave-uniform
                 const float wk = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), j));
                 denom += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wl), j));
-                o = fmaf(wk, v[j], o);
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) o[i] = fmaf(wk, v[j][i], o[i]);
             }
         }
     }
-    return denom > 0.0f ? o / denom : 0.0f;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) o[i] = denom > 0.0f ? o[i] / denom : 0.0f;
 }
 
-// The same for a whole output row of one query head by one wave (a lane owns elements lane, lane + 64, ...): the
-// loads of 16 / (DV / 64) records at a time, all chunks of a record together, so that a unit of a few records costs a
-// single round trip per head.  Writes the normalised row as binary16.
-template <int DV>
-__device__ __forceinline__ void merge_row(const float *acc, const float *ml, int slots, uint16_t *out_row, int lane)
+// N consecutive values of an output row as binary16
+template <int N>
+__device__ __forceinline__ void store_halves(uint16_t *dst, const float (&v)[N])
 {
-    constexpr int CH = DV / kWave; // 1, 2, 4 or 8 elements per lane
-    static_assert(CH == 1 || CH == 2 || CH == 4 || CH == 8, "row width");
-    constexpr int B = CH >= 8 ? 2 : 16 / CH;
-    float o[CH];
+    if constexpr (N == 1) {
+        dst[0] = float_to_half_bits(v[0]);
+    } else {
+        uint32_t w[N / 2];
 #pragma unroll
-    for (int c = 0; c < CH; ++c) o[c] = 0.0f;
-    float m_ref = kMergeNegBig, denom = 0.0f;
-    for (int s0 = 0; s0 < slots; s0 += B) {
-        const int count = slots - s0 < B ? slots - s0 : B;
-        const int s = s0 + (lane < count ? lane : count - 1);
-        const float m_s = record_load(ml + 2 * s);
-        const float l_s = lane < count ? record_load(ml + 2 * s + 1) : 0.0f;
-        float v[B][CH];
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-            const int k = j < count ? j : count - 1; // repeats of the batch's last record are not used
-#pragma unroll
-            for (int c = 0; c < CH; ++c) v[j][c] = record_load(acc + (int64_t)(s0 + k) * DV + c * kWave + lane);
-        }
-        const float m_new = fmaxf(m_ref, wave_max(l_s > 0.0f ? m_s : kMergeNegBig));
-        const float keep = __builtin_amdgcn_exp2f(m_ref - m_new); // 1 when the reference stays
-        m_ref = m_new;
-        denom *= keep;
-#pragma unroll
-        for (int c = 0; c < CH; ++c) o[c] *= keep;
-        const float w = l_s > 0.0f ? __builtin_amdgcn_exp2f(m_s - m_ref) : 0.0f;
-        const float wl = w * l_s;
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-            if (j < count) { // wave-uniform
-                const float wk = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), j));
-                denom += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wl), j));
-#pragma unroll
-                for (int c = 0; c < CH; ++c) o[c] = fmaf(wk, v[j][c], o[c]);
-            }
-        }
+        for (int i = 0; i < N / 2; ++i) w[i] = (uint32_t)float_to_half_bits(v[2 * i]) | (uint32_t)float_to_half_bits(v[2 * i + 1]) << 16;
+        __builtin_memcpy(__builtin_assume_aligned(dst, 2 * N), w, 2 * N);
     }
-    const float inv = denom > 0.0f ? 1.0f / denom : 0.0f;
-#pragma unroll
-    for (int c = 0; c < CH; ++c) out_row[c * kWave + lane] = float_to_half_bits(o[c] * inv);
 }
 
 } // namespace q4kv
