@@ -818,7 +818,8 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
 // ---------------------------------------------------------------------------------------------- merging shared units
 
 constexpr int kMergeThreads = 256;
-constexpr int kMergeQuads = 4; // float4 pieces of a lane that a wave merges at a time
+constexpr int kMergeQuads = 2; // float4 pieces of a lane that a wave merges at a time
+constexpr int kMergeBatch = 4; // records whose pieces are asked for together
 
 // pieces a unit's merge is cut into: one wave each
 template <int DV, int ROWGROUPS>
@@ -827,7 +828,10 @@ template <int DV, int ROWGROUPS>
 constexpr int merge_parts() { return merge_items<DV, ROWGROUPS>() / (kMergeThreads / kWave); }
 
 // The unit that begins in worker w's range and goes on past it: workgroups (w, part) merge its records in worker order.
-// Reading the records once is all there is to do, so every wave has four 16-byte loads of each record in flight.
+// Reading the records once is all there is to do, so every wave has the loads of four records in flight, and takes two pieces
+// of each: of what was tried (records at a time x pieces: 2 x 4, 4 x 4, 8 x 2, 4 x 2) one agent of 8,000 tokens, 256-wide,
+// two layers takes 258.2, 261.0, 254.8, 254.4 us, four agents of up to 6,000, 128-wide, four layers 202.5, 203.3, 205.7, 201.1
+// (two records at a time behind a first pass over the maxima: 260.3 and 202.9).
 template <int DV, int NREP, int ROWGROUPS>
 __global__ __launch_bounds__(kMergeThreads) void chunk_merge_kernel(ChunkParams p)
 {
@@ -843,29 +847,43 @@ __global__ __launch_bounds__(kMergeThreads) void chunk_merge_kernel(ChunkParams 
     if (u.qt * QPOS + rg * kRowsWave / NREP >= p.q_len) return; // a row group past the chunk left no record
     auto record = [&](int s) { return (int64_t)(s == 0 ? u.first_record : (worker + s) * 2) * ROWGROUPS + rg; };
     auto max_and_sum = [&](int s) { return *reinterpret_cast<const float2 *>(p.part_ml + (record(s) * kRowsWave + qn) * 2); };
-    float m_ref = kNegBig;
-#pragma unroll 8
-    for (int s = 0; s < u.slots; ++s) {
-        const float2 ml = max_and_sum(s);
-        if (ml.y > 0.0f) m_ref = fmaxf(m_ref, ml.x);
-    }
-    float l = 0.0f;
+    // kBatch records at a time, everything of them asked for together: a unit of that many costs one trip to memory.  The
+    // reference moves batch by batch.
+    float m_ref = kNegBig, l = 0.0f;
     float4_t o[kMergeQuads];
 #pragma unroll
     for (int k = 0; k < kMergeQuads; ++k) o[k] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 2
-    for (int s = 0; s < u.slots; ++s) {
-        const float2 ml = max_and_sum(s);
-        const float4_t *src = reinterpret_cast<const float4_t *>(p.part_acc) + (record(s) * kQuads + quad0) * kWave + lane;
-        float4_t v[kMergeQuads];
+    for (int s0 = 0; s0 < u.slots; s0 += kMergeBatch) {
+        float2 ml[kMergeBatch];
+        float4_t v[kMergeBatch][kMergeQuads];
 #pragma unroll
-        for (int k = 0; k < kMergeQuads; ++k) v[k] = src[k * kWave];
-        const float wgt = ml.y > 0.0f ? __builtin_amdgcn_exp2f(ml.x - m_ref) : 0.0f;
-        l = fmaf(ml.y, wgt, l);
+        for (int b = 0; b < kMergeBatch; ++b) {
+            const int s = s0 + b < u.slots ? s0 + b : u.slots - 1; // repeats of the last record get no weight
+            ml[b] = max_and_sum(s);
+            const float4_t *src = reinterpret_cast<const float4_t *>(p.part_acc) + (record(s) * kQuads + quad0) * kWave + lane;
 #pragma unroll
-        for (int k = 0; k < kMergeQuads; ++k)
+            for (int k = 0; k < kMergeQuads; ++k) v[b][k] = src[k * kWave];
+        }
+        float m_new = m_ref;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[k][e] = fmaf(v[k][e], wgt, o[k][e]);
+        for (int b = 0; b < kMergeBatch; ++b) {
+            if (s0 + b >= u.slots) ml[b].y = 0.0f;
+            if (ml[b].y > 0.0f) m_new = fmaxf(m_new, ml[b].x);
+        }
+        const float keep = __builtin_amdgcn_exp2f(m_ref - m_new); // 1 when the reference stays
+        m_ref = m_new;
+        l *= keep;
+#pragma unroll
+        for (int k = 0; k < kMergeQuads; ++k) o[k] *= keep;
+#pragma unroll
+        for (int b = 0; b < kMergeBatch; ++b) {
+            const float wgt = ml[b].y > 0.0f ? __builtin_amdgcn_exp2f(ml[b].x - m_ref) : 0.0f;
+            l = fmaf(ml[b].y, wgt, l);
+#pragma unroll
+            for (int k = 0; k < kMergeQuads; ++k)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[k][e] = fmaf(v[b][k][e], wgt, o[k][e]);
+        }
     }
     const float inv = l > 0.0f ? 1.0f / l : 0.0f;
     const int r = rg * kRowsWave + qn, c = u.qt * QPOS + r / NREP;
