@@ -108,8 +108,16 @@ def _check(rc):
         raise Q4KVError(rc, lib().q4kv_last_error().decode())
 
 
+# The handle of the current stream without a Stream object around it: a call's whole marshalling takes 3.4 us, and building
+# the object took 2.8 more (a decode step of nine layers, call by call: 202 us of host work before, 148 after).  Asked
+# anew by every call, as current_stream() would be; a torch without the function gets the object.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dev(t, dtype, name):
@@ -117,7 +125,7 @@ def _dev(t, dtype, name):
         return None
     if not (t.is_cuda and t.is_contiguous() and t.dtype == dtype):
         raise TypeError(f"{name}: need a contiguous {dtype} tensor on the GPU, got {t.dtype} on {t.device}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def make_spec(num_layers, num_q_heads, num_kv_heads, k_dim, v_dim=None, v_aliases_k=False, block_tokens=256,
@@ -225,7 +233,7 @@ def _image_call(fn, spec, kpool, vpool, block_ids, image):
     kp = kpool.c()
     vp = None if spec.v_aliases_k else vpool.c()
     _check(fn(C.byref(spec), C.byref(kp), None if vp is None else C.byref(vp), _dev(block_ids, torch.int32, "block_ids"),
-              block_ids.numel(), C.c_void_p(image.data_ptr()), image.numel(), _stream()))
+              block_ids.numel(), image.data_ptr(), image.numel(), _stream()))
 
 
 def q4kv_export_blocks(spec, kpool, vpool, block_ids, image=None):
@@ -245,7 +253,7 @@ def q4kv_read_probe(buf, sink):
     """Measurement helper: read the contiguous GPU tensor `buf` once (nothing is written); sink: int32 [1] on the GPU."""
     if not (buf.is_cuda and buf.is_contiguous() and sink.is_cuda and sink.numel() >= 1 and sink.element_size() == 4):
         raise ValueError("q4kv_read_probe: contiguous GPU tensors, sink of at least one 4-byte element")
-    _check(lib().q4kv_read_probe(C.c_void_p(buf.data_ptr()), buf.numel() * buf.element_size(), C.c_void_p(sink.data_ptr()),
+    _check(lib().q4kv_read_probe(buf.data_ptr(), buf.numel() * buf.element_size(), sink.data_ptr(),
                                  _stream()))
 
 
@@ -322,7 +330,7 @@ def q4kv_batched_attention(spec, kpool, vpool, q, block_table, seq_len, max_seq_
               _dev(q, torch.float16, "q"), _dev(out, torch.float16, "out"),
               _dev(block_table, torch.int32, "block_table"), block_table.shape[1],
               _dev(seq_len, torch.int32, "seq_len"), A, q_len, max_seq_len, float(sm_scale))
-    tail = (int(split_tokens), layer_begin, layer_end, C.c_void_p(workspace.data_ptr()), workspace.numel(), _stream())
+    tail = (int(split_tokens), layer_begin, layer_end, workspace.data_ptr(), workspace.numel(), _stream())
     if isinstance(window, (list, tuple)) or hasattr(window, "__len__"):      # one window per layer of the call (host)
         if len(window) != layer_end - layer_begin:
             raise ValueError(f"{len(window)} windows for {layer_end - layer_begin} layers")
@@ -354,7 +362,7 @@ def q4kv_batched_attention_static(spec, kpool, vpool, q, out, block_table, seq_l
 def q4kv_decode_plan(spec, seq_len, max_seq_len, workspace, window=0, split_tokens=0, layers_in_call=1):
     """q4kv_decode_plan: prepare `workspace` (uint8 tensor on the GPU) for q4kv_batched_attention_planned calls."""
     _check(lib().q4kv_decode_plan(C.byref(spec), _dev(seq_len, torch.int32, "seq_len"), seq_len.numel(), max_seq_len,
-                                  int(window), int(split_tokens), layers_in_call, C.c_void_p(workspace.data_ptr()),
+                                  int(window), int(split_tokens), layers_in_call, workspace.data_ptr(),
                                   workspace.numel(), _stream()))
 
 
@@ -368,5 +376,5 @@ def q4kv_batched_attention_planned(spec, kpool, vpool, q, out, block_table, max_
         C.byref(spec), C.byref(kp), None if vp is None else C.byref(vp), _dev(q, torch.float16, "q"),
         _dev(out, torch.float16, "out"), _dev(block_table, torch.int32, "block_table"), block_table.shape[1], q.shape[1],
         max_seq_len, float(sm_scale), int(window), int(split_tokens), layer_begin, layer_end,
-        C.c_void_p(workspace.data_ptr()), workspace.numel(), _stream()))
+        workspace.data_ptr(), workspace.numel(), _stream()))
     return out
