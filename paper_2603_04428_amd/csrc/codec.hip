@@ -227,14 +227,12 @@ struct AppendParams {
     int max_blocks, chunk_len, heads, layer_begin, num_blocks, layers;
 };
 
-// STEPS: a wave's round is 16 * STEPS groups.  Four steps fill whole lines of scales and biases (long chunks on many
-// agents: the kernel is then bound by the memory system and the vector ALUs).  A launch that does not fill the chip is a
-// chain of trips to memory -- the length, the block table, the rows of every step -- and takes one step per round: more
-// waves, and the rows, which depend on neither, are asked for before the table.
-template <bool BF, int STEPS>
+template <bool BF>
 __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams pp)
 {
-    constexpr int ROUND = 16 * STEPS; // groups
+    // a wave's round is 64 groups in four steps: whole lines of scales and biases (long chunks on many agents: the kernel is
+    // bound by the memory system and the vector ALUs)
+    constexpr int STEPS = 4, ROUND = 16 * STEPS;
     const int sub = threadIdx.x & 7;
     const int which = blockIdx.z >= (unsigned)pp.layers ? 1 : 0;
     const int a = blockIdx.y, li = blockIdx.z - which * pp.layers, agents = gridDim.y;
@@ -295,12 +293,6 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams pp)
             const uint32_t h = h0 + heads, c = cl - heads * p.chunk_len;
             const bool mine = lane < ROUND && c0 + lane < per_unit;
             if (lane < ROUND) s_src[wave][lane] = (c * p.heads + h) * p.groups_per_row + g;
-            if constexpr (STEPS == 1) {
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                load_rows(0);
-            }
             int64_t dgrp = -1;
             if (mine) {
                 const int t = n0 + (int)c;
@@ -321,7 +313,7 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams pp)
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll 1
         for (int step = 0; step < STEPS; ++step) {
-            if constexpr (STEPS > 1) load_rows(step);
+            load_rows(step);
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const uint32_t l = step * 16 + 8 * j + (lane >> 3);
@@ -357,6 +349,37 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams pp)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
+}
+
+// The same for launches that do not fill the chip (a decode step's token, a chunk of one agent): a chain of trips to memory
+// and of instructions that each wave runs once.  An octet of lanes takes one group, everything stays in registers, and the
+// row is asked for before the length and the table.  Twelve 256-wide layers of ten agents, a plan, an append and a call each
+// 435 -> 426 us, nine 192 + 128-wide ones of three agents 205 -> 195 (rounds of 16 groups per wave before).
+template <bool BF>
+__global__ __launch_bounds__(kThreads) void append_few_kernel(AppendParams p)
+{
+    const int sub = threadIdx.x & 7;
+    const int which = blockIdx.z >= (unsigned)p.layers ? 1 : 0;
+    const int a = blockIdx.y, li = blockIdx.z - which * p.layers;
+    const uint32_t per_row = p.pool[which].groups_per_row, chunk = p.chunk_len;
+    const uint32_t i = blockIdx.x * (kThreads / 8) + (threadIdx.x >> 3); // group in the order of the pool: head, token, group
+    if (i >= chunk * p.heads * per_row) return;
+    const int n0 = p.seq_len_before[a];
+    // quotients of numbers below 2^21 as in the kernel above
+    const uint32_t row = (uint32_t)(((float)i + 0.5f) * (1.0f / (float)per_row)), g = i - row * per_row;
+    const uint32_t h = (uint32_t)(((float)row + 0.5f) * (1.0f / (float)chunk)), c = row - h * chunk;
+    const int64_t src = ((((int64_t)li * gridDim.y + a) * chunk + c) * p.heads + h) * per_row + g;
+    const uint4 raw = *reinterpret_cast<const uint4 *>(p.pool[which].x + src * kGroup + sub * 8);
+    const int t = n0 + (int)c, bi = t / kBlockTokens;
+    int blk = -1;
+    if (t >= 0 && bi < p.max_blocks) blk = p.block_table[(int64_t)a * p.max_blocks + bi];
+    uint16_t sb, bb;
+    const uint32_t word = quantize_octet<BF>(raw, sub, &sb, &bb);
+    if (blk < 0 || blk >= p.num_blocks) return;
+    const int64_t dst = ((((int64_t)(p.layer_begin + li) * p.num_blocks + blk) * p.heads + h) * kBlockTokens + t % kBlockTokens) *
+                            per_row + g;
+    p.pool[which].codes[dst * 8 + sub] = word;
+    if (sub < 2) (sub == 0 ? p.pool[which].scale : p.pool[which].bias)[dst] = sub == 0 ? sb : bb;
 }
 
 // One lane per word: 8 codes -> 8 binary16 values (16 bytes).
@@ -467,23 +490,27 @@ hipError_t launch_append(const q4kv_spec &spec, const q4kv_pool &k, const q4kv_p
     // workgroups per (pool, layer, agent): enough for the chunk, and at most 8 per compute unit over the whole
     // launch (rounded down: a launch of 1.2 rounds takes as long as one of 2)
     const int64_t units = (int64_t)pools * layers * num_agents, slots = (int64_t)compute_units * kWorkgroupsPerCu;
-    // Rounds of one step while they fit the chip at once.  Measured (us, rounds of four steps / of one): one token of ten
-    // agents, 256-wide heads 5.2 / 4.6, of three agents, sixteen 192 + 128-wide heads 7.6 / 4.6; 70 tokens of four
-    // agents, 128-wide 7.6 / 5.2; 512 tokens of one agent, 256-wide 15.7 / 5.5.
-    const bool small = units * ((per_unit + kThreads / 4 - 1) / (kThreads / 4)) <= slots;
-    const int per_workgroup = small ? kThreads / 4 : kThreads; // groups: 16 or 64 per wave
-    int64_t gx = (per_unit + per_workgroup - 1) / per_workgroup;
+    // An octet per group while there are at most 96 groups per workgroup slot of the chip (196,608).  Measured (us, rounds of
+    // 64 groups per wave / an octet each): one token of ten agents, 256-wide heads 4.6 / 2.6, of three agents, sixteen 192 +
+    // 128-wide heads 5.3 / 2.6; 70 tokens of four agents, 128-wide 6.8 / 2.8; 512 tokens of one agent, 256-wide 6.8 / 3.5; by
+    // groups: 128,000 8.2 / 7.5, 164,000 9.4 / 8.3, 192,000 10.3 / 10.1, 320,000 13.8 / 14.8, 800,000 29.2 / 31.9.
+    if (units * per_unit <= 96 * slots) {
+        const dim3 grid((unsigned)((per_unit + kThreads / 8 - 1) / (kThreads / 8)), (unsigned)num_agents, (unsigned)(pools * layers));
+        if (spec.param_format == Q4KV_PARAMS_BF16)
+            hipLaunchKernelGGL(append_few_kernel<true>, grid, dim3(kThreads), 0, stream, p);
+        else
+            hipLaunchKernelGGL(append_few_kernel<false>, grid, dim3(kThreads), 0, stream, p);
+        return hipGetLastError();
+    }
+    int64_t gx = (per_unit + kThreads - 1) / kThreads;
     const int64_t cap = slots / units;
     if (gx > cap) gx = cap;
     if (gx < 1) gx = 1;
     const dim3 grid((unsigned)gx, (unsigned)num_agents, (unsigned)(pools * layers)), block(kThreads);
-    if (spec.param_format == Q4KV_PARAMS_BF16) {
-        if (small) hipLaunchKernelGGL((append_kernel<true, 1>), grid, block, 0, stream, p);
-        else hipLaunchKernelGGL((append_kernel<true, 4>), grid, block, 0, stream, p);
-    } else {
-        if (small) hipLaunchKernelGGL((append_kernel<false, 1>), grid, block, 0, stream, p);
-        else hipLaunchKernelGGL((append_kernel<false, 4>), grid, block, 0, stream, p);
-    }
+    if (spec.param_format == Q4KV_PARAMS_BF16)
+        hipLaunchKernelGGL(append_kernel<true>, grid, block, 0, stream, p);
+    else
+        hipLaunchKernelGGL(append_kernel<false>, grid, block, 0, stream, p);
     return hipGetLastError();
 }
 

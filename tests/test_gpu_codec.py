@@ -305,3 +305,25 @@ def test_long_append_matches_oracle(dims, param_format):
         assert np.array_equal(bits(gp.codes), op.codes[:, :nb])
         assert np.array_equal(bits(gp.scale), op.scale[:, :nb])
         assert np.array_equal(bits(gp.bias), op.bias[:, :nb])
+
+
+@pytest.mark.parametrize("param_format", [0, 1])
+def test_append_in_one_piece_and_in_pieces(param_format):
+    """The kernel of long appends (above 96 groups per workgroup slot: 64 groups per wave and round) writes what the kernel
+    of short ones writes piece by piece: rows of unequal width, group counts that end inside a round, blocks crossed."""
+    heads, dims, A, L, chunk = 6, (192, 128), 3, 2, 1001
+    slots = 8 * torch.cuda.get_device_properties(0).multi_processor_count
+    groups = chunk * heads * (dims[0] // 64)
+    assert 2 * L * A * groups > 96 * slots and 2 * L * A * (groups // 4) <= 96 * slots and groups % 64
+    spec = b.make_spec(L, heads, heads, dims[0], dims[1], param_format=param_format)
+    lens = torch.tensor([254, 0, 300], dtype=torch.int32, device=DEV)
+    table = torch.randperm(18, generator=torch.Generator().manual_seed(3)).view(A, 6).to(torch.int32).to(DEV)
+    table[0, 2] = 18                                                # one id past the pool
+    g = torch.Generator(device=DEV).manual_seed(9)
+    k_new, v_new = (torch.randn((L, A, chunk, heads, d), device=DEV, generator=g).half() for d in dims)
+    pools = [[b.Pool(spec, d, 18, DEV, poison=True) for d in dims] for _ in range(2)]
+    b.q4kv_append(spec, *pools[0], k_new, v_new, table, lens)
+    for c in range(0, chunk, 250):
+        b.q4kv_append(spec, *pools[1], k_new[:, :, c:c + 250].contiguous(), v_new[:, :, c:c + 250].contiguous(), table, lens + c)
+    for one, other in zip(*pools):
+        assert torch.equal(one.codes, other.codes) and torch.equal(one.scale, other.scale) and torch.equal(one.bias, other.bias)
