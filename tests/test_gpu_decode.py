@@ -389,6 +389,39 @@ def test_units_shared_by_many_workgroups(shape, split_tokens):
                  f"{shape} split {split_tokens} window 3000")
 
 
+@pytest.mark.parametrize("agents", [1, 10, 63, 64, 65, 300])
+@pytest.mark.parametrize("layers,window", [(1, 0), (3, 100), (70, 64)])
+def test_plan_words(agents, layers, window):
+    """Every word of the plan that the decode kernels read, on both sides of the 64 agents up to which one wave writes it:
+    lengths below zero, zero, around a tile, above the bound."""
+    heads, msl, split = 8, 2000, 256
+    rng = np.random.default_rng(agents)
+    lens = rng.integers(0, msl + 1, agents)
+    lens[rng.integers(0, agents, agents // 4)] = rng.choice([-3, 0, 1, 63, 64, 65, msl, msl + 5], agents // 4)
+    spec = b.make_spec(layers, 16, heads, 128, 128)
+    ws = torch.full((b.q4kv_attention_workspace_bytes(spec, agents, 1, msl, split, layers),), 0xA5, dtype=torch.uint8, device=DEV)
+    b.q4kv_decode_plan(spec, torch.from_numpy(lens.astype(np.int32)).to(DEV), msl, ws, window, split, layers)
+    n = np.clip(lens, 0, msl)
+    start = np.where((window > 0) & (n > window), n - window, 0) // 64 * 64
+    tpre = np.concatenate([[0], np.cumsum((n - start + 63) // 64)])
+    total = layers * heads * tpre[-1]
+    workers = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    per = (max(-(-total // workers), split // 64) + 3) // 4 * 4
+    empty = np.flatnonzero(n == 0)
+    ints = 6 + 2 * layers + 1 + layers * (2 * agents + 2) + 2 * agents
+    plan = ws[:4 * ints].cpu().numpy().view(np.int32)
+    assert list(plan[:5]) == [total, per, 1, layers, len(empty)] and plan[5] & 1
+    at = 6
+    for want in (heads * tpre[-1] * np.arange(layers + 1), np.zeros(layers), [window], tpre, start):
+        assert np.array_equal(plan[at:at + len(want)], want)
+        at += len(want)
+    at += (layers - 1) * (2 * agents + 2)
+    assert np.array_equal(plan[at:at + agents], n)
+    assert np.array_equal(plan[at + agents:at + agents + len(empty)], empty)
+    counters = ws[(4 * ints + 255) // 256 * 256:][:4 * layers * heads * agents]
+    assert not bool(counters.any())
+
+
 @pytest.mark.parametrize("shape", [(3, 8, 2, 128, False, (1500, 0, 300, 77, 2100)), (2, 4, 1, 256, False, (5000, 130)),
                                    (2, 16, 1, (576, 512), True, (900, 130, 0, 37))])
 def test_planned_calls_equal_plain_calls(shape):
