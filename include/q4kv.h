@@ -140,7 +140,8 @@ int q4kv_append(const q4kv_spec *spec, const q4kv_pool *k, const q4kv_pool *v, c
  *   split_tokens smallest token range handed to one wavefront (multiple of 256), 0 = library picks.  The
  *                tokens of all (layer, KV head, agent) units are dealt out evenly over a fixed set of
  *                wavefronts; this is the floor of a wavefront's share and bounds the partial results kept
- *                per query head.  Must equal the value given to q4kv_attention_workspace_bytes.
+ *                per query head.  Must equal the value given to q4kv_attention_workspace_bytes.  With 0 the share may
+ *                become smaller than q4kv_default_split_tokens says where the lengths are far below max_seq_len.
  *   workspace    device scratch of at least q4kv_attention_workspace_bytes(...) bytes, 16-byte aligned;
  *                contents before and after the call are unspecified.  With q_len > 1 it is optional: a call whose
  *                workspace_bytes is exactly what q4kv_attention_workspace_bytes says may use it to spread few or ragged

@@ -1,5 +1,6 @@
 // The C ABI of libq4kv (include/q4kv.h): argument validation on the host, launch planning
 // (split-K schedule), and nothing else -- every step of the path runs in the kernels.
+#include <algorithm>
 #include <atomic>
 #include <hip/hip_runtime.h>
 
@@ -96,11 +97,25 @@ int pick_split_tokens(const q4kv_spec &s, int num_agents, int max_seq_len, int l
     return (int)blocks * 256;
 }
 
+// How far the plan may lower that floor by itself where the lengths (or a window) leave less than max_seq_len lets the host
+// expect, if the floor was the library's choice: to a tile per wave.  One layer's call with max_seq_len 8,192, 512 tokens per
+// workgroup / 256: ten agents of 300, 256-wide 21.2 / 15.0 us, of 1K-8K with a window of 1,024 19.7 / 18.5, five of them 18.5 /
+// 15.2; ten of 500, 128-wide 16.2 / 13.5; three of 600, 192 + 128-wide 14.1 / 12.6; the shared latent, tokens per
+// wave 512 / 128: twenty agents of 4K of 32K 52.2 / 35.5, five of 1K of 32K, 256 / 64, 30.4 / 21.2.
+int floor_tokens(const q4kv_spec &s, int split_given, int split_used)
+{
+    if (split_given != 0) return split_used;
+    return 64 * (q4kv::mla_decode_supported(s) ? 1 : q4kv::decode_waves_per_workgroup());
+}
+
 // Partial records reserved per (layer, agent, query head): the most workers that can meet in one unit.  A worker's
 // range is at least split_tokens long.  The GQA kernel's workers are workgroups, except that from a certain range
 // length on (decode_solo_quarter_tiles() * 4) every wave takes a quarter of its workgroup's range and writes a record
-// of its own.
-int slots_per_unit(const q4kv_spec &s, int max_seq_len, int split_tokens)
+// of its own.  The shared-latent kernel's workers are waves, and a tile takes one of them as long as a short call's start: with
+// a floor of the library's order records are reserved down to ranges of a tile as far as 12 MB go (a call of many layers
+// gains nothing and gets none; the static scratch holds 16 MB).
+constexpr int64_t kFineRecordBytes = 12 << 20;
+int slots_per_unit(const q4kv_spec &s, int num_agents, int layers, int max_seq_len, int split_tokens)
 {
     const int tiles = (max_seq_len + 63) / 64, min_per = split_tokens / 64;
     int slots = (tiles + min_per - 1) / min_per + 1;
@@ -109,6 +124,10 @@ int slots_per_unit(const q4kv_spec &s, int max_seq_len, int split_tokens)
         if (quarter < q4kv::decode_solo_quarter_tiles()) quarter = q4kv::decode_solo_quarter_tiles();
         const int solo = (tiles + quarter - 1) / quarter + 1;
         if (solo > slots) slots = solo;
+    } else if (split_tokens <= 512) {
+        const int64_t fit = kFineRecordBytes / std::max<int64_t>((int64_t)num_agents * layers * s.num_q_heads * (s.v_dim + 2) * 4, 1);
+        const int fine = (int)(fit < tiles + 1 ? fit : tiles + 1);
+        if (fine > slots) slots = fine;
     }
     return slots;
 }
@@ -253,7 +272,7 @@ size_t q4kv_attention_workspace_bytes(const q4kv_spec *spec, int32_t num_agents,
         return q4kv::chunk_workspace_bytes(*spec, num_agents, q_len, max_seq_len, num_layers_in_call, compute_units(), acc_bytes);
     }
     const int st = split_tokens ? split_tokens : pick_split_tokens(*spec, num_agents, max_seq_len, num_layers_in_call);
-    const int64_t slots = slots_per_unit(*spec, max_seq_len, st);
+    const int64_t slots = slots_per_unit(*spec, num_agents, num_layers_in_call, max_seq_len, st);
     const int64_t units = (int64_t)num_layers_in_call * num_agents * q_len * spec->num_q_heads;
     return plan_bytes(num_agents, num_layers_in_call) + arrival_bytes(*spec, num_agents, num_layers_in_call) +
            (size_t)(units * slots * (spec->v_dim + 2) * (int64_t)sizeof(float));
@@ -305,8 +324,10 @@ static int attention_common(const q4kv_spec *spec, const q4kv_pool *k, const q4k
     a.window = window;
     a.layer_window = layer_window;
     a.split_tokens = split_tokens ? split_tokens : pick_split_tokens(*spec, num_agents, max_seq_len, layers);
-    a.max_slots = slots_per_unit(*spec, max_seq_len, a.split_tokens);
+    a.floor_tokens = floor_tokens(*spec, split_tokens, a.split_tokens);
+    a.max_slots = slots_per_unit(*spec, num_agents, layers, max_seq_len, a.split_tokens);
     a.grid_workgroups = attention_workgroups(*spec);
+    a.compute_units = compute_units();
     a.layer_begin = layer_begin;
     a.layers_in_call = layers;
     a.sm_scale = sm_scale;
@@ -318,7 +339,6 @@ static int attention_common(const q4kv_spec *spec, const q4kv_pool *k, const q4k
                         spec->num_q_heads / spec->num_kv_heads, spec->v_aliases_k);
         size_t acc_bytes = 0;
         const size_t need = q4kv::chunk_workspace_bytes(*spec, num_agents, q_len, max_seq_len, layers, compute_units(), acc_bytes);
-        a.compute_units = compute_units();
         a.chunk_workers = 0;
         a.part_acc = a.part_ml = nullptr;
         // Only a workspace of exactly the size that was asked for these arguments is written: one of any other size was
@@ -451,6 +471,8 @@ int q4kv_decode_plan(const q4kv_spec *spec, const int32_t *seq_len, int32_t num_
     a.window = window;
     a.layer_window = nullptr;
     a.split_tokens = split_tokens ? split_tokens : pick_split_tokens(*spec, num_agents, max_seq_len, num_layers_in_call);
+    a.floor_tokens = floor_tokens(*spec, split_tokens, a.split_tokens);
+    a.max_slots = slots_per_unit(*spec, num_agents, num_layers_in_call, max_seq_len, a.split_tokens);
     a.grid_workgroups = attention_workgroups(*spec);
     a.layers_in_call = num_layers_in_call;
     const size_t need = q4kv_attention_workspace_bytes(spec, num_agents, 1, max_seq_len, a.split_tokens, num_layers_in_call);

@@ -84,14 +84,42 @@ struct LayerWindows {
     int window;
     int w[kMaxWindowLayers];
 };
+struct OneWindow {
+    int window;
+};
 
-// total_waves = workers of the attention launch (workgroups, or waves for the shared-latent kernel).  Workgroup 0 writes the plan described in stream_k.h; all workgroups
-// of the launch share the clearing of the arrival counters (one per (layer, KV head, agent) unit).
+// How finely a call is dealt out when its tiles do not go round.
+struct ShareLimits {
+    int min_tiles;    // a worker's smallest range for which records are reserved whatever the lengths
+    int floor_tiles;  // the smallest it may get (<= min_tiles)
+    int max_slots;    // records reserved per unit
+    int per_multiple; // a range is a multiple of this many tiles (a power of two)
+};
+
+// Tiles per worker: an even share, but no less than a floor.  The host knows max_seq_len only and reserves records for ranges
+// of min_tiles; where the lengths or the window leave far less to do, workers would stand idle at that floor, so the ranges
+// shrink as long as the longest unit (in tiles) still meets no more workers than it has records: ceil(longest / per) + 1.
+__device__ __forceinline__ int tiles_per_worker(int total, int workers, int longest, const ShareLimits &s)
+{
+    int per = (int)(((uint32_t)total + (uint32_t)workers - 1) / (uint32_t)workers); // total < 2^31
+    if (per < s.min_tiles) {
+        const int even = per;
+        per = s.min_tiles;
+        if (s.floor_tiles < s.min_tiles) {
+            const int records = max(s.max_slots - 1, 1);
+            per = min(per, max(max(even, s.floor_tiles), (longest + records - 1) / records));
+        }
+    }
+    return (per + s.per_multiple - 1) & -s.per_multiple;
+}
+
+// total_waves = workers of the attention launch (workgroups, or waves for the shared-latent kernel).  Workgroup 0 writes the
+// plan described in stream_k.h; all workgroups of the launch share the clearing of the arrival counters (one per (layer, KV
+// head, agent) unit).  This is the general form; plan_few_kernel below writes the same plan for most calls.
 __global__ __launch_bounds__(kThreads) void plan_kernel(const int32_t *__restrict__ seq_len, int num_agents,
                                                         int max_seq_len, const LayerWindows lw, int layers,
-                                                        int kv_heads, int total_waves, int min_tiles_per_wave,
-                                                        int per_multiple, int signature, int32_t *__restrict__ plan,
-                                                        int32_t *__restrict__ arrivals)
+                                                        int kv_heads, int total_waves, const ShareLimits limits, int signature,
+                                                        int32_t *__restrict__ plan, int32_t *__restrict__ arrivals)
 {
     {
         const int counters = layers * kv_heads * num_agents; // the host keeps this below 2^31
@@ -100,6 +128,7 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(const int32_t *__restric
     }
     __shared__ int s_wave_sum[kWaves];
     __shared__ int s_cls[kMaxWindowLayers], s_win[kMaxWindowLayers], s_tt[kMaxWindowLayers], s_classes;
+    __shared__ int s_longest; // tiles of the longest unit
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     PlanView pv;
     pv.plan = plan;
@@ -109,6 +138,7 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(const int32_t *__restric
     // Thread li finds the first layer with its window; the class of a layer is the number of such first layers
     // before its own.
     __shared__ int s_first[kMaxWindowLayers];
+    if (tid == 0) s_longest = 0;
     static_assert(kThreads >= kMaxWindowLayers, "one thread per layer");
     if (lw.uniform) {
         if (tid == 0) {
@@ -190,13 +220,16 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(const int32_t *__restric
         const int cb = pv.class_off(c);
         const int window = s_win[c];
         int32_t *tpre = plan + cb + 1, *tstart = plan + cb + 2 + num_agents;
-        int local = 0;
+        int local = 0, longest = 0;
         for (int a = a0; a < a1; ++a) {
             const int n = length(a);
             const int start = first_tile_token(n, window);
             tstart[a] = start;
-            local += n > 0 ? (n - start + kWave - 1) / kWave : 0;
+            const int tiles = n > 0 ? (n - start + kWave - 1) / kWave : 0;
+            local += tiles;
+            longest = max(longest, tiles);
         }
+        if (longest > 0) atomicMax(&s_longest, longest);
         int incl = local; // inclusive scan inside the wave, then over the waves through LDS
 #pragma unroll
         for (int off = 1; off < kWave; off <<= 1) {
@@ -248,11 +281,8 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(const int32_t *__restric
         if (tid < layers) plan[pv.lt_off() + tid] = before + incl - mine;
         if (tid == 0) {
             plan[pv.lt_off() + layers] = total;
-            int per = (int)(((long long)total + total_waves - 1) / total_waves);
-            if (per < min_tiles_per_wave) per = min_tiles_per_wave;
-            per = (per + per_multiple - 1) / per_multiple * per_multiple;
             plan[0] = total;
-            plan[1] = per;
+            plan[1] = tiles_per_worker(total, total_waves, s_longest, limits);
             plan[2] = C;
             plan[3] = layers;
         }
@@ -263,29 +293,56 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(const int32_t *__restric
             total += s_tt[0] * kv_heads;
         }
         plan[pv.lt_off() + layers] = total;
-        int per = (int)(((long long)total + total_waves - 1) / total_waves);
-        if (per < min_tiles_per_wave) per = min_tiles_per_wave;
-        per = (per + per_multiple - 1) / per_multiple * per_multiple;
         plan[0] = total;
-        plan[1] = per;
+        plan[1] = tiles_per_worker(total, total_waves, s_longest, limits);
         plan[2] = C;
         plan[3] = layers;
     }
 }
 
-// The same plan for at most 64 agents and one window for all layers, which is what a decode step and a single small call
-// bring: lane a of the first wave holds agent a, so the kernel is one trip to memory (the lengths), one scan over the
-// lanes and the stores, without barriers.  What it takes is latency: the attention launch waits for every trip of the general
-// kernel above.  One agent of 1,024 tokens, 128-wide, one layer, plan and attention: 12.7 -> 11.2 us a call.
+// Inclusive sum over the lanes of a wave: inside the rows of 16, then from row to row.
+__device__ __forceinline__ int wave_prefix_sum(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false); // row_shr 1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false); // row_bcast15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false); // row_bcast31 into rows 2 and 3
+    return v;
+}
+
+// The largest of the lanes' values, none of them negative, in the same steps (a lane without a source adds zero).
+__device__ __forceinline__ int wave_max_of_counts(int v)
+{
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
+    return __builtin_amdgcn_readlane(v, kWave - 1);
+}
+
+// The same plan for at most 64 agents, with one window for all layers or at most 64 layers, which is what a decode step and
+// a single small call bring: lane a of the first wave holds agent a and lane l layer l, so the kernel is one trip to memory
+// (the lengths), a scan over the lanes per class and the stores, without barriers.  What it takes is latency: the attention
+// launch waits for every trip of the general kernel above.  One agent of 1,024 tokens, 128-wide, one layer, plan and
+// attention: 12.7 -> 11.2 us a call; 48 layers of ten agents, two classes of windows: 320.5 -> 313.5.
+// W: OneWindow, or LayerWindows with a window per layer.
+template <typename W>
 __global__ __launch_bounds__(kThreads) void plan_few_kernel(const int32_t *__restrict__ seq_len, int num_agents,
-                                                            int max_seq_len, int window, int layers, int kv_heads,
-                                                            int total_waves, int min_tiles_per_wave, int per_multiple,
+                                                            int max_seq_len, const W lw, int layers,
+                                                            int kv_heads, int total_waves, const ShareLimits limits,
                                                             int signature, int32_t *__restrict__ plan,
                                                             int32_t *__restrict__ arrivals)
 {
+    constexpr bool kOne = __is_same(W, OneWindow);
     const int tid = threadIdx.x;
-    int n = 0;
+    int n = 0, window_of = 0; // agent tid's length, layer tid's window
     if (blockIdx.x == 0 && tid < num_agents) n = seq_len[tid]; // on its way while the counters are cleared
+    if constexpr (kOne) window_of = max(lw.window, 0);
+    else if (tid < kWave && tid < layers) window_of = max(lw.w[tid], 0);
     const int counters = layers * kv_heads * num_agents;
     for (int i = blockIdx.x * kThreads + tid; i < counters; i += gridDim.x * kThreads) arrivals[i] = 0;
     if (blockIdx.x != 0) return;
@@ -293,40 +350,63 @@ __global__ __launch_bounds__(kThreads) void plan_few_kernel(const int32_t *__res
     pv.plan = plan;
     pv.A = num_agents;
     pv.L = layers;
-    if (tid >= kWave) { // the other waves: every layer is of class 0
-        for (int li = tid - kWave; li < layers; li += kThreads - kWave) plan[pv.cls_off() + li] = 0;
+    if (tid >= kWave) { // the other waves: with one window every layer is of class 0
+        if (kOne)
+            for (int li = tid - kWave; li < layers; li += kThreads - kWave) plan[pv.cls_off() + li] = 0;
         return;
     }
     n = min(max(n, 0), max_seq_len);
-    const int start = (window > 0 && n > window ? n - window : 0) & ~(kWave - 1);
-    const int tiles = n > 0 ? (n - start + kWave - 1) / kWave : 0;
-    int incl = tiles; // inclusive sum over the lanes: inside the rows of 16, then from row to row
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xF, 0xF, false); // row_shr 1, 2, 4, 8
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xF, 0xF, false);
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xF, 0xF, false);
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xF, 0xF, false);
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xA, 0xF, false); // row_bcast15 into rows 1 and 3
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xC, 0xF, false); // row_bcast31 into rows 2 and 3
+    // ---- per class, in the order of their first layers: first visible tile and tile count of every agent, prefix sum over
+    // the agents
+    uint64_t left = kOne ? 1ull : ~0ull >> (kWave - layers); // layers without a class
+    int classes = 0, my_class = 0, my_tiles = 0, longest = 0;      // of layer tid: class, tiles per KV head
+    while (left != 0) {
+        const int window = __builtin_amdgcn_readlane(window_of, __builtin_ctzll(left));
+        const uint64_t same = __builtin_amdgcn_ballot_w64(window_of == window) & left;
+        const int start = (window > 0 && n > window ? n - window : 0) & ~(kWave - 1);
+        const int tiles = n > 0 ? (n - start + kWave - 1) / kWave : 0;
+        const int incl = wave_prefix_sum(tiles), tiles_per_head = __builtin_amdgcn_readlane(incl, kWave - 1);
+        const int cb = pv.class_off(classes);
+        if (tid < num_agents) {
+            plan[cb + 1 + tid] = incl - tiles;
+            plan[cb + 2 + num_agents + tid] = start;
+        }
+        if (tid == 0) {
+            plan[cb] = window;
+            plan[cb + 1 + num_agents] = tiles_per_head;
+        }
+        longest = max(longest, tiles);
+        if (kOne || (same >> tid & 1) != 0) {
+            my_class = classes;
+            my_tiles = tiles_per_head;
+        }
+        left &= ~same;
+        ++classes;
+    }
     const uint64_t is_empty = __builtin_amdgcn_ballot_w64(tid < num_agents && n == 0);
-    const int tiles_per_head = __builtin_amdgcn_readlane(incl, kWave - 1);
-    const int cb = pv.class_off(0);
     if (tid < num_agents) {
         plan[pv.nlen_off() + tid] = n;
-        plan[cb + 1 + tid] = incl - tiles;
-        plan[cb + 2 + num_agents + tid] = start;
         if (n == 0) plan[pv.empty_off() + __builtin_popcountll(is_empty & ((1ull << tid) - 1))] = tid;
     }
-    for (int li = tid; li <= layers; li += kWave) plan[pv.lt_off() + li] = li * kv_heads * tiles_per_head; // the host keeps it below 2^31
+    // ---- tiles before every layer (the host keeps the total below 2^31)
+    int total;
+    if (kOne) {
+        total = layers * kv_heads * my_tiles;
+        for (int li = tid; li < layers; li += kWave) plan[pv.lt_off() + li] = li * kv_heads * my_tiles;
+    } else {
+        const int mine = tid < layers ? my_tiles * kv_heads : 0, incl = wave_prefix_sum(mine);
+        total = __builtin_amdgcn_readlane(incl, kWave - 1);
+        if (tid < layers) {
+            plan[pv.lt_off() + tid] = incl - mine;
+            plan[pv.cls_off() + tid] = my_class;
+        }
+    }
+    longest = wave_max_of_counts(longest);
     if (tid == 0) {
-        const int total = layers * kv_heads * tiles_per_head;
-        int per = (int)(((uint32_t)total + (uint32_t)total_waves - 1) / (uint32_t)total_waves);
-        if (per < min_tiles_per_wave) per = min_tiles_per_wave;
-        per = (per + per_multiple - 1) / per_multiple * per_multiple;
-        plan[cb] = window > 0 ? window : 0;
-        plan[cb + 1 + num_agents] = tiles_per_head;
+        plan[pv.lt_off() + layers] = total;
         plan[0] = total;
-        plan[1] = per;
-        plan[2] = 1;
+        plan[1] = tiles_per_worker(total, total_waves, longest, limits);
+        plan[2] = classes;
         plan[3] = layers;
         plan[4] = __builtin_popcountll(is_empty);
         plan[5] = signature;
@@ -1091,19 +1171,20 @@ hipError_t launch_plan(const AttentionArgs &a, int workers, int per_multiple, hi
     const int64_t counters = (int64_t)a.layers_in_call * a.spec.num_kv_heads * a.num_agents;
     const int helpers = (int)(counters / 8192 < 256 ? counters / 8192 : 256);
     const dim3 grid(1 + helpers), block(kThreads);
-    const int min_tiles = a.split_tokens / kWave;
+    const ShareLimits limits{a.split_tokens / kWave, a.floor_tokens / kWave, a.max_slots, per_multiple};
     if (a.layer_window == nullptr && a.num_agents <= kWave) {
-        hipLaunchKernelGGL(plan_few_kernel, grid, block, 0, stream, a.seq_len, a.num_agents, a.max_seq_len, a.window,
-                           a.layers_in_call, a.spec.num_kv_heads, workers, min_tiles, per_multiple, a.plan_signature, a.plan,
-                           a.arrivals);
+        hipLaunchKernelGGL(plan_few_kernel<OneWindow>, grid, block, 0, stream, a.seq_len, a.num_agents, a.max_seq_len, OneWindow{a.window},
+                           a.layers_in_call, a.spec.num_kv_heads, workers, limits, a.plan_signature, a.plan, a.arrivals);
         return hipGetLastError();
     }
     LayerWindows lw;
     lw.uniform = a.layer_window == nullptr;
     lw.window = a.window;
     for (int i = 0; i < kMaxWindowLayers; ++i) lw.w[i] = (!lw.uniform && i < a.layers_in_call) ? a.layer_window[i] : 0;
-    hipLaunchKernelGGL(plan_kernel, grid, block, 0, stream, a.seq_len, a.num_agents, a.max_seq_len, lw, a.layers_in_call,
-                       a.spec.num_kv_heads, workers, min_tiles, per_multiple, a.plan_signature, a.plan, a.arrivals);
+    const bool few = !lw.uniform && a.num_agents <= kWave && a.layers_in_call <= kWave;
+    hipLaunchKernelGGL(few ? plan_few_kernel<LayerWindows> : plan_kernel, grid, block, 0, stream, a.seq_len,
+                       a.num_agents, a.max_seq_len, lw, a.layers_in_call, a.spec.num_kv_heads, workers, limits, a.plan_signature,
+                       a.plan, a.arrivals);
     return hipGetLastError();
 }
 

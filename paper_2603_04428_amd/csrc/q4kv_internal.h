@@ -29,6 +29,7 @@ struct AttentionArgs {
     int max_blocks, num_agents, q_len, max_seq_len, window;
     const int32_t *layer_window; // host, [layers_in_call]: one window per layer of the call, or nullptr: `window` for all
     int split_tokens;           // smallest token range one wave takes (multiple of 256)
+    int floor_tokens;           // the plan may go down to this where fewer tokens are to be seen than max_seq_len allows
     int max_slots;              // partial records reserved per (layer, agent, query head)
     int grid_workgroups;        // workgroups of the attention launch (two per compute unit)
     int layer_begin, layers_in_call;
@@ -47,7 +48,7 @@ struct MergeParams;
 StreamParams stream_params(const AttentionArgs &a);
 MergeParams merge_params(const AttentionArgs &a);
 // workers: how many equal tile ranges the plan cuts the call into, each a multiple of per_multiple tiles long; needs
-// split_tokens, plan, arrivals
+// split_tokens, floor_tokens, max_slots, plan, arrivals
 hipError_t launch_plan(const AttentionArgs &a, int workers, int per_multiple, hipStream_t stream);
 
 // true when a decode (q_len == 1) kernel exists for these head shapes

@@ -422,6 +422,52 @@ def test_plan_words(agents, layers, window):
     assert not bool(counters.any())
 
 
+@pytest.mark.parametrize("layers,agents", [(1, 64), (63, 3), (64, 2), (65, 2), (5, 65)])
+def test_plan_with_many_windows(layers, agents):
+    """A window per layer on both sides of the 64 layers and 64 agents up to which one wave writes the plan."""
+    lens = [(37 * a) % 200 for a in range(agents)]
+    w = synth.small(46, layers, 2, 1, 64, 64, False, lens)
+    spec, kpool, vpool, table, table_d = gpu_cache(w)
+    ospec, okp, ovp, otable = host_cache(w)
+    windows = [[0, 70, 1, -5, 500, 128][(l * l) % 6] for l in range(layers)]
+    got = run_gpu(w, spec, kpool, vpool, table_d, lens, window=windows)
+    want = oracle.attention(ospec, okp, ovp, w.q_all().numpy(), otable, lens, w.sm_scale, window_per_layer=windows)
+    assert_close(got, want, f"{layers} layers, {agents} agents")
+
+
+@pytest.mark.parametrize("shape,bound", [((1, 16, 8, 256, False, (300,) * 10), 8192), ((2, 8, 2, 128, False, (700, 64, 1)), 32768),
+                                         ((1, 16, 16, (192, 128), False, (501, 130)), 6007),
+                                         ((1, 16, 1, (576, 512), True, (1000, 65, 0, 400)), 32768),
+                                         ((1, 16, 1, (576, 512), True, (2000, 64)), 2048)])
+def test_ranges_shrink_where_the_bound_is_far(shape, bound):
+    """Lengths far below max_seq_len: the plan deals out ranges below the floor the host reserves records for, and no unit meets
+    more workers than it has records."""
+    L, Hq, Hkv, D, alias, lens = shape
+    Dk, Dv = D if isinstance(D, tuple) else (D, D)
+    w = synth.small(45, L, Hq, Hkv, Dk, Dv, alias, lens)
+    spec, kpool, vpool, table, table_d = gpu_cache(w)
+    wide = torch.full((len(lens), (bound + 255) // 256), -1, dtype=torch.int32, device=DEV)
+    wide[:, :table_d.shape[1]] = table_d
+    sl, q = torch.tensor(lens, dtype=torch.int32, device=DEV), w.q_all(DEV)
+    need = b.q4kv_attention_workspace_bytes(spec, len(lens), 1, bound, 0, L)
+    ws = torch.full((need,), 0xA5, dtype=torch.uint8, device=DEV)
+    out = torch.empty((L, len(lens), 1, Hq, Dv), dtype=torch.float16, device=DEV)
+    b.q4kv_decode_plan(spec, sl, bound, ws, layers_in_call=L)
+    total, per = ws[:8].cpu().numpy().view(np.int32)
+    tiles, T = [-(-n // 64) for n in lens], -(-bound // 64)
+    floor = b.q4kv_default_split_tokens(spec, len(lens), 1, bound, L) // 64
+    slots = need // (L * len(lens) * Hq * (Dv + 2) * 4) if alias else -(-T // floor) + 1
+    assert total == L * Hkv * sum(tiles) and per == (1 if alias else 4) and -(-max(tiles) // per) + 1 <= slots
+    b.q4kv_batched_attention_planned(spec, kpool, vpool, q, out, wide, bound, w.sm_scale, ws, layer_begin=0, layer_end=L)
+    plain = b.q4kv_batched_attention(spec, kpool, vpool, q, wide, sl, bound, w.sm_scale)
+    assert torch.equal(out, plain)
+    ospec, okp, ovp, otable = host_cache(w)
+    assert_close(out.cpu().numpy(), oracle.attention(ospec, okp, ovp, w.q_all().numpy(), otable, list(lens), w.sm_scale), f"{shape}")
+    if not alias:                                                    # the general plan kernel: a window per layer
+        each = b.q4kv_batched_attention(spec, kpool, vpool, q, wide, sl, bound, w.sm_scale, [0] * L)
+        assert torch.equal(each, plain)
+
+
 @pytest.mark.parametrize("shape", [(3, 8, 2, 128, False, (1500, 0, 300, 77, 2100)), (2, 4, 1, 256, False, (5000, 130)),
                                    (2, 16, 1, (576, 512), True, (900, 130, 0, 37))])
 def test_planned_calls_equal_plain_calls(shape):
