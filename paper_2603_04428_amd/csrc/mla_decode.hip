@@ -530,6 +530,8 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
 
 // Merge the partials of every (layer, agent, query head) in slot order: binary32, output binary16.  A thread owns
 // four consecutive output elements of one head (16-byte loads); v_dim / 4 threads share a head.
+// B: records whose loads are issued together.
+template <int B>
 __global__ __launch_bounds__(kThreads) void combine_kernel(const float *__restrict__ part_acc,
                                                            const float *__restrict__ part_ml,
                                                            const int32_t *__restrict__ plan, uint16_t *__restrict__ out,
@@ -560,31 +562,31 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const float *__restri
     }
     const float *ml = part_ml + unit * max_slots * 2;
     const float *acc = part_acc + unit * max_slots * v_dim + e;
-    // Four slots at a time: every load of a group is issued before anything is computed, so a unit costs one
-    // memory round trip per group instead of two dependent ones per slot.  The running reference moves group by
-    // group (with at most four slots: exactly the maximum over all slots, then one weighted sum in slot order).
+    // B slots at a time: every load of a group is issued before anything is computed, so a unit costs one memory round trip per
+    // group.  Past the last slot a group reads that slot again and gives it no weight.  The running reference moves group by
+    // group (with one group: exactly the maximum over all slots, then one weighted sum in slot order).
     float m = kNegBig, denom = 0.0f;
     float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    for (int s0 = 0; s0 < slots; s0 += 4) {
-        float mm[4], ll[4];
-        float4 a[4];
+    for (int s0 = 0; s0 < slots; s0 += B) {
+        float mm[B], ll[B];
+        float4 a[B];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const bool in = s0 + k < slots;
-            const float2 t = in ? *reinterpret_cast<const float2 *>(ml + 2 * (s0 + k)) : make_float2(kNegBig, 0.0f);
+        for (int k = 0; k < B; ++k) {
+            const int at = min(s0 + k, slots - 1);
+            const float2 t = *reinterpret_cast<const float2 *>(ml + 2 * at);
             mm[k] = t.x;
-            ll[k] = t.y;
-            a[k] = in ? *reinterpret_cast<const float4 *>(acc + (long long)(s0 + k) * v_dim) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            ll[k] = s0 + k < slots ? t.y : 0.0f;
+            a[k] = *reinterpret_cast<const float4 *>(acc + (long long)at * v_dim);
         }
         float m_new = m;
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int k = 0; k < B; ++k)
             if (ll[k] > 0.0f) m_new = fmaxf(m_new, mm[k]);
         const float keep = __builtin_amdgcn_exp2f(m - m_new); // 1 when the reference stays, 0 while nothing was added yet
         denom *= keep;
         o.x *= keep; o.y *= keep; o.z *= keep; o.w *= keep;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < B; ++k) {
             if (!(ll[k] > 0.0f)) continue;
             const float wgt = __builtin_amdgcn_exp2f(mm[k] - m_new);
             denom = fmaf(wgt, ll[k], denom);
@@ -607,7 +609,11 @@ hipError_t launch_combine(const AttentionArgs &a, hipStream_t stream)
     if (units == 0) return hipSuccess;
     const int units_per_block = kThreads / (a.spec.v_dim / 4); // v_dim is a multiple of 64 and at most 1,024 here
     const int64_t blocks = (units + units_per_block - 1) / units_per_block;
-    hipLaunchKernelGGL(combine_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, a.part_acc, a.part_ml, a.plan,
+    // Up to two workgroups per compute unit the kernel is a chain of trips to memory, and a long agent of a short call has up to
+    // a hundred records: sixteen of them a trip (one layer, five agents of 32K tokens, a call 55.2 -> 48.1 us).  With more, the
+    // memory is busy and a unit has about nine records: four.
+    const auto kernel = blocks <= 2 * a.compute_units ? combine_kernel<16> : combine_kernel<4>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, a.part_acc, a.part_ml, a.plan,
                        a.out, a.spec.num_q_heads, a.spec.num_kv_heads, a.num_agents, a.spec.v_dim, a.max_slots,
                        a.layers_in_call, (long long)units, a.plan_signature);
     return hipGetLastError();
