@@ -37,23 +37,23 @@ CODEC_FILES = ("codec.hip", "q4_device.h", "q4kv_internal.h")
 CHUNK_FILES = ("chunk_attention.hip", "chunk_rules.h", "q4_device.h", "q4kv_internal.h")
 MEASURED_TRAFFIC = {
     "gemma12b_10agents_48layers_ragged_1k_8k_decode": {
-        "read": 4810489180, "written": 12899328, "file": "profiles/decode_attention_gemma10_ragged.md",
-        "files": DECODE_FILES, "sources": "2696fa166c24"},
+        "read": 4787400907, "written": 20898816, "file": "profiles/decode_attention_gemma10_ragged.md",
+        "files": DECODE_FILES, "sources": "045966d38e90"},
     "llama8b_5agents_32layers_4k_decode": {
-        "read": 776482287, "written": 8527872, "file": "profiles/decode_attention_llama8b_5x4k.md",
-        "files": DECODE_FILES, "sources": "2696fa166c24"},
+        "read": 768070822, "written": 8134656, "file": "profiles/decode_attention_llama8b_5x4k.md",
+        "files": DECODE_FILES, "sources": "045966d38e90"},
     "dsv2lite_mla_per_head_5agents_27layers_8k_decode": {
         "read": 3190513568, "written": 3088896, "file": "profiles/decode_attention_mla_per_head_5x8k.md",
         "files": DECODE_FILES, "sources": "2696fa166c24"},
     "dsv2lite_mla_latent_5agents_27layers_32k_decode": {
-        "read": 1444164298, "written": 52770386, "file": "profiles/mla_decode_dsv2lite_5x32k.md",
-        "files": LATENT_FILES, "sources": "13faf3a37a5c"},
+        "read": 1442866214, "written": 37927936, "file": "profiles/mla_decode_dsv2lite_5x32k.md",
+        "files": LATENT_FILES, "sources": "e49c7c33b916"},
     "quantize_4k_cache": {
         "read": 1610806417, "written": 452984832, "file": "profiles/decode_attention_gemma10_ragged.md",
-        "files": CODEC_FILES, "sources": "8a85bc6548f9"},
+        "files": CODEC_FILES, "sources": "d4c016786039"},
     "dequantize_4k_cache": {
         "read": 453043366, "written": 1610615430, "file": "profiles/decode_attention_gemma10_ragged.md",
-        "files": CODEC_FILES, "sources": "8a85bc6548f9"},
+        "files": CODEC_FILES, "sources": "d4c016786039"},
 }
 
 
