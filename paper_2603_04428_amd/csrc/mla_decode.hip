@@ -399,7 +399,8 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
             // not the exact running maximum: it moves only when a tile's maximum exceeds it by more than 7 (in log2
             // units) and then to 4 below that maximum, so the accumulators are rescaled a handful of times per unit instead of
             // in every other tile.  p <= 2^7 then, and p * s stays inside binary16 for scales up to kLiftScale; a tile with a
-            // larger one (values spread over thousands) keeps p <= 2^3, which is enough for any binary16 scale.
+            // larger one (values spread over thousands) keeps p <= 2^2.5: the widest group that can be stored, +-65504, has
+            // the scale 8736 (as bfloat16 8768), and 2^2.5 * 8768 = 49600.
             float zs = p.score_scale * kCodeScaleA;
             if (__builtin_expect(!(p.score_scale > 0.0f), 0)) { // the maximum may not be taken before the scale is applied
                 asm volatile("");
@@ -421,7 +422,7 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
 #pragma unroll
             for (int i = 0; i < 16; ++i) mt = fmaxf(mt, z[i / 4][i % 4]);
             mt = xor32_max(xor16_max(mt)) * zs;
-            const bool moved = mt > m_run + (big ? 3.0f : 7.0f); // the same in the four lanes of a head
+            const bool moved = mt > m_run + (big ? 2.5f : 7.0f); // the same in the four lanes of a head
             const float m_new = moved ? mt - (big ? 0.0f : 4.0f) : m_run;
             const float alpha = moved ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.0f;
             m_run = m_new;

@@ -163,6 +163,62 @@ def test_latent_value_scales_near_the_end_of_binary16(tokens, param_format):
     assert_close(got[..., ~wide].astype(np.float16), want[..., ~wide].astype(np.float16), "ordinary elements")
 
 
+def steered(lens, param_format, scale, bias, q, value_groups):
+    """A one-layer latent cache whose scores are given: group 8 (no part of the values) holds code 1 throughout, token t of
+    the one agent scale[t] and bias[t] there, and the only query element that is not zero is the first of that group, so that
+    every head's product with token t is q * (scale[t] + bias[t]).  value_groups: (group, scale, bias), scalars or one
+    per token, NaN where the workload's own stay.  Returns what a call and its oracle take."""
+    w = mla(47, 1, lens)
+    spec, kpool, vpool, table, table_d = gpu_cache(w, param_format=param_format)
+    ospec, okp, ovp, otable = host_cache(w, param_format=param_format)
+    to_bits = oracle.f2bf if param_format else oracle.f2h
+    n = lens[0]
+    blk, slot = otable[0, np.arange(n) // 256], np.arange(n) % 256
+    okp.codes[0, blk, 0, slot, 64:] = 0x11111111
+    for g, s, c in ((8, scale, bias),) + tuple(value_groups):
+        for arr, v in ((okp.scale, s), (okp.bias, c)):
+            v = np.broadcast_to(np.asarray(v, np.float64), (n,))
+            new = np.array([to_bits(float(x)) for x in np.nan_to_num(v)], np.uint16)
+            arr[0, blk, 0, slot, g] = np.where(np.isnan(v), arr[0, blk, 0, slot, g], new)
+    for i in range((n + 255) // 256):
+        for dev, host, t in ((kpool.codes, okp.codes, np.int32), (kpool.scale, okp.scale, np.int16), (kpool.bias, okp.bias, np.int16)):
+            dev[:, int(table[0, i])] = torch.from_numpy(np.ascontiguousarray(host[:, otable[0, i]]).view(t)).to(DEV)
+    qs = torch.zeros_like(w.q_all())
+    qs[..., 512] = q
+    return (spec, kpool, vpool, qs.to(DEV), table_d, torch.tensor(lens, dtype=torch.int32, device=DEV), n), (ospec, okp, ovp, qs.numpy(), otable, list(lens))
+
+
+def assert_steered(gpu, host, sm_scale, split_tokens, wide_groups, what):
+    """The usual tolerance, but 2^-11 of the widest value (every weight is rounded to binary16 once) on wide_groups."""
+    got = b.q4kv_batched_attention(*gpu, sm_scale, 0, split_tokens)
+    torch.cuda.synchronize()
+    got = got.cpu().numpy()
+    want = oracle.attention(*host, sm_scale)
+    wide = np.zeros(512, bool)
+    for g in wide_groups:
+        wide[64 * g:64 * g + 64] = True
+    g64, w64 = got.astype(np.float64), want.astype(np.float64)
+    assert np.isfinite(g64).all(), what
+    assert np.all(np.abs(g64 - w64)[..., wide] <= 2.0 ** -11 * 65504 + 2e-3 * np.abs(w64[..., wide])), what
+    assert_close(got[..., ~wide], want[..., ~wide], what)
+
+
+LN2 = float(np.log(2.0))   # as sm_scale: a product is a score in log2 units
+
+
+@pytest.mark.parametrize("param_format", [0, 1])
+@pytest.mark.parametrize("rise", [2.4375, 2.96875])
+def test_latent_largest_scales_under_a_maximum_that_rises(rise, param_format):
+    """The widest group that can be stored (+-65,504: scale 8,736, as bfloat16 8,768), and a maximum that rises from tile to
+    tile by as much as the kernel lets pass without moving its reference, or by more: the product of weight and
+    scale must stay inside binary16.  Four tiles of one wave."""
+    n = 256
+    tile = np.arange(n) // 64
+    bias = np.where(np.arange(n) % 2 == 0, rise * tile, 0.0)
+    gpu, host = steered((n,), param_format, 0.0, bias, 1.0, [(2, 8768.0 if param_format else 8736.0, -65280.0)])
+    assert_steered(gpu, host, LN2, 256, [2], f"rise {rise}")
+
+
 def test_config3_full_size_sampled_units():
     """Config 3 (5 agents x 32,768 tokens x 27 layers, 576/512 latent, 16 heads) at full size, all layers in one
     call with the default split, as the benchmark launches it; the oracle recomputes a seeded sample of
