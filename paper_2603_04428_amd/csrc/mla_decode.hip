@@ -324,7 +324,7 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
                 for (int i = 0; i < GV / 2; ++i) s_top = i == 0 ? s[0] : pk_max_u16(s_top, s[i]);
             }
             // wave-uniform: some value scale of the tile is too large for probabilities up to 2^7 (see the softmax)
-            const bool big = __builtin_amdgcn_ballot_w64((s_top & 0xffffu) > kLiftScaleBits || (s_top >> 16) > kLiftScaleBits) != 0ull;
+            const int parts = __builtin_amdgcn_ballot_w64((s_top & 0xffffu) > kLiftScaleBits || (s_top >> 16) > kLiftScaleBits) != 0ull ? 2 : 1;
             // the next tile starts travelling (into the buffer the previous tile was read from)
             // (behind the last tile nothing does: the wave would have to wait for it before it leaves; 3,000 to 9,000
             // tokens of five agents, eight layers, a plan, an append and a call each: 334 -> 321 us)
@@ -332,170 +332,190 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
             __builtin_amdgcn_sched_barrier(0);
             wave_lds_sync();
 
-            // ---- scores of the 64 tokens, four 16-token sets: z[j][r] is token slot_token(qk, j, r), head col, in units of
-            // 2^-24 / score_scale.  Every operand register is read again from LDS for the next set (the scales: for
-            // the next pair of sets) right after its last use: with one wave per SIMD nothing else hides the latency.
-            float z[4][4];
-            const float4_t zero = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-            const uint32_t *const k_at[2] = {cb + row_even * W + 2 * qk, cb + row_odd * W + 2 * qk};
-            const uint16_t *const bt_at[2] = {bt + row_even * BTP + ((GK > 8 && qk >= 2) ? 8 : 0),
-                                              bt + row_odd * BTP + ((GK > 8 && qk >= 2) ? 8 : 0)};
-            const uint16_t *const sc_at = sc + qk * 8;
-            uint2 kw[GK]; // code words 8g + 2qk, 8g + 2qk + 1 of this lane's row
-            uint4 s8[GK]; // scales of the tokens this lane gets results for, two sets
-            uint2 b0, b1; // bias row (slots as in qsop)
-            b0 = *reinterpret_cast<const uint2 *>(bt_at[0]);
-            b1 = *reinterpret_cast<const uint2 *>(bt_at[0] + 4);
+            // A tile with a large value scale is taken in two parts, first the even rows r of every slot, then the odd ones (see the
+            // softmax); everything that the second part reads is still in LDS.
+            float raised = 0.0f; // how far m_run lies above its place between the two
+            int part = 0;
+            do {
+                // ---- scores of the 64 tokens, four 16-token sets: z[j][r] is token slot_token(qk, j, r), head col, in units of
+                // 2^-24 / score_scale.  Every operand register is read again from LDS for the next set (the scales: for
+                // the next pair of sets) right after its last use: with one wave per SIMD nothing else hides the latency.
+                float z[4][4];
+                const float4_t zero = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+                const uint32_t *const k_at[2] = {cb + row_even * W + 2 * qk, cb + row_odd * W + 2 * qk};
+                const uint16_t *const bt_at[2] = {bt + row_even * BTP + ((GK > 8 && qk >= 2) ? 8 : 0),
+                                                  bt + row_odd * BTP + ((GK > 8 && qk >= 2) ? 8 : 0)};
+                const uint16_t *const sc_at = sc + qk * 8;
+                uint2 kw[GK]; // code words 8g + 2qk, 8g + 2qk + 1 of this lane's row
+                uint4 s8[GK]; // scales of the tokens this lane gets results for, two sets
+                uint2 b0, b1; // bias row (slots as in qsop)
+                b0 = *reinterpret_cast<const uint2 *>(bt_at[0]);
+                b1 = *reinterpret_cast<const uint2 *>(bt_at[0] + 4);
 #pragma unroll
-            for (int g = 0; g < GK; ++g) {
-                kw[g] = *reinterpret_cast<const uint2 *>(k_at[0] + 8 * g);
-                s8[g] = *reinterpret_cast<const uint4 *>(sc_at + g * 32);
-            }
-            // value side: column block c of the tile's rows, 16 tokens x 16 elements per slot, transposed by the read
-            const uint32_t *const v_at = cb + v_row * W;
-            auto load_columns = [&](int c) __attribute__((always_inline)) {
-                return __builtin_amdgcn_ds_read_tr4_b64_v2i32((lds_int2_ptr)(v_at + 2 * c));
-            };
-            constexpr int kAhead = 4;
-            int2_t vw[kAhead];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint2 c0 = b0, c1 = b1;
-                if (qk >= 2) {
-                    c1 = make_uint2(0u, 0u);
-                    if (GK <= 8) c0 = make_uint2(0u, 0u);
+                for (int g = 0; g < GK; ++g) {
+                    kw[g] = *reinterpret_cast<const uint2 *>(k_at[0] + 8 * g);
+                    s8[g] = *reinterpret_cast<const uint4 *>(sc_at + g * 32);
                 }
-                // bias term: A = b[t][.], B = group sums of q
-                float4_t sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(words_to_half8(c0.x, c0.y, c1.x, c1.y), qsop, zero, 0, 0, 0);
-                if (j < 3) {
-                    b0 = *reinterpret_cast<const uint2 *>(bt_at[(j + 1) & 1] + (j + 1) * 16 * BTP);
-                    b1 = *reinterpret_cast<const uint2 *>(bt_at[(j + 1) & 1] + (j + 1) * 16 * BTP + 4);
-                }
-                float4_t d[GK];
+                // value side: column block c of the tile's rows, 16 tokens x 16 elements per slot, transposed by the read
+                const uint32_t *const v_at = cb + v_row * W;
+                auto load_columns = [&](int c) __attribute__((always_inline)) {
+                    return __builtin_amdgcn_ds_read_tr4_b64_v2i32((lds_int2_ptr)(v_at + 2 * c));
+                };
+                constexpr int kAhead = 4;
+                int2_t vw[kAhead];
 #pragma unroll
-                for (int g = 0; g < GK + 1; ++g) {
-                    if (g < GK) {
-                        d[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(code_operand(kw[g].x), qop[g][0], zero, 0, 0, 0);
-                        d[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(code_operand(kw[g].y), qop[g][1], d[g], 0, 0, 0);
-                        if (j < 3) kw[g] = *reinterpret_cast<const uint2 *>(k_at[(j + 1) & 1] + (j + 1) * 16 * W + 8 * g);
+                for (int j = 0; j < 4; ++j) {
+                    uint2 c0 = b0, c1 = b1;
+                    if (qk >= 2) {
+                        c1 = make_uint2(0u, 0u);
+                        if (GK <= 8) c0 = make_uint2(0u, 0u);
                     }
-                    if (g == 0) {
+                    // bias term: A = b[t][.], B = group sums of q
+                    float4_t sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(words_to_half8(c0.x, c0.y, c1.x, c1.y), qsop, zero, 0, 0, 0);
+                    if (j < 3) {
+                        b0 = *reinterpret_cast<const uint2 *>(bt_at[(j + 1) & 1] + (j + 1) * 16 * BTP);
+                        b1 = *reinterpret_cast<const uint2 *>(bt_at[(j + 1) & 1] + (j + 1) * 16 * BTP + 4);
+                    }
+                    float4_t d[GK];
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) sum[r] *= 0x1p-24f; // the products' unit
-                    } else { // the results of the group before
-                        const uint32_t s4[4] = {s8[g - 1].x, s8[g - 1].y, s8[g - 1].z, s8[g - 1].w};
+                    for (int g = 0; g < GK + 1; ++g) {
+                        if (g < GK) {
+                            d[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(code_operand(kw[g].x), qop[g][0], zero, 0, 0, 0);
+                            d[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(code_operand(kw[g].y), qop[g][1], d[g], 0, 0, 0);
+                            if (j < 3) kw[g] = *reinterpret_cast<const uint2 *>(k_at[(j + 1) & 1] + (j + 1) * 16 * W + 8 * g);
+                        }
+                        if (g == 0) {
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) sum[r] = fmaf(half_of(s4[r], j & 1), d[g - 1][r], sum[r]);
-                        if (j == 1) s8[g - 1] = *reinterpret_cast<const uint4 *>(sc_at + (GK + g - 1) * 32);
-                        if (j == 3 && g <= kAhead) vw[g - 1] = load_columns(g - 1);
+                            for (int r = 0; r < 4; ++r) sum[r] *= 0x1p-24f; // the products' unit
+                        } else { // the results of the group before
+                            const uint32_t s4[4] = {s8[g - 1].x, s8[g - 1].y, s8[g - 1].z, s8[g - 1].w};
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) sum[r] = fmaf(half_of(s4[r], j & 1), d[g - 1][r], sum[r]);
+                            if (j == 1) s8[g - 1] = *reinterpret_cast<const uint4 *>(sc_at + (GK + g - 1) * 32);
+                            if (j == 3 && g <= kAhead) vw[g - 1] = load_columns(g - 1);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) z[j][r] = sum[r];
+                }
+
+                // ---- online softmax of head col over the tile.  m_run is the reference the exponentials are taken against,
+                // not the exact running maximum: it moves only when a tile's maximum exceeds it by more than 7 (in log2
+                // units) and then to 4 below that maximum, so the accumulators are rescaled a handful of times per unit instead of
+                // in every other tile.  p <= 2^7 then, and p * s stays inside binary16 for scales up to kLiftScale.  In a tile with a
+                // larger one (values spread over thousands) the even rows keep p <= 2^2.5, against the maximum itself: the widest
+                // group that can be stored, +-65504, has the scale 8736 (as bfloat16 8768), and 2^2.5 * 8768 = 49600.  The
+                // odd rows, whose p is divided by 16 below, follow with the reference 4 lower: the division costs no bits there either.
+                float zs = p.score_scale * kCodeScaleA;
+                if (__builtin_expect(!(p.score_scale > 0.0f), 0)) { // the maximum may not be taken before the scale is applied
+                    asm volatile("");
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) z[i / 4][i % 4] *= zs;
+                    zs = 1.0f;
+                }
+                if (__builtin_expect(edge, 0)) {
+                    int t0 = cur.t0;
+                    asm volatile("" : "+s"(t0)); // else the comparisons move out of the two parts' loop, into every tile
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int t = t0 + slot_token(qk, j, r);
+                            if (!(cur.reachable && t >= cur.first && t < cur.n)) z[j][r] = -INFINITY;
+                        }
+                }
+                float slack = 7.0f, below = 4.0f, m_ref = m_run;
+                if (__builtin_expect(parts > 1, 0)) {
+                    asm volatile("");
+#pragma unroll
+                    for (int i = 0; i < 16; ++i)
+                        if ((i & 1) != part) z[i / 4][i % 4] = -INFINITY;
+                    slack = part == 0 ? 2.5f : 6.5f;
+                    below = part == 0 ? 0.0f : 4.0f;
+                    m_ref -= raised;
+                }
+                float mt = -INFINITY;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) mt = fmaxf(mt, z[i / 4][i % 4]);
+                mt = xor32_max(xor16_max(mt)) * zs;
+                const bool above = mt > m_ref + slack; // the same in the four lanes of a head
+                const float m_new = above ? mt - below : m_ref;
+                const bool moved = m_new != m_run;
+                const float alpha = moved ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.0f;
+                raised = above ? 4.0f - below : 0.0f;
+                m_run = m_new;
+                float psum = 0.0f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const float pr = __builtin_amdgcn_exp2f(fmaf(z[i / 4][i % 4], zs, -m_new)); // 0 for a masked token
+                    z[i / 4][i % 4] = pr;
+                    psum += pr;
+                }
+                l_run = fmaf(l_run, alpha, psum);
+                if (!first_tile && __builtin_amdgcn_ballot_w64(moved) != 0ull) { // accumulators are zero in a unit's first tile
+                    pbacc *= alpha;
+#pragma unroll
+                    for (int c = 0; c < 4 * GV; ++c) acc[c] *= alpha;
+                }
+
+                // ---- values: per tile half, B = p * s of tokens slot_token(qk, 2 h2 + {0, 1}, r) in register r, in two binary16
+                // terms.  The product of two binary16 numbers minus its rounded value is a binary16 number again (barring
+                // underflow), so hi + lo carries p s to about 22 bits.  With hi alone an agent of a handful of tokens,
+                // where one or two rounding errors of p s make up the whole error of an output, can leave the tolerance
+                // when the latent holds channels of several times the usual magnitude.
+                // The codes of the odd rows r arrive 16 times larger (code_operand): their p is a sixteenth.  That costs
+                // no bits, because the reference lies 4 below the maximum.
+                half2_t p16[2][4];
+#pragma unroll
+                for (int h2 = 0; h2 < 2; ++h2) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) p16[h2][r] = half2_t{(half_t)z[2 * h2][r], (half_t)z[2 * h2 + 1][r]};
+                    const half8_t pop = words_to_half8(half2_to_bits(p16[h2][0]), half2_to_bits(p16[h2][1]), half2_to_bits(p16[h2][2]),
+                                                       half2_to_bits(p16[h2][3]));
+                    // bias sums of this half: rows = groups (rows past GV repeat a valid row, unused)
+                    const int g_row = (col % 8) < GV ? (col % 8) : GV - 1;
+                    const uint4 b8 = *reinterpret_cast<const uint4 *>(bg + ((h2 * GV + g_row) * 4 + qk) * 8);
+                    pbacc = __builtin_amdgcn_mfma_f32_16x16x32_f16(words_to_half8(b8.x, b8.y, b8.z, b8.w), pop, pbacc, 0, 0, 0);
+                    const half2_t sixteenth = half2_t{(half_t)0.0625f, (half_t)0.0625f};
+                    p16[h2][1] *= sixteenth;
+                    p16[h2][3] *= sixteenth;
+                }
+                half8_t ps_hi[2], ps_lo[2];
+                auto scaled = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int h2 = 0; h2 < 2; ++h2) {
+                        const uint4 sv = *reinterpret_cast<const uint4 *>(sc_at + (h2 * GK + g) * 32);
+                        const half2_t s2[4] = {bits_to_half2(sv.x), bits_to_half2(sv.y), bits_to_half2(sv.z), bits_to_half2(sv.w)};
+                        half2_t hi[4], lo[4];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            hi[r] = p16[h2][r] * s2[r];
+                            lo[r] = __builtin_elementwise_fma(p16[h2][r], s2[r], -hi[r]);
+                        }
+                        ps_hi[h2] = words_to_half8(half2_to_bits(hi[0]), half2_to_bits(hi[1]), half2_to_bits(hi[2]), half2_to_bits(hi[3]));
+                        ps_lo[h2] = words_to_half8(half2_to_bits(lo[0]), half2_to_bits(lo[1]), half2_to_bits(lo[2]), half2_to_bits(lo[3]));
+                    }
+                };
+                half8_t cop[2] = {code_operand((uint32_t)vw[0].x), code_operand((uint32_t)vw[0].y)};
+#pragma unroll
+                for (int c = 0; c < 4 * GV; ++c) {
+                    if (c % 4 == 0) scaled(c / 4);
+                    if (c + kAhead < 4 * GV) vw[c % kAhead] = load_columns(c + kAhead);
+                    const half8_t a0 = cop[0], a1 = cop[1];
+                    acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, ps_hi[0], acc[c], 0, 0, 0);
+                    acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, ps_lo[0], acc[c], 0, 0, 0);
+                    acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, ps_hi[1], acc[c], 0, 0, 0);
+                    acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, ps_lo[1], acc[c], 0, 0, 0);
+                    if (c + 1 < 4 * GV) { // the next block's operands, while this one is multiplied
+                        cop[0] = code_operand((uint32_t)vw[(c + 1) % kAhead].x);
+                        cop[1] = code_operand((uint32_t)vw[(c + 1) % kAhead].y);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) z[j][r] = sum[r];
-            }
-
-            // ---- online softmax of head col over the tile.  m_run is the reference the exponentials are taken against,
-            // not the exact running maximum: it moves only when a tile's maximum exceeds it by more than 7 (in log2
-            // units) and then to 4 below that maximum, so the accumulators are rescaled a handful of times per unit instead of
-            // in every other tile.  p <= 2^7 then, and p * s stays inside binary16 for scales up to kLiftScale; a tile with a
-            // larger one (values spread over thousands) keeps p <= 2^2.5: the widest group that can be stored, +-65504, has
-            // the scale 8736 (as bfloat16 8768), and 2^2.5 * 8768 = 49600.
-            float zs = p.score_scale * kCodeScaleA;
-            if (__builtin_expect(!(p.score_scale > 0.0f), 0)) { // the maximum may not be taken before the scale is applied
-                asm volatile("");
-#pragma unroll
-                for (int i = 0; i < 16; ++i) z[i / 4][i % 4] *= zs;
-                zs = 1.0f;
-            }
-            if (__builtin_expect(edge, 0)) {
-                asm volatile("");
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int t = cur.t0 + slot_token(qk, j, r);
-                        if (!(cur.reachable && t >= cur.first && t < cur.n)) z[j][r] = -INFINITY;
-                    }
-            }
-            float mt = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) mt = fmaxf(mt, z[i / 4][i % 4]);
-            mt = xor32_max(xor16_max(mt)) * zs;
-            const bool moved = mt > m_run + (big ? 2.5f : 7.0f); // the same in the four lanes of a head
-            const float m_new = moved ? mt - (big ? 0.0f : 4.0f) : m_run;
-            const float alpha = moved ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.0f;
-            m_run = m_new;
-            float psum = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float pr = __builtin_amdgcn_exp2f(fmaf(z[i / 4][i % 4], zs, -m_new)); // 0 for a masked token
-                z[i / 4][i % 4] = pr;
-                psum += pr;
-            }
-            l_run = fmaf(l_run, alpha, psum);
-            if (!first_tile && __builtin_amdgcn_ballot_w64(moved) != 0ull) { // accumulators are zero in a unit's first tile
-                pbacc *= alpha;
-#pragma unroll
-                for (int c = 0; c < 4 * GV; ++c) acc[c] *= alpha;
-            }
-
-            // ---- values: per tile half, B = p * s of tokens slot_token(qk, 2 h2 + {0, 1}, r) in register r, in two binary16
-            // terms.  The product of two binary16 numbers minus its rounded value is a binary16 number again (barring
-            // underflow), so hi + lo carries p s to about 22 bits.  With hi alone an agent of a handful of tokens,
-            // where one or two rounding errors of p s make up the whole error of an output, can leave the tolerance
-            // when the latent holds channels of several times the usual magnitude.
-            // The codes of the odd rows r arrive 16 times larger (code_operand): their p is a sixteenth.  That costs
-            // no bits, because the reference lies 4 below the maximum.
-            half2_t p16[2][4];
-#pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) p16[h2][r] = half2_t{(half_t)z[2 * h2][r], (half_t)z[2 * h2 + 1][r]};
-                const half8_t pop = words_to_half8(half2_to_bits(p16[h2][0]), half2_to_bits(p16[h2][1]), half2_to_bits(p16[h2][2]),
-                                                   half2_to_bits(p16[h2][3]));
-                // bias sums of this half: rows = groups (rows past GV repeat a valid row, unused)
-                const int g_row = (col % 8) < GV ? (col % 8) : GV - 1;
-                const uint4 b8 = *reinterpret_cast<const uint4 *>(bg + ((h2 * GV + g_row) * 4 + qk) * 8);
-                pbacc = __builtin_amdgcn_mfma_f32_16x16x32_f16(words_to_half8(b8.x, b8.y, b8.z, b8.w), pop, pbacc, 0, 0, 0);
-                const half2_t sixteenth = half2_t{(half_t)0.0625f, (half_t)0.0625f};
-                p16[h2][1] *= sixteenth;
-                p16[h2][3] *= sixteenth;
-            }
-            half8_t ps_hi[2], ps_lo[2];
-            auto scaled = [&](int g) __attribute__((always_inline)) {
-#pragma unroll
-                for (int h2 = 0; h2 < 2; ++h2) {
-                    const uint4 sv = *reinterpret_cast<const uint4 *>(sc_at + (h2 * GK + g) * 32);
-                    const half2_t s2[4] = {bits_to_half2(sv.x), bits_to_half2(sv.y), bits_to_half2(sv.z), bits_to_half2(sv.w)};
-                    half2_t hi[4], lo[4];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        hi[r] = p16[h2][r] * s2[r];
-                        lo[r] = __builtin_elementwise_fma(p16[h2][r], s2[r], -hi[r]);
-                    }
-                    ps_hi[h2] = words_to_half8(half2_to_bits(hi[0]), half2_to_bits(hi[1]), half2_to_bits(hi[2]), half2_to_bits(hi[3]));
-                    ps_lo[h2] = words_to_half8(half2_to_bits(lo[0]), half2_to_bits(lo[1]), half2_to_bits(lo[2]), half2_to_bits(lo[3]));
-                }
-            };
-            half8_t cop[2] = {code_operand((uint32_t)vw[0].x), code_operand((uint32_t)vw[0].y)};
-#pragma unroll
-            for (int c = 0; c < 4 * GV; ++c) {
-                if (c % 4 == 0) scaled(c / 4);
-                if (c + kAhead < 4 * GV) vw[c % kAhead] = load_columns(c + kAhead);
-                const half8_t a0 = cop[0], a1 = cop[1];
-                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, ps_hi[0], acc[c], 0, 0, 0);
-                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, ps_lo[0], acc[c], 0, 0, 0);
-                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, ps_hi[1], acc[c], 0, 0, 0);
-                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, ps_lo[1], acc[c], 0, 0, 0);
-                if (c + 1 < 4 * GV) { // the next block's operands, while this one is multiplied
-                    cop[0] = code_operand((uint32_t)vw[(c + 1) % kAhead].x);
-                    cop[1] = code_operand((uint32_t)vw[(c + 1) % kAhead].y);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            wave_lds_sync(); // the next tile rewrites sc / bg / bt
-            first_tile = false;
+                wave_lds_sync(); // the next tile rewrites sc / bg / bt
+                first_tile = false;
+            } while (__builtin_expect(++part < parts, 0));
             cur = nxt;
             buf ^= 1;
             ++x;

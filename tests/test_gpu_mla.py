@@ -219,6 +219,22 @@ def test_latent_largest_scales_under_a_maximum_that_rises(rise, param_format):
     assert_steered(gpu, host, LN2, 256, [2], f"rise {rise}")
 
 
+@pytest.mark.parametrize("param_format", [0, 1])
+@pytest.mark.parametrize("wide_tiles", ["first", "all", "odd", "even"])
+def test_latent_small_weights_beside_wide_values(wide_tiles, param_format):
+    """One token of weight 1 and 2,048 of weight 2^-13.5 in odd places carry the result together, and group 2 is wide in some
+    or all tiles: the small weights keep the bits of a binary16 number (weights of 2^-17.5 would be off by 0.5 %, three times
+    the tolerance).  All tiles are one wave's; alternating ones must not move the reference for good."""
+    n = 4096
+    t = np.arange(n)
+    bias = np.where(t == 0, 0.0, np.where(t % 2 == 1, -13.5, -30.0))
+    wide = {"first": t < 64, "all": t >= 0, "odd": t // 64 % 2 == 1, "even": t // 64 % 2 == 0}[wide_tiles]
+    odd = np.where(t == 0, 0.0, np.where(t % 2 == 1, 4.0, np.nan))
+    gpu, host = steered((n,), param_format, 0.0, bias, 1.0,
+                        [(0, odd, np.where(np.isnan(odd), np.nan, 0.0)), (2, np.where(wide, 1000.0, np.nan), np.where(wide, -7500.0, np.nan))])
+    assert_steered(gpu, host, LN2, n, [2], f"wide tiles: {wide_tiles}")
+
+
 def test_config3_full_size_sampled_units():
     """Config 3 (5 agents x 32,768 tokens x 27 layers, 576/512 latent, 16 heads) at full size, all layers in one
     call with the default split, as the benchmark launches it; the oracle recomputes a seeded sample of
