@@ -48,7 +48,7 @@ constexpr int kWaves = kThreads / kWave;
 constexpr int kHeads = 16;          // query heads per latent head: the M (or N) extent of the matrix tiles
 constexpr float kNegBig = -1.0e30f; // "minus infinity" that survives subtraction
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr uint32_t kLiftScaleBits = 0x5FE0; // binary16 504: 2^7 times that is still below 65504
+constexpr uint32_t kLiftScaleBits = 0x5BE0; // binary16 252: 2^8 times that is still below 65504
 
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 typedef const __attribute__((address_space(1))) void *global_ptr_t;
@@ -403,7 +403,9 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
                 // ---- online softmax of head col over the tile.  m_run is the reference the exponentials are taken against,
                 // not the exact running maximum: it moves only when a tile's maximum exceeds it by more than 7 (in log2
                 // units) and then to 4 below that maximum, so the accumulators are rescaled a handful of times per unit instead of
-                // in every other tile.  p <= 2^7 then, and p * s stays inside binary16 for scales up to kLiftScale.  In a tile with a
+                // in every other tile.  p <= 2^7 then, and p * s stays inside binary16 for scales up to kLiftScale with one binary
+                // place to spare: the maximum is rounded once more than the exponents are, and from 2^18 on that is a few per
+                // cent of p (at 2^19, with the line at 504, 130.25 * 504 was infinite).  In a tile with a
                 // larger one (values spread over thousands) the even rows keep p <= 2^2.5, against the maximum itself: the widest
                 // group that can be stored, +-65504, has the scale 8736 (as bfloat16 8768), and 2^2.5 * 8768 = 49600.  The
                 // odd rows, whose p is divided by 16 below, follow with the reference 4 lower: the division costs no bits there either.

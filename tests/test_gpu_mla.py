@@ -235,6 +235,18 @@ def test_latent_small_weights_beside_wide_values(wide_tiles, param_format):
     assert_steered(gpu, host, LN2, n, [2], f"wide tiles: {wide_tiles}")
 
 
+@pytest.mark.parametrize("param_format", [0, 1])
+@pytest.mark.parametrize("sm_scale,rise", [(0.932101309299469, 2.25), (0.9075980186462402, 2.3125), (0.7001401782035828, 3.0)])
+def test_latent_scores_so_large_that_their_spacing_counts(sm_scale, rise, param_format):
+    """Scores around 2^19, where binary32 numbers are 1/16 apart: a weight may exceed the one that the rounded maximum stands
+    for by a few per cent, which the bound on weight times scale has to leave room for (scale 504 was the last one that took
+    weights up to 2^7: 130.25 * 504 is past binary16)."""
+    n = 128
+    up = np.arange(n) == 64
+    gpu, host = steered((n,), param_format, np.where(up, rise / 64, 0.0), 8192.0, 64.0, [(2, 504.0, -3780.0)])
+    assert_steered(gpu, host, sm_scale, 256, [2], f"sm_scale {sm_scale}")
+
+
 def test_config3_full_size_sampled_units():
     """Config 3 (5 agents x 32,768 tokens x 27 layers, 576/512 latent, 16 heads) at full size, all layers in one
     call with the default split, as the benchmark launches it; the oracle recomputes a seeded sample of
