@@ -143,7 +143,9 @@ int q4kv_append(const q4kv_spec *spec, const q4kv_pool *k, const q4kv_pool *v, c
  *                per query head.  Must equal the value given to q4kv_attention_workspace_bytes.  With 0 the share may
  *                become smaller than q4kv_default_split_tokens says where the lengths are far below max_seq_len.
  *   workspace    device scratch of at least q4kv_attention_workspace_bytes(...) bytes, 16-byte aligned;
- *                contents before and after the call are unspecified.  With q_len > 1 it is optional: a call whose
+ *                contents before and after the call are unspecified.  (Of the size told for split_tokens == 0 a call on a
+ *                shared latent needs only the part that it is told for q4kv_default_split_tokens, and deals out coarser
+ *                ranges with less than the whole: a workspace sized for a larger batch serves the smaller ones.)  With q_len > 1 it is optional: a call whose
  *                workspace_bytes is exactly what q4kv_attention_workspace_bytes says may use it to spread few or ragged
  *                agents over the whole chip.  Its contents (a decode plan, say) are then lost, and calls that overlap in
  *                time need one each.  With any other workspace_bytes (a decode call's workspace) or NULL the call
@@ -187,7 +189,8 @@ int q4kv_batched_attention_windows(const q4kv_spec *spec, const q4kv_pool *k, co
  * lengths the plan was made from.  A workspace may be used for any number of planned calls on one stream, one after
  * the other; when the lengths change (every decode step), or another call has used the workspace, plan again (a call
  * with q_len > 1 uses one of its own size only, see `workspace` above).  A workspace prepared for other arguments
- * makes the planned call do nothing (it is detected on the device; `out` is left as it was).  Shapes, workspace size,
+ * makes the planned call do nothing (it is detected on the device; `out` is left as it was); so does a plan for a shared
+ * latent that was given the whole size told for split_tokens == 0 when the planned call is given less.  Shapes, workspace size,
  * error codes and results (bit-identical to q4kv_batched_attention with the same arguments) as described there. */
 int q4kv_decode_plan(const q4kv_spec *spec, const int32_t *seq_len, int32_t num_agents, int32_t max_seq_len,
                      int32_t window, int32_t split_tokens, int32_t num_layers_in_call, void *workspace,

@@ -111,11 +111,8 @@ int floor_tokens(const q4kv_spec &s, int split_given, int split_used)
 // Partial records reserved per (layer, agent, query head): the most workers that can meet in one unit.  A worker's
 // range is at least split_tokens long.  The GQA kernel's workers are workgroups, except that from a certain range
 // length on (decode_solo_quarter_tiles() * 4) every wave takes a quarter of its workgroup's range and writes a record
-// of its own.  The shared-latent kernel's workers are waves, and a tile takes one of them as long as a short call's start: with
-// a floor of the library's order records are reserved down to ranges of a tile as far as 12 MB go (a call of many layers
-// gains nothing and gets none; the static scratch holds 16 MB).
-constexpr int64_t kFineRecordBytes = 12 << 20;
-int slots_per_unit(const q4kv_spec &s, int num_agents, int layers, int max_seq_len, int split_tokens)
+// of its own.
+int slots_per_unit(const q4kv_spec &s, int max_seq_len, int split_tokens)
 {
     const int tiles = (max_seq_len + 63) / 64, min_per = split_tokens / 64;
     int slots = (tiles + min_per - 1) / min_per + 1;
@@ -124,10 +121,6 @@ int slots_per_unit(const q4kv_spec &s, int num_agents, int layers, int max_seq_l
         if (quarter < q4kv::decode_solo_quarter_tiles()) quarter = q4kv::decode_solo_quarter_tiles();
         const int solo = (tiles + quarter - 1) / quarter + 1;
         if (solo > slots) slots = solo;
-    } else if (split_tokens <= 512) {
-        const int64_t fit = kFineRecordBytes / std::max<int64_t>((int64_t)num_agents * layers * s.num_q_heads * (s.v_dim + 2) * 4, 1);
-        const int fine = (int)(fit < tiles + 1 ? fit : tiles + 1);
-        if (fine > slots) slots = fine;
     }
     return slots;
 }
@@ -154,6 +147,39 @@ int plan_signature(const q4kv_spec &s, int num_agents, int max_seq_len, int laye
 size_t arrival_bytes(const q4kv_spec &s, int num_agents, int layers)
 {
     return ((size_t)layers * s.num_kv_heads * num_agents * sizeof(int32_t) + 255) / 256 * 256;
+}
+
+// How a decode call's workspace is laid out: plan, arrival counters, records.
+//
+// A call needs `least` bytes.  The shared-latent kernel's workers are waves, and a tile takes one of them as long as a short
+// call's start: in a workspace of `fine` bytes a call whose floor is the library's choice keeps records down to ranges of
+// a tile (fine_slots of them per unit; 0: no more than it has anyway), as far as 12 MB go (a call of many layers gains
+// nothing and gets none; the static scratch holds 16 MB).  `wanted` is what callers are told.  It does not fall as agents,
+// layers or max_seq_len grow, up to those 12 MB, so that a workspace for the largest batch keeps fine records for every
+// smaller one; one that was sized for another call and has less than `fine` serves with the ranges of the default split.
+constexpr int64_t kFineRecordBytes = 12 << 20;
+struct DecodeLayout {
+    size_t records; // offset of the partial records
+    int slots, fine_slots;
+    size_t least, fine, wanted;
+};
+DecodeLayout decode_layout(const q4kv_spec &s, int num_agents, int layers, int max_seq_len, int split_tokens)
+{
+    const int64_t unit_bytes = (int64_t)layers * num_agents * s.num_q_heads * (s.v_dim + 2) * (int64_t)sizeof(float); // a record of each
+    DecodeLayout d;
+    d.records = plan_bytes(num_agents, layers) + arrival_bytes(s, num_agents, layers);
+    d.slots = slots_per_unit(s, max_seq_len, split_tokens);
+    d.least = d.wanted = d.fine = d.records + (size_t)(unit_bytes * d.slots);
+    d.fine_slots = 0;
+    if (q4kv::mla_decode_supported(s)) {
+        const int64_t bytes = std::min(unit_bytes * (((int64_t)max_seq_len + 63) / 64 + 1), kFineRecordBytes);
+        d.wanted = std::max(d.least, d.records + (size_t)bytes);
+        if (bytes / unit_bytes > d.slots) {
+            d.fine_slots = (int)(bytes / unit_bytes);
+            d.fine = d.records + (size_t)(unit_bytes * d.fine_slots);
+        }
+    }
+    return d;
 }
 
 } // namespace
@@ -272,10 +298,8 @@ size_t q4kv_attention_workspace_bytes(const q4kv_spec *spec, int32_t num_agents,
         return q4kv::chunk_workspace_bytes(*spec, num_agents, q_len, max_seq_len, num_layers_in_call, compute_units(), acc_bytes);
     }
     const int st = split_tokens ? split_tokens : pick_split_tokens(*spec, num_agents, max_seq_len, num_layers_in_call);
-    const int64_t slots = slots_per_unit(*spec, num_agents, num_layers_in_call, max_seq_len, st);
-    const int64_t units = (int64_t)num_layers_in_call * num_agents * q_len * spec->num_q_heads;
-    return plan_bytes(num_agents, num_layers_in_call) + arrival_bytes(*spec, num_agents, num_layers_in_call) +
-           (size_t)(units * slots * (spec->v_dim + 2) * (int64_t)sizeof(float));
+    const DecodeLayout d = decode_layout(*spec, num_agents, num_layers_in_call, max_seq_len, st);
+    return split_tokens ? d.least : d.wanted;
 }
 
 // planned: the workspace already holds the plan of q4kv_decode_plan for these arguments (seq_len is then not needed)
@@ -325,7 +349,6 @@ static int attention_common(const q4kv_spec *spec, const q4kv_pool *k, const q4k
     a.layer_window = layer_window;
     a.split_tokens = split_tokens ? split_tokens : pick_split_tokens(*spec, num_agents, max_seq_len, layers);
     a.floor_tokens = floor_tokens(*spec, split_tokens, a.split_tokens);
-    a.max_slots = slots_per_unit(*spec, num_agents, layers, max_seq_len, a.split_tokens);
     a.grid_workgroups = attention_workgroups(*spec);
     a.compute_units = compute_units();
     a.layer_begin = layer_begin;
@@ -357,17 +380,26 @@ static int attention_common(const q4kv_spec *spec, const q4kv_pool *k, const q4k
         return fail(Q4KV_ESHAPE, "no decode kernel for k_dim=%d v_dim=%d n_rep=%d alias=%d", spec->k_dim, spec->v_dim,
                     spec->num_q_heads / spec->num_kv_heads, spec->v_aliases_k);
 
-    const size_t need = q4kv_attention_workspace_bytes(spec, num_agents, q_len, max_seq_len, a.split_tokens, layers);
-    if (!workspace || workspace_bytes < need || !aligned16(workspace))
-        return fail(Q4KV_EWORKSPACE, "workspace needs %zu bytes (16-byte aligned), got %zu", need, workspace_bytes);
-    const int64_t units = (int64_t)layers * num_agents * q_len * spec->num_q_heads;
+    const DecodeLayout d = decode_layout(*spec, num_agents, layers, max_seq_len, a.split_tokens);
+    if (!workspace || workspace_bytes < d.least || !aligned16(workspace))
+        return fail(Q4KV_EWORKSPACE, "workspace needs %zu bytes (16-byte aligned), got %zu", d.least, workspace_bytes);
+    const int64_t units = (int64_t)layers * num_agents * spec->num_q_heads;
+    const int fine_slots = workspace_bytes >= d.fine ? d.fine_slots : 0;
     a.plan = static_cast<int32_t *>(workspace);
     a.arrivals = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + plan_bytes(num_agents, layers));
-    a.part_acc = reinterpret_cast<float *>(static_cast<char *>(workspace) + plan_bytes(num_agents, layers) +
-                                           arrival_bytes(*spec, num_agents, layers));
-    a.part_ml = a.part_acc + units * a.max_slots * spec->v_dim;
+    a.part_acc = reinterpret_cast<float *>(static_cast<char *>(workspace) + d.records);
     a.plan_signature = plan_signature(*spec, num_agents, max_seq_len, layers, a.split_tokens, layer_window ? -1 : window,
                                       a.grid_workgroups);
+    a.max_slots = d.slots;
+    a.fine_slots = 0;
+    if (planned) {
+        a.fine_slots = fine_slots; // the plan says which of the two it was made for
+    } else if (fine_slots > 0 && split_tokens == 0) {
+        a.max_slots = fine_slots;
+        a.plan_signature ^= q4kv::kFineRecords;
+    }
+    a.part_ml = a.part_acc + units * a.max_slots * spec->v_dim;
+    a.fine_ml = a.part_acc + units * a.fine_slots * spec->v_dim;
 
     hipError_t e = hipSuccess;
     if (!planned) e = mla ? q4kv::launch_mla_decode_plan(a, st) : q4kv::launch_decode_plan(a, st);
@@ -431,8 +463,9 @@ int q4kv_batched_attention_static(const q4kv_spec *spec, const q4kv_pool *k, con
     // the size first, from host arithmetic alone: a call that does not fit launches nothing and touches no device state
     if (spec && num_agents > 0 && q_len == 1 && max_seq_len >= 0 && layer_end > layer_begin && split_tokens >= 0 &&
         split_tokens % 256 == 0 && check_spec(spec) == Q4KV_OK) {
-        const size_t need =
-            q4kv_attention_workspace_bytes(spec, num_agents, q_len, max_seq_len, split_tokens, layer_end - layer_begin);
+        const int layers = layer_end - layer_begin;
+        const size_t need = decode_layout(*spec, num_agents, layers, max_seq_len,
+                                          split_tokens ? split_tokens : pick_split_tokens(*spec, num_agents, max_seq_len, layers)).least;
         if (need > (size_t)Q4KV_STATIC_SCRATCH_BYTES)
             return fail(Q4KV_EWORKSPACE,
                         "the call needs %zu bytes of workspace, the static scratch array holds %u: pass fewer layers "
@@ -472,16 +505,20 @@ int q4kv_decode_plan(const q4kv_spec *spec, const int32_t *seq_len, int32_t num_
     a.layer_window = nullptr;
     a.split_tokens = split_tokens ? split_tokens : pick_split_tokens(*spec, num_agents, max_seq_len, num_layers_in_call);
     a.floor_tokens = floor_tokens(*spec, split_tokens, a.split_tokens);
-    a.max_slots = slots_per_unit(*spec, num_agents, num_layers_in_call, max_seq_len, a.split_tokens);
     a.grid_workgroups = attention_workgroups(*spec);
     a.layers_in_call = num_layers_in_call;
-    const size_t need = q4kv_attention_workspace_bytes(spec, num_agents, 1, max_seq_len, a.split_tokens, num_layers_in_call);
-    if (!workspace || workspace_bytes < need || !aligned16(workspace))
-        return fail(Q4KV_EWORKSPACE, "workspace needs %zu bytes (16-byte aligned), got %zu", need, workspace_bytes);
+    const DecodeLayout d = decode_layout(*spec, num_agents, num_layers_in_call, max_seq_len, a.split_tokens);
+    if (!workspace || workspace_bytes < d.least || !aligned16(workspace))
+        return fail(Q4KV_EWORKSPACE, "workspace needs %zu bytes (16-byte aligned), got %zu", d.least, workspace_bytes);
     a.plan = static_cast<int32_t *>(workspace);
     a.arrivals = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + plan_bytes(num_agents, num_layers_in_call));
     a.plan_signature = plan_signature(*spec, num_agents, max_seq_len, num_layers_in_call, a.split_tokens, window,
                                       a.grid_workgroups);
+    a.max_slots = d.slots;
+    if (split_tokens == 0 && d.fine_slots > 0 && workspace_bytes >= d.fine) {
+        a.max_slots = d.fine_slots;
+        a.plan_signature ^= q4kv::kFineRecords;
+    }
     hipStream_t st = (hipStream_t)hip_stream;
     const hipError_t e = mla ? q4kv::launch_mla_decode_plan(a, st) : q4kv::launch_decode_plan(a, st);
     return e == hipSuccess ? Q4KV_OK : fail(Q4KV_EHIP, "plan launch: %s", hipGetErrorString(e));

@@ -53,13 +53,25 @@ constexpr uint32_t kLiftScaleBits = 0x5BE0; // binary16 252: 2^8 times that is s
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 typedef const __attribute__((address_space(1))) void *global_ptr_t;
 
+// The records of a call: maxima and denominators, number per unit.  A planned call brings a second pair, for a plan made in a
+// workspace with room for more records (slots 0: this one has not); which of them holds stands in the plan's signature.
+struct Records {
+    float *ml;
+    int slots;
+};
+__device__ __forceinline__ bool fine_plan(const int32_t *plan, int signature, const Records &fine)
+{
+    return fine.slots > 0 && plan[5] == (signature ^ kFineRecords);
+}
+
 struct MlaParams {
     const uint32_t *codes;
     const uint16_t *scale, *bias;
     const uint16_t *q;
     StreamParams stream;
-    float *part_acc, *part_ml;
-    int q_heads, max_slots;
+    float *part_acc;
+    Records records, fine;
+    int q_heads;
     float score_scale; // sm_scale * log2(e): scores are kept in log2 units
 };
 
@@ -153,7 +165,10 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
     const int wave = uniform(tid / kWave);
     const int gw = blockIdx.x * kWaves + wave; // this wave's index in the launch
 
-    const TileStream ts(p.stream);
+    const bool fine = fine_plan(p.stream.plan, p.stream.plan_signature, p.fine);
+    StreamParams sp = p.stream;
+    if (fine) sp.plan_signature ^= kFineRecords;
+    const TileStream ts(sp);
     const int per = ts.per, N = ts.N;
     const long long x_begin = (long long)gw * per;
     if (x_begin >= N) return;
@@ -535,7 +550,7 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
             pb[r] = odd ? other : pbacc[r];
             pb[4 + r] = odd ? pbacc[r] : other;
         }
-        const int64_t rec = (unit0 + col) * p.max_slots + slot;
+        const int64_t rec = (unit0 + col) * (fine ? p.fine.slots : p.records.slots) + slot;
         float *dst = p.part_acc + rec * DV + 4 * qk;
 #pragma unroll
         for (int c = 0; c < 4 * GV; ++c) {
@@ -545,8 +560,9 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
             *reinterpret_cast<float4_t *>(dst + 16 * c) = o;
         }
         if (qk == 0) {
-            p.part_ml[rec * 2] = m_run;
-            p.part_ml[rec * 2 + 1] = l_tot;
+            float *ml = (fine ? p.fine.ml : p.records.ml) + rec * 2;
+            ml[0] = m_run;
+            ml[1] = l_tot;
         }
     }
 }
@@ -556,12 +572,14 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
 // B: records whose loads are issued together.
 template <int B>
 __global__ __launch_bounds__(kThreads) void combine_kernel(const float *__restrict__ part_acc,
-                                                           const float *__restrict__ part_ml,
+                                                           const Records records, const Records fine,
                                                            const int32_t *__restrict__ plan, uint16_t *__restrict__ out,
                                                            int q_heads, int kv_heads, int num_agents, int v_dim,
-                                                           int max_slots, int layers, long long units, int signature)
+                                                           int layers, long long units, int signature)
 {
-    if (plan[5] != signature) return; // a plan made for other arguments: the attention launch did nothing either
+    const bool is_fine = fine_plan(plan, signature, fine);
+    if (!is_fine && plan[5] != signature) return; // a plan made for other arguments: the attention launch did nothing either
+    const int max_slots = is_fine ? fine.slots : records.slots;
     const int threads_per_unit = v_dim / 4;
     const long long unit = (long long)blockIdx.x * (kThreads / threads_per_unit) + threadIdx.x / threads_per_unit;
     if (unit >= units) return; // (layer in call, agent, query head)
@@ -583,7 +601,7 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const float *__restri
         const long long u0 = (long long)plan[pv.lt_off() + li] + (long long)kvh * pv.tiles_per_head(cb) + tpre[agent];
         slots = (int)((u0 + tiles - 1) / per - u0 / per) + 1;
     }
-    const float *ml = part_ml + unit * max_slots * 2;
+    const float *ml = (is_fine ? fine.ml : records.ml) + unit * max_slots * 2;
     const float *acc = part_acc + unit * max_slots * v_dim + e;
     // B slots at a time: every load of a group is issued before anything is computed, so a unit costs one memory round trip per
     // group.  Past the last slot a group reads that slot again and gives it no weight.  The running reference moves group by
@@ -636,9 +654,9 @@ hipError_t launch_combine(const AttentionArgs &a, hipStream_t stream)
     // a hundred records: sixteen of them a trip (one layer, five agents of 32K tokens, a call 55.2 -> 48.1 us).  With more, the
     // memory is busy and a unit has about nine records: four.
     const auto kernel = blocks <= 2 * a.compute_units ? combine_kernel<16> : combine_kernel<4>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, a.part_acc, a.part_ml, a.plan,
-                       a.out, a.spec.num_q_heads, a.spec.num_kv_heads, a.num_agents, a.spec.v_dim, a.max_slots,
-                       a.layers_in_call, (long long)units, a.plan_signature);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, a.part_acc, Records{a.part_ml, a.max_slots},
+                       Records{a.fine_ml, a.fine_slots}, a.plan, a.out, a.spec.num_q_heads, a.spec.num_kv_heads, a.num_agents,
+                       a.spec.v_dim, a.layers_in_call, (long long)units, a.plan_signature);
     return hipGetLastError();
 }
 
@@ -649,9 +667,10 @@ hipError_t launch_mla_t(const AttentionArgs &a, hipStream_t stream)
     p.codes = a.k.codes; p.scale = a.k.scale; p.bias = a.k.bias;
     p.q = a.q;
     p.stream = stream_params(a);
-    p.part_acc = a.part_acc; p.part_ml = a.part_ml;
+    p.part_acc = a.part_acc;
+    p.records = Records{a.part_ml, a.max_slots};
+    p.fine = Records{a.fine_ml, a.fine_slots};
     p.q_heads = a.spec.num_q_heads;
-    p.max_slots = a.max_slots;
     p.score_scale = a.sm_scale * kLog2e;
     hipLaunchKernelGGL((mla_decode_kernel<GK, GV, BF>), dim3(a.grid_workgroups), dim3(kThreads), 0, stream, p);
     return hipGetLastError();

@@ -19,6 +19,8 @@ hipError_t launch_append(const q4kv_spec &spec, const q4kv_pool &k, const q4kv_p
                          const int32_t *seq_len_before, int num_agents, int chunk_len, int layer_begin, int layer_end,
                          int compute_units, hipStream_t stream);
 
+constexpr int kFineRecords = 2; // bit that is turned round in the signature of a plan made for more records (csrc/api.hip)
+
 struct AttentionArgs {
     q4kv_spec spec;
     q4kv_pool k, v;             // v == k when the V rows alias the K rows
@@ -37,6 +39,8 @@ struct AttentionArgs {
     int32_t *plan;              // workspace: tile plan written by the plan kernel
     float *part_acc;            // workspace: [units][max_slots][v_dim]
     float *part_ml;             // workspace: [units][max_slots][2]  (running max in log2 units, denominator)
+    int fine_slots;             // planned shared-latent call: max_slots if the plan's signature says kFineRecords (0: it may not)
+    float *fine_ml;             // and its part_ml
     int32_t *arrivals;          // workspace: [layers_in_call][kv_heads][num_agents] waves that have left a unit
     int compute_units;          // of the device
     int chunk_workers;          // q_len > 1: workgroups that share all tiles evenly (part_acc, part_ml: two records each); 0: none

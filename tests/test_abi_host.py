@@ -174,6 +174,25 @@ def test_workspace_and_split_queries():
     assert b.q4kv_attention_workspace_bytes(gemma, 10, 1, 8192, 100, 48) == 0   # not a multiple of 256
 
 
+def test_latent_workspace_for_a_batch_serves_its_parts():
+    """The size asked for does not fall as agents, layers or the bound of the lengths grow while the default split stays what it is,
+    so that a workspace allocated for the largest call holds the smaller ones; and a call with a split of its own asks for that
+    split's records only."""
+    spec = b.make_spec(27, 16, 1, 576, 512, True)
+    layers, bounds = (1, 2, 3, 8, 27), (64, 1000, 1024, 2048, 4096, 8192, 32768)
+    calls = [(a, l, m) for m in bounds for l in layers for a in range(1, 33)]
+    size = {c: b.q4kv_attention_workspace_bytes(spec, c[0], 1, c[2], 0, c[1]) for c in calls}
+    split = {c: b.q4kv_default_split_tokens(spec, c[0], 1, c[2], c[1]) for c in calls}
+    for a, l, m in calls:
+        smaller = [(a - 1, l, m)] + [(a, k, m) for k in layers if k < l] + [(a, l, k) for k in bounds if k < m]
+        assert all(size[c] <= size[a, l, m] for c in smaller if c in size and split[c] == split[a, l, m])
+        assert size[a, l, m] >= b.q4kv_attention_workspace_bytes(spec, a, 1, m, split[a, l, m], l)
+    for a, m, split in ((1, 8192, 256), (4, 8192, 256), (4, 8192, 512), (5, 32768, 256), (20, 32768, 512)):
+        plan = ((6 + 2 + 1 + 2 * a + 2 + 2 * a) * 4 + 255) // 256 * 256 + (a * 4 + 255) // 256 * 256
+        slots = -(-(m // 64) // (split // 64)) + 1
+        assert b.q4kv_attention_workspace_bytes(spec, a, 1, m, split, 1) == plan + a * 16 * slots * (512 + 2) * 4
+
+
 def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(b, "_lib", None)
     monkeypatch.setattr(b, "LIB_PATH", "/nonexistent/libq4kv.so")

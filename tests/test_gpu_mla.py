@@ -247,6 +247,48 @@ def test_latent_scores_so_large_that_their_spacing_counts(sm_scale, rise, param_
     assert_steered(gpu, host, sm_scale, 256, [2], f"sm_scale {sm_scale}")
 
 
+def test_latent_workspace_sized_for_another_call():
+    """A workspace is sized once, for the largest batch, and serves the smaller ones; what a call needs at least is what ranges of
+    the default split need.  Nothing is written past it."""
+    bound, agents = 4096, (8, 7, 4, 3, 1)
+    w = mla(48, 1, (700, 64, 300, 1, 65, 500, 20, 900))
+    spec, kpool, vpool, table, table_d = gpu_cache(w)
+    ospec, okp, ovp, otable = host_cache(w)
+    sl = torch.tensor(w.seq_lens, dtype=torch.int32, device=DEV)
+    wide = torch.full((8, bound // 256), -1, dtype=torch.int32, device=DEV)
+    wide[:, :table_d.shape[1]] = table_d
+    want = oracle.attention(ospec, okp, ovp, w.q_all().numpy(), otable, w.seq_lens, w.sm_scale)
+    largest = b.q4kv_attention_workspace_bytes(spec, 8, 1, bound, 0, 1)
+    for a in agents:
+        q = w.q_all(DEV)[:, :a].contiguous()
+        split = b.q4kv_default_split_tokens(spec, a, 1, bound, 1)
+        least = b.q4kv_attention_workspace_bytes(spec, a, 1, bound, split, 1)
+        assert least <= largest
+        for size in (largest, least):
+            ws = torch.full((size + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+            args = (spec, kpool, vpool, q, wide[:a].contiguous())
+            got = b.q4kv_batched_attention(*args, sl[:a].contiguous(), bound, w.sm_scale, workspace=ws[:size])
+            b.q4kv_decode_plan(spec, sl[:a].contiguous(), bound, ws[:size])
+            out = torch.full_like(got, float("nan"))
+            b.q4kv_batched_attention_planned(*args[:4], out, args[4], bound, w.sm_scale, ws[:size])
+            torch.cuda.synchronize()
+            assert torch.equal(out, got) and bool((ws[size:] == 0xA5).all())
+            assert_close(got.cpu().numpy(), want[:, :a], f"{a} agents, workspace of {size}")
+        # a plan made with room for more records is not walked by a call that has less: it does nothing
+        big = torch.empty(largest, dtype=torch.uint8, device=DEV)
+        b.q4kv_decode_plan(spec, sl[:a].contiguous(), bound, big)
+        out.fill_(float("nan"))
+        b.q4kv_batched_attention_planned(*args[:4], out, args[4], bound, w.sm_scale, big[:least])
+        torch.cuda.synchronize()
+        assert bool(out.isnan().all())
+        b.q4kv_batched_attention_planned(*args[:4], out, args[4], bound, w.sm_scale, big, split_tokens=split)
+        torch.cuda.synchronize()
+        assert_close(out.cpu().numpy(), want[:, :a], f"{a} agents, planned with the default split named")
+        with pytest.raises(b.Q4KVError) as e:
+            b.q4kv_batched_attention(*args, sl[:a].contiguous(), bound, w.sm_scale, workspace=ws[:least - 8])
+        assert e.value.code == -4
+
+
 def test_config3_full_size_sampled_units():
     """Config 3 (5 agents x 32,768 tokens x 27 layers, 576/512 latent, 16 heads) at full size, all layers in one
     call with the default split, as the benchmark launches it; the oracle recomputes a seeded sample of
