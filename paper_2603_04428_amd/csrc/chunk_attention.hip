@@ -858,7 +858,7 @@ __global__ __launch_bounds__(kMergeThreads) void chunk_merge_kernel(ChunkParams 
         float4_t v[kMergeBatch][kMergeQuads];
 #pragma unroll
         for (int b = 0; b < kMergeBatch; ++b) {
-            const int s = s0 + b < u.slots ? s0 + b : u.slots - 1; // repeats of the last record get no weight
+            const int s = s0 + b < u.slots ? s0 + b : u.slots - 1; // repeats of the last record are not used
             ml[b] = max_and_sum(s);
             const float4_t *src = reinterpret_cast<const float4_t *>(p.part_acc) + (record(s) * kQuads + quad0) * kWave + lane;
 #pragma unroll
@@ -867,7 +867,6 @@ __global__ __launch_bounds__(kMergeThreads) void chunk_merge_kernel(ChunkParams 
         float m_new = m_ref;
 #pragma unroll
         for (int b = 0; b < kMergeBatch; ++b) {
-            if (s0 + b >= u.slots) ml[b].y = 0.0f;
             if (ml[b].y > 0.0f) m_new = fmaxf(m_new, ml[b].x);
         }
         const float keep = __builtin_amdgcn_exp2f(m_ref - m_new); // 1 when the reference stays
@@ -877,6 +876,7 @@ __global__ __launch_bounds__(kMergeThreads) void chunk_merge_kernel(ChunkParams 
         for (int k = 0; k < kMergeQuads; ++k) o[k] *= keep;
 #pragma unroll
         for (int b = 0; b < kMergeBatch; ++b) {
+            if (s0 + b >= u.slots) break; // the same for the whole wave; a weight of zero would turn an infinite sum into NaN
             const float wgt = ml[b].y > 0.0f ? __builtin_amdgcn_exp2f(ml[b].x - m_ref) : 0.0f;
             l = fmaf(ml[b].y, wgt, l);
 #pragma unroll

@@ -418,3 +418,22 @@ def test_shared_chunk_replays_from_a_graph():
         want = call(None, ws2)
         torch.cuda.synchronize()
         assert torch.equal(out, want), f"replay {step}"
+
+
+def test_shared_chunk_with_an_infinite_value():
+    """A cached infinity (bias of group 0, scale zero) that every row sees makes that group's outputs infinite, whatever the number
+    of records that are merged; here 28 or 29 a unit, and the merge takes them four at a time."""
+    w = synth.small(68, 1, 16, 8, 256, 256, False, (7000,), q_len=64)
+    spec, kpool, vpool, table, table_d = gpu_cache(w)
+    for t in range(6000, 7000, 10):
+        vpool.scale[:, int(table[0, t // 256]), :, t % 256, 0] = 0
+        vpool.bias[:, int(table[0, t // 256]), :, t % 256, 0] = 0x7C00
+    sl, q, msl = torch.tensor(w.final_lens(), dtype=torch.int32, device=DEV), w.q_all(DEV), max(w.final_lens())
+    ws = torch.empty(b.q4kv_attention_workspace_bytes(spec, 1, w.q_len, msl, 0, 1), dtype=torch.uint8, device=DEV)
+    alone = b.q4kv_batched_attention(spec, kpool, vpool, q, table_d, sl, msl, w.sm_scale)
+    shared = b.q4kv_batched_attention(spec, kpool, vpool, q, table_d, sl, msl, w.sm_scale, workspace=ws)
+    torch.cuda.synchronize()
+    assert not torch.equal(alone[..., 64:], shared[..., 64:])        # the call with shares is another sum
+    for out in (alone, shared):
+        assert bool((out[..., :64] == float("inf")).all())
+    assert_close(shared[..., 64:].cpu().numpy(), alone[..., 64:].cpu().numpy())
