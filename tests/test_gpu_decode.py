@@ -463,9 +463,44 @@ def test_ranges_shrink_where_the_bound_is_far(shape, bound):
     assert torch.equal(out, plain)
     ospec, okp, ovp, otable = host_cache(w)
     assert_close(out.cpu().numpy(), oracle.attention(ospec, okp, ovp, w.q_all().numpy(), otable, list(lens), w.sm_scale), f"{shape}")
-    if not alias:                                                    # the general plan kernel: a window per layer
+    if not alias:                                                    # the plan with a window per layer
         each = b.q4kv_batched_attention(spec, kpool, vpool, q, wide, sl, bound, w.sm_scale, [0] * L)
         assert torch.equal(each, plain)
+
+
+MANY = tuple((37 * a) % 300 + 1 for a in range(70))
+
+
+@pytest.mark.parametrize("shape,bound,per", [((1, 4, 2, 64, False, MANY), 8192, 4),               # a floor of 8 tiles becomes 4, one per wave
+                                             ((1, 4, 2, 64, False, (4096,) + MANY), 8192, 4),       # 64 tiles fit the records beside the
+                                             ((1, 4, 2, 64, False, (4097,) + MANY), 8192, 8),       # first worker's, 16; 65 take 5 each: 8
+                                             ((65, 4, 1, 64, False, (300, 64)), 8192, 4),
+                                             ((1, 16, 1, (576, 512), True, MANY), 2048, 1),
+                                             ((65, 16, 1, (576, 512), True, (300, 20)), 2048, 2)])  # 5 tiles, 4 records
+def test_ranges_shrink_in_the_general_plan(shape, bound, per):
+    """The same in the plan kernel of more than 64 agents, or of more than 64 layers with a window each: as far as the longest
+    unit's records allow, and nothing is written past the workspace."""
+    L, Hq, Hkv, D, alias, lens = shape
+    Dk, Dv = D if isinstance(D, tuple) else (D, D)
+    w = synth.small(47, L, Hq, Hkv, Dk, Dv, alias, lens)
+    spec, kpool, vpool, table, table_d = gpu_cache(w)
+    ospec, okp, ovp, otable = host_cache(w)
+    A = len(lens)
+    wide = torch.full((A, (bound + 255) // 256), -1, dtype=torch.int32, device=DEV)
+    wide[:, :table_d.shape[1]] = table_d
+    assert b.q4kv_default_split_tokens(spec, A, 1, bound, L) == (256 if alias and L == 1 else 512)
+    need = b.q4kv_attention_workspace_bytes(spec, A, 1, bound, 0, L)
+    ws = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+    windows = [(0, 70, 200)[l % 3] for l in range(L)]
+    got = b.q4kv_batched_attention(spec, kpool, vpool, w.q_all(DEV), wide, torch.tensor(lens, dtype=torch.int32, device=DEV), bound,
+                                   w.sm_scale, windows if L > 1 else 0, workspace=ws[:need])
+    torch.cuda.synchronize()
+    assert int(ws[4:8].cpu().numpy().view(np.int32)[0]) == per and bool((ws[need:] == 0xA5).all())
+    slots = need // (L * A * Hq * (Dv + 2) * 4)
+    assert -(-max(-(-n // 64) for n in lens) // per) + 1 <= slots
+    want = oracle.attention(ospec, okp, ovp, w.q_all().numpy(), otable, list(lens), w.sm_scale,
+                            **(dict(window_per_layer=windows) if L > 1 else {}))
+    assert_close(got.cpu().numpy(), want, f"{shape}")
 
 
 @pytest.mark.parametrize("shape", [(3, 8, 2, 128, False, (1500, 0, 300, 77, 2100)), (2, 4, 1, 256, False, (5000, 130)),
