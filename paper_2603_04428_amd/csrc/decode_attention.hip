@@ -93,12 +93,17 @@ struct ShareLimits {
     int min_tiles;    // a worker's smallest range for which records are reserved whatever the lengths
     int floor_tiles;  // the smallest it may get (<= min_tiles)
     int max_slots;    // records reserved per unit
+    int square;       // ranges of p tiles only where the longest unit has up to square * p * p
     int per_multiple; // a range is a multiple of this many tiles (a power of two)
 };
 
 // Tiles per worker: an even share, but no less than a floor.  The host knows max_seq_len only and reserves records for ranges
 // of min_tiles; where the lengths or the window leave far less to do, workers would stand idle at that floor, so the ranges
 // shrink as long as the longest unit (in tiles) still meets no more workers than it has records: ceil(longest / per) + 1.
+// And as long as they pay: where a unit's records are merged by a kernel of its own, behind the last range, a range of p tiles costs
+// p tiles and longest / p records.  The shared latent's tile takes 4 us and a record 0.13, so the line is at 40 p^2; one
+// layer, one agent, ranges as short as records allow / of the default split / by this rule: 2K tokens 21.1 / 31.4 / 21.4, 4K 25.2 / 31.4 /
+// 25.5, 8K 34.0 / 33.2 / 29.7, 16K 50.5 / 37.8 / 37.7, 32K 55.6 / 46.0 / 46.2; five of 3K-9K 34.6 / 38.5 / 34.9.
 __device__ __forceinline__ int tiles_per_worker(int total, int workers, int longest, const ShareLimits &s)
 {
     int per = (int)(((uint32_t)total + (uint32_t)workers - 1) / (uint32_t)workers); // total < 2^31
@@ -107,7 +112,9 @@ __device__ __forceinline__ int tiles_per_worker(int total, int workers, int long
         per = s.min_tiles;
         if (s.floor_tiles < s.min_tiles) {
             const int records = max(s.max_slots - 1, 1);
-            per = min(per, max(max(even, s.floor_tiles), (longest + records - 1) / records));
+            int least = max(max(even, s.floor_tiles), (longest + records - 1) / records);
+            while (least < per && s.square * least * least < longest) ++least;
+            per = min(per, least);
         }
     }
     return (per + s.per_multiple - 1) & -s.per_multiple;
@@ -1171,7 +1178,9 @@ hipError_t launch_plan(const AttentionArgs &a, int workers, int per_multiple, hi
     const int64_t counters = (int64_t)a.layers_in_call * a.spec.num_kv_heads * a.num_agents;
     const int helpers = (int)(counters / 8192 < 256 ? counters / 8192 : 256);
     const dim3 grid(1 + helpers), block(kThreads);
-    const ShareLimits limits{a.split_tokens / kWave, a.floor_tokens / kWave, a.max_slots, per_multiple};
+    // the GQA kernel's ranges shrink to four tiles from eight at most, and its last workgroup merges sixteen records a trip
+    const int square = per_multiple == 1 ? 40 : 1 << 24;
+    const ShareLimits limits{a.split_tokens / kWave, a.floor_tokens / kWave, a.max_slots, square, per_multiple};
     if (a.layer_window == nullptr && a.num_agents <= kWave) {
         hipLaunchKernelGGL(plan_few_kernel<OneWindow>, grid, block, 0, stream, a.seq_len, a.num_agents, a.max_seq_len, OneWindow{a.window},
                            a.layers_in_call, a.spec.num_kv_heads, workers, limits, a.plan_signature, a.plan, a.arrivals);

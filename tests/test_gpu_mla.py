@@ -289,6 +289,24 @@ def test_latent_workspace_sized_for_another_call():
         assert e.value.code == -4
 
 
+@pytest.mark.parametrize("n,per", [(1000, 1), (2560, 1), (2561, 2), (10240, 2), (10241, 3), (23040, 3), (23041, 4), (32768, 4)])
+def test_latent_ranges_of_a_long_agent_keep_some_length(n, per):
+    """A unit's records are merged one trip after another, so the ranges of a long agent shrink less: to p tiles where the
+    longest unit has up to 40 p^2 (times in csrc/decode_attention.hip)."""
+    w = mla(49, 1, (n, 30))
+    spec, kpool, vpool, table, table_d = gpu_cache(w)
+    sl = torch.tensor(w.seq_lens, dtype=torch.int32, device=DEV)
+    ws = torch.empty(b.q4kv_attention_workspace_bytes(spec, 2, 1, 32768, 0, 1), dtype=torch.uint8, device=DEV)
+    b.q4kv_decode_plan(spec, sl, 32768, ws)
+    assert list(ws[:8].cpu().numpy().view(np.int32)) == [(n + 63) // 64 + 1, per]
+    wide = torch.full((2, 128), -1, dtype=torch.int32, device=DEV)
+    wide[:, :table_d.shape[1]] = table_d
+    got = b.q4kv_batched_attention(spec, kpool, vpool, w.q_all(DEV), wide, sl, 32768, w.sm_scale, workspace=ws)
+    torch.cuda.synchronize()
+    for a in (0, 1):
+        assert_close(got[0, a].cpu().numpy(), oracle_unit(w, 0, a, 0, w.seq_lens[a]), f"{n} tokens, agent {a}")
+
+
 def test_config3_full_size_sampled_units():
     """Config 3 (5 agents x 32,768 tokens x 27 layers, 576/512 latent, 16 heads) at full size, all layers in one
     call with the default split, as the benchmark launches it; the oracle recomputes a seeded sample of
