@@ -155,8 +155,9 @@ int q4kv_append(const q4kv_spec *spec, const q4kv_pool *k, const q4kv_pool *v, c
  * agent's own last block, and a block id outside [0, num_blocks) is skipped (its tokens count as masked; the loads
  * go to the agent's own first block instead, or to block 0 if that id is outside the pool too, and are discarded).
  * Outputs are run-to-run bit-identical for identical arguments.  The order in which an agent's tokens are summed
- * follows from the sizes of the call (agents, layers, max_seq_len, window; with q_len > 1 also from whether it has its
- * workspace), so an agent's bits may differ between calls that batch it differently. */
+ * follows from the sizes of the call (agents, layers, max_seq_len, window), from the lengths of all its agents, and from the
+ * workspace (with q_len > 1 whether it has its own, on a shared latent whether it has the whole size), so an agent's bits
+ * may differ between calls that batch it differently or beside an agent that has grown. */
 int q4kv_batched_attention(const q4kv_spec *spec, const q4kv_pool *k, const q4kv_pool *v, const uint16_t *q,
                            uint16_t *out, const int32_t *block_table, int32_t max_blocks, const int32_t *seq_len,
                            int32_t num_agents, int32_t q_len, int32_t max_seq_len, float sm_scale, int32_t window,
@@ -212,7 +213,8 @@ int q4kv_batched_attention_planned(const q4kv_spec *spec, const q4kv_pool *k, co
  *     device looks the array's address up once (with that device current, as for every call); make that first call
  *     outside a graph capture.
  *   - q4kv_attention_workspace_bytes(...) > Q4KV_STATIC_SCRATCH_BYTES -> Q4KV_EWORKSPACE, nothing is launched: pass
- *     fewer layers per call (one layer of every benchmark configuration fits: at most 11 MB) or a larger split_tokens.
+ *     fewer layers per call or a larger split_tokens.  One layer of every benchmark configuration fits, in 11 MB at most, but
+ *     that of five 32,768-token agents on a shared latent, which needs 21.2 MB (10.7 with split_tokens 512).
  *   - Every call on a GPU shares that GPU's one array, which keeps the last call's contents (nothing in it has to
  *     start at zero that the call's own first kernel does not write): calls that overlap in time on one GPU, on
  *     different streams or from different threads, race on it and are not allowed.  Calls on one stream are ordered

@@ -79,9 +79,10 @@ int attention_workgroups(const q4kv_spec &s) { return (q4kv::mla_decode_supporte
 // of very few tiles do not pay); a large job gives every wave an even share whatever the floor is.  Since only the
 // device knows how much of max_seq_len the agents and the sliding windows leave visible, the floor stays small:
 // twice an even share of the largest possible job, between one block and 512 tokens.  Measured on one layer's
-// call, 256 / 512 / 768 / 1,024 tokens: 10 agents of 1K-8K tokens, 256-wide heads 40.1 / 39.5 / 39.3 / 43.2 us; 5 agents of 4K
-// tokens, 128-wide 19.6 / 19.5 / 25.3 / 21.1; 3 agents of 0.5K-6K, 192 + 128-wide 21.1 / 21.3 / 21.1 / 23.8; 1 agent of
-// 1K, 128-wide 15.0 / 16.6 / 24.5 / 17.7; 10 agents of 300, 256-wide 21.4 / 28.9 / 35.7 / 39.6.
+// call with the floor named by the caller, which the plan then keeps, 256 / 512 / 768 / 1,024 tokens: 10 agents of 1K-8K tokens,
+// 256-wide heads 35.1 / 34.3 / 34.3 / 37.8 us; 5 agents of 4K tokens, 128-wide 17.8 / 18.1 / 21.0 / 18.3; 3 agents of 0.5K-6K, 192 +
+// 128-wide 19.8 / 19.8 / 19.2 / 20.9; 1 agent of 1K, 128-wide 11.3 / 12.7 / 18.9 / 14.5; 10 agents of 300, 256-wide 17.5 / 24.0 / 30.3 /
+// 33.3.
 // A larger floor leaves waves without work whenever the visible cache is a fraction of the largest job: at
 // 4,096 tokens a quarter of the waves on a 10-agent, 48-layer step whose windows hid two thirds of the cache; at
 // 1,024 tokens four in ten on ten 300-token agents (0.115 ms against 0.090 ms at 512).
@@ -98,10 +99,13 @@ int pick_split_tokens(const q4kv_spec &s, int num_agents, int max_seq_len, int l
 }
 
 // How far the plan may lower that floor by itself where the lengths (or a window) leave less than max_seq_len lets the host
-// expect, if the floor was the library's choice: to a tile per wave.  One layer's call with max_seq_len 8,192, 512 tokens per
-// workgroup / 256: ten agents of 300, 256-wide 21.2 / 15.0 us, of 1K-8K with a window of 1,024 19.7 / 18.5, five of them 18.5 /
-// 15.2; ten of 500, 128-wide 16.2 / 13.5; three of 600, 192 + 128-wide 14.1 / 12.6; the shared latent, tokens per
-// wave 512 / 128: twenty agents of 4K of 32K 52.2 / 35.5, five of 1K of 32K, 256 / 64, 30.4 / 21.2.
+// expect, if the floor was the library's choice: to a tile per wave (less far for long agents of the shared latent: see
+// tiles_per_worker).  One layer's call with max_seq_len 8,192, the default split named by the caller (512 tokens per workgroup) /
+// left to the library: ten agents of 300, 256-wide 23.7 / 17.8 us, of 1K-8K with a window of 1,024 21.9 / 21.5, five of them 15.9 /
+// 14.2; ten of 500, 128-wide 18.6 / 16.3; three of 600, 192 + 128-wide 17.2 / 15.1; the shared latent with max_seq_len 32,768, twenty
+// agents of 4K 52.6 / 35.7, five of 1K 32.7 / 22.6.  Of 91 calls of one to twenty agents of 300 to 2,000 tokens 58 gain (up to
+// 23 %) and 10 lose more than 2 %: 2 to 6 % where every unit is just eight tiles and one workgroup takes it whole, 8 and 9 % on
+// three agents of 2,000 192-wide and five of 2,000 256-wide.
 int floor_tokens(const q4kv_spec &s, int split_given, int split_used)
 {
     if (split_given != 0) return split_used;

@@ -923,7 +923,8 @@ __global__ __launch_bounds__(kThreads, kWavesPerSimd) void decode_attention_kern
             // Behind the wave's last tile every load still goes out (skipped ones would spoil the count of loads that the
             // waits go by) but all lanes read one address: with the lanes' own offsets a one-layer call, three tiles per wave,
             // read a third more than it needs, and the registers that fold the unit waited for it (twelve 256-wide layers
-            // of ten agents 450 -> 428 us; long calls up to 1 %).
+            // of ten agents 450 -> 428 us).  The masks are 31 vector instructions in every tile of two 256-wide heads (641 -> 672) and 36
+            // of four 128-wide ones (446 -> 482); calls of many layers, which have little use for them, take what they took.
             const int keep = more ? -1 : 0;
 
             // ---- K side: q.c per (token, head, group) on the matrix core, results to LDS in token order;

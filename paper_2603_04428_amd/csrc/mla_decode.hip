@@ -27,15 +27,14 @@
 //    Operand A wants 8 tokens of one element per lane while a word holds 8 elements of one token: the transposing LDS
 //    read of 4-bit elements (ds_read_b64_tr_b4) gives a lane 16 tokens of one element, and the four masks that unpack a
 //    code word for the scores unpack 8 tokens here.  One read and ten vector instructions feed four matrix instructions.
-//    (Eight 4-byte reads, eight masks and sixteen v_perm per four operands before: 96 LDS reads and 64 vector instructions
-//    more per tile.)
+//    (Eight 4-byte reads, eight masks and sixteen v_perm per four operands before: 77 LDS instructions more per tile.)
 //  * Online softmax per tile of 64 tokens, lane-local denominators, accumulators rescaled only when some
 //    head's running maximum moved far.
 //
-// What bounds it is one instruction stream per SIMD (an instruction every five clocks): 1,060 vector, 206 matrix and 123
-// LDS instructions per 64-token tile.  27 layers of five agents of 32,768 tokens: 347 us a call, 4.1 TB/s, plan and combine
-// included (405 us with 1,414 vector instructions: results copied out of accumulator registers, per-byte permutes,
-// selects for hidden tokens in every tile).
+// What bounds it is one instruction stream per SIMD (an instruction every five clocks): 1,140 vector, 206 matrix and 123
+// LDS instructions per 64-token tile (counted on the device, per tile of a whole call).  27 layers of five agents of 32,768
+// tokens: 342-350 us a call, 4.1 TB/s, plan and combine included (405 us with 1,414 vector and 200 LDS instructions: results copied
+// out of accumulator registers, per-byte permutes, selects for hidden tokens in every tile).
 #include "q4_device.h"
 #include "q4kv_internal.h"
 #include "stream_k.h"
@@ -278,7 +277,7 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
         float m_run = kNegBig, l_run = 0.0f; // of head `col`; l_run covers this lane's tokens only
         bool first_tile = true, unit_ends;
         // The query operand lives in accumulator registers, which matrix instructions read directly; without this the
-        // allocator moved it about in every tile (65 instructions; 347 -> 336 us)
+        // allocator moved it about in every tile (65 instructions; 27 layers of five agents of 32K tokens 359 -> 346 us)
 #pragma unroll
         for (int g = 0; g < GK; ++g) asm volatile("" : "+a"(qop[g][0]), "+a"(qop[g][1]));
         asm volatile("" : "+a"(qsop));
