@@ -37,23 +37,23 @@ CODEC_FILES = ("codec.hip", "q4_device.h", "q4kv_internal.h")
 CHUNK_FILES = ("chunk_attention.hip", "chunk_rules.h", "q4_device.h", "q4kv_internal.h")
 MEASURED_TRAFFIC = {
     "gemma12b_10agents_48layers_ragged_1k_8k_decode": {
-        "read": 4787400907, "written": 20898816, "file": "profiles/decode_attention_gemma10_ragged.md",
-        "files": DECODE_FILES, "sources": "045966d38e90"},
+        "read": 4786905372, "written": 20898816, "file": "profiles/decode_attention_gemma10_ragged.md",
+        "files": DECODE_FILES, "sources": "d96d8a094186"},
     "llama8b_5agents_32layers_4k_decode": {
-        "read": 768070822, "written": 8134656, "file": "profiles/decode_attention_llama8b_5x4k.md",
-        "files": DECODE_FILES, "sources": "045966d38e90"},
+        "read": 767897678, "written": 8134656, "file": "profiles/decode_attention_llama8b_5x4k.md",
+        "files": DECODE_FILES, "sources": "d96d8a094186"},
     "dsv2lite_mla_per_head_5agents_27layers_8k_decode": {
-        "read": 3190513568, "written": 3088896, "file": "profiles/decode_attention_mla_per_head_5x8k.md",
-        "files": DECODE_FILES, "sources": "2696fa166c24"},
+        "read": 3190045245, "written": 2958848, "file": "profiles/decode_attention_mla_per_head_5x8k.md",
+        "files": DECODE_FILES, "sources": "d96d8a094186"},
     "dsv2lite_mla_latent_5agents_27layers_32k_decode": {
-        "read": 1442866214, "written": 37927936, "file": "profiles/mla_decode_dsv2lite_5x32k.md",
-        "files": LATENT_FILES, "sources": "e49c7c33b916"},
+        "read": 1442816854, "written": 37899659, "file": "profiles/mla_decode_dsv2lite_5x32k.md",
+        "files": LATENT_FILES, "sources": "d33b1c1bf217"},
     "quantize_4k_cache": {
-        "read": 1610806417, "written": 452984832, "file": "profiles/decode_attention_gemma10_ragged.md",
-        "files": CODEC_FILES, "sources": "d4c016786039"},
+        "read": 1610807914, "written": 452984832, "file": "profiles/decode_attention_gemma10_ragged.md",
+        "files": CODEC_FILES, "sources": "ef1468fd419e"},
     "dequantize_4k_cache": {
-        "read": 453043366, "written": 1610615430, "file": "profiles/decode_attention_gemma10_ragged.md",
-        "files": CODEC_FILES, "sources": "d4c016786039"},
+        "read": 453042913, "written": 1610616730, "file": "profiles/decode_attention_gemma10_ragged.md",
+        "files": CODEC_FILES, "sources": "ef1468fd419e"},
 }
 
 
@@ -355,7 +355,7 @@ def bench_latent(args, torch, b, synth, build_device_cache, **kw):
     """Decode over the shared-latent cache (DeepSeek-V2-Lite-shaped: 5 agents x 32,768 tokens x 27 layers, one
     576-wide Q4 row per token read by 16 heads), all layers in one call; reported as HBM GB/s."""
     return bench_decode_only(args, torch, b, build_device_cache, synth.config(3),
-                             "mla_decode_kernel<9,8,false> (+ plan_kernel and combine_kernel in the same call)",
+                             "mla_decode_kernel<9,8,false> (+ plan_few_kernel and combine_kernel in the same call)",
                              oracle_sample=([0], [0]), **kw)
 
 
@@ -363,7 +363,7 @@ def bench_llama(args, torch, b, synth, build_device_cache, **kw):
     """Decode over the Llama-3.1-8B-shaped cache of configuration 1 (5 agents x 4,096 tokens x 32 layers, 32 query /
     8 KV heads, 128 wide): a short call (0.15 ms), so plan and combine weigh in it."""
     return bench_decode_only(args, torch, b, build_device_cache, synth.config(1),
-                             "decode_attention_kernel<128,128,4,false> (+ plan_kernel in the same call)",
+                             "decode_attention_kernel<128,128,4,false> (+ plan_few_kernel in the same call)",
                              oracle_sample=([0, 10, 21, 31], None), **kw)
 
 
@@ -371,14 +371,14 @@ def bench_tiny(args, torch, b, synth, build_device_cache, **kw):
     """Configuration 0 (1 agent x 1,024 tokens x 1 layer, Llama-shaped): 1.2 MB of cache that stays in the caches of
     the chip, so the figure of interest is the latency of one call (plan + attention + combine), `decode_us`."""
     return bench_decode_only(args, torch, b, build_device_cache, synth.config(0),
-                             "decode_attention_kernel<128,128,4,false> (+ plan_kernel in the same call)",
+                             "decode_attention_kernel<128,128,4,false> (+ plan_few_kernel in the same call)",
                              oracle_sample=([0], None), **kw)
 
 
 def bench_per_head(args, torch, b, synth, build_device_cache, **kw):
     """Decode over the decompressed per-head form of the same model's cache (keys 192, values 128, 16 KV heads)."""
     return bench_decode_only(args, torch, b, build_device_cache, synth.per_head_mla_config(),
-                             "decode_attention_kernel<192,128,1,false> (+ plan_kernel in the same call)",
+                             "decode_attention_kernel<192,128,1,false> (+ plan_few_kernel in the same call)",
                              oracle_sample=([0, 26], None), **kw)
 
 
@@ -843,7 +843,7 @@ def main():
                      "traffic": traffic_for(w.name)[0] if args.layer_windows == "global" and not args.split_tokens
                      else None,
                      "traffic_source": traffic_for(w.name)[1],
-                     "kernel": "decode_attention_kernel<256,256,2,false> (+ plan_kernel in the same call)"},
+                     "kernel": "decode_attention_kernel<256,256,2,false> (+ plan_few_kernel in the same call)"},
         "roofline_quantize": {"bound": "hbm", "achieved": quant_bytes / (qua_ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBPS,
                               "unit": "GB/s", "frac": quant_bytes / (qua_ms * 1e-3) / 1e9 / HBM_PEAK_GBPS,
                               "traffic": traffic_for("quantize_4k_cache")[0],
