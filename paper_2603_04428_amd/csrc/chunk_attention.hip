@@ -867,6 +867,11 @@ __global__ __launch_bounds__(kMergeThreads) void chunk_merge_kernel(ChunkParams 
         float m_new = m_ref;
 #pragma unroll
         for (int b = 0; b < kMergeBatch; ++b) {
+            if (s0 + b >= u.slots) { // no weight, and nothing to give it to: zero times an infinite sum would be NaN
+                ml[b].y = 0.0f;
+#pragma unroll
+                for (int k = 0; k < kMergeQuads; ++k) v[b][k] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            }
             if (ml[b].y > 0.0f) m_new = fmaxf(m_new, ml[b].x);
         }
         const float keep = __builtin_amdgcn_exp2f(m_ref - m_new); // 1 when the reference stays
@@ -876,7 +881,6 @@ __global__ __launch_bounds__(kMergeThreads) void chunk_merge_kernel(ChunkParams 
         for (int k = 0; k < kMergeQuads; ++k) o[k] *= keep;
 #pragma unroll
         for (int b = 0; b < kMergeBatch; ++b) {
-            if (s0 + b >= u.slots) break; // the same for the whole wave; a weight of zero would turn an infinite sum into NaN
             const float wgt = ml[b].y > 0.0f ? __builtin_amdgcn_exp2f(ml[b].x - m_ref) : 0.0f;
             l = fmaf(ml[b].y, wgt, l);
 #pragma unroll
