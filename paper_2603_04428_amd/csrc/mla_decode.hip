@@ -348,7 +348,6 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
 
             // A tile with a large value scale is taken in two parts, first the even rows r of every slot, then the odd ones (see the
             // softmax); everything that the second part reads is still in LDS.
-            float raised = 0.0f; // how far m_run lies above its place between the two
             int part = 0;
             do {
                 // ---- scores of the 64 tokens, four 16-token sets: z[j][r] is token slot_token(qk, j, r), head col, in units of
@@ -449,7 +448,7 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
                         if ((i & 1) != part) z[i / 4][i % 4] = -INFINITY;
                     slack = part == 0 ? 2.5f : 6.5f;
                     below = part == 0 ? 0.0f : 4.0f;
-                    m_ref -= raised;
+                    m_ref += part == 0 ? 4.0f : -4.0f; // from 4 below the maximum to the maximum, and back
                 }
                 float mt = -INFINITY;
 #pragma unroll
@@ -457,10 +456,6 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
                 mt = xor32_max(xor16_max(mt)) * zs;
                 const bool above = mt > m_ref + slack; // the same in the four lanes of a head
                 const float m_new = above ? mt - below : m_ref;
-                const bool moved = m_new != m_run;
-                const float alpha = moved ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.0f;
-                raised = above ? 4.0f - below : 0.0f;
-                m_run = m_new;
                 float psum = 0.0f;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
@@ -468,12 +463,15 @@ __global__ __launch_bounds__(kThreads, 1) void mla_decode_kernel(const MlaParams
                     z[i / 4][i % 4] = pr;
                     psum += pr;
                 }
-                l_run = fmaf(l_run, alpha, psum);
-                if (!first_tile && __builtin_amdgcn_ballot_w64(moved) != 0ull) { // accumulators are zero in a unit's first tile
+                if (!first_tile && __builtin_amdgcn_ballot_w64(m_new != m_run) != 0ull) { // in a unit's first tile all sums are zero
+                    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new); // 1 for a head whose reference stays
+                    l_run *= alpha;
                     pbacc *= alpha;
 #pragma unroll
                     for (int c = 0; c < 4 * GV; ++c) acc[c] *= alpha;
                 }
+                l_run += psum;
+                m_run = m_new;
 
                 // ---- values: per tile half, B = p * s of tokens slot_token(qk, 2 h2 + {0, 1}, r) in register r, in two binary16
                 // terms.  The product of two binary16 numbers minus its rounded value is a binary16 number again (barring
