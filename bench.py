@@ -46,8 +46,8 @@ MEASURED_TRAFFIC = {
         "read": 3190045245, "written": 2958848, "file": "profiles/decode_attention_mla_per_head_5x8k.md",
         "files": DECODE_FILES, "sources": "d96d8a094186"},
     "dsv2lite_mla_latent_5agents_27layers_32k_decode": {
-        "read": 1442816854, "written": 37899659, "file": "profiles/mla_decode_dsv2lite_5x32k.md",
-        "files": LATENT_FILES, "sources": "d33b1c1bf217"},
+        "read": 1442820110, "written": 37895622, "file": "profiles/mla_decode_dsv2lite_5x32k.md",
+        "files": LATENT_FILES, "sources": "3aeca27a0fd8"},
     "quantize_4k_cache": {
         "read": 1610807914, "written": 452984832, "file": "profiles/decode_attention_gemma10_ragged.md",
         "files": CODEC_FILES, "sources": "ef1468fd419e"},

@@ -31,9 +31,9 @@
 //  * Online softmax per tile of 64 tokens, lane-local denominators, accumulators rescaled only when some
 //    head's running maximum moved far.
 //
-// What bounds it is one instruction stream per SIMD (an instruction every five clocks): 1,140 vector, 206 matrix and 123
+// What bounds it is one instruction stream per SIMD (an instruction every five clocks): 1,132 vector, 206 matrix and 123
 // LDS instructions per 64-token tile (counted on the device, per tile of a whole call).  27 layers of five agents of 32,768
-// tokens: 342-350 us a call, 4.1 TB/s, plan and combine included (405 us with 1,414 vector and 200 LDS instructions: results copied
+// tokens: 342-355 us a call, 4.1 TB/s, plan and combine included (405 us with 1,414 vector and 200 LDS instructions: results copied
 // out of accumulator registers, per-byte permutes, selects for hidden tokens in every tile).
 #include "q4_device.h"
 #include "q4kv_internal.h"
