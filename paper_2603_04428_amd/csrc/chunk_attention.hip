@@ -864,16 +864,20 @@ __global__ __launch_bounds__(kMergeThreads) void chunk_merge_kernel(ChunkParams 
 #pragma unroll
             for (int k = 0; k < kMergeQuads; ++k) v[b][k] = src[k * kWave];
         }
+        if (s0 + kMergeBatch > u.slots) { // the repeats get no weight, and nothing to give it to: zero times an infinite sum is NaN
+            asm volatile(""); // a branch: whole batches do not pay for the selects
+#pragma unroll
+            for (int b = 1; b < kMergeBatch; ++b)
+                if (s0 + b >= u.slots) {
+                    ml[b].y = 0.0f;
+#pragma unroll
+                    for (int k = 0; k < kMergeQuads; ++k) v[b][k] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+                }
+        }
         float m_new = m_ref;
 #pragma unroll
-        for (int b = 0; b < kMergeBatch; ++b) {
-            if (s0 + b >= u.slots) { // no weight, and nothing to give it to: zero times an infinite sum would be NaN
-                ml[b].y = 0.0f;
-#pragma unroll
-                for (int k = 0; k < kMergeQuads; ++k) v[b][k] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-            }
+        for (int b = 0; b < kMergeBatch; ++b)
             if (ml[b].y > 0.0f) m_new = fmaxf(m_new, ml[b].x);
-        }
         const float keep = __builtin_amdgcn_exp2f(m_ref - m_new); // 1 when the reference stays
         m_ref = m_new;
         l *= keep;
