@@ -18,12 +18,17 @@
 //    one piece / two: 70 tokens of four agents, 128-wide 60.6 / 50.5 us, 512 tokens of ten agents, six layers 2,878 /
 //    2,738 us; 24 tokens of five agents, 192 + 128-wide 170 / 154 us.
 //  * KV tiles are fetched as Q4 (codes + scale/bias, prefetched one tile ahead into registers) and staged
-//    ONCE per workgroup in LDS, row-major: V_hat dequantized to binary16, K as the packed code words themselves (a
-//    lane's A operand of a matrix instruction is exactly one word, four of them one 16-byte LDS read).  The dims inside
+//    ONCE per workgroup in LDS: V_hat dequantized to binary16, row-major, K as matrix operands (a lane's A operand is exactly
+//    one code word, unpacked to the integers c and, for odd nibbles, 16 c against q/16), [word][token].  The dims inside
 //    a word appear in the order the nibble masks deliver them (0,4,1,5,2,6,3,7): the query operand uses the same order
 //    for K, the output store undoes it for V_hat.
-//  * K stays factored, S^T = sum_g s[t,g] (C_g Q_g^T) + b Qsum^T: a code word masked in place is eight binary16
-//    subnormals (c 2^-24, odd nibbles 16 c 2^-24 against q/16), the matrix core multiplies them exactly, and the
+//  * Unpacking while staging instead of in every one of the eight waves takes 96 of 338 vector instructions out of a wave's
+//    32 tokens (256-wide).  Measured, one call, packed / unpacked: 256-wide 512 tokens of ten agents of 4K-32K 2,440 / 2,356
+//    us, of one behind 8,000 123.7 / 121.8; 128-wide, four agents, two layers 424 / 414; 192 + 128 265 / 257; 64-wide 107 /
+//    100.  It is 8.6 % fewer clocks on the long call, of which the power limit gives a third back: 1.87 -> 1.81 GHz.  Where
+//    the unpacked tile does not fit into LDS (chunk_unpacks_keys) the code words are staged as they are and unpacked by each
+//    wave, masked in place into binary16 subnormals (c 2^-24).
+//  * K stays factored, S^T = sum_g s[t,g] (C_g Q_g^T) + b Qsum^T: the matrix core multiplies the codes exactly, and the
 //    per-(token, group) scale meets the binary32 result of each group; the bias term is one more matrix
 //    instruction per 32 tokens whose contraction runs over the groups (group sums of q split into a binary16 high
 //    and low part).  A K row dequantized to binary16 would carry an absolute rounding error of 2^-11 |K_hat|,
@@ -249,6 +254,9 @@ struct Stage {
 constexpr int chunk_pieces(int dk) { return dk == 256 ? 1 : 2; }
 // KV tokens per tile
 constexpr int chunk_tile(int dk, int ksplit) { return kSub * chunk_pieces(dk) * ksplit; }
+// Whether the K tile is unpacked when it is staged: two tiles of K and V_hat and the query operand have 160 KB.  128 rows of
+// 256-wide heads (64-token tiles) would need 182, of 192 + 128-wide ones (128 tokens) 193.
+constexpr bool chunk_unpacks_keys(int dk, int ksplit) { return dk <= 128 || ksplit == 1; }
 
 // KSPLIT 1: 256 rows per workgroup; 2: 128 rows, the two halves of the waves share the tokens of a tile.
 // SHARES: the workgroup takes an equal share of all tiles; else one unit.
@@ -263,20 +271,23 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
     constexpr int VPITCH = DV + 16;    // halves; 8 banks mod 64 (40 at 64-wide rows), see above
     constexpr int DTILES = DV / 32;    // 32-dim tiles of O^T
     constexpr int NP = chunk_pieces(DK), TILE = chunk_tile(DK, KSPLIT);
-    constexpr int QREG = DK == 256 ? 1 : (DK == 192 ? 2 : GK); // groups whose query operand stays in registers; the rest in LDS
-    constexpr int QLDS = GK - QREG;
+    constexpr bool KFULL = chunk_unpacks_keys(DK, KSPLIT);
+    // matrix instructions (4 per group) whose query operand stays in registers; the rest lie in LDS
+    constexpr int QREG = DK == 256 ? (KFULL ? 5 : 4) : (DK == 192 ? 8 : 4 * GK);
+    constexpr int QLDS = 4 * GK - QREG;
     constexpr int QROWS = ROWGROUPS * kWave; // lanes that hold query operands of their own
     typedef Stage<DK, kChunkThreads, TILE> SK; // staging of the K rows of a tile ...
     typedef Stage<DV, kChunkThreads, TILE> SV; // ... and of its V rows
 
     // two tiles each: while the waves multiply against one, they unpack the next into the other
-    __shared__ __attribute__((aligned(16))) uint32_t k_lds[2][TILE * KPITCH]; // K code words as they are in the pool
+    // K, unpacked: the 8 codes of a word as a matrix operand, [word][token]; else the code words as they are in the pool
+    __shared__ __attribute__((aligned(16))) uint32_t k_lds[2][KFULL ? TILE * DK / 2 : TILE * KPITCH];
     __shared__ __attribute__((aligned(16))) half_t v_lds[2][TILE * VPITCH];   // V_hat
     // K scale [group][32-token half][lane / 32][16 values in the order a lane's scores have]
     __shared__ __attribute__((aligned(16))) half_t ks_lds[2][GK * TILE];
     // K bias [token][8]: groups 0..3 (zero padded) twice, against the high and the low parts of the group sums of q
     __shared__ __attribute__((aligned(16))) half_t kb_lds[2][TILE * 8];
-    __shared__ __attribute__((aligned(16))) half8_t q_lds[QLDS > 0 ? QLDS * 4 * QROWS : 1];
+    __shared__ __attribute__((aligned(16))) half8_t q_lds[QLDS > 0 ? QLDS * QROWS : 1];
     __shared__ int s_pre[kMaxStreamAgents + 1], s_len[kMaxStreamAgents];
 
     const int wave = scalar(threadIdx.x / kWave);
@@ -406,7 +417,6 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         // accumulator.
         struct RowDequant {
             half2_t s2, s16, b2;
-            bool ok;
         };
         auto row_params = [&](const uint32_t (&sb)[2], bool ok) {
             RowDequant r;
@@ -419,26 +429,30 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             r.s2 = half2_t{s, s};
             r.b2 = half2_t{b, b};
             r.s16 = r.s2 * half2_t{(half_t)0.0625f, (half_t)0.0625f};
-            r.ok = ok;
             return r;
         };
         auto store_word = [&](half_t *dst, uint32_t raw, const RowDequant &r) {
-            const uint32_t word = r.ok ? raw : 0u, w8 = word >> 8;
-            const half2_t v0 = pk_fma(nibbles_lo(word), r.s2, r.b2);    // dims 0, 4
-            const half2_t v1 = pk_fma(nibbles_hi16(word), r.s16, r.b2); // dims 1, 5
+            const uint32_t w8 = raw >> 8;
+            const half2_t v0 = pk_fma(nibbles_lo(raw), r.s2, r.b2);     // dims 0, 4
+            const half2_t v1 = pk_fma(nibbles_hi16(raw), r.s16, r.b2);  // dims 1, 5
             const half2_t v2 = pk_fma(nibbles_lo(w8), r.s2, r.b2);      // dims 2, 6
             const half2_t v3 = pk_fma(nibbles_hi16(w8), r.s16, r.b2);   // dims 3, 7
             *reinterpret_cast<uint4 *>(dst) = make_uint4(half2_to_bits(v0), half2_to_bits(v1), half2_to_bits(v2), half2_to_bits(v3));
         };
-        auto store_codes = [&](uint32_t *dst, const uint32_t (&raw)[SK::WPT], bool ok) {
+        auto store_codes = [&](uint32_t *dst, const uint32_t (&raw)[SK::WPT]) {
             if constexpr (SK::WPT % 4 == 0) {
 #pragma unroll
                 for (int w = 0; w < SK::WPT; w += 4)
-                    *reinterpret_cast<uint4 *>(dst + w) =
-                        ok ? make_uint4(raw[w], raw[w + 1], raw[w + 2], raw[w + 3]) : make_uint4(0u, 0u, 0u, 0u);
+                    *reinterpret_cast<uint4 *>(dst + w) = make_uint4(raw[w], raw[w + 1], raw[w + 2], raw[w + 3]);
             } else {
-                *reinterpret_cast<uint2 *>(dst) = ok ? make_uint2(raw[0], raw[1]) : make_uint2(0u, 0u);
+                *reinterpret_cast<uint2 *>(dst) = make_uint2(raw[0], raw[1]);
             }
+        };
+        // the codes of a word as exact small integers: c (dims 0, 4, 2, 6) and 16 c (dims 1, 5, 3, 7)
+        auto store_unpacked = [&](uint32_t *dst, uint32_t raw) {
+            const uint32_t w8 = raw >> 8;
+            *reinterpret_cast<uint4 *>(dst) = make_uint4(half2_to_bits(nibbles_lo(raw)), half2_to_bits(nibbles_hi16(raw)),
+                                                         half2_to_bits(nibbles_lo(w8)), half2_to_bits(nibbles_hi16(w8)));
         };
         // a code word as the A operand of a matrix instruction: the nibbles masked in place are binary16 subnormals
         // c 2^-24 (dims 0, 4, 2, 6 of the word) and 16 c 2^-24 (dims 1, 5, 3, 7)
@@ -457,7 +471,8 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             kb_lds[b][k_tok * 8 + 4 + k_grp] = r.b2.x;
         };
         auto row_ok = [&](int t0, int tok, bool ok_tile) { return ok_tile && (t0 + tok < t_end); };
-        const int k_dst = k_tok * KPITCH + k_w0, v_dst = v_tok * VPITCH + v_w0 * 8;
+        const int k_dst = KFULL ? (k_w0 * TILE + k_tok) * 4 : k_tok * KPITCH + k_w0, v_dst = v_tok * VPITCH + v_w0 * 8;
+        constexpr int kWordStep = TILE * 4; // from one word's operands to the next one's
 
         // the first tile is on its way while the queries are unpacked
         const int t_last = part_t0 < part_t1 ? part_t0 + (part_t1 - 1 - part_t0) / TILE * TILE : 0; // start of the last tile
@@ -481,7 +496,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         // tokens inside [all_first, all_vis) are visible to every row of this wave and need no masks
         const int all_vis = row_sees(u.qt * QPOS + rg * kRowsWave / NREP);
         const int all_first = row_hides(row_sees(u.qt * QPOS + (rg * kRowsWave + kRowsWave - 1) / NREP));
-        half8_t qop[QREG][4]; // [group][matrix instruction]: the 8 dims of word 8 g + 4 h + i
+        half8_t qop[QREG]; // [matrix instruction 4 g + i]: the 8 dims of word 8 g + 4 h + i
         half8_t qsop;         // lower half of the wave: group sums of q, high parts in slots 0..3, low parts in 4..7; else 0
         {
             float qs[GK];
@@ -500,8 +515,8 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                                               e23.x, e67.x, e23.y * sixteenth, e67.y * sixteenth};
                     qs[g] += ((float)e01.x + (float)e01.y) + ((float)e23.x + (float)e23.y) +
                              ((float)e45.x + (float)e45.y) + ((float)e67.x + (float)e67.y);
-                    if (g < QREG) qop[g < QREG ? g : 0][i] = v;
-                    else if (my_sub == 0) q_lds[((g - QREG) * 4 + i) * QROWS + rg * kWave + lane] = v;
+                    if (4 * g + i < QREG) qop[4 * g + i < QREG ? 4 * g + i : 0] = v;
+                    else if (my_sub == 0) q_lds[(4 * g + i - QREG) * QROWS + rg * kWave + lane] = v;
                 }
             }
             half_t part[8];
@@ -526,7 +541,8 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
 
         // operand reads: K row of M row qn; V_hat by the transposing read (token 8 h + 2 e (+ 1), dims 16 (lane/16 % 2) + 4 c)
         const int m_token = 16 * (qn / 16) + 8 * ((qn / 4) % 2) + 2 * (qn % 4) + (qn / 8) % 2;
-        const int k_lane = m_token * KPITCH + 4 * h;
+        const int k_lane = KFULL ? 4 * h * kWordStep + m_token * 4 : m_token * KPITCH + 4 * h;
+        constexpr int kPiece = KFULL ? kSub * 4 : kSub * KPITCH; // from one 32-token piece to the next
         const int v_lane = (8 * h + 2 * ((lane % 16) / 4)) * VPITCH + 16 * ((lane / 16) % 2) + 4 * (lane % 4);
 
         // One barrier per tile: tile i is multiplied out of buffer i % 2 while tile i + 1 (already in registers) is
@@ -535,7 +551,13 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         if (part_t0 < part_t1) {
             const RowDequant kr = row_params(ksb, row_ok(part_t0, k_tok, ok_cur));
             const RowDequant vr = row_params(vsb, row_ok(part_t0, v_tok, ok_cur));
-            if (k_on) store_codes(k_lds[0] + k_dst, kraw, kr.ok);
+            if constexpr (KFULL) {
+#pragma unroll
+                for (int w = 0; w < SK::WPT; ++w)
+                    if (k_on) store_unpacked(k_lds[0] + k_dst + w * kWordStep, kraw[w]);
+            } else if (k_on) {
+                store_codes(k_lds[0] + k_dst, kraw);
+            }
             if (k_params_writer) store_k_params(0, kr);
             if (v_on) {
 #pragma unroll
@@ -556,25 +578,38 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
 
             // this wave's NP pieces of 32 tokens
             const int sub = my_sub * NP, ts = t0 + kSub * sub;
-            const uint32_t *k_row = k_cur + sub * kSub * KPITCH + k_lane;
+            const uint32_t *k_row = k_cur + sub * kPiece + k_lane;
             const half_t *ks_row = ks_cur + sub * kSub + 16 * h;
-            // ---- S^T = sum_g s_g (C_g Q_g^T) + b Qsum^T in binary32, in units of 2^-24
+            // ---- S^T = sum_g s_g (C_g Q_g^T) + b Qsum^T in binary32, in units of kUnit
+            constexpr float kUnit = KFULL ? 1.0f : 0x1p-24f;
             float16_t zero;
 #pragma unroll
             for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
             auto q_operand = [&](int k) { // matrix instruction k = 4 group + i
-                if (k / 4 < QREG) return qop[k / 4 < QREG ? k / 4 : 0][k % 4];
-                return q_lds[(k - 4 * QREG) * QROWS + rg * kWave + lane];
+                if (k < QREG) return qop[k < QREG ? k : 0];
+                return q_lds[(k - QREG) * QROWS + rg * kWave + lane];
             };
             float16_t st[NP];
-            uint4 words[NP]; // code words 8 g + 4 h .. + 3 of this lane's token
+            // this lane's token: the operands of the kKeysAhead matrix instructions to come, or the code words 8 g + 4 h .. + 3
+            constexpr int kKeysAhead = 2;
+            uint4 words[NP], keys[kKeysAhead][NP];
+            auto load_keys = [&](int k, int n) { // matrix instruction k of piece n
+                return *reinterpret_cast<const uint4 *>(k_row + n * kPiece + (8 * (k / 4) + k % 4) * kWordStep);
+            };
 #pragma unroll
             for (int n = 0; n < NP; ++n) {
                 const half8_t ba = *reinterpret_cast<const half8_t *>(kb_cur + ((sub + n) * kSub + m_token) * 8);
                 st[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ba, qsop, zero, 0, 0, 0);
             }
 #pragma unroll
-            for (int n = 0; n < NP; ++n) words[n] = *reinterpret_cast<const uint4 *>(k_row + n * kSub * KPITCH);
+            for (int n = 0; n < NP; ++n) {
+                if constexpr (KFULL) {
+#pragma unroll
+                    for (int k = 0; k < kKeysAhead; ++k) keys[k][n] = load_keys(k, n);
+                } else {
+                    words[n] = *reinterpret_cast<const uint4 *>(k_row + n * kPiece);
+                }
+            }
             half8_t qk = q_operand(0);
 #pragma unroll
             for (int g = 0; g < GK; ++g) {
@@ -583,19 +618,29 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                 uint4 sc[NP], sc1[NP]; // scales of the lane's first and last 8 scores
 #pragma unroll
                 for (int n = 0; n < NP; ++n) {
-                    w[n][0] = words[n].x; w[n][1] = words[n].y; w[n][2] = words[n].z; w[n][3] = words[n].w;
+                    if constexpr (!KFULL) {
+                        w[n][0] = words[n].x; w[n][1] = words[n].y; w[n][2] = words[n].z; w[n][3] = words[n].w;
+                    }
                     d[n] = zero;
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
+                    const int k = 4 * g + i;
                     const half8_t qi = qk;
-                    if (4 * g + i + 1 < 4 * GK) qk = q_operand(4 * g + i + 1);
+                    if (k + 1 < 4 * GK) qk = q_operand(k + 1);
 #pragma unroll
                     for (int n = 0; n < NP; ++n) {
                         if (i == 2) sc[n] = *reinterpret_cast<const uint4 *>(ks_row + g * TILE + n * kSub);
                         if (i == 3) sc1[n] = *reinterpret_cast<const uint4 *>(ks_row + g * TILE + n * kSub + 8);
-                        if (i == 3 && g + 1 < GK) words[n] = *reinterpret_cast<const uint4 *>(k_row + n * kSub * KPITCH + 8 * (g + 1));
-                        d[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(code_operand(w[n][i]), qi, d[n], 0, 0, 0);
+                        half8_t a;
+                        if constexpr (KFULL) {
+                            a = __builtin_bit_cast(half8_t, keys[k % kKeysAhead][n]);
+                            if (k + kKeysAhead < 4 * GK) keys[k % kKeysAhead][n] = load_keys(k + kKeysAhead, n);
+                        } else {
+                            if (i == 3 && g + 1 < GK) words[n] = *reinterpret_cast<const uint4 *>(k_row + n * kPiece + 8 * (g + 1));
+                            a = code_operand(w[n][i]);
+                        }
+                        d[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, qi, d[n], 0, 0, 0);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -605,7 +650,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
                         const half2_t sh = bits_to_half2(s8[i / 2]);
-                        const float prev = g == 0 ? st[n][i] * 0x1p-24f : st[n][i]; // the bias term enters in the products' unit
+                        const float prev = g == 0 ? st[n][i] * kUnit : st[n][i]; // the bias term enters in the products' unit
                         st[n][i] = fmaf((float)((i & 1) ? sh.y : sh.x), d[n][i], prev);
                     }
                     // pinned: else the multiplies of all groups sink to the scores' first use and every product stays live
@@ -616,7 +661,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            const float zscale = p.score_scale * 16777216.0f; // scores are in units of 2^-24
+            const float zscale = p.score_scale / kUnit;
 
             // ---- online softmax per query row (lane column), then P^T in binary16 as the next B operand
             const bool masked = !(ok_this && ts >= all_first && ts + NP * kSub <= all_vis); // wave-uniform
@@ -705,17 +750,30 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                 const half8_t a = va[s % kAhead];
                 if (s + kAhead < kSteps) va[s % kAhead] = load_va(s + kAhead);
                 o_acc[s / kPerTile] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pt[s % kPerTile], o_acc[s / kPerTile], 0, 0, 0);
+                // the next tile's K, then its V, a word at a time; behind each the registers are free for the tile after that
                 if (s == 0) {
                     const RowDequant kr = row_params(ksb, row_ok(t0 + TILE, k_tok, ok_next && more));
-                    if (k_on) store_codes(k_lds[buf ^ 1] + k_dst, kraw, kr.ok);
+                    if constexpr (!KFULL) {
+                        if (k_on) store_codes(k_lds[buf ^ 1] + k_dst, kraw);
+                    }
                     if (k_params_writer) store_k_params(buf ^ 1, kr);
-                    row_ahead = tile_row0(t_ahead, entry_ahead, ok_ahead); // the registers are free: the tile after that
-                    load_k(row_ahead);
+                    row_ahead = tile_row0(t_ahead, entry_ahead, ok_ahead);
                 }
+                constexpr int kWords = (KFULL ? SK::WPT : 0) + SV::WPT, kFirstV = kWords - SV::WPT;
+                constexpr int kAfterK = kFirstV > 0 ? (kFirstV - 1) * kSteps / kWords + 1 : 0;
+                constexpr int kAfterV = (kWords - 1) * kSteps / kWords + 1;
+                static_assert(kAfterV < kSteps, "room for every word and the loads behind it");
 #pragma unroll
-                for (int w = 0; w < SV::WPT; ++w)
-                    if (w * kSteps / SV::WPT == s && v_on) store_word(v_lds[buf ^ 1] + v_dst + 8 * w, vraw[w], vr);
-                if (s == (SV::WPT - 1) * kSteps / SV::WPT + 1) load_v(row_ahead);
+                for (int w = 0; w < kWords; ++w)
+                    if (w * kSteps / kWords == s) {
+                        if (w < kFirstV) {
+                            if (k_on) store_unpacked(k_lds[buf ^ 1] + k_dst + w * kWordStep, kraw[w < kFirstV ? w : 0]);
+                        } else if (v_on) {
+                            store_word(v_lds[buf ^ 1] + v_dst + 8 * (w - kFirstV), vraw[w < kFirstV ? 0 : w - kFirstV], vr);
+                        }
+                    }
+                if (s == kAfterK) load_k(row_ahead);
+                if (s == kAfterV) load_v(row_ahead);
                 __builtin_amdgcn_sched_barrier(0);
             }
             ok_cur = ok_next;
