@@ -44,10 +44,21 @@
 //    transposing read touches are then two tokens apart, and with a pitch of 8 banks (mod 64) the four tokens x 64
 //    bytes of half a wave fall into all 64 banks.
 //  * At 256-wide heads the accumulators of 32 rows (128 registers) leave no room for the whole query operand (64) if
-//    two waves are to share a SIMD: three of its four groups lie in LDS, in operand order; at 192-wide keys one of three.
+//    two waves are to share a SIMD: what does not fit (QREG) lies in LDS, in operand order; some of it at 128 and 192 too.
 //    With KSPLIT = 2 the two waves of a row group read one copy, which the first one writes before the barrier in front of
 //    the tile loop.
-//  * Softmax is online, per query row (= per lane column): scores in binary32, log2 domain, 32 tokens at a time.
+//  * Softmax is online, per query row (= per lane column): scores in binary32, log2 domain.  The reference of a row moves when
+//    some row of its wave exceeds it by more than kSlack, all rows of the wave together: every move rescales the accumulators.
+//    The denominator is the sum of the weights as they are multiplied, rounded to binary16 (v_dot2_f32_f16, a pair at a time):
+//    a row that one token dominates then loses nothing to the rounding.
+//  * A wave works a step ahead of itself: step i takes the scores of tile i and then, between the matrix instructions of the
+//    product of tile i - 1, the softmax of tile i.  The tiles are staged beside the scores, V one step behind K.  Measured
+//    against scores, softmax and product one after the other, one call: 256-wide 512 tokens of ten agents of 6,000, three layers 1,894 /
+//    1,849 us (4.05e6 / 3.80e6 clocks; the power limit lowers the clock by the half of that), a window of 1,024 339 / 309;
+//    128-wide two layers of four agents 414 / 389, 192 + 128 257 / 244, 64-wide 599 / 566.
+//  * Every variant runs without scratch memory, and a test holds the build to that: in a build that spilled, the compiler
+//    put a spill behind a loop over part of the threads but before all were switched on again.  What the tile loop does not
+//    need is therefore worked out again behind it from opaque copies (lane_again, fresh), and nothing in front of it diverges.
 //  * Two forms of launch: one workgroup per unit (layer, agent, KV head, row tile); or, given a workspace, where the units are
 //    fewer than two per compute unit and it gains something (chunk_rules.h), one workgroup per compute unit, each with an
 //    equal contiguous range of all units' tiles.  A unit cut by a range's end leaves un-normalised sums, maxima and
@@ -56,11 +67,14 @@
 // Measured, 256-wide heads, ten agents of 4K-32K tokens, a 512-token chunk, one layer: 1.82 ms = 805 TFLOP/s with shares, 2.0
 // without (16 rows per wave on 16x16x32 instructions, one workgroup per unit: 2.28 ms); one agent of 8,000 tokens 0.11 +
 // 0.02 ms with, 0.315 without (0.364 ms).
-// A wave spends 5,150 clocks on 32 tokens: 2,200 on the scores (163 vector, 17 matrix instructions), 630 on the softmax
-// (100), 1,580 on the product (16 matrix instructions, 75 vector ones for the staging), 750 at the barrier, because the
-// older wave of a SIMD wins its arbitrations and the younger one finishes alone.  Holding the second wave half a step
-// behind by two barriers per step (its vector work against the other's matrix work) cost 15 %: the scores' chain is
-// longer than the product.  Wave priorities by phase, deeper operand reads: no change.
+// A wave issues 214 vector and 33 matrix instructions per 32 tokens (256-wide); the matrix pipe is busy 41 % of the time, a
+// wave waits for LDS or the barrier a third of it.  The clock falls as the pipe fills (2.0 GHz at 37 %, 1.9 at 41 %), so a
+// clock saved is worth about half.  64 rows per wave at one wave per SIMD (half the LDS reads per row, the accumulators
+// in the accumulator file): 3.64e6 clocks against 3.21e6, because one wave issues one instruction of any kind in five clocks.
+// Holding the second wave of a SIMD half a step behind by two barriers per step cost 15 %.  Wave priorities by phase,
+// deeper operand reads: no change.
+#include <utility>
+
 #include "chunk_rules.h"
 #include "q4_device.h"
 #include "q4kv_internal.h"
@@ -170,7 +184,9 @@ struct ChunkStream {
     __device__ __forceinline__ ChunkUnit locate(const ChunkParams &p, int x, int &at, int &tiles, int &n) const
     {
         ChunkUnit u;
-        const int layer_tiles = scalar(pre[p.num_agents]);
+        int agents = p.num_agents;
+        asm volatile("" : "+s"(agents)); // else the address below is kept in a vector register from one part to the next
+        const int layer_tiles = scalar(pre[agents]);
         u.li = x / layer_tiles;
         int r = x - u.li * layer_tiles;
         int lo = 0, hi = p.num_agents - 1; // largest a with pre[a] <= r (every agent has tiles)
@@ -247,6 +263,14 @@ struct Stage {
     static_assert(WORDS % WPT == 0 && ACTIVE <= THREADS, "tile split");
 };
 
+template <bool B> struct Flag { static constexpr bool value = B; };
+template <int I> struct Index { static constexpr int value = I; };
+template <class F, int... I>
+__device__ __forceinline__ void for_each_index(F &&f, std::integer_sequence<int, I...>) { (f(Index<I>()), ...); }
+// f(Index<0>()) ... f(Index<N - 1>()): a loop that is unrolled whatever its size, with indexes that `if constexpr` can see
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F &&f) { for_each_index(f, std::make_integer_sequence<int, N>()); }
+
 // ---------------------------------------------------------------------------------------------- attention
 
 // 32-token pieces of a tile that a wave multiplies at once.  Two give it two independent chains of matrix instructions
@@ -273,7 +297,8 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
     constexpr int NP = chunk_pieces(DK), TILE = chunk_tile(DK, KSPLIT);
     constexpr bool KFULL = chunk_unpacks_keys(DK, KSPLIT);
     // matrix instructions (4 per group) whose query operand stays in registers; the rest lie in LDS
-    constexpr int QREG = DK == 256 ? (KFULL ? 5 : 4) : (DK == 192 ? 8 : 4 * GK);
+    // (as many as leave every variant without scratch memory)
+    constexpr int QREG = DK == 256 ? (KFULL ? 5 : 4) : (DK == 192 ? 7 : (DK == 128 && KSPLIT == 1 ? 5 : 4));
     constexpr int QLDS = 4 * GK - QREG;
     constexpr int QROWS = ROWGROUPS * kWave; // lanes that hold query operands of their own
     typedef Stage<DK, kChunkThreads, TILE> SK; // staging of the K rows of a tile ...
@@ -337,11 +362,17 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         }
         // ---- this lane's query row: column qn of its wave's 32 (both halves of the wave hold the same row).  Asked for before
         // the length and the block table, which are two trips to memory for the first tile (0.3-0.6 us of every call).
-        const int c = u.qt * QPOS + (rg * kRowsWave + qn) / NREP, head = u.kvh * NREP + (rg * kRowsWave + qn) % NREP;
-        const int64_t q_row = (((int64_t)u.li * p.num_agents + u.agent) * p.q_len + min(c, p.q_len - 1)) * p.q_heads + head;
+        // Rows of q and of the output: a uniform place for the row tile and 32 bits per lane from there.
+        const int64_t tile_row = (((int64_t)u.li * p.num_agents + u.agent) * p.q_len + u.qt * QPOS) * p.q_heads + u.kvh * NREP;
+        auto row_in_tile = [&](int pos, int r) __attribute__((always_inline)) {
+            uint32_t heads = p.q_heads;
+            asm volatile("" : "+s"(heads)); // else it is moved to a vector register that is kept for the next part
+            return (uint32_t)pos * heads + (uint32_t)(r % NREP);
+        };
+        const int my_row = rg * kRowsWave + qn;
         uint4 q_raw[GK][4];
         {
-            const uint16_t *src = p.q + q_row * DK + 32 * h;
+            const uint16_t *src = p.q + tile_row * DK + (uint64_t)row_in_tile(min(my_row / NREP, p.q_len - 1 - u.qt * QPOS), my_row) * DK + 32 * h;
 #pragma unroll
             for (int g = 0; g < GK; ++g)
 #pragma unroll
@@ -368,21 +399,31 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         const int v_tok = v_on ? (tid % 16) + 16 * (tid / (16 * SV::TPR)) : 0, v_w0 = v_on ? ((tid / 16) % SV::TPR) * SV::WPT : 0;
         const int k_grp = (k_w0 * 8) / kGroup, v_grp = (v_w0 * 8) / kGroup;
         const uint32_t k_off = 4 * (k_tok * SK::WORDS + k_w0), v_off = 4 * (v_tok * SV::WORDS + v_w0);
-        const uint32_t k_poff = 2 * (k_tok * GK + k_grp), v_poff = 2 * (v_tok * GV + v_grp);
+        // the thread's place, worked out again: kept through the tile loop (or out of this one) it would cost registers
+        auto lane_again = []() __attribute__((always_inline)) {
+            int t = threadIdx.x;
+            asm volatile("" : "+v"(t));
+            return t & (kWave - 1);
+        };
+        // what follows from k_off or v_off is worked out where it is needed: kept, each would take a register through the tile loop
+        auto fresh = [](uint32_t v) __attribute__((always_inline)) {
+            asm volatile("" : "+v"(v));
+            return v;
+        };
+        auto params_at = [&](uint32_t words_at) __attribute__((always_inline)) { return (fresh(words_at) >> 5) * 2; };
         // A block id outside the pool: the tile's (unconditional) loads go to the agent's own first block instead -- to
         // block 0 only if that id is outside the pool as well -- and everything they bring is discarded.
         const int own0 = scalar(table[0]);
         const int fallback_blk = own0 >= 0 && own0 < p.num_blocks ? own0 : 0;
-        auto block_of = [&](int t0) { // fetched well before it is needed: a trip to memory in the tile loop otherwise
-            const int bi = t0 / kBlockTokens;
-            return bi < p.max_blocks ? table[bi] : -1;
-        };
-        auto tile_row0 = [&](int t0, int entry, bool &ok) {
+        // Fetched well before it is needed: a trip to memory in the tile loop otherwise.  No branch (a load that may or may not be
+        // in flight makes the compiler wait for all), and entries past the row are told apart where they are used.
+        auto block_of = [&](int t0) __attribute__((always_inline)) { return table[min(t0 / kBlockTokens, p.max_blocks - 1)]; };
+        auto tile_row0 = [&](int t0, int entry, bool &ok) __attribute__((always_inline)) {
             const int blk = scalar(entry);
-            ok = blk >= 0 && blk < p.num_blocks;
+            ok = blk >= 0 && blk < p.num_blocks && t0 / kBlockTokens < p.max_blocks;
             return (((int64_t)layer * p.num_blocks + (ok ? blk : fallback_blk)) * p.kv_heads + u.kvh) * kBlockTokens + (t0 % kBlockTokens);
         };
-        auto load_words = [&](const uint32_t *src, auto &dst) {
+        auto load_words = [&](const uint32_t *src, auto &dst) __attribute__((always_inline)) {
             constexpr int N = sizeof(dst) / sizeof(uint32_t);
             if constexpr (N % 4 == 0) {
 #pragma unroll
@@ -396,20 +437,22 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             }
         };
         // a uniform base and a 32-bit byte offset per lane
-        auto at = [](auto *base, uint32_t byte_off) {
+        auto at = [](auto *base, uint32_t byte_off) __attribute__((always_inline)) {
             asm volatile("" : "+v"(byte_off)); // else base + offset is kept as one 64-bit pointer per lane and array
             return reinterpret_cast<decltype(base)>(reinterpret_cast<const char *>(base) + byte_off);
         };
         // threads without a share load row 0 of the tile again (a valid address) and never store
-        auto load_k = [&](int64_t row0) {
+        auto load_k = [&](int64_t row0) __attribute__((always_inline)) {
             load_words(at(p.k_codes + row0 * SK::WORDS, k_off), kraw);
-            ksb[0] = *at(p.k_scale + row0 * GK, k_poff);
-            ksb[1] = *at(p.k_bias + row0 * GK, k_poff);
+            const uint32_t params = params_at(k_off);
+            ksb[0] = *at(p.k_scale + row0 * GK, params);
+            ksb[1] = *at(p.k_bias + row0 * GK, params);
         };
-        auto load_v = [&](int64_t row0) {
+        auto load_v = [&](int64_t row0) __attribute__((always_inline)) {
             load_words(at(p.v_codes + row0 * SV::WORDS, v_off), vraw);
-            vsb[0] = *at(p.v_scale + row0 * GV, v_poff);
-            vsb[1] = *at(p.v_bias + row0 * GV, v_poff);
+            const uint32_t params = params_at(v_off);
+            vsb[0] = *at(p.v_scale + row0 * GV, params);
+            vsb[1] = *at(p.v_bias + row0 * GV, params);
         };
         // Dequantization of the staged rows happens one code word (8 dims, one 16-byte store) at a time, so that the
         // matrix loops below can take a word between their steps.  Rows of an unreachable block and rows at or past
@@ -418,7 +461,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         struct RowDequant {
             half2_t s2, s16, b2;
         };
-        auto row_params = [&](const uint32_t (&sb)[2], bool ok) {
+        auto row_params = [&](const uint32_t (&sb)[2], bool ok) __attribute__((always_inline)) {
             RowDequant r;
             // bfloat16 parameters of binary16-range data convert exactly (8 significant bits into 11) unless they are
             // below 2^-14, where the difference is far below what binary16 operands resolve anyway
@@ -431,7 +474,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             r.s16 = r.s2 * half2_t{(half_t)0.0625f, (half_t)0.0625f};
             return r;
         };
-        auto store_word = [&](half_t *dst, uint32_t raw, const RowDequant &r) {
+        auto store_word = [&](half_t *dst, uint32_t raw, const RowDequant &r) __attribute__((always_inline)) {
             const uint32_t w8 = raw >> 8;
             const half2_t v0 = pk_fma(nibbles_lo(raw), r.s2, r.b2);     // dims 0, 4
             const half2_t v1 = pk_fma(nibbles_hi16(raw), r.s16, r.b2);  // dims 1, 5
@@ -439,7 +482,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             const half2_t v3 = pk_fma(nibbles_hi16(w8), r.s16, r.b2);   // dims 3, 7
             *reinterpret_cast<uint4 *>(dst) = make_uint4(half2_to_bits(v0), half2_to_bits(v1), half2_to_bits(v2), half2_to_bits(v3));
         };
-        auto store_codes = [&](uint32_t *dst, const uint32_t (&raw)[SK::WPT]) {
+        auto store_codes = [&](uint32_t *dst, const uint32_t (&raw)[SK::WPT]) __attribute__((always_inline)) {
             if constexpr (SK::WPT % 4 == 0) {
 #pragma unroll
                 for (int w = 0; w < SK::WPT; w += 4)
@@ -449,28 +492,27 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             }
         };
         // the codes of a word as exact small integers: c (dims 0, 4, 2, 6) and 16 c (dims 1, 5, 3, 7)
-        auto store_unpacked = [&](uint32_t *dst, uint32_t raw) {
+        auto store_unpacked = [&](uint32_t *dst, uint32_t raw) __attribute__((always_inline)) {
             const uint32_t w8 = raw >> 8;
             *reinterpret_cast<uint4 *>(dst) = make_uint4(half2_to_bits(nibbles_lo(raw)), half2_to_bits(nibbles_hi16(raw)),
                                                          half2_to_bits(nibbles_lo(w8)), half2_to_bits(nibbles_hi16(w8)));
         };
         // a code word as the A operand of a matrix instruction: the nibbles masked in place are binary16 subnormals
         // c 2^-24 (dims 0, 4, 2, 6 of the word) and 16 c 2^-24 (dims 1, 5, 3, 7)
-        auto code_operand = [&](uint32_t w) {
+        auto code_operand = [&](uint32_t w) __attribute__((always_inline)) {
             const uint32_t w8 = w >> 8;
             return __builtin_bit_cast(half8_t, make_uint4(w & 0x000F000Fu, w & 0x00F000F0u, w8 & 0x000F000Fu, w8 & 0x00F000F0u));
         };
         // scale and bias of a K row go to LDS beside the codes, written by the thread that holds the first word of the
         // group; token t of a 32-token half is score register 4 (2 (t/16) + t%2) + (t%8)/2 of half (t%16)/8 of the wave
         const bool k_params_writer = k_on && (k_w0 * 8) % kGroup == 0;
-        const int ks_dst = k_grp * TILE + (k_tok / kSub) * kSub + ((k_tok % 16) / 8) * 16 +
-                           4 * (2 * ((k_tok % kSub) / 16) + k_tok % 2) + (k_tok % 8) / 2;
-        auto store_k_params = [&](int b, const RowDequant &r) {
-            ks_lds[b][ks_dst] = r.s2.x;
-            kb_lds[b][k_tok * 8 + k_grp] = r.b2.x;
-            kb_lds[b][k_tok * 8 + 4 + k_grp] = r.b2.x;
+        auto store_k_params = [&](int b, const RowDequant &r) __attribute__((always_inline)) {
+            const int at = (int)(fresh(k_off) / 4), tok = at / SK::WORDS, grp = at % SK::WORDS / 8;
+            ks_lds[b][grp * TILE + (tok / kSub) * kSub + ((tok % 16) / 8) * 16 + 4 * (2 * ((tok % kSub) / 16) + tok % 2) + (tok % 8) / 2] = r.s2.x;
+            kb_lds[b][tok * 8 + grp] = r.b2.x;
+            kb_lds[b][tok * 8 + 4 + grp] = r.b2.x;
         };
-        auto row_ok = [&](int t0, int tok, bool ok_tile) { return ok_tile && (t0 + tok < t_end); };
+        auto row_ok = [&](int t0, int tok, bool ok_tile) __attribute__((always_inline)) { return ok_tile && (t0 + tok < t_end); };
         const int k_dst = KFULL ? (k_w0 * TILE + k_tok) * 4 : k_tok * KPITCH + k_w0, v_dst = v_tok * VPITCH + v_w0 * 8;
         constexpr int kWordStep = TILE * 4; // from one word's operands to the next one's
 
@@ -478,11 +520,11 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         const int t_last = part_t0 < part_t1 ? part_t0 + (part_t1 - 1 - part_t0) / TILE * TILE : 0; // start of the last tile
         const int second = min(part_t0 + TILE, t_last);
         bool ok_next = false, ok_cur = false;
-        int64_t row_b = 0;
+        int64_t row_next = 0;
         if (part_t0 < part_t1) { // entry 0 of the table is there already
             const int entry0 = part_t0 < kBlockTokens ? own0 : block_of(part_t0), entry1 = second < kBlockTokens ? own0 : block_of(second);
             const int64_t row_a = tile_row0(part_t0, entry0, ok_cur);
-            row_b = tile_row0(second, entry1, ok_next);
+            row_next = tile_row0(second, entry1, ok_next);
             load_k(row_a);
             load_v(row_a);
         }
@@ -490,9 +532,8 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         // ---- what this lane's row sees, and its query operand
         const bool wave_live = u.qt * QPOS + rg * kRowsWave / NREP < p.q_len; // the wave's first row; wave-uniform
         // rows past the chunk repeat its last position (and are not stored)
-        auto row_sees = [&](int pos) { return n - (p.q_len - 1 - min(pos, p.q_len - 1)); };
-        auto row_hides = [&](int vis) { return window > 0 && vis > window ? vis - window : 0; };
-        const int row_vis = row_sees(c), row_first = row_hides(row_vis);
+        auto row_sees = [&](int pos) __attribute__((always_inline)) { return n - (p.q_len - 1 - min(pos, p.q_len - 1)); };
+        auto row_hides = [&](int vis) __attribute__((always_inline)) { return window > 0 && vis > window ? vis - window : 0; };
         // tokens inside [all_first, all_vis) are visible to every row of this wave and need no masks
         const int all_vis = row_sees(u.qt * QPOS + rg * kRowsWave / NREP);
         const int all_first = row_hides(row_sees(u.qt * QPOS + (rg * kRowsWave + kRowsWave - 1) / NREP));
@@ -534,9 +575,9 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         for (int d = 0; d < DTILES; ++d)
 #pragma unroll
             for (int i = 0; i < 16; ++i) o_acc[d][i] = 0.0f;
-        // m_run: the reference the exponentials are taken against.  It moves only when a tile's maximum exceeds it by
-        // more than kSlack (log2 units), so the accumulators are rescaled a few times per row, not once per tile.
-        constexpr float kSlack = 3.0f;
+        // m_run: the reference the exponentials are taken against.  It moves only when a tile's maximum exceeds some row's by
+        // more than kSlack (log2 units), so the accumulators are rescaled a few times per unit, not once per tile.
+        constexpr float kSlack = 5.0f; // 8: 2 % faster, but the error against 64 bits grows from 3.3e-4 to 3.5e-4; 3: 2 % slower
         float m_run = kNegBig, l_run = 0.0f; // l_run: this lane's tokens only
 
         // operand reads: K row of M row qn; V_hat by the transposing read (token 8 h + 2 e (+ 1), dims 16 (lane/16 % 2) + 4 c)
@@ -545,60 +586,35 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         constexpr int kPiece = KFULL ? kSub * 4 : kSub * KPITCH; // from one 32-token piece to the next
         const int v_lane = (8 * h + 2 * ((lane % 16) / 4)) * VPITCH + 16 * ((lane / 16) % 2) + 4 * (lane % 4);
 
-        // One barrier per tile: tile i is multiplied out of buffer i % 2 while tile i + 1 (already in registers) is
-        // unpacked into the other buffer and tile i + 2 is fetched.
-        int buf = 0;
-        if (part_t0 < part_t1) {
-            const RowDequant kr = row_params(ksb, row_ok(part_t0, k_tok, ok_cur));
-            const RowDequant vr = row_params(vsb, row_ok(part_t0, v_tok, ok_cur));
-            if constexpr (KFULL) {
+        // One barrier per tile.  Step i takes the scores of tile i and, while its softmax is worked out, the product of tile
+        // i - 1; it stages V of tile i and K of tile i + 1 and asks for the tiles behind those.
+        int buf = 0, t0 = part_t0, entry_ahead = -1;
+        const int sub = my_sub * NP; // this wave's NP pieces of 32 tokens
+        float16_t zero;
+        half8_t pt[2 * NP]; // P^T of the tile before, [16-token step]
 #pragma unroll
-                for (int w = 0; w < SK::WPT; ++w)
-                    if (k_on) store_unpacked(k_lds[0] + k_dst + w * kWordStep, kraw[w]);
-            } else if (k_on) {
-                store_codes(k_lds[0] + k_dst, kraw);
-            }
-            if (k_params_writer) store_k_params(0, kr);
-            if (v_on) {
-#pragma unroll
-                for (int w = 0; w < SV::WPT; ++w) store_word(v_lds[0] + v_dst + 8 * w, vraw[w], vr);
-            }
-            load_k(row_b);
-            load_v(row_b);
-        }
-        __syncthreads();
-        for (int t0 = part_t0; t0 < part_t1; t0 += TILE) {
-            const uint32_t *k_cur = k_lds[buf];
-            const half_t *v_cur = v_lds[buf], *ks_cur = ks_lds[buf], *kb_cur = kb_lds[buf];
-            const bool ok_this = ok_cur;
-            const bool more = t0 + TILE < part_t1;
-            const int t_ahead = min(t0 + 2 * TILE, t_last), entry_ahead = block_of(t_ahead); // past the end: the last tile again, never used
-            int64_t row_ahead = 0;
-            bool ok_ahead = false;
+        for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
 
-            // this wave's NP pieces of 32 tokens
-            const int sub = my_sub * NP, ts = t0 + kSub * sub;
-            const uint32_t *k_row = k_cur + sub * kPiece + k_lane;
-            const half_t *ks_row = ks_cur + sub * kSub + 16 * h;
-            // ---- S^T = sum_g s_g (C_g Q_g^T) + b Qsum^T in binary32, in units of kUnit
-            constexpr float kUnit = KFULL ? 1.0f : 0x1p-24f;
-            float16_t zero;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
-            auto q_operand = [&](int k) { // matrix instruction k = 4 group + i
-                if (k < QREG) return qop[k < QREG ? k : 0];
-                return q_lds[(k - QREG) * QROWS + rg * kWave + lane];
+        // ---- S^T = sum_g s_g (C_g Q_g^T) + b Qsum^T in binary32, in units of kUnit
+        constexpr float kUnit = KFULL ? 1.0f : 0x1p-24f;
+        auto scores = [&](float16_t (&st)[NP], bool more, int64_t row_ahead) __attribute__((always_inline)) {
+            const uint32_t *k_row = k_lds[buf] + sub * kPiece + k_lane;
+            const half_t *ks_row = ks_lds[buf] + sub * kSub + 16 * (lane_again() / 32);
+            const half_t *kb_row = kb_lds[buf] + (sub * kSub + (KFULL ? (int)(fresh(k_lane) / 4) % kSub : m_token)) * 8;
+            auto q_operand = [&](auto index) __attribute__((always_inline)) { // matrix instruction 4 group + i
+                constexpr int k = index.value;
+                if constexpr (k < QREG) return qop[k];
+                else return q_lds[(k - QREG) * QROWS + rg * kWave + lane];
             };
-            float16_t st[NP];
             // this lane's token: the operands of the kKeysAhead matrix instructions to come, or the code words 8 g + 4 h .. + 3
             constexpr int kKeysAhead = 2;
             uint4 words[NP], keys[kKeysAhead][NP];
-            auto load_keys = [&](int k, int n) { // matrix instruction k of piece n
+            auto load_keys = [&](int k, int n) __attribute__((always_inline)) { // matrix instruction k of piece n
                 return *reinterpret_cast<const uint4 *>(k_row + n * kPiece + (8 * (k / 4) + k % 4) * kWordStep);
             };
 #pragma unroll
             for (int n = 0; n < NP; ++n) {
-                const half8_t ba = *reinterpret_cast<const half8_t *>(kb_cur + ((sub + n) * kSub + m_token) * 8);
+                const half8_t ba = *reinterpret_cast<const half8_t *>(kb_row + n * kSub * 8);
                 st[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ba, qsop, zero, 0, 0, 0);
             }
 #pragma unroll
@@ -610,176 +626,201 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                     words[n] = *reinterpret_cast<const uint4 *>(k_row + n * kPiece);
                 }
             }
-            half8_t qk = q_operand(0);
-#pragma unroll
-            for (int g = 0; g < GK; ++g) {
-                uint32_t w[NP][4];
-                float16_t d[NP];
-                uint4 sc[NP], sc1[NP]; // scales of the lane's first and last 8 scores
-#pragma unroll
-                for (int n = 0; n < NP; ++n) {
-                    if constexpr (!KFULL) {
-                        w[n][0] = words[n].x; w[n][1] = words[n].y; w[n][2] = words[n].z; w[n][3] = words[n].w;
-                    }
-                    d[n] = zero;
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int k = 4 * g + i;
-                    const half8_t qi = qk;
-                    if (k + 1 < 4 * GK) qk = q_operand(k + 1);
+            half8_t qk = q_operand(Index<0>());
+            const RowDequant kr = row_params(ksb, row_ok(t0 + TILE, (int)(fresh(k_off) / (4 * SK::WORDS)), ok_next && more));
+            const RowDequant vr = row_params(vsb, row_ok(t0, (int)(fresh(v_off) / (4 * SV::WORDS)), ok_cur));
+            if constexpr (!KFULL) {
+                if (k_on) store_codes(k_lds[buf ^ 1] + k_dst, kraw);
+            }
+            if (k_params_writer) store_k_params(buf ^ 1, kr);
+            float16_t d[NP];
+            uint4 sc[NP], sc1[NP]; // scales of the lane's first and last 8 scores
+            uint32_t w4[NP][4];
+            unrolled<4 * GK>([&](auto index) __attribute__((always_inline)) {
+                constexpr int k = index.value, g = k / 4, i = k % 4;
+                if constexpr (i == 0) {
 #pragma unroll
                     for (int n = 0; n < NP; ++n) {
-                        if (i == 2) sc[n] = *reinterpret_cast<const uint4 *>(ks_row + g * TILE + n * kSub);
-                        if (i == 3) sc1[n] = *reinterpret_cast<const uint4 *>(ks_row + g * TILE + n * kSub + 8);
-                        half8_t a;
-                        if constexpr (KFULL) {
-                            a = __builtin_bit_cast(half8_t, keys[k % kKeysAhead][n]);
-                            if (k + kKeysAhead < 4 * GK) keys[k % kKeysAhead][n] = load_keys(k + kKeysAhead, n);
-                        } else {
-                            if (i == 3 && g + 1 < GK) words[n] = *reinterpret_cast<const uint4 *>(k_row + n * kPiece + 8 * (g + 1));
-                            a = code_operand(w[n][i]);
+                        if constexpr (!KFULL) {
+                            w4[n][0] = words[n].x; w4[n][1] = words[n].y; w4[n][2] = words[n].z; w4[n][3] = words[n].w;
                         }
-                        d[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, qi, d[n], 0, 0, 0);
+                        d[n] = zero;
+                    }
+                }
+                const half8_t qi = qk;
+                if constexpr (k + 1 < 4 * GK) qk = q_operand(Index<k + 1>());
+#pragma unroll
+                for (int n = 0; n < NP; ++n) {
+                    if constexpr (i == 2) sc[n] = *reinterpret_cast<const uint4 *>(ks_row + g * TILE + n * kSub);
+                    if constexpr (i == 3) sc1[n] = *reinterpret_cast<const uint4 *>(ks_row + g * TILE + n * kSub + 8);
+                    half8_t a;
+                    if constexpr (KFULL) {
+                        a = __builtin_bit_cast(half8_t, keys[k % kKeysAhead][n]);
+                        if constexpr (k + kKeysAhead < 4 * GK) keys[k % kKeysAhead][n] = load_keys(k + kKeysAhead, n);
+                    } else {
+                        if constexpr (i == 3 && g + 1 < GK) words[n] = *reinterpret_cast<const uint4 *>(k_row + n * kPiece + 8 * (g + 1));
+                        a = code_operand(w4[n][i]);
+                    }
+                    d[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, qi, d[n], 0, 0, 0);
+                }
+                // the next tile's K, then this one's V, a word at a time; behind each its registers are free for the tile after that
+                constexpr int kWords = (KFULL ? SK::WPT : 0) + SV::WPT, kFirstV = kWords - SV::WPT;
+                unrolled<kWords>([&](auto word) __attribute__((always_inline)) {
+                    constexpr int w = word.value;
+                    if constexpr (w * 4 * GK / kWords == k) {
+                        if constexpr (w < kFirstV) {
+                            if (k_on) store_unpacked(k_lds[buf ^ 1] + k_dst + w * kWordStep, kraw[w]);
+                        } else {
+                            if (v_on) store_word(v_lds[buf] + v_dst + 8 * (w - kFirstV), vraw[w - kFirstV], vr);
+                        }
+                    }
+                });
+                constexpr int kAfterK = kFirstV > 0 ? (kFirstV - 1) * 4 * GK / kWords : 0;
+                if constexpr (k == kAfterK) load_k(row_ahead);
+                if constexpr (k == (kWords - 1) * 4 * GK / kWords) {
+                    load_v(row_next);
+                    entry_ahead = block_of(min(t0 + 3 * TILE, t_last)); // for the next step: a trip to memory in every one otherwise
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (i == 3) {
+#pragma unroll
+                    for (int n = 0; n < NP; ++n) {
+                        const uint32_t s8[8] = {sc[n].x, sc[n].y, sc[n].z, sc[n].w, sc1[n].x, sc1[n].y, sc1[n].z, sc1[n].w};
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) {
+                            const half2_t sh = bits_to_half2(s8[e / 2]);
+                            const float prev = g == 0 ? st[n][e] * kUnit : st[n][e]; // the bias term enters in the products' unit
+                            st[n][e] = fmaf((float)((e & 1) ? sh.y : sh.x), d[n][e], prev);
+                        }
+                        // pinned: else the multiplies of all groups sink to the scores' first use and every product stays live
+#pragma unroll
+                        for (int e = 0; e < 16; e += 8)
+                            asm volatile("" : "+v"(st[n][e]), "+v"(st[n][e + 1]), "+v"(st[n][e + 2]), "+v"(st[n][e + 3]), "+v"(st[n][e + 4]),
+                                         "+v"(st[n][e + 5]), "+v"(st[n][e + 6]), "+v"(st[n][e + 7]));
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
-#pragma unroll
-                for (int n = 0; n < NP; ++n) {
-                    const uint32_t s8[8] = {sc[n].x, sc[n].y, sc[n].z, sc[n].w, sc1[n].x, sc1[n].y, sc1[n].z, sc1[n].w};
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const half2_t sh = bits_to_half2(s8[i / 2]);
-                        const float prev = g == 0 ? st[n][i] * kUnit : st[n][i]; // the bias term enters in the products' unit
-                        st[n][i] = fmaf((float)((i & 1) ? sh.y : sh.x), d[n][i], prev);
-                    }
-                    // pinned: else the multiplies of all groups sink to the scores' first use and every product stays live
-#pragma unroll
-                    for (int i = 0; i < 16; i += 8)
-                        asm volatile("" : "+v"(st[n][i]), "+v"(st[n][i + 1]), "+v"(st[n][i + 2]), "+v"(st[n][i + 3]), "+v"(st[n][i + 4]),
-                                     "+v"(st[n][i + 5]), "+v"(st[n][i + 6]), "+v"(st[n][i + 7]));
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            const float zscale = p.score_scale / kUnit;
+            });
+        };
 
-            // ---- online softmax per query row (lane column), then P^T in binary16 as the next B operand
-            const bool masked = !(ok_this && ts >= all_first && ts + NP * kSub <= all_vis); // wave-uniform
-            const bool general = masked || !(p.score_scale > 0.0f); // the path that assumes nothing
-            float mx = kNegBig;
-            if (general) {
-#pragma unroll
-                for (int n = 0; n < NP; ++n)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        float z = st[n][i] * zscale;
-                        const int t = ts + kSub * n + 16 * (i / 8) + 8 * h + 2 * (i % 4) + ((i / 4) & 1);
-                        if (!(ok_this && t < row_vis && t >= row_first)) z = kNegBig;
-                        st[n][i] = z;
-                        mx = fmaxf(mx, z);
-                    }
-            } else { // interior, positive scale: the maximum can be taken before the scale is applied
-#pragma unroll
-                for (int n = 0; n < NP; ++n)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, st[n][i]);
-                mx *= zscale;
-            }
-            mx = xor32_max(mx); // the row's tokens live in two lanes
-            const bool moved = mx > m_run + kSlack;
-            const float m_new = moved ? mx : m_run;
-            float sum = 0.0f;
-            if (general) {
-#pragma unroll
-                for (int n = 0; n < NP; ++n)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        float pr = __builtin_amdgcn_exp2f(st[n][i] - m_new);
-                        pr = st[n][i] > 0.5f * kNegBig ? pr : 0.0f; // also a row with nothing visible yet
-                        st[n][i] = pr;
-                        sum += pr;
-                    }
-            } else {
-#pragma unroll
-                for (int n = 0; n < NP; ++n)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const float pr = __builtin_amdgcn_exp2f(fmaf(st[n][i], zscale, -m_new));
-                        st[n][i] = pr;
-                        sum += pr;
-                    }
-            }
-            half8_t pt[2 * NP]; // [16-token step]
-#pragma unroll
-            for (int s = 0; s < 2 * NP; ++s) {
-                const float16_t &v = st[s / 2];
-                const int o = 8 * (s % 2);
-                pt[s] = half8_t{(half_t)v[o], (half_t)v[o + 1], (half_t)v[o + 2], (half_t)v[o + 3],
-                                (half_t)v[o + 4], (half_t)v[o + 5], (half_t)v[o + 6], (half_t)v[o + 7]};
-            }
-            if (__builtin_amdgcn_ballot_w64(moved) != 0ull) { // rare after a row's first tiles
-                const float alpha = moved ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.0f;
-                l_run *= alpha;
-#pragma unroll
-                for (int d = 0; d < DTILES; ++d)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) o_acc[d][i] *= alpha;
-            }
-            m_run = m_new;
-            l_run += sum;
-
-            // ---- O^T += V_hat^T P^T, the operand reads one step ahead; the next tile's V rows are dequantized
-            // between the steps
-            const half_t *v_row = v_cur + sub * kSub * VPITCH + v_lane;
+        // ---- O^T += V_hat^T P^T of the tile before , the operand reads ahead; between the matrix instructions the online
+        // softmax of the scores per query row (lane column) and their P^T (SOFT), which the next step multiplies.  SCALED: the
+        // scores are in log2 units already.
+        auto product = [&](auto soft, float16_t (&st)[NP], float zs) __attribute__((always_inline)) {
+            constexpr bool SOFT = soft.value;
             constexpr int kPerTile = 2 * NP, kSteps = kPerTile * DTILES, kAhead = 2;
-            auto load_va = [&](int step) { // step = 2 NP * dim tile + 16-token step
+            const half_t *v_row = v_lds[buf ^ 1] + sub * kSub * VPITCH + fresh(v_lane);
+            auto load_va = [&](int step) __attribute__((always_inline)) { // step = 2 NP * dim tile + 16-token step
                 const half_t *src = v_row + (step % kPerTile) * 16 * VPITCH + (step / kPerTile) * 32;
                 const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)src);
                 const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(src + VPITCH));
                 return __builtin_bit_cast(half8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
             };
-            // The next tile's words were asked for a tile ago: they are not touched before this point, so that memory has
-            // a whole tile's time to answer.  Past the last tile the staging stores zeros into the idle buffer:
-            // straight-line code keeps the mix.
-            const RowDequant vr = row_params(vsb, row_ok(t0 + TILE, v_tok, ok_next && more));
             half8_t va[kAhead];
 #pragma unroll
             for (int s = 0; s < kAhead; ++s) va[s] = load_va(s);
+            float mx = kNegBig, m_new = 0.0f, sum = 0.0f;
+            bool moved = false;
+            uint32_t next[8 * NP];
+            auto item = [&](auto index) __attribute__((always_inline)) {
+                constexpr int j = index.value;
+                if constexpr (j < 2 * NP) { // the maximum, before the scale is applied (which is positive)
 #pragma unroll
-            for (int s = 0; s < kSteps; ++s) {
-                const half8_t a = va[s % kAhead];
-                if (s + kAhead < kSteps) va[s % kAhead] = load_va(s + kAhead);
-                o_acc[s / kPerTile] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pt[s % kPerTile], o_acc[s / kPerTile], 0, 0, 0);
-                // the next tile's K, then its V, a word at a time; behind each the registers are free for the tile after that
-                if (s == 0) {
-                    const RowDequant kr = row_params(ksb, row_ok(t0 + TILE, k_tok, ok_next && more));
-                    if constexpr (!KFULL) {
-                        if (k_on) store_codes(k_lds[buf ^ 1] + k_dst, kraw);
-                    }
-                    if (k_params_writer) store_k_params(buf ^ 1, kr);
-                    row_ahead = tile_row0(t_ahead, entry_ahead, ok_ahead);
+                    for (int i = 0; i < 8; ++i) mx = fmaxf(mx, st[j / 2][8 * (j % 2) + i]);
+                } else if constexpr (j == 2 * NP) {
+                    mx = xor32_max(mx * zs); // the row's tokens live in two lanes
+                    moved = __builtin_amdgcn_ballot_w64(mx > m_run + kSlack) != 0ull;
+                    m_new = moved ? fmaxf(m_run, mx) : m_run;
+                } else {
+                    constexpr int e = j - 2 * NP - 1;
+                    const float a = __builtin_amdgcn_exp2f(fmaf(st[e / 8][2 * (e % 8)], zs, -m_new));
+                    const float b = __builtin_amdgcn_exp2f(fmaf(st[e / 8][2 * (e % 8) + 1], zs, -m_new));
+                    const half2_t w = half2_t{(half_t)a, (half_t)b};
+                    sum = __builtin_amdgcn_fdot2(w, half2_t{(half_t)1.0f, (half_t)1.0f}, sum, false); // of the rounded weights
+                    next[e] = half2_to_bits(w);
+                    asm volatile("" : "+v"(next[e]), "+v"(sum)); // else the additions are put off and every weight stays live
                 }
-                constexpr int kWords = (KFULL ? SK::WPT : 0) + SV::WPT, kFirstV = kWords - SV::WPT;
-                constexpr int kAfterK = kFirstV > 0 ? (kFirstV - 1) * kSteps / kWords + 1 : 0;
-                constexpr int kAfterV = (kWords - 1) * kSteps / kWords + 1;
-                static_assert(kAfterV < kSteps, "room for every word and the loads behind it");
-#pragma unroll
-                for (int w = 0; w < kWords; ++w)
-                    if (w * kSteps / kWords == s) {
-                        if (w < kFirstV) {
-                            if (k_on) store_unpacked(k_lds[buf ^ 1] + k_dst + w * kWordStep, kraw[w < kFirstV ? w : 0]);
-                        } else if (v_on) {
-                            store_word(v_lds[buf ^ 1] + v_dst + 8 * (w - kFirstV), vraw[w < kFirstV ? 0 : w - kFirstV], vr);
-                        }
-                    }
-                if (s == kAfterK) load_k(row_ahead);
-                if (s == kAfterV) load_v(row_ahead);
+            };
+            constexpr int kItems = 10 * NP + 1;
+            unrolled<kSteps>([&](auto index) __attribute__((always_inline)) {
+                constexpr int s = index.value;
+                const half8_t a = va[s % kAhead];
+                if constexpr (s + kAhead < kSteps) va[s % kAhead] = load_va(s + kAhead);
+                o_acc[s / kPerTile] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pt[s % kPerTile], o_acc[s / kPerTile], 0, 0, 0);
+                if constexpr (SOFT) {
+                    constexpr int first = (s * kItems + kSteps - 1) / kSteps, last = ((s + 1) * kItems + kSteps - 1) / kSteps;
+                    unrolled<last - first>([&](auto j) __attribute__((always_inline)) { item(Index<first + j.value>()); });
+                }
                 __builtin_amdgcn_sched_barrier(0);
+            });
+            if constexpr (SOFT) {
+                if (__builtin_expect(moved, 0)) { // rare after a unit's first tiles
+                    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+                    l_run *= alpha;
+#pragma unroll
+                    for (int d = 0; d < DTILES; ++d)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) o_acc[d][i] *= alpha;
+                }
+                m_run = m_new;
+                l_run += sum;
+#pragma unroll
+                for (int s = 0; s < 2 * NP; ++s)
+                    pt[s] = __builtin_bit_cast(half8_t, make_uint4(next[4 * s], next[4 * s + 1], next[4 * s + 2], next[4 * s + 3]));
             }
-            ok_cur = ok_next;
-            ok_next = ok_ahead;
-            __syncthreads(); // every wave is done with this buffer and has filled its part of the other
-            buf ^= 1;
+        };
+        if (part_t0 < part_t1) {
+            const RowDequant kr = row_params(ksb, row_ok(part_t0, k_tok, ok_cur));
+            if constexpr (KFULL) {
+#pragma unroll
+                for (int w = 0; w < SK::WPT; ++w)
+                    if (k_on) store_unpacked(k_lds[0] + k_dst + w * kWordStep, kraw[w]);
+            } else if (k_on) {
+                store_codes(k_lds[0] + k_dst, kraw);
+            }
+            if (k_params_writer) store_k_params(0, kr);
+            load_k(row_next);
+            entry_ahead = block_of(min(part_t0 + 2 * TILE, t_last));
+            // the first step's product is that of no tile: zeros times zeros
+            constexpr int kZeros = TILE * VPITCH / 8; // 16 bytes each; the last threads repeat the last one
+#pragma unroll
+            for (int i = 0; i < kZeros; i += kChunkThreads)
+                reinterpret_cast<uint4 *>(&v_lds[1][0])[min(i + tid, kZeros - 1)] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int s = 0; s < 2 * NP; ++s) pt[s] = __builtin_bit_cast(half8_t, make_uint4(0u, 0u, 0u, 0u));
+            __syncthreads();
+            do {
+                const int ts = t0 + kSub * sub;
+                const int t_ahead = min(t0 + 2 * TILE, t_last); // past the end: the last tile again, never used
+                bool ok_ahead;
+                const int64_t row_ahead = tile_row0(t_ahead, entry_ahead, ok_ahead);
+                float16_t st[NP];
+                scores(st, t0 + TILE < part_t1, row_ahead);
+                // tokens that every row of the wave sees need no masks; the path with masks assumes nothing of the scale
+                float zs = p.score_scale / kUnit;
+                if (__builtin_expect(!(ok_cur && ts >= all_first && ts + NP * kSub <= all_vis && p.score_scale > 0.0f), 0)) {
+                    const int ln = lane_again();
+                    const int row_vis = row_sees(u.qt * QPOS + (rg * kRowsWave + ln % 32) / NREP), row_first = row_hides(row_vis);
+#pragma unroll
+                    for (int n = 0; n < NP; ++n)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) {
+                            const int t = ts + kSub * n + 16 * (i / 8) + 8 * (ln / 32) + 2 * (i % 4) + ((i / 4) & 1);
+                            const float z = st[n][i] * zs;
+                            st[n][i] = ok_cur && t < row_vis && t >= row_first ? z : 2.0f * kNegBig; // a weight of 0 against any reference
+                        }
+                    zs = 1.0f;
+                }
+                product(Flag<true>(), st, zs);
+                ok_cur = ok_next;
+                ok_next = ok_ahead;
+                row_next = row_ahead;
+                t0 += TILE;
+                __syncthreads(); // every wave is done with these buffers and has filled its part of the others
+                buf ^= 1;
+            } while (t0 < part_t1);
+            float16_t none[NP];
+            product(Flag<false>(), none, 0.0f);
         }
 
         float l_tot = xor32_sum(l_run);
@@ -789,16 +830,17 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             constexpr int MT = (int)(2 * TILE * VPITCH * sizeof(half_t) / (ROWGROUPS * kWave * 16 * sizeof(float))) < DTILES
                                    ? (int)(2 * TILE * VPITCH * sizeof(half_t) / (ROWGROUPS * kWave * 16 * sizeof(float))) : DTILES;
             static_assert(MT >= 1, "room for one dim tile");
+            const int ln = lane_again();
             float *ml = reinterpret_cast<float *>(&k_lds[0][0]);
             float *xch = reinterpret_cast<float *>(&v_lds[0][0]);
             if (my_sub == 1 && wave_live) {
-                ml[(rg * 2) * kWave + lane] = m_run;
-                ml[(rg * 2 + 1) * kWave + lane] = l_tot;
+                ml[(rg * 2) * kWave + ln] = m_run;
+                ml[(rg * 2 + 1) * kWave + ln] = l_tot;
             }
             __syncthreads();
             float w_lo = 1.0f, w_hi = 0.0f;
             if (my_sub == 0 && wave_live) {
-                const float m_hi = ml[(rg * 2) * kWave + lane], l_hi = ml[(rg * 2 + 1) * kWave + lane];
+                const float m_hi = ml[(rg * 2) * kWave + ln], l_hi = ml[(rg * 2 + 1) * kWave + ln];
                 const float m_new = fmaxf(m_run, m_hi);
                 w_lo = __builtin_amdgcn_exp2f(m_run - m_new);
                 w_hi = __builtin_amdgcn_exp2f(m_hi - m_new);
@@ -812,7 +854,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                     for (int d = d0; d < d0 + MT && d < DTILES; ++d)
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
-                            *reinterpret_cast<float4_t *>(xch + (((rg * MT + d - d0) * 4 + j) * kWave + lane) * 4) =
+                            *reinterpret_cast<float4_t *>(xch + (((rg * MT + d - d0) * 4 + j) * kWave + ln) * 4) =
                                 float4_t{o_acc[d][4 * j], o_acc[d][4 * j + 1], o_acc[d][4 * j + 2], o_acc[d][4 * j + 3]};
                 }
                 __syncthreads();
@@ -821,7 +863,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                     for (int d = d0; d < d0 + MT && d < DTILES; ++d)
 #pragma unroll
                         for (int j = 0; j < 4; ++j) {
-                            const float4_t v = *reinterpret_cast<const float4_t *>(xch + (((rg * MT + d - d0) * 4 + j) * kWave + lane) * 4);
+                            const float4_t v = *reinterpret_cast<const float4_t *>(xch + (((rg * MT + d - d0) * 4 + j) * kWave + ln) * 4);
 #pragma unroll
                             for (int e = 0; e < 4; ++e) o_acc[d][4 * j + e] = fmaf(v[e], w_hi, o_acc[d][4 * j + e] * w_lo);
                         }
@@ -834,13 +876,10 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         if (wave_live && my_sub == 0) {
             if (whole) { // ---- normalise and store
                 const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
-                // the row's place again, from values the compiler does not know to be the same: kept through the tile
-                // loop they would cost registers that it does not have
-                int ln = threadIdx.x & (kWave - 1);
-                asm volatile("" : "+v"(ln));
-                const int r = rg * kRowsWave + ln % 32, pos = u.qt * QPOS + r / NREP;
-                const bool store = pos < p.q_len;
-                uint16_t *dst = p.out + ((((int64_t)u.li * p.num_agents + u.agent) * p.q_len + pos) * p.q_heads + u.kvh * NREP + r % NREP) * DV;
+                const int ln = lane_again();
+                const int r = rg * kRowsWave + ln % 32;
+                const bool store = u.qt * QPOS + r / NREP < p.q_len;
+                uint16_t *dst = p.out + tile_row * DV + (uint64_t)row_in_tile(r / NREP, r) * DV;
 #pragma unroll
                 for (int d = 0; d < DTILES; ++d)
 #pragma unroll
@@ -851,14 +890,15 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                     }
             } else { // ---- this workgroup's part of a shared unit, un-normalised
                 const int64_t rec = ((int64_t)worker * 2 + (x - begin > range_begin ? 1 : 0)) * ROWGROUPS + rg;
-                float *acc = p.part_acc + (rec * (DV / 8) * kWave + lane) * 4;
+                const int ln = lane_again();
+                float *acc = p.part_acc + (rec * (DV / 8) * kWave + ln) * 4;
 #pragma unroll
                 for (int d = 0; d < DTILES; ++d)
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
                         *reinterpret_cast<float4_t *>(acc + (d * 4 + j) * kWave * 4) =
                             float4_t{o_acc[d][4 * j], o_acc[d][4 * j + 1], o_acc[d][4 * j + 2], o_acc[d][4 * j + 3]};
-                if (h == 0) *reinterpret_cast<float2 *>(p.part_ml + (rec * kRowsWave + qn) * 2) = make_float2(m_run, l_tot);
+                if (ln < 32) *reinterpret_cast<float2 *>(p.part_ml + (rec * kRowsWave + ln) * 2) = make_float2(m_run, l_tot);
             }
         }
         if (SHARES && threadIdx.x == 0 && begin == 0 && part_end < tiles) {
@@ -870,6 +910,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             s->token_row = ((int64_t)u.li * p.num_agents + u.agent) * p.q_len;
         }
         x += SHARES ? part_end - begin : 1;
+        if constexpr (SHARES) __syncthreads(); // the last product still reads V_hat where the next part begins with zeros
     }
 }
 

@@ -124,3 +124,25 @@ def test_the_gpu_tests_of_256_rows_take_256_rows(rules):
     assert all(r[3] == 1 for r in got)
     got = rules([call(c, 0) for c in WIDE_ALONE])
     assert [r[0] for r in got] == [256] * len(WIDE_ALONE)
+
+
+def test_chunk_kernels_need_no_scratch_memory():
+    """The kernel metadata of the built library: every chunk attention kernel keeps all it has in registers (the header of
+    csrc/chunk_attention.hip tells what a spill did)."""
+    import struct
+
+    import msgpack
+
+    from paper_2603_04428_amd import build
+
+    data = open(build.LIB, "rb").read()
+    scratch, at = {}, data.find(b"AMDGPU\0\0")
+    while at >= 0:
+        name_size, size, kind = struct.unpack_from("<III", data, at - 12)
+        if name_size == 7 and kind == 32:   # an ELF note of kernel metadata
+            for kernel in msgpack.unpackb(data[at + 8:at + 8 + size])["amdhsa.kernels"]:
+                scratch[kernel[".name"]] = kernel[".private_segment_fixed_size"]
+        at = data.find(b"AMDGPU\0\0", at + 1)
+    chunk = {k: v for k, v in scratch.items() if "chunk_attention_kernel" in k}
+    assert len(chunk) == 128                # 4 widths, 4 head groupings, 2 row counts, with and without shares, 2 formats
+    assert not {k: v for k, v in chunk.items() if v}

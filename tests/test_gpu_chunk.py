@@ -62,6 +62,21 @@ def test_chunk_matches_oracle_small(shape):
     assert_close(got, want, f"{shape}")
 
 
+@pytest.mark.parametrize("shape", [(4, 2, 256), (4, 4, (192, 128)), (8, 2, 128), (8, 1, 64)])
+def test_chunk_around_the_edges_of_its_tiles(shape):
+    """Units of one, two and a few tiles of 32, 64 and 128 tokens, and one token more or less: the product runs a tile
+    behind the scores, so the first, the second and the last tile of a unit each take a turn of their own."""
+    Hq, Hkv, D = shape
+    Dk, Dv = D if isinstance(D, tuple) else (D, D)
+    for C in (2, 40):                                        # tokens seen by the last row: 2 or 40 more than these
+        lens = (0, 29, 30, 31, 61, 62, 63, 125, 126, 127, 191, 254) if C == 2 else (0, 24, 88, 89, 216, 473)
+        w = synth.small(52, 1, Hq, Hkv, Dk, Dv, False, lens, q_len=C)
+        got, _ = append_chunk_and_attend(w)
+        ospec, okp, ovp, otable = host_cache(w)
+        want = oracle.attention(ospec, okp, ovp, w.q_all().numpy(), otable, w.final_lens(), w.sm_scale)
+        assert_close(got, want, f"{shape} {C}")
+
+
 @pytest.mark.parametrize("seed", [44, 45, 46, 47, 48, 49])
 def test_chunk_tolerance_does_not_depend_on_the_draw(seed):
     """Short contexts with the generator's large key channels make a softmax that a few keys dominate: the case in
