@@ -316,7 +316,6 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
     __shared__ int s_pre[kMaxStreamAgents + 1], s_len[kMaxStreamAgents];
 
     const int wave = scalar(threadIdx.x / kWave);
-    const int rg = wave % ROWGROUPS, my_sub = wave / ROWGROUPS; // row group; with KSPLIT 2 the half of a tile's tokens
 
     // ---- the range of tiles this workgroup takes: whole unit blockIdx (consecutive workgroups of one XCD share a KV
     // head), or an equal share of all tiles (consecutive shares on one XCD)
@@ -360,6 +359,12 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             u.li = unit / (p.kv_heads * p.num_agents);
             part_end = 1;
         }
+        // Row group; with KSPLIT 2 the half of a tile's tokens.  Waves w and w + 4 share a SIMD.  They are the two halves of one row
+        // group where all groups have rows of the chunk, else neighbours are, so that the groups that have some spread over all
+        // SIMDs.  Neighbours / halves w and w + 4: 2 tokens of two agents of up to 5,000, 192 + 128-wide, four layers 124 / 141
+        // us, 9 of four of 2,600, 256-wide, five layers 199 / 221; 70 of four, 128-wide, all live but in the last tile, four layers 199 / 195.
+        const bool all_live = KSPLIT == 1 || u.qt * QPOS + (ROWGROUPS - 1) * kRowsWave / NREP < p.q_len;
+        const int rg = all_live ? wave % ROWGROUPS : wave / KSPLIT, my_sub = all_live ? wave / ROWGROUPS : wave % KSPLIT;
         // ---- this lane's query row: column qn of its wave's 32 (both halves of the wave hold the same row).  Asked for before
         // the length and the block table, which are two trips to memory for the first tile (0.3-0.6 us of every call).
         // Rows of q and of the output: a uniform place for the row tile and 32 bits per lane from there.
@@ -577,7 +582,10 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             for (int i = 0; i < 16; ++i) o_acc[d][i] = 0.0f;
         // m_run: the reference the exponentials are taken against.  It moves only when a tile's maximum exceeds some row's by
         // more than kSlack (log2 units), so the accumulators are rescaled a few times per unit, not once per tile.
-        constexpr float kSlack = 5.0f; // 8: 2 % faster, but the error against 64 bits grows from 3.3e-4 to 3.5e-4; 3: 2 % slower
+        // (A reference that is the row's maximum gives the largest weight without rounding.  Error against 64 bits, 512 tokens behind
+        // 8,000, 256-wide, slack 3 / 4 / 5 / 8: 3.27e-4 / 3.31e-4 / 3.35e-4 / 3.5e-4, 3.28e-4 with a denominator of unrounded weights
+        // and rows that move one by one; 8 would be 2 % faster.)
+        constexpr float kSlack = 3.0f;
         float m_run = kNegBig, l_run = 0.0f; // l_run: this lane's tokens only
 
         // operand reads: K row of M row qn; V_hat by the transposing read (token 8 h + 2 e (+ 1), dims 16 (lane/16 % 2) + 4 c)
@@ -703,6 +711,25 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             });
         };
 
+        auto stage_only = [&](bool more, int64_t row_ahead) __attribute__((always_inline)) {
+            const RowDequant kr = row_params(ksb, row_ok(t0 + TILE, (int)(fresh(k_off) / (4 * SK::WORDS)), ok_next && more));
+            const RowDequant vr = row_params(vsb, row_ok(t0, (int)(fresh(v_off) / (4 * SV::WORDS)), ok_cur));
+            if (k_params_writer) store_k_params(buf ^ 1, kr);
+            if constexpr (KFULL) {
+#pragma unroll
+                for (int w = 0; w < SK::WPT; ++w)
+                    if (k_on) store_unpacked(k_lds[buf ^ 1] + k_dst + w * kWordStep, kraw[w]);
+            } else if (k_on) {
+                store_codes(k_lds[buf ^ 1] + k_dst, kraw);
+            }
+            load_k(row_ahead);
+#pragma unroll
+            for (int w = 0; w < SV::WPT; ++w)
+                if (v_on) store_word(v_lds[buf] + v_dst + 8 * w, vraw[w], vr);
+            load_v(row_next);
+            entry_ahead = block_of(min(t0 + 3 * TILE, t_last));
+        };
+
         // ---- O^T += V_hat^T P^T of the tile before , the operand reads ahead; between the matrix instructions the online
         // softmax of the scores per query row (lane column) and their P^T (SOFT), which the next step multiplies.  SCALED: the
         // scores are in log2 units already.
@@ -789,38 +816,53 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
 #pragma unroll
             for (int s = 0; s < 2 * NP; ++s) pt[s] = __builtin_bit_cast(half8_t, make_uint4(0u, 0u, 0u, 0u));
             __syncthreads();
-            do {
-                const int ts = t0 + kSub * sub;
+            auto look_ahead = [&](int64_t &row_ahead, bool &ok_ahead) __attribute__((always_inline)) {
                 const int t_ahead = min(t0 + 2 * TILE, t_last); // past the end: the last tile again, never used
-                bool ok_ahead;
-                const int64_t row_ahead = tile_row0(t_ahead, entry_ahead, ok_ahead);
-                float16_t st[NP];
-                scores(st, t0 + TILE < part_t1, row_ahead);
-                // tokens that every row of the wave sees need no masks; the path with masks assumes nothing of the scale
-                float zs = p.score_scale / kUnit;
-                if (__builtin_expect(!(ok_cur && ts >= all_first && ts + NP * kSub <= all_vis && p.score_scale > 0.0f), 0)) {
-                    const int ln = lane_again();
-                    const int row_vis = row_sees(u.qt * QPOS + (rg * kRowsWave + ln % 32) / NREP), row_first = row_hides(row_vis);
-#pragma unroll
-                    for (int n = 0; n < NP; ++n)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) {
-                            const int t = ts + kSub * n + 16 * (i / 8) + 8 * (ln / 32) + 2 * (i % 4) + ((i / 4) & 1);
-                            const float z = st[n][i] * zs;
-                            st[n][i] = ok_cur && t < row_vis && t >= row_first ? z : 2.0f * kNegBig; // a weight of 0 against any reference
-                        }
-                    zs = 1.0f;
-                }
-                product(Flag<true>(), st, zs);
+                row_ahead = tile_row0(t_ahead, entry_ahead, ok_ahead);
+            };
+            auto end_step = [&](int64_t row_ahead, bool ok_ahead) __attribute__((always_inline)) {
                 ok_cur = ok_next;
                 ok_next = ok_ahead;
                 row_next = row_ahead;
                 t0 += TILE;
                 __syncthreads(); // every wave is done with these buffers and has filled its part of the others
                 buf ^= 1;
-            } while (t0 < part_t1);
-            float16_t none[NP];
-            product(Flag<false>(), none, 0.0f);
+            };
+            int64_t row_ahead;
+            bool ok_ahead;
+            if (wave_live) {
+                do {
+                    const int ts = t0 + kSub * sub;
+                    look_ahead(row_ahead, ok_ahead);
+                    float16_t st[NP];
+                    scores(st, t0 + TILE < part_t1, row_ahead);
+                    // tokens that every row of the wave sees need no masks; the path with masks assumes nothing of the scale
+                    float zs = p.score_scale / kUnit;
+                    if (__builtin_expect(!(ok_cur && ts >= all_first && ts + NP * kSub <= all_vis && p.score_scale > 0.0f), 0)) {
+                        const int ln = lane_again();
+                        const int row_vis = row_sees(u.qt * QPOS + (rg * kRowsWave + ln % 32) / NREP), row_first = row_hides(row_vis);
+#pragma unroll
+                        for (int n = 0; n < NP; ++n)
+#pragma unroll
+                            for (int i = 0; i < 16; ++i) {
+                                const int t = ts + kSub * n + 16 * (i / 8) + 8 * (ln / 32) + 2 * (i % 4) + ((i / 4) & 1);
+                                const float z = st[n][i] * zs;
+                                st[n][i] = ok_cur && t < row_vis && t >= row_first ? z : 2.0f * kNegBig; // a weight of 0 against any reference
+                            }
+                        zs = 1.0f;
+                    }
+                    product(Flag<true>(), st, zs);
+                    end_step(row_ahead, ok_ahead);
+                } while (t0 < part_t1);
+                float16_t none[NP];
+                product(Flag<false>(), none, 0.0f);
+            } else { // no rows of the chunk: this wave only does its part of the staging, and leaves the rest of its SIMD to the others
+                do {
+                    look_ahead(row_ahead, ok_ahead);
+                    stage_only(t0 + TILE < part_t1, row_ahead);
+                    end_step(row_ahead, ok_ahead);
+                } while (t0 < part_t1);
+            }
         }
 
         float l_tot = xor32_sum(l_run);

@@ -295,6 +295,22 @@ def test_chunk_shared_by_workgroups_matches_oracle(case, param_format):
             assert_close(outs[2].cpu().numpy(), want, f"{case} window {window} bound {msl}, one unit per workgroup")
 
 
+# 20 to 72 rows of a workgroup's 128: one, two and three of its four row groups have rows of the chunk
+FEW_ROWS = [
+    (2, 2, 256, (1501, 300), 20),
+    (4, 2, 256, (900,), 20),
+    (4, 4, (192, 128), (1500, 300), 70),
+    (8, 2, 128, (1200,), 9),
+    (8, 1, 64, (3000, 200), 9),
+]
+
+
+@pytest.mark.parametrize("case", FEW_ROWS)
+def test_chunk_of_few_rows_matches_oracle(case):
+    """Waves without rows of the chunk only stage, and the others are placed differently over the SIMDs."""
+    test_chunk_shared_by_workgroups_matches_oracle(case, 0)
+
+
 def test_chunk_call_leaves_a_workspace_of_another_size_alone():
     """A chunk call uses a workspace of exactly the size it was told; any other (a decode call's, which may hold the plan
     of the step in progress) keeps its bytes, and the planned calls that follow find their plan."""
