@@ -308,7 +308,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
     // K, unpacked: the 8 codes of a word as a matrix operand, [word][token]; else the code words as they are in the pool
     __shared__ __attribute__((aligned(16))) uint32_t k_lds[2][KFULL ? TILE * DK / 2 : TILE * KPITCH];
     __shared__ __attribute__((aligned(16))) half_t v_lds[2][TILE * VPITCH];   // V_hat
-    // K scale [group][32-token half][lane / 32][16 values in the order a lane's scores have]
+    // K scale [group][token]: a lane's first 8 scores take tokens 8 (lane / 32) .. + 7 of its 32, the last 8 those 16 further on
     __shared__ __attribute__((aligned(16))) half_t ks_lds[2][GK * TILE];
     // K bias [token][8]: groups 0..3 (zero padded) twice, against the high and the low parts of the group sums of q
     __shared__ __attribute__((aligned(16))) half_t kb_lds[2][TILE * 8];
@@ -509,11 +509,11 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             return __builtin_bit_cast(half8_t, make_uint4(w & 0x000F000Fu, w & 0x00F000F0u, w8 & 0x000F000Fu, w8 & 0x00F000F0u));
         };
         // scale and bias of a K row go to LDS beside the codes, written by the thread that holds the first word of the
-        // group; token t of a 32-token half is score register 4 (2 (t/16) + t%2) + (t%8)/2 of half (t%16)/8 of the wave
+        // group.  In token order: in the scores' order every wave worked out the place with 22 instructions a tile instead of 12.
         const bool k_params_writer = k_on && (k_w0 * 8) % kGroup == 0;
         auto store_k_params = [&](int b, const RowDequant &r) __attribute__((always_inline)) {
             const int at = (int)(fresh(k_off) / 4), tok = at / SK::WORDS, grp = at % SK::WORDS / 8;
-            ks_lds[b][grp * TILE + (tok / kSub) * kSub + ((tok % 16) / 8) * 16 + 4 * (2 * ((tok % kSub) / 16) + tok % 2) + (tok % 8) / 2] = r.s2.x;
+            ks_lds[b][grp * TILE + tok] = r.s2.x;
             kb_lds[b][tok * 8 + grp] = r.b2.x;
             kb_lds[b][tok * 8 + 4 + grp] = r.b2.x;
         };
@@ -607,7 +607,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         constexpr float kUnit = KFULL ? 1.0f : 0x1p-24f;
         auto scores = [&](float16_t (&st)[NP], bool more, int64_t row_ahead) __attribute__((always_inline)) {
             const uint32_t *k_row = k_lds[buf] + sub * kPiece + k_lane;
-            const half_t *ks_row = ks_lds[buf] + sub * kSub + 16 * (lane_again() / 32);
+            const half_t *ks_row = ks_lds[buf] + sub * kSub + 8 * (lane_again() / 32);
             const half_t *kb_row = kb_lds[buf] + (sub * kSub + (KFULL ? (int)(fresh(k_lane) / 4) % kSub : m_token)) * 8;
             auto q_operand = [&](auto index) __attribute__((always_inline)) { // matrix instruction 4 group + i
                 constexpr int k = index.value;
@@ -660,7 +660,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
 #pragma unroll
                 for (int n = 0; n < NP; ++n) {
                     if constexpr (i == 2) sc[n] = *reinterpret_cast<const uint4 *>(ks_row + g * TILE + n * kSub);
-                    if constexpr (i == 3) sc1[n] = *reinterpret_cast<const uint4 *>(ks_row + g * TILE + n * kSub + 8);
+                    if constexpr (i == 3) sc1[n] = *reinterpret_cast<const uint4 *>(ks_row + g * TILE + n * kSub + 16);
                     half8_t a;
                     if constexpr (KFULL) {
                         a = __builtin_bit_cast(half8_t, keys[k % kKeysAhead][n]);
@@ -696,9 +696,9 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                         const uint32_t s8[8] = {sc[n].x, sc[n].y, sc[n].z, sc[n].w, sc1[n].x, sc1[n].y, sc1[n].z, sc1[n].w};
 #pragma unroll
                         for (int e = 0; e < 16; ++e) {
-                            const half2_t sh = bits_to_half2(s8[e / 2]);
+                            const half2_t sh = bits_to_half2(s8[4 * (e / 8) + e % 4]); // tokens 2 (e % 4) and one more of 8
                             const float prev = g == 0 ? st[n][e] * kUnit : st[n][e]; // the bias term enters in the products' unit
-                            st[n][e] = fmaf((float)((e & 1) ? sh.y : sh.x), d[n][e], prev);
+                            st[n][e] = fmaf((float)((e & 4) ? sh.y : sh.x), d[n][e], prev);
                         }
                         // pinned: else the multiplies of all groups sink to the scores' first use and every product stays live
 #pragma unroll
