@@ -22,7 +22,7 @@
 //    one code word, unpacked to the integers c and, for odd nibbles, 16 c against q/16), [word][token].  The dims inside
 //    a word appear in the order the nibble masks deliver them (0,4,1,5,2,6,3,7): the query operand uses the same order
 //    for K, the output store undoes it for V_hat.
-//  * Unpacking while staging instead of in every one of the eight waves takes 96 of 338 vector instructions out of a wave's
+//  * Unpacking while staging instead of in every one of the eight waves takes 96 of 305 vector instructions out of a wave's
 //    32 tokens (256-wide).  Measured, one call, packed / unpacked: 256-wide 512 tokens of ten agents of 4K-32K 2,440 / 2,356
 //    us, of one behind 8,000 123.7 / 121.8; 128-wide, four agents, two layers 424 / 414; 192 + 128 265 / 257; 64-wide 107 /
 //    100.  It is 8.6 % fewer clocks on the long call, of which the power limit gives a third back: 1.87 -> 1.81 GHz.  Where
@@ -53,9 +53,9 @@
 //    a row that one token dominates then loses nothing to the rounding.
 //  * A wave works a step ahead of itself: step i takes the scores of tile i and then, between the matrix instructions of the
 //    product of tile i - 1, the softmax of tile i.  The tiles are staged beside the scores, V one step behind K.  Measured
-//    against scores, softmax and product one after the other, one call: 256-wide 512 tokens of ten agents of 6,000, three layers 1,894 /
-//    1,849 us (4.05e6 / 3.80e6 clocks; the power limit lowers the clock by the half of that), a window of 1,024 339 / 309;
-//    128-wide two layers of four agents 414 / 389, 192 + 128 257 / 244, 64-wide 599 / 566.
+//    against scores, softmax and product one after the other, one call: 256-wide 512 tokens of ten agents of 6,000, three layers 1,844 /
+//    1,821 us (4.05e6 / 3.80e6 clocks; the power limit lowers the clock by the half of that), a window of 1,024 330 / 311;
+//    128-wide two layers of four agents 406 / 396, 192 + 128 253 / 248, 64-wide 599 / 584.
 //  * Every variant runs without scratch memory, and a test holds the build to that: in a build that spilled, the compiler
 //    put a spill behind a loop over part of the threads but before all were switched on again.  What the tile loop does not
 //    need is therefore worked out again behind it from opaque copies (lane_again, fresh), and nothing in front of it diverges.
@@ -67,8 +67,8 @@
 // Measured, 256-wide heads, ten agents of 4K-32K tokens, a 512-token chunk, one layer: 1.82 ms = 805 TFLOP/s with shares, 2.0
 // without (16 rows per wave on 16x16x32 instructions, one workgroup per unit: 2.28 ms); one agent of 8,000 tokens 0.11 +
 // 0.02 ms with, 0.315 without (0.364 ms).
-// A wave issues 214 vector and 33 matrix instructions per 32 tokens (256-wide); the matrix pipe is busy 41 % of the time, a
-// wave waits for LDS or the barrier a third of it.  The clock falls as the pipe fills (2.0 GHz at 37 %, 1.9 at 41 %), so a
+// A wave issues 270 vector and 33 matrix instructions per 32 tokens (256-wide; 305 and 33 while every wave unpacked the keys); the
+// matrix pipe is busy 45 % of the time, a wave waits for LDS or the barrier a third of it.  The clock falls as the pipe fills (2.0 GHz at 42 %, 1.9 at 45 %), so a
 // clock saved is worth about half.  64 rows per wave at one wave per SIMD (half the LDS reads per row, the accumulators
 // in the accumulator file): 3.64e6 clocks against 3.21e6, because one wave issues one instruction of any kind in five clocks.
 // Holding the second wave of a SIMD half a step behind by two barriers per step cost 15 %.  Wave priorities by phase,
