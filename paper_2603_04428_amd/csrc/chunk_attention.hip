@@ -49,8 +49,9 @@
 //    the tile loop.
 //  * Softmax is online, per query row (= per lane column): scores in binary32, log2 domain.  The reference of a row moves when
 //    some row of its wave exceeds it by more than kSlack, all rows of the wave together: every move rescales the accumulators.
-//    The denominator is the sum of the weights as they are multiplied, rounded to binary16 (v_dot2_f32_f16, a pair at a time):
-//    a row that one token dominates then loses nothing to the rounding.
+//    The denominator sums the weights in binary32, as they are before they are rounded for the product.  (A sum of the
+//    rounded ones is 8 instructions fewer per 32 tokens and up to 6 % closer where few tokens dominate, but a token in front
+//    of 131,071 of weight 2^-25.2 then comes out 1.9e-3 off.)
 //  * A wave works a step ahead of itself: step i takes the scores of tile i and then, between the matrix instructions of the
 //    product of tile i - 1, the softmax of tile i.  The tiles are staged beside the scores, V one step behind K.  Measured
 //    against scores, softmax and product one after the other, one call: 256-wide 512 tokens of ten agents of 6,000, three layers 1,844 /
@@ -583,8 +584,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         // m_run: the reference the exponentials are taken against.  It moves only when a tile's maximum exceeds some row's by
         // more than kSlack (log2 units), so the accumulators are rescaled a few times per unit, not once per tile.
         // (A reference that is the row's maximum gives the largest weight without rounding.  Error against 64 bits, 512 tokens behind
-        // 8,000, 256-wide, slack 3 / 4 / 5 / 8: 3.27e-4 / 3.31e-4 / 3.35e-4 / 3.5e-4, 3.28e-4 with a denominator of unrounded weights
-        // and rows that move one by one; 8 would be 2 % faster.)
+        // 8,000, 256-wide, slack 3 / 4 / 5 / 8: 3.27e-4 / 3.31e-4 / 3.35e-4 / 3.5e-4; 8 would be 2 % faster.)
         constexpr float kSlack = 3.0f;
         float m_run = kNegBig, l_run = 0.0f; // l_run: this lane's tokens only
 
@@ -763,7 +763,8 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                     const float a = __builtin_amdgcn_exp2f(fmaf(st[e / 8][2 * (e % 8)], zs, -m_new));
                     const float b = __builtin_amdgcn_exp2f(fmaf(st[e / 8][2 * (e % 8) + 1], zs, -m_new));
                     const half2_t w = half2_t{(half_t)a, (half_t)b};
-                    sum = __builtin_amdgcn_fdot2(w, half2_t{(half_t)1.0f, (half_t)1.0f}, sum, false); // of the rounded weights
+                    sum += a; // the weights themselves: a long tail of weights that round to little or nothing still counts
+                    sum += b;
                     next[e] = half2_to_bits(w);
                     asm volatile("" : "+v"(next[e]), "+v"(sum)); // else the additions are put off and every weight stays live
                 }

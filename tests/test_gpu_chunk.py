@@ -311,6 +311,34 @@ def test_chunk_of_few_rows_matches_oracle(case):
     test_chunk_shared_by_workgroups_matches_oracle(case, 0)
 
 
+@pytest.mark.parametrize("bits_down", [16.0, 20.3, 25.2, 26.4])
+@pytest.mark.parametrize("shape", [(2, 2, 256), (2, 2, 64), (4, 2, 128), (2, 2, (192, 128))])
+def test_chunk_with_a_long_light_tail(shape, bits_down):
+    """One token of weight 1 in front of 131,071 of weight 2^-bits_down, values +1 and -1 in turn: the output is 1 over the
+    denominator, in which each weight of the tail is less than binary16 resolves and all of them together are not.  Tolerance: the
+    output's rounding (2^-12 below 1) and that of a binary32 sum of 1 and a lane's at most 2,048 parts of the tail (2^-24 each)."""
+    Hq, Hkv, D = shape
+    Dk, Dv = D if isinstance(D, tuple) else (D, D)
+    C, n = 2, 131072
+    spec = b.make_spec(1, Hq, Hkv, Dk, Dv, False)
+    kpool, vpool = b.Pool(spec, Dk, n // 256), b.Pool(spec, Dv, n // 256)     # codes and scales 0: a row is its bias
+    kpool.bias[0, 0, :, 0] = 0x3C00
+    vpool.bias[:, :, :, 0::2] = 0x3C00
+    vpool.bias[:, :, :, 1::2] = 0xBC00 - 0x10000
+    ospec = oracle.make_spec(1, Hq, Hkv, Dk, Dv, False)
+    okp, ovp = oracle.Pool(ospec, Dk, n // 256), oracle.Pool(ospec, Dv, n // 256)
+    okp.bias[...], ovp.bias[...] = bits(kpool.bias), bits(vpool.bias)
+    table = np.arange(n // 256, dtype=np.int32)[None]
+    q = np.ones((1, 1, C, Hq, Dk), np.float16)
+    sm_scale = bits_down * np.log(2.0) / Dk
+    _, exact = oracle.attention(ospec, okp, ovp, q, table, [n], sm_scale, return_f64=True)
+    got = b.q4kv_batched_attention(spec, kpool, vpool, torch.from_numpy(q).to(DEV), torch.from_numpy(table).to(DEV),
+                                   torch.tensor([n], dtype=torch.int32, device=DEV), n, sm_scale)
+    torch.cuda.synchronize()
+    err = np.abs(got.cpu().numpy().astype(np.float64) - exact).max()
+    assert err < 2.0 ** -12 + 2048 * 2.0 ** -24, f"{shape} 2^-{bits_down}: {err:.3e}"
+
+
 def test_chunk_call_leaves_a_workspace_of_another_size_alone():
     """A chunk call uses a workspace of exactly the size it was told; any other (a decode call's, which may hold the plan
     of the step in progress) keeps its bytes, and the planned calls that follow find their plan."""
