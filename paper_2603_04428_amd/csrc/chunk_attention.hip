@@ -48,7 +48,8 @@
 //    With KSPLIT = 2 the two waves of a row group read one copy, which the first one writes before the barrier in front of
 //    the tile loop.
 //  * Softmax is online, per query row (= per lane column): scores in binary32, log2 domain.  The reference of a row moves when
-//    some row of its wave exceeds it by more than kSlack, all rows of the wave together: every move rescales the accumulators.
+//    the row exceeds it by more than kSlack, which rescales the accumulators.  (Moving all rows of a wave together rescales less
+//    often, 0.5 % over 25 calls, and makes a row's rounding depend on the rows beside it.)
 //    The denominator sums the weights in binary32, as they are before they are rounded for the product.  (A sum of the
 //    rounded ones is 8 instructions fewer per 32 tokens and up to 6 % closer where few tokens dominate, but a token in front
 //    of 131,071 of weight 2^-25.2 then comes out 1.9e-3 off.)
@@ -581,10 +582,10 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         for (int d = 0; d < DTILES; ++d)
 #pragma unroll
             for (int i = 0; i < 16; ++i) o_acc[d][i] = 0.0f;
-        // m_run: the reference the exponentials are taken against.  It moves only when a tile's maximum exceeds some row's by
-        // more than kSlack (log2 units), so the accumulators are rescaled a few times per unit, not once per tile.
+        // m_run: the reference the exponentials are taken against.  It moves only when a tile's maximum exceeds it by more than
+        // kSlack (log2 units), so the accumulators are rescaled a few times per row, not once per tile.
         // (A reference that is the row's maximum gives the largest weight without rounding.  Error against 64 bits, 512 tokens behind
-        // 8,000, 256-wide, slack 3 / 4 / 5 / 8: 3.27e-4 / 3.31e-4 / 3.35e-4 / 3.5e-4; 8 would be 2 % faster.)
+        // 8,000, 256-wide, with a denominator of rounded weights, slack 3 / 4 / 5 / 8: 3.27e-4 / 3.31e-4 / 3.35e-4 / 3.5e-4; 8 would be 2 % faster.)
         constexpr float kSlack = 3.0f;
         float m_run = kNegBig, l_run = 0.0f; // l_run: this lane's tokens only
 
@@ -756,8 +757,9 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                     for (int i = 0; i < 8; ++i) mx = fmaxf(mx, st[j / 2][8 * (j % 2) + i]);
                 } else if constexpr (j == 2 * NP) {
                     mx = xor32_max(mx * zs); // the row's tokens live in two lanes
-                    moved = __builtin_amdgcn_ballot_w64(mx > m_run + kSlack) != 0ull;
-                    m_new = moved ? fmaxf(m_run, mx) : m_run;
+                    const bool mine = mx > m_run + kSlack; // of this row alone: its bits do not depend on its neighbours
+                    m_new = mine ? mx : m_run;
+                    moved = __builtin_amdgcn_ballot_w64(mine) != 0ull;
                 } else {
                     constexpr int e = j - 2 * NP - 1;
                     const float a = __builtin_amdgcn_exp2f(fmaf(st[e / 8][2 * (e % 8)], zs, -m_new));

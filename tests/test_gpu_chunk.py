@@ -311,6 +311,26 @@ def test_chunk_of_few_rows_matches_oracle(case):
     test_chunk_shared_by_workgroups_matches_oracle(case, 0)
 
 
+@pytest.mark.parametrize("shape", [(4, 2, 256, (700, 40), 60), (4, 4, (192, 128), (500,), 130), (8, 2, 128, (900,), 70), (8, 1, 64, (300, 65), 33)])
+def test_a_row_does_not_depend_on_the_other_rows_of_its_chunk(shape):
+    """Queries of other positions eight times larger: the rows that keep theirs give the same bits, with and without shares."""
+    Hq, Hkv, D, lens, C = shape
+    Dk, Dv = D if isinstance(D, tuple) else (D, D)
+    w = synth.small(69, 1, Hq, Hkv, Dk, Dv, False, lens, q_len=C)
+    _, (spec, kpool, vpool, table_d) = append_chunk_and_attend(w)
+    sl, msl, q = torch.tensor(w.final_lens(), dtype=torch.int32, device=DEV), 512 * 256, w.q_all(DEV)
+    wide = torch.nn.functional.pad(table_d, (0, 512 - table_d.shape[1])).contiguous()
+    kept = torch.zeros(C, dtype=torch.bool, device=DEV)
+    kept[::5] = True
+    q2 = torch.where(kept[None, None, :, None, None], q, 8 * q)
+    ws = torch.empty(b.q4kv_attention_workspace_bytes(spec, len(lens), C, msl, 0, 1), dtype=torch.uint8, device=DEV)
+    for workspace in (ws, None):
+        one, two = (b.q4kv_batched_attention(spec, kpool, vpool, x, wide, sl, msl, w.sm_scale, workspace=workspace) for x in (q, q2))
+        torch.cuda.synchronize()
+        assert torch.equal(one[:, :, kept], two[:, :, kept]), f"{shape} shares {workspace is not None}"
+        assert not torch.equal(one, two)
+
+
 @pytest.mark.parametrize("bits_down", [16.0, 20.3, 25.2, 26.4])
 @pytest.mark.parametrize("shape", [(2, 2, 256), (2, 2, 64), (4, 2, 128), (2, 2, (192, 128))])
 def test_chunk_with_a_long_light_tail(shape, bits_down):
