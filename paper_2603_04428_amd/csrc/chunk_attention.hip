@@ -19,15 +19,17 @@
 //    2,738 us; 24 tokens of five agents, 192 + 128-wide 170 / 154 us.
 //  * KV tiles are fetched as Q4 (codes + scale/bias, prefetched one tile ahead into registers) and staged
 //    ONCE per workgroup in LDS: V_hat dequantized to binary16, row-major, K as matrix operands (a lane's A operand is exactly
-//    one code word, unpacked to the integers c and, for odd nibbles, 16 c against q/16), [word][token].  The dims inside
+//    one code word, masked in place into eight binary16 subnormals: c 2^-24 and, for odd nibbles, 16 c 2^-24 against q/16), [word][token].  The dims inside
 //    a word appear in the order the nibble masks deliver them (0,4,1,5,2,6,3,7): the query operand uses the same order
 //    for K, the output store undoes it for V_hat.
 //  * Unpacking while staging instead of in every one of the eight waves takes 96 of 305 vector instructions out of a wave's
 //    32 tokens (256-wide).  Measured, one call, packed / unpacked: 256-wide 512 tokens of ten agents of 4K-32K 2,440 / 2,356
 //    us, of one behind 8,000 123.7 / 121.8; 128-wide, four agents, two layers 424 / 414; 192 + 128 265 / 257; 64-wide 107 /
 //    100.  It is 8.6 % fewer clocks on the long call, of which the power limit gives a third back: 1.87 -> 1.81 GHz.  Where
-//    the unpacked tile does not fit into LDS (chunk_unpacks_keys) the code words are staged as they are and unpacked by each
-//    wave, masked in place into binary16 subnormals (c 2^-24).
+//    the unpacked tile does not fit into LDS (chunk_unpacks_keys) the code words are staged as they are and masked by each
+//    wave.  Whole numbers in place of the subnormals, in the one form and not in the other, gave the two forms different bits:
+//    the matrix core aligns products by their exponents, which leaves subnormal codes 8e-7 of a score's product where whole numbers
+//    leave 2e-8.  No output shows that (errors against 64 bits 3.277e-4 and 3.275e-4), and they cost 4 instructions a word more.
 //  * K stays factored, S^T = sum_g s[t,g] (C_g Q_g^T) + b Qsum^T: the matrix core multiplies the codes exactly, and the
 //    per-(token, group) scale meets the binary32 result of each group; the bias term is one more matrix
 //    instruction per 32 tokens whose contraction runs over the groups (group sums of q split into a binary16 high
@@ -498,17 +500,14 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                 *reinterpret_cast<uint2 *>(dst) = make_uint2(raw[0], raw[1]);
             }
         };
-        // the codes of a word as exact small integers: c (dims 0, 4, 2, 6) and 16 c (dims 1, 5, 3, 7)
-        auto store_unpacked = [&](uint32_t *dst, uint32_t raw) __attribute__((always_inline)) {
-            const uint32_t w8 = raw >> 8;
-            *reinterpret_cast<uint4 *>(dst) = make_uint4(half2_to_bits(nibbles_lo(raw)), half2_to_bits(nibbles_hi16(raw)),
-                                                         half2_to_bits(nibbles_lo(w8)), half2_to_bits(nibbles_hi16(w8)));
-        };
         // a code word as the A operand of a matrix instruction: the nibbles masked in place are binary16 subnormals
         // c 2^-24 (dims 0, 4, 2, 6 of the word) and 16 c 2^-24 (dims 1, 5, 3, 7)
         auto code_operand = [&](uint32_t w) __attribute__((always_inline)) {
             const uint32_t w8 = w >> 8;
             return __builtin_bit_cast(half8_t, make_uint4(w & 0x000F000Fu, w & 0x00F000F0u, w8 & 0x000F000Fu, w8 & 0x00F000F0u));
+        };
+        auto store_unpacked = [&](uint32_t *dst, uint32_t w) __attribute__((always_inline)) {
+            *reinterpret_cast<half8_t *>(dst) = code_operand(w);
         };
         // scale and bias of a K row go to LDS beside the codes, written by the thread that holds the first word of the
         // group.  In token order: in the scores' order every wave worked out the place with 22 instructions a tile instead of 12.
@@ -604,8 +603,8 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
 #pragma unroll
         for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
 
-        // ---- S^T = sum_g s_g (C_g Q_g^T) + b Qsum^T in binary32, in units of kUnit
-        constexpr float kUnit = KFULL ? 1.0f : 0x1p-24f;
+        // ---- S^T = sum_g s_g (C_g Q_g^T) + b Qsum^T in binary32, in units of 2^-24
+        constexpr float kUnit = 0x1p-24f;
         auto scores = [&](float16_t (&st)[NP], bool more, int64_t row_ahead) __attribute__((always_inline)) {
             const uint32_t *k_row = k_lds[buf] + sub * kPiece + k_lane;
             const half_t *ks_row = ks_lds[buf] + sub * kSub + 8 * (lane_again() / 32);

@@ -432,6 +432,25 @@ def test_chunk_of_256_rows_without_shares_matches_oracle(case):
     assert_close(got, want, f"{case}")
 
 
+ONE_TILE = [(64, 8, D, (0, 1, 15, 2, 14, 3, 13, 4, 12, 5, 11, 6, 10, 7, 9, 8, 0), 17) for D in (256, (192, 128))]
+
+
+@pytest.mark.parametrize("case", ONE_TILE)
+def test_keys_unpacked_when_staged_give_the_bits_of_packed_ones(case):
+    """Seventeen agents of at most 32 tokens take 256 rows per workgroup (keys unpacked when staged), each of them alone 128 (by
+    every wave): one tile is summed in the same order by both."""
+    Hq, Hkv, D, lens, C = case
+    Dk, Dv = D if isinstance(D, tuple) else (D, D)
+    w = synth.small(70, 1, Hq, Hkv, Dk, Dv, False, lens, q_len=C)
+    got, (spec, kpool, vpool, table_d) = append_chunk_and_attend(w)
+    sl, q = torch.tensor(w.final_lens(), dtype=torch.int32, device=DEV), w.q_all(DEV)
+    for a in range(len(lens)):
+        one = b.q4kv_batched_attention(spec, kpool, vpool, q[:, a:a + 1].contiguous(), table_d[a:a + 1].contiguous(), sl[a:a + 1].contiguous(),
+                                       max(w.final_lens()), w.sm_scale)
+        torch.cuda.synchronize()
+        assert torch.equal(one.cpu()[:, 0], torch.from_numpy(got[:, a])), f"{D} agent {a}"
+
+
 @pytest.mark.parametrize("scale", [-0.11, 0.0])
 @pytest.mark.parametrize("D", [64, 256])
 def test_shared_chunk_with_a_scale_that_is_not_positive(scale, D):
