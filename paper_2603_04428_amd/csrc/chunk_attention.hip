@@ -59,7 +59,10 @@
 //    product of tile i - 1, the softmax of tile i.  The tiles are staged beside the scores, V one step behind K.  Measured
 //    against scores, softmax and product one after the other, one call: 256-wide 512 tokens of ten agents of 6,000, three layers 1,844 /
 //    1,821 us (4.05e6 / 3.80e6 clocks; the power limit lowers the clock by the half of that), a window of 1,024 330 / 311;
-//    128-wide two layers of four agents 406 / 396, 192 + 128 253 / 248, 64-wide 599 / 584.
+//    128-wide two layers of four agents 406 / 396, 192 + 128 253 / 248, 64-wide 599 / 584.  The first step is a copy of its own
+//    without a product, which a unit of few tiles would feel: with a product of zeros / without, 94 tokens of two agents behind
+//    900, 128-wide, six layers 201 / 191 us (append included), 70 tokens of four agents 57.7 / 56.0, 256-wide 71.0 / 68.5, 700 tokens behind 300
+//    49.3 / 47.0.  (A branch round the product inside the loop made the compiler copy or spill the accumulators.)
 //  * Every variant runs without scratch memory, and a test holds the build to that: in a build that spilled, the compiler
 //    put a spill behind a loop over part of the threads but before all were switched on again.  What the tile loop does not
 //    need is therefore worked out again behind it from opaque copies (lane_again, fresh), and nothing in front of it diverges.
@@ -302,7 +305,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
     constexpr bool KFULL = chunk_unpacks_keys(DK, KSPLIT);
     // matrix instructions (4 per group) whose query operand stays in registers; the rest lie in LDS
     // (as many as leave every variant without scratch memory)
-    constexpr int QREG = DK == 256 ? (KFULL ? 5 : 4) : (DK == 192 ? 7 : (DK == 128 && KSPLIT == 1 ? 5 : 4));
+    constexpr int QREG = DK == 256 ? (KFULL ? 5 : 4) : (DK == 192 ? 7 : (DK == 128 && KSPLIT == 1 && !SHARES ? 5 : 4));
     constexpr int QLDS = 4 * GK - QREG;
     constexpr int QROWS = ROWGROUPS * kWave; // lanes that hold query operands of their own
     typedef Stage<DK, kChunkThreads, TILE> SK; // staging of the K rows of a tile ...
@@ -730,10 +733,45 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             entry_ahead = block_of(min(t0 + 3 * TILE, t_last));
         };
 
-        // ---- O^T += V_hat^T P^T of the tile before , the operand reads ahead; between the matrix instructions the online
-        // softmax of the scores per query row (lane column) and their P^T (SOFT), which the next step multiplies.  SCALED: the
-        // scores are in log2 units already.
-        auto product = [&](auto soft, float16_t (&st)[NP], float zs) __attribute__((always_inline)) {
+        // ---- online softmax of the scores per query row (lane column) and their P^T, in kItems pieces
+        struct Softmax {
+            float mx = kNegBig, m_new = 0.0f, sum = 0.0f;
+            bool moved = false;
+            uint32_t next[8 * NP];
+        };
+        constexpr int kItems = 10 * NP + 1;
+        auto softmax_item = [&](auto index, Softmax &x, const float16_t (&st)[NP], float zs) __attribute__((always_inline)) {
+            constexpr int j = index.value;
+            if constexpr (j < 2 * NP) { // the maximum, before the scale is applied (which is positive)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x.mx = fmaxf(x.mx, st[j / 2][8 * (j % 2) + i]);
+            } else if constexpr (j == 2 * NP) {
+                x.mx = xor32_max(x.mx * zs); // the row's tokens live in two lanes
+                const bool mine = x.mx > m_run + kSlack; // of this row alone: its bits do not depend on its neighbours
+                x.m_new = mine ? x.mx : m_run;
+                x.moved = __builtin_amdgcn_ballot_w64(mine) != 0ull;
+            } else {
+                constexpr int e = j - 2 * NP - 1;
+                const float a = __builtin_amdgcn_exp2f(fmaf(st[e / 8][2 * (e % 8)], zs, -x.m_new));
+                const float b = __builtin_amdgcn_exp2f(fmaf(st[e / 8][2 * (e % 8) + 1], zs, -x.m_new));
+                const half2_t w = half2_t{(half_t)a, (half_t)b};
+                x.sum += a; // the weights themselves: a long tail of weights that round to little or nothing still counts
+                x.sum += b;
+                x.next[e] = half2_to_bits(w);
+                asm volatile("" : "+v"(x.next[e]), "+v"(x.sum)); // else the additions are put off and every weight stays live
+            }
+        };
+        auto softmax_done = [&](const Softmax &x) __attribute__((always_inline)) {
+            m_run = x.m_new;
+            l_run += x.sum;
+#pragma unroll
+            for (int s = 0; s < 2 * NP; ++s)
+                pt[s] = __builtin_bit_cast(half8_t, make_uint4(x.next[4 * s], x.next[4 * s + 1], x.next[4 * s + 2], x.next[4 * s + 3]));
+        };
+
+        // ---- O^T += V_hat^T P^T of the tile before, the operand reads ahead; between the matrix instructions the softmax of the
+        // scores (SOFT), whose P^T the next step multiplies
+        auto product = [&](auto soft, const float16_t (&st)[NP], float zs) __attribute__((always_inline)) {
             constexpr bool SOFT = soft.value;
             constexpr int kPerTile = 2 * NP, kSteps = kPerTile * DTILES, kAhead = 2;
             const half_t *v_row = v_lds[buf ^ 1] + sub * kSub * VPITCH + fresh(v_lane);
@@ -746,31 +784,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             half8_t va[kAhead];
 #pragma unroll
             for (int s = 0; s < kAhead; ++s) va[s] = load_va(s);
-            float mx = kNegBig, m_new = 0.0f, sum = 0.0f;
-            bool moved = false;
-            uint32_t next[8 * NP];
-            auto item = [&](auto index) __attribute__((always_inline)) {
-                constexpr int j = index.value;
-                if constexpr (j < 2 * NP) { // the maximum, before the scale is applied (which is positive)
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) mx = fmaxf(mx, st[j / 2][8 * (j % 2) + i]);
-                } else if constexpr (j == 2 * NP) {
-                    mx = xor32_max(mx * zs); // the row's tokens live in two lanes
-                    const bool mine = mx > m_run + kSlack; // of this row alone: its bits do not depend on its neighbours
-                    m_new = mine ? mx : m_run;
-                    moved = __builtin_amdgcn_ballot_w64(mine) != 0ull;
-                } else {
-                    constexpr int e = j - 2 * NP - 1;
-                    const float a = __builtin_amdgcn_exp2f(fmaf(st[e / 8][2 * (e % 8)], zs, -m_new));
-                    const float b = __builtin_amdgcn_exp2f(fmaf(st[e / 8][2 * (e % 8) + 1], zs, -m_new));
-                    const half2_t w = half2_t{(half_t)a, (half_t)b};
-                    sum += a; // the weights themselves: a long tail of weights that round to little or nothing still counts
-                    sum += b;
-                    next[e] = half2_to_bits(w);
-                    asm volatile("" : "+v"(next[e]), "+v"(sum)); // else the additions are put off and every weight stays live
-                }
-            };
-            constexpr int kItems = 10 * NP + 1;
+            Softmax x;
             unrolled<kSteps>([&](auto index) __attribute__((always_inline)) {
                 constexpr int s = index.value;
                 const half8_t a = va[s % kAhead];
@@ -778,24 +792,20 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
                 o_acc[s / kPerTile] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pt[s % kPerTile], o_acc[s / kPerTile], 0, 0, 0);
                 if constexpr (SOFT) {
                     constexpr int first = (s * kItems + kSteps - 1) / kSteps, last = ((s + 1) * kItems + kSteps - 1) / kSteps;
-                    unrolled<last - first>([&](auto j) __attribute__((always_inline)) { item(Index<first + j.value>()); });
+                    unrolled<last - first>([&](auto j) __attribute__((always_inline)) { softmax_item(Index<first + j.value>(), x, st, zs); });
                 }
                 __builtin_amdgcn_sched_barrier(0);
             });
             if constexpr (SOFT) {
-                if (__builtin_expect(moved, 0)) { // rare after a unit's first tiles
-                    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+                if (__builtin_expect(x.moved, 0)) { // rare after a unit's first tiles
+                    const float alpha = __builtin_amdgcn_exp2f(m_run - x.m_new);
                     l_run *= alpha;
 #pragma unroll
                     for (int d = 0; d < DTILES; ++d)
 #pragma unroll
                         for (int i = 0; i < 16; ++i) o_acc[d][i] *= alpha;
                 }
-                m_run = m_new;
-                l_run += sum;
-#pragma unroll
-                for (int s = 0; s < 2 * NP; ++s)
-                    pt[s] = __builtin_bit_cast(half8_t, make_uint4(next[4 * s], next[4 * s + 1], next[4 * s + 2], next[4 * s + 3]));
+                softmax_done(x);
             }
         };
         if (part_t0 < part_t1) {
@@ -810,13 +820,6 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             if (k_params_writer) store_k_params(0, kr);
             load_k(row_next);
             entry_ahead = block_of(min(part_t0 + 2 * TILE, t_last));
-            // the first step's product is that of no tile: zeros times zeros
-            constexpr int kZeros = TILE * VPITCH / 8; // 16 bytes each; the last threads repeat the last one
-#pragma unroll
-            for (int i = 0; i < kZeros; i += kChunkThreads)
-                reinterpret_cast<uint4 *>(&v_lds[1][0])[min(i + tid, kZeros - 1)] = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-            for (int s = 0; s < 2 * NP; ++s) pt[s] = __builtin_bit_cast(half8_t, make_uint4(0u, 0u, 0u, 0u));
             __syncthreads();
             auto look_ahead = [&](int64_t &row_ahead, bool &ok_ahead) __attribute__((always_inline)) {
                 const int t_ahead = min(t0 + 2 * TILE, t_last); // past the end: the last tile again, never used
@@ -832,30 +835,38 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             };
             int64_t row_ahead;
             bool ok_ahead;
-            if (wave_live) {
-                do {
-                    const int ts = t0 + kSub * sub;
-                    look_ahead(row_ahead, ok_ahead);
-                    float16_t st[NP];
-                    scores(st, t0 + TILE < part_t1, row_ahead);
-                    // tokens that every row of the wave sees need no masks; the path with masks assumes nothing of the scale
-                    float zs = p.score_scale / kUnit;
-                    if (__builtin_expect(!(ok_cur && ts >= all_first && ts + NP * kSub <= all_vis && p.score_scale > 0.0f), 0)) {
-                        const int ln = lane_again();
-                        const int row_vis = row_sees(u.qt * QPOS + (rg * kRowsWave + ln % 32) / NREP), row_first = row_hides(row_vis);
+            auto step = [&](auto first) __attribute__((always_inline)) {
+                const int ts = t0 + kSub * sub;
+                look_ahead(row_ahead, ok_ahead);
+                float16_t st[NP];
+                scores(st, t0 + TILE < part_t1, row_ahead);
+                // tokens that every row of the wave sees need no masks; the path with masks assumes nothing of the scale
+                float zs = p.score_scale / kUnit;
+                if (__builtin_expect(!(ok_cur && ts >= all_first && ts + NP * kSub <= all_vis && p.score_scale > 0.0f), 0)) {
+                    const int ln = lane_again();
+                    const int row_vis = row_sees(u.qt * QPOS + (rg * kRowsWave + ln % 32) / NREP), row_first = row_hides(row_vis);
 #pragma unroll
-                        for (int n = 0; n < NP; ++n)
+                    for (int n = 0; n < NP; ++n)
 #pragma unroll
-                            for (int i = 0; i < 16; ++i) {
-                                const int t = ts + kSub * n + 16 * (i / 8) + 8 * (ln / 32) + 2 * (i % 4) + ((i / 4) & 1);
-                                const float z = st[n][i] * zs;
-                                st[n][i] = ok_cur && t < row_vis && t >= row_first ? z : 2.0f * kNegBig; // a weight of 0 against any reference
-                            }
-                        zs = 1.0f;
-                    }
+                        for (int i = 0; i < 16; ++i) {
+                            const int t = ts + kSub * n + 16 * (i / 8) + 8 * (ln / 32) + 2 * (i % 4) + ((i / 4) & 1);
+                            const float z = st[n][i] * zs;
+                            st[n][i] = ok_cur && t < row_vis && t >= row_first ? z : 2.0f * kNegBig; // a weight of 0 against any reference
+                        }
+                    zs = 1.0f;
+                }
+                if constexpr (first.value) {
+                    Softmax x;
+                    unrolled<kItems>([&](auto j) __attribute__((always_inline)) { softmax_item(j, x, st, zs); });
+                    softmax_done(x);
+                } else {
                     product(Flag<true>(), st, zs);
-                    end_step(row_ahead, ok_ahead);
-                } while (t0 < part_t1);
+                }
+                end_step(row_ahead, ok_ahead);
+            };
+            if (wave_live) {
+                step(Flag<true>()); // no tile before: no product
+                while (t0 < part_t1) step(Flag<false>());
                 float16_t none[NP];
                 product(Flag<false>(), none, 0.0f);
             } else { // no rows of the chunk: this wave only does its part of the staging, and leaves the rest of its SIMD to the others
@@ -954,7 +965,6 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             s->token_row = ((int64_t)u.li * p.num_agents + u.agent) * p.q_len;
         }
         x += SHARES ? part_end - begin : 1;
-        if constexpr (SHARES) __syncthreads(); // the last product still reads V_hat where the next part begins with zeros
     }
 }
 
