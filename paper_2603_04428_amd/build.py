@@ -1,6 +1,9 @@
 """Compile libq4kv.so (hand-written HIP for gfx950 + the C ABI) in-tree with hipcc."""
+import hashlib
 import os
+import re
 import subprocess
+import sys
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
@@ -19,19 +22,55 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 # instructions write vector registers directly instead of accumulator registers that must be copied out first.
 VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
 FILE_FLAGS = {"chunk_attention.hip": VGPR_FORM, "mla_decode.hip": VGPR_FORM}
+# Files whose kernels must keep everything in vector registers, and the flags that make the compiler say so.  A chunk kernel that
+# spilled gave wild addresses: the spill was behind a divergent loop, where some lanes were still switched off.
+NO_SPILLS = ["chunk_attention.hip"]
+RESOURCES = ["-Rpass-analysis=kernel-resource-usage", "-fno-caret-diagnostics"]
+
+
+def spills(remarks):
+    """What the compiler's resource remarks say of kernels that use scratch memory, spill or hold values in accumulator registers."""
+    found, kernel = [], None
+    for name, what, count in re.findall(r"remark: +(?:Function Name: (\S+)|(ScratchSize \[bytes/lane\]|VGPRs Spill|AGPRs): (\d+))", remarks):
+        kernel = name or kernel
+        if what and int(count):
+            found.append(f"{kernel}: {what} {count}")
+    return found
+
+
+def sources_hash():
+    """Names a state of everything the library is compiled from; the library carries the one it was built from as text."""
+    h = hashlib.sha256(repr([SOURCES, FLAGS, FILE_FLAGS]).encode())
+    for d in (CSRC, os.path.join(HERE, os.pardir, "include")):
+        for name in sorted(os.listdir(d)):
+            h.update(name.encode() + b"\0")
+            with open(os.path.join(d, name), "rb") as f:
+                h.update(f.read())
+    return h.hexdigest()
 
 
 def build(verbose=False):
+    stamp = f"q4kv sources {sources_hash()}"
     with tempfile.TemporaryDirectory(prefix="q4kv_build_") as tmp:
         def compile_one(src):
             obj = os.path.join(tmp, src.replace(".hip", ".o"))
             cmd = [HIPCC] + FLAGS + FILE_FLAGS.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj]
+            if src in NO_SPILLS:
+                cmd += RESOURCES
             if verbose:
                 print(" ".join(cmd))
-            subprocess.check_call(cmd)
+            done = subprocess.run(cmd, stderr=subprocess.PIPE, text=True)
+            sys.stderr.write("".join(line for line in done.stderr.splitlines(True) if RESOURCES[0][1:] not in line))
+            done.check_returncode()
+            if src in NO_SPILLS and spills(done.stderr):
+                raise RuntimeError(f"{src}: kernels that do not keep everything in registers:\n" + "\n".join(spills(done.stderr)))
             return obj
         with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1, 8)) as pool:
             objs = list(pool.map(compile_one, SOURCES))
+        with open(os.path.join(tmp, "stamp.c"), "w") as f:
+            f.write(f'__attribute__((used)) static const char q4kv_sources[] = "{stamp}";\n')
+        objs.append(os.path.join(tmp, "stamp.o"))
+        subprocess.check_call([HIPCC, "-x", "c", "-fPIC", "-c", os.path.join(tmp, "stamp.c"), "-o", objs[-1]])
         cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-sanitize", "-o", LIB] + objs
         if verbose:
             print(" ".join(cmd))

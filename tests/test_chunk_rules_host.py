@@ -128,6 +128,30 @@ def test_the_gpu_tests_of_256_rows_take_256_rows(rules):
     assert [r[0] for r in got] == [256, 256, 128, 128]
 
 
+def test_the_library_is_built_from_these_sources():
+    """Else the next test reads the kernels of another state of the sources, and so does every GPU test."""
+    from paper_2603_04428_amd import binding, build
+
+    binding.lib()                           # raises and says how to build where there is no library
+    with open(build.LIB, "rb") as f:
+        assert f"q4kv sources {build.sources_hash()}".encode() in f.read(), "sources changed since the library was built: build it again"
+
+
+def test_a_build_with_a_spilling_chunk_kernel_is_refused():
+    from paper_2603_04428_amd import build
+
+    line = "/a/chunk_attention.hip:289:1: remark: %s [-Rpass-analysis=kernel-resource-usage]\n"
+    names = ("    AGPRs: %d", "    ScratchSize [bytes/lane]: %d", "    SGPRs Spill: 7", "    VGPRs Spill: %d")
+
+    def remarks(kernel, agprs, scratch, spilled):
+        return "".join(line % t for t in ("Function Name: " + kernel, "    VGPRs: 256", names[0] % agprs, names[1] % scratch, names[2], names[3] % spilled))
+
+    assert build.spills(remarks("_Z1a", 0, 0, 0) + remarks("_Z1b", 0, 0, 0)) == []
+    assert build.spills(remarks("_Z1a", 0, 0, 0) + remarks("_Z1b", 0, 8, 1)) == ["_Z1b: ScratchSize [bytes/lane] 8", "_Z1b: VGPRs Spill 1"]
+    assert build.spills(remarks("_Z1a", 12, 0, 0) + remarks("_Z1b", 0, 0, 0)) == ["_Z1a: AGPRs 12"]
+    assert "chunk_attention.hip" in build.NO_SPILLS
+
+
 def test_chunk_kernels_need_no_scratch_memory():
     """The kernel metadata of the built library: every chunk attention kernel keeps all it has in registers (the header of
     csrc/chunk_attention.hip tells what a spill did)."""
@@ -143,8 +167,8 @@ def test_chunk_kernels_need_no_scratch_memory():
         name_size, size, kind = struct.unpack_from("<III", data, at - 12)
         if name_size == 7 and kind == 32:   # an ELF note of kernel metadata
             for kernel in msgpack.unpackb(data[at + 8:at + 8 + size])["amdhsa.kernels"]:
-                scratch[kernel[".name"]] = kernel[".private_segment_fixed_size"]
+                scratch[kernel[".name"]] = [kernel[k] for k in (".private_segment_fixed_size", ".vgpr_spill_count", ".agpr_count")]
         at = data.find(b"AMDGPU\0\0", at + 1)
     chunk = {k: v for k, v in scratch.items() if "chunk_attention_kernel" in k}
     assert len(chunk) == 128                # 4 widths, 4 head groupings, 2 row counts, with and without shares, 2 formats
-    assert not {k: v for k, v in chunk.items() if v}
+    assert not {k: v for k, v in chunk.items() if any(v)}
