@@ -21,6 +21,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 # These kernels read most of their matrix results with vector instructions (scales, softmax), so their matrix
 # instructions write vector registers directly instead of accumulator registers that must be copied out first.
 VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+# What a file is compiled for one by one; once, with nothing defined, where it is not named.
+PARTS = {"chunk_attention.hip": [f"-DQ4KV_CHUNK_WIDTH={width}" for width in (256, 192, 128, 64)]}
 FILE_FLAGS = {"chunk_attention.hip": VGPR_FORM, "mla_decode.hip": VGPR_FORM}
 # Files whose kernels must keep everything in vector registers, and the flags that make the compiler say so.  A chunk kernel that
 # spilled gave wild addresses: the spill was behind a divergent loop, where some lanes were still switched off.
@@ -40,7 +42,7 @@ def spills(remarks):
 
 def sources_hash():
     """Names a state of everything the library is compiled from; the library carries the one it was built from as text."""
-    h = hashlib.sha256(repr([SOURCES, FLAGS, FILE_FLAGS]).encode())
+    h = hashlib.sha256(repr([SOURCES, FLAGS, PARTS, FILE_FLAGS]).encode())
     for d in (CSRC, os.path.join(HERE, os.pardir, "include")):
         for name in sorted(os.listdir(d)):
             h.update(name.encode() + b"\0")
@@ -52,9 +54,10 @@ def sources_hash():
 def build(verbose=False):
     stamp = f"q4kv sources {sources_hash()}"
     with tempfile.TemporaryDirectory(prefix="q4kv_build_") as tmp:
-        def compile_one(src):
-            obj = os.path.join(tmp, src.replace(".hip", ".o"))
-            cmd = [HIPCC] + FLAGS + FILE_FLAGS.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj]
+        def compile_one(job):
+            src, part = job
+            obj = os.path.join(tmp, src.replace(".hip", (part or "") + ".o"))
+            cmd = [HIPCC] + FLAGS + ([part] if part else []) + FILE_FLAGS.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj]
             if src in NO_SPILLS:
                 cmd += RESOURCES
             if verbose:
@@ -65,8 +68,9 @@ def build(verbose=False):
             if src in NO_SPILLS and spills(done.stderr):
                 raise RuntimeError(f"{src}: kernels that do not keep everything in registers:\n" + "\n".join(spills(done.stderr)))
             return obj
-        with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1, 8)) as pool:
-            objs = list(pool.map(compile_one, SOURCES))
+        jobs = sorted(((src, part) for src in SOURCES for part in PARTS.get(src, [None])), key=lambda job: job[1] is None)  # the long ones first
+        with ThreadPoolExecutor(max_workers=min(len(jobs), os.cpu_count() or 1, 8)) as pool:
+            objs = list(pool.map(compile_one, jobs))
         with open(os.path.join(tmp, "stamp.c"), "w") as f:
             f.write(f'__attribute__((used)) static const char q4kv_sources[] = "{stamp}";\n')
         objs.append(os.path.join(tmp, "stamp.o"))

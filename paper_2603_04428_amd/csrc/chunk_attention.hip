@@ -1127,6 +1127,20 @@ hipError_t launch_chunk_d(const AttentionArgs &a, int n_rep, hipStream_t stream)
 
 } // namespace
 
+// The file is compiled once for each key width (Q4KV_CHUNK_WIDTH): 32 kernels a time, all four at once.
+template <int DK>
+hipError_t launch_chunk_width(const AttentionArgs &a, int n_rep, hipStream_t stream);
+template <>
+hipError_t launch_chunk_width<Q4KV_CHUNK_WIDTH>(const AttentionArgs &a, int n_rep, hipStream_t stream)
+{
+    return launch_chunk_d<Q4KV_CHUNK_WIDTH, Q4KV_CHUNK_WIDTH == 192 ? 128 : Q4KV_CHUNK_WIDTH>(a, n_rep, stream);
+}
+
+#if Q4KV_CHUNK_WIDTH == 64
+template <> hipError_t launch_chunk_width<128>(const AttentionArgs &a, int n_rep, hipStream_t stream);
+template <> hipError_t launch_chunk_width<192>(const AttentionArgs &a, int n_rep, hipStream_t stream);
+template <> hipError_t launch_chunk_width<256>(const AttentionArgs &a, int n_rep, hipStream_t stream);
+
 size_t chunk_workspace_bytes(const q4kv_spec &s, int num_agents, int q_len, int max_seq_len, int layers, int compute_units,
                              size_t &acc_bytes)
 {
@@ -1155,12 +1169,13 @@ hipError_t launch_chunk_attention(const AttentionArgs &a, hipStream_t stream)
 {
     const int n_rep = a.spec.num_q_heads / a.spec.num_kv_heads;
     switch (a.spec.k_dim) {
-    case 64: return launch_chunk_d<64, 64>(a, n_rep, stream);
-    case 128: return launch_chunk_d<128, 128>(a, n_rep, stream);
-    case 192: return launch_chunk_d<192, 128>(a, n_rep, stream);
-    case 256: return launch_chunk_d<256, 256>(a, n_rep, stream);
+    case 64: return launch_chunk_width<64>(a, n_rep, stream);
+    case 128: return launch_chunk_width<128>(a, n_rep, stream);
+    case 192: return launch_chunk_width<192>(a, n_rep, stream);
+    case 256: return launch_chunk_width<256>(a, n_rep, stream);
     default: return hipErrorInvalidValue;
     }
 }
+#endif
 
 } // namespace q4kv
