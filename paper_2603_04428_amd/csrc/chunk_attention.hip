@@ -340,7 +340,9 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         if (x >= x1) return;
     }
     if constexpr (GK < 4) { // bias slots of groups the rows do not have: zero once (their q sums are zero too)
-        for (int i = threadIdx.x; i < 2 * TILE * 8 / 2; i += kChunkThreads) reinterpret_cast<uint32_t *>(&kb_lds[0][0])[i] = 0u;
+        static_assert(TILE * 8 % kChunkThreads == 0, "words of the two tiles' slots: the same number for every thread");
+#pragma unroll
+        for (int i = 0; i < TILE * 8; i += kChunkThreads) reinterpret_cast<uint32_t *>(&kb_lds[0][0])[i + threadIdx.x] = 0u;
         __syncthreads();
     }
 
@@ -409,7 +411,6 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
         const bool k_on = SK::ACTIVE == kChunkThreads || tid < SK::ACTIVE, v_on = SV::ACTIVE == kChunkThreads || tid < SV::ACTIVE;
         const int k_tok = k_on ? (tid % 16) + 16 * (tid / (16 * SK::TPR)) : 0, k_w0 = k_on ? ((tid / 16) % SK::TPR) * SK::WPT : 0;
         const int v_tok = v_on ? (tid % 16) + 16 * (tid / (16 * SV::TPR)) : 0, v_w0 = v_on ? ((tid / 16) % SV::TPR) * SV::WPT : 0;
-        const int k_grp = (k_w0 * 8) / kGroup, v_grp = (v_w0 * 8) / kGroup;
         const uint32_t k_off = 4 * (k_tok * SK::WORDS + k_w0), v_off = 4 * (v_tok * SV::WORDS + v_w0);
         // the thread's place, worked out again: kept through the tile loop (or out of this one) it would cost registers
         auto lane_again = []() __attribute__((always_inline)) {
@@ -714,17 +715,21 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             });
         };
 
-        auto stage_only = [&](bool more, int64_t row_ahead) __attribute__((always_inline)) {
-            const RowDequant kr = row_params(ksb, row_ok(t0 + TILE, (int)(fresh(k_off) / (4 * SK::WORDS)), ok_next && more));
-            const RowDequant vr = row_params(vsb, row_ok(t0, (int)(fresh(v_off) / (4 * SV::WORDS)), ok_cur));
-            if (k_params_writer) store_k_params(buf ^ 1, kr);
+        auto stage_keys = [&](int b, const RowDequant &kr) __attribute__((always_inline)) {
+            if (k_params_writer) store_k_params(b, kr);
             if constexpr (KFULL) {
 #pragma unroll
                 for (int w = 0; w < SK::WPT; ++w)
-                    if (k_on) store_unpacked(k_lds[buf ^ 1] + k_dst + w * kWordStep, kraw[w]);
+                    if (k_on) store_unpacked(k_lds[b] + k_dst + w * kWordStep, kraw[w]);
             } else if (k_on) {
-                store_codes(k_lds[buf ^ 1] + k_dst, kraw);
+                store_codes(k_lds[b] + k_dst, kraw);
             }
+        };
+        // what `scores` does beside its matrix instructions: ksb and kraw hold tile t0 + TILE, vsb and vraw tile t0
+        auto stage_only = [&](bool more, int64_t row_ahead) __attribute__((always_inline)) {
+            const RowDequant kr = row_params(ksb, row_ok(t0 + TILE, (int)(fresh(k_off) / (4 * SK::WORDS)), ok_next && more));
+            const RowDequant vr = row_params(vsb, row_ok(t0, (int)(fresh(v_off) / (4 * SV::WORDS)), ok_cur));
+            stage_keys(buf ^ 1, kr);
             load_k(row_ahead);
 #pragma unroll
             for (int w = 0; w < SV::WPT; ++w)
@@ -809,15 +814,7 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             }
         };
         if (part_t0 < part_t1) {
-            const RowDequant kr = row_params(ksb, row_ok(part_t0, k_tok, ok_cur));
-            if constexpr (KFULL) {
-#pragma unroll
-                for (int w = 0; w < SK::WPT; ++w)
-                    if (k_on) store_unpacked(k_lds[0] + k_dst + w * kWordStep, kraw[w]);
-            } else if (k_on) {
-                store_codes(k_lds[0] + k_dst, kraw);
-            }
-            if (k_params_writer) store_k_params(0, kr);
+            stage_keys(0, row_params(ksb, row_ok(part_t0, k_tok, ok_cur)));
             load_k(row_next);
             entry_ahead = block_of(min(part_t0 + 2 * TILE, t_last));
             __syncthreads();
