@@ -6,7 +6,7 @@ import subprocess
 
 import pytest
 
-from tests.test_gpu_chunk import ONE_TILE, WIDE_ALONE, WIDE_SHARED
+from tests.test_gpu_chunk import ONE_TILE, WIDE_ALONE, WIDE_EDGES, WIDE_SHARED
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SHAPES = {"256": (8, 2), "128": (8, 4), "192": (16, 1), "64": (1, 8)}   # head width: KV heads, query heads per KV head
@@ -122,8 +122,8 @@ def test_the_gpu_tests_of_256_rows_take_256_rows(rules):
     assert [r[1:] for r in got] == [(256, 1, 1)] * len(WIDE_SHARED)
     got = rules([call(c, 131072)[:5] + ((300,),) for c in WIDE_SHARED])   # with a window they may take either
     assert all(r[3] == 1 for r in got)
-    got = rules([call(c, 0) for c in WIDE_ALONE])
-    assert [r[0] for r in got] == [256] * len(WIDE_ALONE)
+    got = rules([call(c, 0) for c in WIDE_ALONE + WIDE_EDGES])
+    assert [r[0] for r in got] == [256] * len(WIDE_ALONE + WIDE_EDGES)
     got = rules([call(c, 0) for c in ONE_TILE] + [call((*c[:3], c[3][:1], c[4]), max(c[3]) + c[4]) for c in ONE_TILE])
     assert [r[0] for r in got] == [256, 256, 128, 128]
 

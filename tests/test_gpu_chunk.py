@@ -64,8 +64,8 @@ def test_chunk_matches_oracle_small(shape):
 
 @pytest.mark.parametrize("shape", [(4, 2, 256), (4, 4, (192, 128)), (8, 2, 128), (8, 1, 64)])
 def test_chunk_around_the_edges_of_its_tiles(shape):
-    """Units of one, two and a few tiles of 32, 64 and 128 tokens, and one token more or less: the product runs a tile
-    behind the scores, so the first, the second and the last tile of a unit each take a turn of their own."""
+    """Units of one, two and a few tiles of 64 and 128 tokens (128 rows per workgroup), and one token more or less: the product
+    runs a tile behind the scores, so the first, the second and the last tile of a unit each take a turn of their own."""
     Hq, Hkv, D = shape
     Dk, Dv = D if isinstance(D, tuple) else (D, D)
     for C in (2, 40):                                        # tokens seen by the last row: 2 or 40 more than these
@@ -430,6 +430,17 @@ def test_chunk_of_256_rows_without_shares_matches_oracle(case):
     ospec, okp, ovp, otable = host_cache(w)
     want = oracle.attention(ospec, okp, ovp, w.q_all().numpy(), otable, w.final_lens(), w.sm_scale)
     assert_close(got, want, f"{case}")
+
+
+# Calls that take 256 rows per workgroup without shares, tiles of 32 (256-wide), else 64 tokens: the last row sees one tile, two, three
+# and one token more or less
+WIDE_EDGES = [(64, 8, D, tuple(n + d - 17 for n in (tile, 2 * tile, 3 * tile) for d in (-1, 0, 1)) * 2, 17)
+              for D, tile in ((256, 32), ((192, 128), 64), (128, 64), (64, 64))]
+
+
+@pytest.mark.parametrize("case", WIDE_EDGES)
+def test_chunk_of_256_rows_around_the_edges_of_its_tiles(case):
+    test_chunk_of_256_rows_without_shares_matches_oracle(case)
 
 
 ONE_TILE = [(64, 8, D, (0, 1, 15, 2, 14, 3, 13, 4, 12, 5, 11, 6, 10, 7, 9, 8, 0), 17) for D in (256, (192, 128))]
