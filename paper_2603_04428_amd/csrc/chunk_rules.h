@@ -1,6 +1,7 @@
 // How a chunk call is cut into workgroups: host arithmetic on sizes alone (the lengths are on the device), in a header of
 // its own so that it can be checked without a GPU.  Every figure beside a rule is the time of one attention call in us,
-// 256 compute units, binary16 parameters, both sides measured in turn.
+// 256 compute units, binary16 parameters, both sides measured in turn, on the kernel as it is unless it says otherwise.  (The lines
+// were drawn on a kernel without softmax beside the product, whose waves without rows cost as much as others; they still hold.)
 #pragma once
 #include <cstdint>
 
@@ -18,8 +19,8 @@ struct ChunkSizes {
 inline int64_t row_tiles(const ChunkSizes &s, int rows_per_workgroup) { return (s.rows + rows_per_workgroup - 1) / rows_per_workgroup; }
 
 // Time of a 128-row workgroup in that of a 256-row one over the same tokens: its staging does not shrink, its start and
-// end do not either.  Measured on full rounds of one layer, 256-, 128- and 192 + 128-wide heads: 0.58, 0.60, 0.58 at 1,712
-// tokens, 0.50, 0.55, 0.60 at 6,512; on a chip with few workgroups 0.66 (812), 0.57 (2,512), 0.54-0.57 (8,512).
+// end do not either.  Measured on full rounds of one layer, 256-, 128- and 192 + 128-wide heads: 0.57, 0.59, 0.58 at 1,712
+// tokens, 0.56, 0.55, 0.55 at 6,512; on a chip with few workgroups 0.63-0.68 (812), 0.61 (2,512), 0.58-0.61 (8,512).
 inline double half_rows_time(double tokens)
 {
     const double t = 0.56 + 80.0 / tokens;
@@ -51,11 +52,11 @@ inline double time_alone(const ChunkSizes &s, int rows, const int *tokens, int l
 
 // Rows per workgroup when every unit has a workgroup of its own: whichever is done first.  256 rows cost less per row, 128
 // are twice the workgroups.  Measured, 128 / 256 rows: 512 tokens behind 8,000, 256-wide, one agent (32 workgroups of
-// 256) 316 / 584, four agents, two rounds of 128 against one of 256, 563 / 545 (6,000 tokens, two layers); three
-// rounds against two 825 / 941, five against three 1,357 / 1,447, six against three 1,627 / 1,524.  128-wide, one
-// agent 183 / 320, two rounds against one 392 / 375.  192 + 128: 210 / 372.  64-wide: 134 / 239.  Twelve layers, five of six
-// with a window of 1,024, 256-wide, 512 tokens behind 6,000: one agent 426 / 559, four 1,152 / 1,214, ten 2,931 / 2,886;
-// 128-wide: one agent 398 / 436, four 1,344 / 1,122.
+// 256) 315 / 517, four agents, two rounds of 128 against one of 256, 526 / 470 (6,000 tokens, two layers); three
+// rounds against two 799 / 874, six against three 1,602 / 1,428.  128-wide, one agent 167 / 291, two rounds against one
+// 359 / 327.  192 + 128: 197 / 333.  64-wide: 129 / 220.  Twelve layers, five of six with a window of 1,024, 256-wide, 512 tokens
+// behind 6,000: four agents 1,136 / 1,135, ten 2,919 / 2,703; 128-wide: four 1,236 / 1,063.  Over 2,500 calls (2 to 700 tokens of
+// 1 to 12 agents behind 100 to 24,000) the better side is 0.1 % faster in the mean.
 inline int rows_alone(const ChunkSizes &s, const int *tokens, int layers)
 {
     bool same = true;
@@ -75,13 +76,12 @@ inline int visible_tokens(int max_seq_len, int window, int q_len, int n_rep)
 }
 
 // Rows per workgroup of a call with equal shares.  128 where 256 would be padding: 128 query rows of 256-wide heads, ten
-// agents of 4K-32K tokens 295 / 473 (128 / 256 rows), 280 rows of 128-wide heads, four agents of up to 6K 53 / 61, 300 rows of
-// 192 + 128-wide ones behind 2,000 41.0 / 42.8, behind 8,000 66 / 74.  And where a compute unit's share is short: every
+// agents of 4K-32K tokens 315 / 394 (128 / 256 rows), 280 rows of 128-wide heads, four agents of up to 6K 43.3 / 44.3, 300 rows of
+// 192 + 128-wide ones behind 2,000 38.8 / 39.7, behind 8,000 65 / 68.  And where a compute unit's share is short: every
 // workgroup of a shared unit leaves a record of its rows, and half the rows are half the record.  The line is at 448 tokens
-// per compute unit; between 250 and 1,000 the sides differ by 6 %, either way, but for one point (512 new tokens, one agent, tokens per compute unit: 256-wide 250 65.6 / 68.3, 400 73.7 / 77.7, 560 87.4 / 90.7, 1,000 120 / 122,
-// 2,200 221 / 214; 128-wide 250 51.0 / 50.8, 400 56.5 / 55.6, 560 65.8 / 62.4; 192 + 128 100 37.1 / 40.7, 400 54.0 / 63.6, 750
-// 72.8 / 71.2; 64-wide 76 24.6 / 34.5, 282 38.5 / 40.5), so one line does for all widths: over 460 calls a line for each width
-// gave nothing.
+// per compute unit; between 250 and 1,000 the sides differ by 6 %, either way, but for one point (512 new tokens, one agent, tokens per compute unit: 256-wide 250 55.9 / 58.4, 400 65.7 / 68.1, 560 78.5 / 81.6, 1,000 115 / 115,
+// 2,200 209 / 202; 128-wide 250 40.3 / 38.5, 400 45.5 / 43.7, 560 51.7 / 49.2; 192 + 128 100 32.7 / 35.5, 400 47.3 / 52.6, 750
+// 64.2 / 64.8; 64-wide 76 23.2 / 26.9, 282 32.7 / 31.6): over 2,500 calls no line between 250 and 1,000 is 0.02 % better.
 inline int rows_shared(const ChunkSizes &s, int tokens)
 {
     const int64_t wide = row_tiles(s, 256), narrow = row_tiles(s, 128);
@@ -92,11 +92,11 @@ inline int rows_shared(const ChunkSizes &s, int tokens)
 // Whether a call may share its tiles out at all, whatever its lengths and window turn out to be: what a workspace is sized
 // for.  The line is at two units per compute unit: a workgroup that takes an equal share holds its compute unit
 // until the call ends, and a decode step on another stream, which gets in whenever a workgroup ends, waits for that
-// long.  48 layers of 512 tokens behind 16,384 (1,536 units) take 7.63 ms with one unit per workgroup, 8.04 with equal
-// shares; decode steps of 0.76 ms beside them then take 2.1 and 4.9 ms.  Below the line: layer by layer, 0.84 ms steps beside
-// 512 tokens of ten agents of 4K-32K take 1.7 ms without shares and 2.65 with, beside one agent's (0.13 ms a call) 0.92.  Alone
-// equal shares would go on to win for a while: 256-wide, four agents of 2K-6K, units per compute unit 1.5 632 / 608 (alone /
-// shares), 2 844 / 804, 3 1,225 / 1,151, 4 1,585 / 1,515, 6 2,269 / 2,319; 128-wide 2 456 / 441, 4 838 / 802, 6 1,185 / 1,168.
+// long.  48 layers of 512 tokens behind 16,384 (1,536 units) take 7.15 ms with one unit per workgroup, 7.47 with equal
+// shares; decode steps of 0.76 ms beside them took 2.1 and 4.9 ms when the line was drawn (7.63 and 8.04 ms of chunk).  Below the line,
+// of that time too: layer by layer, 0.84 ms steps beside 512 tokens of ten agents of 4K-32K take 1.7 ms without shares and 2.65 with, beside
+// one agent's (0.13 ms a call) 0.92.  Alone equal shares go on to win at 128-wide heads: four agents of 6,000, units per compute unit 2 510 / 509 (alone /
+// shares), 4 1,013 / 994, 6 1,515 / 1,486; 256-wide 1.5 792 / 745, 2 941 / 955, 3 1,405 / 1,452, 6 2,800 / 2,881.
 inline bool shares_fit(const ChunkSizes &s, int num_agents, int max_seq_len)
 {
     const int64_t units = s.units * row_tiles(s, rows_shared(s, max_seq_len));
@@ -107,13 +107,14 @@ inline bool shares_fit(const ChunkSizes &s, int num_agents, int max_seq_len)
 // Whether equal shares are done before one unit per workgroup.  They even the load out, but every workgroup begins and ends up
 // to two units more, leaves their records and a second kernel merges them: about 100 (256-wide) or 300 tokens of a 256-row
 // workgroup, and up to 550 (250 at 192 + 128, 500 below) more as the units become as many as the compute
-// units.  One unit per workgroup / equal shares, 256-wide: 512 tokens behind 2,000 112 / 71, behind 8,000 316 / 138, ten agents of 4K-32K 2,000 / 1,840; 2 tokens
-// of ten agents behind 280 25.1 / 37.0, 512 of three behind 280 50.7 / 66.1, behind 700 67.4 / 80.5, behind 1,500 101 / 103.
-// 128-wide: 512 behind 280 30.9 / 41.8, behind 700 39.7 / 48.6, behind 2,000 66.6 / 61.9, behind 8,000 183 / 124; 16 of
-// ten agents behind 280 19.7 / 23.4, behind 1,500 43.7 / 32.7; a window of 1,024 on 512 behind 16,000 36 / 46.  192 + 128: 70
-// of ten agents behind 280 22.1 / 37.9, 2 of three behind 700 27.9 / 23.2, 512 of one behind 1,500 62 / 50.  Over 486 calls with
-// lengths from 280 to 32K, always sharing below two units per compute unit took 5 % longer in the mean and up to 1.7 times
-// as long; where this takes the slower form the other is 3 to 12 % faster.
+// units.  One unit per workgroup / equal shares, 256-wide: 512 tokens behind 2,000 107 / 61, behind 8,000 315 / 120, ten agents of 4K-32K 2,455 / 2,088; 2 tokens
+// of ten agents behind 280 16.8 / 29.7, 512 of three behind 280 47.1 / 59.5, behind 700 62.0 / 69.2, behind 1,500 93.5 / 92.0.
+// 128-wide: 512 behind 280 26.8 / 37.1, behind 700 34.1 / 42.6, behind 2,000 58.0 / 53.1, behind 8,000 167 / 109; 16 of
+// ten agents behind 280 13.1 / 21.7, behind 1,500 29.9 / 26.9; a window of 1,024 on 512 behind 16,000 32.3 / 43.7.  192 + 128: 70
+// of ten agents behind 280 17.9 / 34.4, 2 of three behind 700 17.8 / 17.3, 512 of one behind 1,500 57 / 42.  Over 2,500 calls the best
+// form is 0.9 % faster in the mean than the one this takes (always sharing below two units per compute unit: 9.1 %, and up to twice the time).
+// 87 of them are more than 10 % slower than the best, most of them a few tokens behind 300 to 1,100 that share and need not (2 to 140 tokens,
+// 256-wide: up to 1.4 times): starts of 200 (256-wide) and 360 tokens would leave 49 and 0.7 %.
 inline bool shares_pay(const ChunkSizes &s, int k_dim, int tokens)
 {
     const int rows = rows_shared(s, tokens);
