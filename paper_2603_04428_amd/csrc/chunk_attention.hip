@@ -6,9 +6,10 @@
 // Unlike decode this is a dense contraction: the q_len * n_rep query rows that share one KV head form the
 // M side of two GEMMs per KV tile (S = Q K^T, O += P V), so it runs on the matrix cores.  What bounds it is each wave's
 // own chain (operand reads, dependent products, scales, maximum, exponentials, products) and the barrier behind it, with two
-// waves per SIMD to fill the gaps: the issue port is taken two thirds of the time, the matrix pipe 42 %.  A vector instruction takes
-// 4.5 clocks of the port, a 32x32x16 matrix instruction about 5 (and 32 of the pipe), a 16x16x32 one 8.6 (and
-// 17): the products are cut so that everything the vector unit prepares -- unpacked keys above all -- serves 32 query rows.
+// waves per SIMD to fill the gaps: matrix pipe and LDS are each busy 46 % of the time.  A vector instruction takes
+// 4.5 clocks of the issue port, a 32x32x16 matrix instruction about 5 (and 32 of the pipe), a 16x16x32 one 8.6 (and
+// 17): the products are cut so that what a wave prepares itself (scales, weights) serves 32 query rows, and what can be prepared once
+// (unpacked keys, values) all rows of the workgroup.
 //
 //  * A workgroup of eight waves owns 256 query rows of one (layer, agent, KV head) -- 256/n_rep consecutive chunk
 //    positions times the n_rep query heads of the group -- 32 rows per wave; or 128 rows, when its waves 0..3 take the
@@ -28,8 +29,8 @@
 //    100.  It is 8.6 % fewer clocks on the long call, of which the power limit gives a third back: 1.87 -> 1.81 GHz.  Where
 //    the unpacked tile does not fit into LDS (chunk_unpacks_keys) the code words are staged as they are and masked by each
 //    wave.  Whole numbers in place of the subnormals, in the one form and not in the other, gave the two forms different bits:
-//    the matrix core aligns products by their exponents, which leaves subnormal codes 8e-7 of a score's product where whole numbers
-//    leave 2e-8.  No output shows that (errors against 64 bits 3.277e-4 and 3.275e-4), and they cost 4 instructions a word more.
+//    the matrix core's sums are 2e-8 off with them and 8e-7 with subnormals.  Outputs do not show that (errors against 64 bits
+//    3.275e-4 and 3.277e-4).  They cost 4 instructions a word more and save the bias term's change of unit, 16 a piece.
 //  * K stays factored, S^T = sum_g s[t,g] (C_g Q_g^T) + b Qsum^T: the matrix core multiplies the codes exactly, and the
 //    per-(token, group) scale meets the binary32 result of each group; the bias term is one more matrix
 //    instruction per 32 tokens whose contraction runs over the groups (group sums of q split into a binary16 high
@@ -53,29 +54,30 @@
 //    the row exceeds it by more than kSlack, which rescales the accumulators.  (Moving all rows of a wave together rescales less
 //    often, 0.5 % over 25 calls, and makes a row's rounding depend on the rows beside it.)
 //    The denominator sums the weights in binary32, as they are before they are rounded for the product.  (A sum of the
-//    rounded ones is 8 instructions fewer per 32 tokens and up to 6 % closer where few tokens dominate, but a token in front
+//    rounded ones is 8 instructions fewer per 32 tokens and up to 7 % closer where few tokens dominate, but a token in front
 //    of 131,071 of weight 2^-25.2 then comes out 1.9e-3 off.)
 //  * A wave works a step ahead of itself: step i takes the scores of tile i and then, between the matrix instructions of the
 //    product of tile i - 1, the softmax of tile i.  The tiles are staged beside the scores, V one step behind K.  Measured
 //    against scores, softmax and product one after the other, one call: 256-wide 512 tokens of ten agents of 6,000, three layers 1,844 /
 //    1,821 us (4.05e6 / 3.80e6 clocks; the power limit lowers the clock by the half of that), a window of 1,024 330 / 311;
-//    128-wide two layers of four agents 406 / 396, 192 + 128 253 / 248, 64-wide 599 / 584.  The first step is a copy of its own
+//    128-wide two layers of four agents 406 / 396, 192 + 128 253 / 248, 64-wide 599 / 584 (with the references of a wave moved together
+//    and a denominator of rounded weights, 0.9 % of it).  The first step is a copy of its own
 //    without a product, which a unit of few tiles would feel: with a product of zeros / without, 94 tokens of two agents behind
 //    900, 128-wide, six layers 201 / 191 us (append included), 70 tokens of four agents 57.7 / 56.0, 256-wide 71.0 / 68.5, 700 tokens behind 300
 //    49.3 / 47.0.  (A branch round the product inside the loop made the compiler copy or spill the accumulators.)
-//  * Every variant runs without scratch memory, and a test holds the build to that: in a build that spilled, the compiler
+//  * Every variant runs without scratch memory or spills, and build.py refuses one that does not: in a build that spilled, the compiler
 //    put a spill behind a loop over part of the threads but before all were switched on again.  What the tile loop does not
-//    need is therefore worked out again behind it from opaque copies (lane_again, fresh), and nothing in front of it diverges.
+//    need is therefore worked out again behind it from opaque copies (lane_again, fresh).  What still diverges: the prefix sums
+//    over the agents (ChunkStream::fill) and the staging of threads without a share (k_on, v_on, k_params_writer).
 //  * Two forms of launch: one workgroup per unit (layer, agent, KV head, row tile); or, given a workspace, where the units are
 //    fewer than two per compute unit and it gains something (chunk_rules.h), one workgroup per compute unit, each with an
 //    equal contiguous range of all units' tiles.  A unit cut by a range's end leaves un-normalised sums, maxima and
 //    denominators of every part in the workspace, and a second small kernel merges them in order.
 //
-// Measured, 256-wide heads, ten agents of 4K-32K tokens, a 512-token chunk, one layer: 1.82 ms = 805 TFLOP/s with shares, 2.0
-// without (16 rows per wave on 16x16x32 instructions, one workgroup per unit: 2.28 ms); one agent of 8,000 tokens 0.11 +
-// 0.02 ms with, 0.315 without (0.364 ms).
-// A wave issues 270 vector and 33 matrix instructions per 32 tokens (256-wide; 305 and 33 while every wave unpacked the keys); the
-// matrix pipe is busy 45 % of the time, a wave waits for LDS or the barrier a third of it.  The clock falls as the pipe fills (2.0 GHz at 42 %, 1.9 at 45 %), so a
+// Measured, 256-wide heads, a 512-token chunk, one layer: ten agents of 4K-32K tokens (20,700 in the mean) 2.09 ms = 823 TFLOP/s
+// with shares, 2.45 without; one agent behind 8,000 0.120 ms with, 0.315 without; 48 layers of ten agents, one unit per
+// workgroup, 89.9 ms = 903 TFLOP/s.  There a wave issues 271 vector and 33 matrix instructions per 32 tokens (305 and 33 while every
+// wave unpacked the keys) and waits to issue 22 % of the time; the clock falls as the pipe fills (1.99 GHz at 42 %, 1.92 to 1.95 at 46 %), so a
 // clock saved is worth about half.  64 rows per wave at one wave per SIMD (half the LDS reads per row, the accumulators
 // in the accumulator file): 3.64e6 clocks against 3.21e6, because one wave issues one instruction of any kind in five clocks.
 // Holding the second wave of a SIMD half a step behind by two barriers per step cost 15 %.  Wave priorities by phase,
