@@ -14,7 +14,7 @@ SOURCES = ["api.hip", "codec.hip", "decode_attention.hip", "chunk_attention.hip"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # No fast-math anywhere: the quantizer needs IEEE binary32 division and rounding.
-# packed-fp32 instruction selection is switched off (its forms have been unreliable on the test machines).
+# packed-fp32 instruction selection is switched off (some of its forms have given wrong results on this hardware).
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-fno-gpu-sanitize"]
