@@ -964,6 +964,9 @@ __global__ __launch_bounds__(kChunkThreads, 2) void chunk_attention_kernel(Chunk
             s->token_row = ((int64_t)u.li * p.num_agents + u.agent) * p.q_len;
         }
         x += SHARES ? part_end - begin : 1;
+        // A part of no tokens has had no barrier, and the next one may place the row groups differently: a wave that is late would
+        // write this part's queries over the next one's.
+        if constexpr (SHARES && KSPLIT == 2) if (part_t0 >= part_t1) __syncthreads();
     }
 }
 

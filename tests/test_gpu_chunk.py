@@ -479,6 +479,30 @@ def test_shared_chunk_with_a_scale_that_is_not_positive(scale, D):
         assert_close(got.cpu().numpy(), want, f"scale {scale} width {D} shares {workspace is not None}")
 
 
+@pytest.mark.parametrize("shape", [(32, 8, 128), (16, 16, (192, 128)), (8, 4, 256)])
+def test_shared_chunk_with_agents_that_see_nothing(shape):
+    """Agents without tokens, or with fewer than the chunk has positions, between long ones: a workgroup's range then has parts of no
+    tokens, before parts whose row groups lie on other waves (a chunk's last 128-row tile is partly empty, its first are not)."""
+    Hq, Hkv, D = shape
+    Dk, Dv = D if isinstance(D, tuple) else (D, D)
+    C = 70 if Hq // Hkv > 1 else 150
+    w = synth.small(71, 1, Hq, Hkv, Dk, Dv, False, (600, 2500, 300, 300, 1900, 300, 300, 1100), q_len=C)
+    _, (spec, kpool, vpool, table_d) = append_chunk_and_attend(w)
+    ospec, okp, ovp, otable = host_cache(w)
+    lens = [0, w.final_lens()[1], 0, 0, w.final_lens()[4], 30, 0, w.final_lens()[7]]
+    sl, msl, q = torch.tensor(lens, dtype=torch.int32, device=DEV), 512 * 256, w.q_all(DEV)
+    wide = torch.nn.functional.pad(table_d, (0, 512 - table_d.shape[1])).contiguous()
+    for bound, table in ((max(lens), table_d), (msl, wide)):
+        need = b.q4kv_attention_workspace_bytes(spec, len(lens), C, bound, 0, 1)
+        ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+        for window in (0, 300):
+            want = oracle.attention(ospec, okp, ovp, w.q_all().numpy(), otable, lens, w.sm_scale, window=window)
+            for workspace in (ws, None):
+                got = b.q4kv_batched_attention(spec, kpool, vpool, q, table, sl, bound, w.sm_scale, window, workspace=workspace)
+                torch.cuda.synchronize()
+                assert_close(got.cpu().numpy(), want, f"{shape} bound {bound} window {window} shares {workspace is not None}")
+
+
 def test_chunk_of_more_agents_than_shares_are_numbered_for():
     """Shares are dealt out to 256 agents at most: one more and the call asks for no workspace and runs without."""
     lens = [(37 * i) % 90 for i in range(257)]
