@@ -30,7 +30,8 @@
 //    the unpacked tile does not fit into LDS (chunk_unpacks_keys) the code words are staged as they are and masked by each
 //    wave.  Whole numbers in place of the subnormals, in the one form and not in the other, gave the two forms different bits:
 //    the matrix core's sums are 2e-8 off with them and 8e-7 with subnormals.  Outputs do not show that (errors against 64 bits
-//    3.275e-4 and 3.277e-4).  They cost 4 instructions a word more and save the bias term's change of unit, 16 a piece.
+//    3.275e-4 and 3.277e-4).  They cost 4 instructions a word more and save the bias term's change of unit, 16 a piece: whole numbers /
+//    subnormals 64-wide, ten agents, six layers 597 / 613 us, 128-wide, ten agents, three layers 2,043 / 2,072, 192 + 128 1,257 / 1,243, 256 1,944 / 1,937.
 //  * K stays factored, S^T = sum_g s[t,g] (C_g Q_g^T) + b Qsum^T: the matrix core multiplies the codes exactly, and the
 //    per-(token, group) scale meets the binary32 result of each group; the bias term is one more matrix
 //    instruction per 32 tokens whose contraction runs over the groups (group sums of q split into a binary16 high
@@ -76,9 +77,9 @@
 //
 // Measured, 256-wide heads, a 512-token chunk, one layer: ten agents of 4K-32K tokens (20,700 in the mean) 2.09 ms = 823 TFLOP/s
 // with shares, 2.45 without; one agent behind 8,000 0.120 ms with, 0.315 without; 48 layers of ten agents, one unit per
-// workgroup, 89.9 ms = 903 TFLOP/s.  There a wave issues 271 vector and 33 matrix instructions per 32 tokens (305 and 33 while every
-// wave unpacked the keys) and waits to issue 22 % of the time; the clock falls as the pipe fills (1.99 GHz at 42 %, 1.92 to 1.95 at 46 %), so a
-// clock saved is worth about half.  64 rows per wave at one wave per SIMD (half the LDS reads per row, the accumulators
+// workgroup, 88.1 to 89.9 ms = 921 to 903 TFLOP/s (boxes differ).  There a wave issues 271 vector and 33 matrix instructions per 32 tokens (305 and 33 while every
+// wave unpacked the keys) and waits to issue 22 % of the time; the clock falls as the pipe fills (on one box 1.99 GHz at 42 %, 1.92 at 45 %; others
+// run at 1.95 to 1.99 at 46 %), so a clock saved is worth about half.  64 rows per wave at one wave per SIMD (half the LDS reads per row, the accumulators
 // in the accumulator file): 3.64e6 clocks against 3.21e6, because one wave issues one instruction of any kind in five clocks.
 // Holding the second wave of a SIMD half a step behind by two barriers per step cost 15 %.  Wave priorities by phase,
 // deeper operand reads: no change.
